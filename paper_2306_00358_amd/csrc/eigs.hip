@@ -30,7 +30,8 @@
 // Check:      H = V (V M)^T, H = Z diag(theta) Z^T (Householder reduction to
 //             tridiagonal form in one workgroup, k_sytrd_small, then divide
 //             and conquer on the tridiagonal in another, k_stedc_small in
-//             stedc.hip, and one small GEMM for Z^T = Z_T^T Q^T),
+//             stedc.hip, and the reflectors applied to its rows,
+//             k_backtransform),
 //             Ritz vectors X = Z^T V, residuals |(Z^T Y)_i - theta_i X_i|.
 // Converged when the residuals of the `need` leading pairs are below
 // tol * theta_1; otherwise the sweeps continue from X.  The first check
@@ -670,24 +671,31 @@ void launch_chol_inv_batched(const CholItem* d_items, int count, int pmax, int p
 
 // Householder reduction of a small symmetric matrix to tridiagonal form in
 // one workgroup, for the Rayleigh-Ritz step (its tridiagonal eigenproblem
-// goes to the divide and conquer of k_stedc_small).  H (p x p, symmetric, 3 <= p <=
-// 128) lives in registers: thread t = 8 i + q holds row i's entries in
-// columns q, q + 8, ..., so a matrix-vector product is 16 FMAs per thread and
-// a reduction over 8 neighbouring lanes.  For k = 0 .. p-3 the entries of row
-// k past the diagonal, x (the column, by symmetry), give v (v_0 = 1) and tau
-// with (I - tau v v^T) x = beta e_1, and the trailing block takes
-// A <- A - v w^T - w v^T, w = tau A v - (tau^2 / 2) (v^T A v) v (the standard
-// symmetric two-sided update).  The reflectors are kept in LDS; Q = H_0 H_1
-// ... H_{p-3} is then accumulated from the back, as Q^T in the same register
-// layout, and written over H column-major as the reduction matrix the
-// tridiagonal solver expects; d (p) and e (p - 1) receive the tridiagonal.
-// Every loop has a fixed trip count and every sum a fixed order.
-constexpr int kTrdThreads = 1024;
-// threads of a launch for p rows: the 8 lanes of every row below p, whole
-// waves, at least 128 (the threads that clear the 128-entry vectors); fewer
-// waves than 1024 threads for small p make every barrier cheaper
-static inline int trd_threads(int p) { return std::max(128, (8 * p + 63) / 64 * 64); }
-
+// goes to the divide and conquer of k_stedc_small).  For k = 0 .. p-3 the
+// entries of row k past the diagonal, x (the column, by symmetry), give v
+// (v_0 = 1) and tau with (I - tau v v^T) x = beta e_1, and the trailing block
+// takes A <- A - v w^T - w v^T, w = tau A v - (tau^2 / 2) (v^T A v) v (the
+// standard symmetric two-sided update).  d (p) and e (p - 1) receive the
+// tridiagonal and H the reflectors: v_k in row k (zero outside its columns
+// k+1 ..), the taus in row p - 2; k_backtransform applies Q = H_0 H_1 ...
+// H_{p-3} to the tridiagonal's eigenvectors.  Every loop has a fixed trip
+// count and every sum a fixed order.
+//
+// What bounds it is the latency of one step's dependency chain, not its
+// arithmetic, and after that the LDS instructions of all waves together, so
+// the layout keeps both short: 4 waves, NC columns per lane (1 for p <= 64, 2
+// up to 128); lane c of wave w holds A[w + 4 r][c (+ 64)] in registers.  A v is
+// then one FMA per row and column with v_i as a scalar (readlane) and a sum of
+// 4 partials through LDS; the update takes v_i, w_i the same way; the only
+// cross-lane sums are |x|^2 and v^T A v.  The wave that owns row k+1 publishes
+// it as soon as step k has updated it.  Two barriers per step, which wait
+// for LDS only (trd_barrier): the global stores of v_k stay in flight, where
+// a fenced barrier waits for them.  Square root and divisions come from
+// v_rsq_f64 / v_rcp_f64 and Newton steps.  Against 8 lanes per row in up to 16
+// waves with d, e stored to global memory as they are found (and Q^T
+// accumulated at the end, an s_barrier over 16 waves alone 467 cycles): p = 64
+// 172 -> 61 us, p = 128 415 -> 208 us, and 16 and 43 us for the back-transform
+// (which replaces a 7 us product, or 30 us inside the divide and conquer).
 // another lane of the same 8-lane group (DPP: quad_perm [1,0,3,2],
 // quad_perm [2,3,0,1], row_half_mirror); every lane of the group is active
 template <int kCtrl>
@@ -705,169 +713,341 @@ __device__ __forceinline__ double trd_sum8(double v) {
   return v + trd_dpp<0x141>(v);
 }
 
+// sum over the wave, the same bits in every lane: rows of 16 lanes by DPP
+// (the last step row_mirror), then across the rows
+__device__ __forceinline__ double trd_sum64(double v) {
+  v = trd_sum8(v);
+  v += trd_dpp<0x140>(v);
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// workgroup barrier that orders LDS accesses only: global stores in flight
+// are not waited for
+__device__ __forceinline__ void trd_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// 1 / sqrt(x) and 1 / x from the hardware estimates and two Newton steps
+__device__ __forceinline__ double trd_rsq(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(y, fma(-0.5 * x * y, y, 0.5), y);
+  return fma(y, fma(-0.5 * x * y, y, 0.5), y);
+}
+
+__device__ __forceinline__ double trd_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
+template <int NC>
 __device__ __forceinline__ void sytrd_body(double* __restrict__ H, int p, double* __restrict__ d,
                                            double* __restrict__ e) {
-  // reflector k at Vr[128 k + c], zero outside its columns k+1 .. p-1; the
-  // vectors of a step are likewise zero outside the trailing block, so the
-  // register loops below need no bounds tests
-  extern __shared__ double Vr[];
-  __shared__ double vsa[2][128], wsa[128], wvs[128], taus[128];
-  const int t = threadIdx.x, i = t >> 3, q = t & 7;
-  const bool own = i < p;
-  double a[16];
+  constexpr int R = 16 * NC;  // rows per wave
+  __shared__ double xs[64 * NC], part[4][64 * NC];
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  double a[NC][R];  // a[q][r]: row w + 4 r, column lane + 64 q
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int c = q + 8 * r;
-    a[r] = (own && c < p) ? H[i * p + c] : 0.0;
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const int i = w + 4 * r, c = lane + 64 * q;
+      a[q][r] = (i < p && c < p) ? H[i * p + c] : 0.0;
+    }
+  // lane c keeps d, e and tau of the indices c (+ 64)
+  double dl[NC], el[NC], tl[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) dl[q] = el[q] = tl[q] = 0.0;
+  // H is in registers (waited for here, so that the loop holds no wait for
+  // vector memory): its rows may take the reflectors
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (w == 0) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) xs[lane + 64 * q] = a[q][0];  // row 0
   }
-  if (t < 128) wsa[t] = wvs[t] = 0.0;
   for (int k = 0; k + 2 < p; ++k) {
-    const int o = k + 1;
-    double* vs = vsa[k & 1];
-    if (i == k) {
-      // row k's eight owners (eight lanes of one wave) form the reflector
-      // from their own entries and publish it with tau, beta and d_k
-      double s2 = 0.0, x0 = 0.0, dk = 0.0;
+    trd_barrier();
+    double x[NC], v[NC];
+    double s2 = 0.0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = q + 8 * r;
-        s2 += (c >= o && c < p) ? a[r] * a[r] : 0.0;
-        x0 = c == o ? a[r] : x0;
-        dk = c == k ? a[r] : dk;
-      }
-      const double nrm2 = trd_sum8(s2);
-      x0 = trd_sum8(x0);  // one lane holds it, the others add zeros
-      dk = trd_sum8(dk);
-      double beta, tau, scale;
-      if (nrm2 == 0.0) {
-        beta = x0;
-        tau = 0.0;
-        scale = 0.0;
-      } else {
-        beta = -copysign(sqrt(nrm2), x0);
-        tau = (beta - x0) / beta;
-        scale = 1.0 / (x0 - beta);
-      }
+    for (int q = 0; q < NC; ++q) {
+      x[q] = xs[lane + 64 * q];
+      s2 += lane + 64 * q > k ? x[q] * x[q] : 0.0;  // columns past p are zero
+    }
+    const double nrm2 = trd_sum64(s2);
+    const double x0 = readlane_f64(NC == 2 && k + 1 >= 64 ? x[NC - 1] : x[0], (k + 1) & 63);
+    double beta, tau, scale;
+    if (nrm2 >= 0x1p-960) {
+      const double y = trd_rsq(nrm2);
+      beta = -copysign(nrm2 * y, x0);
+      tau = 1.0 + fabs(x0) * y;  // (beta - x0) / beta, beta and x0 of opposite signs
+      scale = trd_rcp(x0 - beta);
+    } else if (nrm2 == 0.0) {
+      beta = x0;
+      tau = 0.0;
+      scale = 0.0;
+    } else {  // near the bottom of the range: the plain operations
+      beta = -copysign(sqrt(nrm2), x0);
+      tau = (beta - x0) / beta;
+      scale = 1.0 / (x0 - beta);
+    }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = q + 8 * r;
-        const double v = c == o ? 1.0 : ((c > o && c < p) ? a[r] * scale : 0.0);
-        vs[c] = v;
-        Vr[128 * k + c] = v;
-      }
-      if (q == 0) {
-        taus[k] = tau;
-        e[k] = beta;
-        d[k] = dk;
+    for (int q = 0; q < NC; ++q) {
+      const int c = lane + 64 * q;
+      v[q] = c == k + 1 ? 1.0 : (c > k + 1 ? x[q] * scale : 0.0);
+      dl[q] = c == k ? x[q] : dl[q];
+      el[q] = c == k ? beta : el[q];
+      tl[q] = c == k ? tau : tl[q];
+    }
+    // (A v)_c over this wave's rows (v_i = 0 for the finished ones; groups of
+    // four rows that are all finished are skipped: a uniform test)
+    double vi[R];
+    double acc[NC][2];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) acc[q][0] = acc[q][1] = 0.0;
+#pragma unroll
+    for (int g = 0; g < R; g += 4) {
+      if (4 * (g + 4) <= k + 1) continue;
+#pragma unroll
+      for (int r = g; r < g + 4; ++r) {
+        vi[r] = readlane_f64(v[r >> 4], (w + 4 * r) & 63);
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+          acc[q][r & 1] = fma(a[q][r], vi[r], acc[q][r & 1]);
       }
     }
-    __syncthreads();
-    const double tau = taus[k];
-    // (tau A v)_i for the rows of the trailing block
-    const bool act = own && i >= o;
-    double acc = 0.0;
-    if (act) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc += a[r] * vs[q + 8 * r];
+    for (int q = 0; q < NC; ++q) part[w][lane + 64 * q] = acc[q][0] + acc[q][1];
+    // the reflector's row of H (one wave, a different one each step)
+    if (w == (k & 3)) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+        if (lane + 64 * q < p) H[k * p + lane + 64 * q] = v[q];
     }
-    const double wraw = tau * trd_sum8(acc);
-    if (own && q == 0) {
-      wsa[i] = act ? wraw : 0.0;
-      wvs[i] = act ? wraw * vs[i] : 0.0;
-    }
-    __syncthreads();
-    // alpha = -tau/2 v^T w: every 8-lane group sums the rows' products w_i v_i
-    // over its rows q + 8 r (together all p) -- the same bits everywhere
+    trd_barrier();
+    double ws[NC];
     double pv = 0.0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) pv += wvs[q + 8 * r];
-    const double alpha = -0.5 * tau * trd_sum8(pv);
-    if (act) {
-      const double vi = vs[i], wi = wraw + alpha * vi;
+    for (int q = 0; q < NC; ++q) {
+      const int c = lane + 64 * q;
+      const double s = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+      ws[q] = c > k ? tau * s : 0.0;  // finished columns take no part
+      pv = fma(ws[q], v[q], pv);
+    }
+    const double alpha = -0.5 * tau * trd_sum64(pv);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = q + 8 * r;
-        a[r] -= vi * (wsa[c] + alpha * vs[c]) + wi * vs[c];
+    for (int q = 0; q < NC; ++q) ws[q] = fma(alpha, v[q], ws[q]);
+    const int r1 = (k + 1) >> 2;  // row k+1 in its wave, in the first group not skipped
+#pragma unroll
+    for (int g = 0; g < R; g += 4) {
+      if (4 * (g + 4) <= k + 1) continue;
+#pragma unroll
+      for (int r = g; r < g + 4; ++r) {
+        const double wi = readlane_f64(ws[r >> 4], (w + 4 * r) & 63);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) a[q][r] = fma(-vi[r], ws[q], fma(-wi, v[q], a[q][r]));
+      }
+      if (g == (r1 & ~3) && w == ((k + 1) & 3)) {  // publish row k+1 for the next step
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const double y0 = a[q][g], y1 = a[q][g + 1], y2 = a[q][g + 2], y3 = a[q][g + 3];
+          const double lo = (r1 & 1) ? y1 : y0, hi = (r1 & 1) ? y3 : y2;
+          xs[lane + 64 * q] = (r1 & 2) ? hi : lo;
+        }
       }
     }
   }
-  // the last 2 x 2 block
-  if (i == p - 2 || i == p - 1) {
+  // the last 2 x 2 block: its rows through LDS (xs holds row p - 2 already)
+  __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int c = q + 8 * r;
-      if (c == i) d[i] = a[r];
-      if (i == p - 1 && c == p - 2) e[p - 2] = a[r];
-    }
+  for (int q = 0; q < NC; ++q) {
+    const int c = lane + 64 * q;
+    dl[q] = c == p - 2 ? xs[c] : dl[q];
+    if (c == p - 2) el[q] = xs[p - 1];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (w + 4 * r == p - 1) part[0][c] = a[q][r];
   }
   __syncthreads();
-  // Q from the back, held as Q^T: rows j >= k+1 of Q^T take
-  // -(tau Q^T v)_j v^T (v zero outside columns k+1 ..)
+  if (w == 0) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) a[r] = (own && q + 8 * r == i) ? 1.0 : 0.0;
+    for (int q = 0; q < NC; ++q) {
+      const int c = lane + 64 * q;
+      if (c < p) d[c] = c == p - 1 ? part[0][c] : dl[q];
+      if (c < p - 1) e[c] = el[q];
+      if (c < p - 2) H[(p - 2) * p + c] = tl[q];
+    }
+  }
+}
+
+template <int NC>
+__global__ __launch_bounds__(256) void k_sytrd_small(double* __restrict__ H, int p,
+                                                          double* __restrict__ d,
+                                                          double* __restrict__ e) {
+  sytrd_body<NC>(H, p, d, e);
+}
+
+static void launch_sytrd(double* H, int p, double* d, double* e, hipStream_t s) {
+  if (p <= 64)
+    hipLaunchKernelGGL(k_sytrd_small<1>, dim3(1), dim3(256), 0, s, H, p, d, e);
+  else
+    hipLaunchKernelGGL(k_sytrd_small<2>, dim3(1), dim3(256), 0, s, H, p, d, e);
+}
+
+// Rows z of Zt (p x p, the tridiagonal's eigenvectors) become the rows Q z,
+// Q = H_0 ... H_{p-3} from the reflectors sytrd_body leaves in V (p x p):
+// for k = p-3 .. 0, z <- z - tau_k (v_k^T z) v_k.  Rows row0 .. row0 + rows -
+// 1 of Zt; row c goes to out + c ldo, its first nout entries (out may be Zt:
+// a row is read and written by the same lanes).  Eight lanes per row, 32 rows
+// per workgroup, V in LDS; a step is 8 NC products per lane, an 8-lane sum
+// and 8 NC updates, with the next v loaded meanwhile.  The rows are
+// independent, so they spread over workgroups (compute units), where the
+// accumulation of Q^T inside the reduction's own workgroup was bound by one
+// compute unit's LDS reads of v.
+constexpr int kBackRows = 32;
+template <int NC>
+__device__ __forceinline__ void backtransform_body(const double* __restrict__ V, int p,
+                                                   const double* Zt, int row0, int rows,
+                                                   double* out, long long ldo, int nout,
+                                                   int block) {
+  constexpr int W = 64 * NC, C = 8 * NC;
+  extern __shared__ double Vs[];  // (p - 2) x W, columns past p zero
+  __shared__ double taus[128];
+  const int t = threadIdx.x;
+  for (int x = t; x < (p - 2) * W; x += 256) {
+    const int k = x / W, c = x % W;
+    Vs[x] = c < p ? V[k * p + c] : 0.0;
+  }
+  if (t < p - 2) taus[t] = V[(p - 2) * p + t];
+  const int g = block * kBackRows + (t >> 3), u = t & 7;
+  const int row = row0 + (g < rows ? g : rows - 1);
+  // columns 16 (r / 2) + 2 u + r % 2
+  double z[C], v[C];
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    const int c = 16 * (r >> 1) + 2 * u + (r & 1);
+    z[r] = c < p ? Zt[(long long)row * p + c] : 0.0;
+  }
+  __syncthreads();
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  auto load = [&](int k, double (&x)[C]) {
+#pragma unroll
+    for (int r = 0; r < C; r += 2) {
+      const d2 y = *(const d2*)(Vs + k * W + 8 * r + 2 * u);
+      x[r] = y.x;
+      x[r + 1] = y.y;
+    }
+  };
+  load(p - 3, v);
+  double tau = taus[p - 3];
   for (int k = p - 3; k >= 0; --k) {
-    const double* v = Vr + 128 * k;
-    const bool act = own && i > k;
-    double acc = 0.0;
-    if (act) {
+    double vn[C];
+    const int kn = k > 0 ? k - 1 : 0;
+    load(kn, vn);
+    const double tn = taus[kn];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc += a[r] * v[q + 8 * r];
-    }
-    const double y = taus[k] * trd_sum8(acc);
-    if (act) {
+    for (int r = 0; r < C; ++r) acc[r & 3] = fma(z[r], v[r], acc[r & 3]);
+    const double y = tau * trd_sum8((acc[0] + acc[1]) + (acc[2] + acc[3]));
 #pragma unroll
-      for (int r = 0; r < 16; ++r) a[r] -= y * v[q + 8 * r];
-    }
+    for (int r = 0; r < C; ++r) z[r] = fma(-y, v[r], z[r]);
+#pragma unroll
+    for (int r = 0; r < C; ++r) v[r] = vn[r];
+    tau = tn;
   }
-  // Q column-major: H[c + j p] = Q[c][j] = Q^T[j][c]
-  if (own) {
+  if (g < rows) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int c = q + 8 * r;
-      if (c < p) H[c + i * p] = a[r];
+    for (int r = 0; r < C; ++r) {
+      const int c = 16 * (r >> 1) + 2 * u + (r & 1);
+      if (c < nout) out[(long long)row * ldo + c] = z[r];
     }
   }
 }
 
-__global__ __launch_bounds__(kTrdThreads) void k_sytrd_small(double* __restrict__ H, int p,
-                                                             double* __restrict__ d,
-                                                             double* __restrict__ e) {
-  sytrd_body(H, p, d, e);
+template <int NC>
+__global__ __launch_bounds__(256) void k_backtransform(const double* __restrict__ V, int p,
+                                                       const double* Zt, int row0, int rows,
+                                                       double* out, long long ldo, int nout) {
+  backtransform_body<NC>(V, p, Zt, row0, rows, out, ldo, nout, blockIdx.x);
 }
 
-// All eigenpairs of a small symmetric matrix M (n x n, 3 <= n <= 128,
-// row-major, overwritten): W ascending, M <- the eigenvector rows (row c for
-// W[c]); E (n doubles) is scratch, *info = 1 when a result is not finite.
-// Two single-workgroup launches: the Householder reduction and the divide and
-// conquer with its back-transform.
-bool dense_eig_small(double* M, int n, double* W, double* E, int* info, hipStream_t s) {
-  static bool lds_set = hipFuncSetAttribute((const void*)k_sytrd_small,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)((size_t)128 * 128 * sizeof(double))) ==
-                        hipSuccess;
-  if (!lds_set || n < 3 || n > 128) return false;
-  hipLaunchKernelGGL(k_sytrd_small, dim3(1), dim3(trd_threads(n)), (size_t)128 * n * sizeof(double),
-                     s, M, n, W, E);
-  return tridiag_eig_small_back(W, E, n, W, M, info, s);
+static inline size_t back_lds(int p, int nc) { return (size_t)(p - 2) * 64 * nc * sizeof(double); }
+
+// false when the launch's LDS cannot be had
+static bool launch_backtransform(const double* V, int p, const double* Zt, int row0, int rows,
+                                 double* out, hipStream_t s) {
+  static const bool lds_set =
+      hipFuncSetAttribute((const void*)k_backtransform<2>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)back_lds(128, 2)) == hipSuccess;
+  if (!lds_set || p < 3 || p > 128) return false;
+  const dim3 grid((rows + kBackRows - 1) / kBackRows);
+  if (p <= 64)
+    hipLaunchKernelGGL(k_backtransform<1>, grid, dim3(256), back_lds(p, 1), s, V, p, Zt, row0,
+                       rows, out, (long long)p, p);
+  else
+    hipLaunchKernelGGL(k_backtransform<2>, grid, dim3(256), back_lds(p, 2), s, V, p, Zt, row0,
+                       rows, out, (long long)p, p);
+  return true;
+}
+
+// Eigenpairs of a small symmetric matrix M (n x n, 3 <= n <= 128, row-major,
+// overwritten): W ascending, rows n - rows .. n - 1 of Zt (n x n) <- the
+// eigenvectors of the `rows` largest (row c for W[c]; the other rows are
+// scratch); E (n doubles) is scratch, *info = 1 when a result is not finite.
+// Three launches: the Householder reduction, the divide and conquer (one
+// workgroup each) and the back-transform of the rows wanted.
+bool dense_eig_small(double* M, int n, int rows, double* W, double* E, double* Zt, int* info,
+                     hipStream_t s) {
+  if (n < 3 || n > 128) return false;
+  launch_sytrd(M, n, W, E, s);
+  return tridiag_eig_small(W, E, n, W, Zt, info, s) &&
+         launch_backtransform(M, n, Zt, n - rows, rows, Zt, s);
 }
 
 // The same reduction for every problem of a lockstep batch whose block
-// eigensolver is still iterating: H (p x p) -> Q^T, diagonal into W, the
-// off-diagonal into G (free during the Rayleigh-Ritz step).
-__global__ __launch_bounds__(kTrdThreads) void k_group_sytrd(const GroupStep* __restrict__ dsc) {
+// eigensolver is still iterating: H (p x p) -> reflectors, diagonal into W,
+// the off-diagonal into G (free during the Rayleigh-Ritz step).
+template <int NC>
+__global__ __launch_bounds__(256) void k_group_sytrd(const GroupStep* __restrict__ dsc) {
   const GroupStep& g = dsc[blockIdx.x];
   if (!g.ctl->iter) return;  // uniform
-  sytrd_body(g.H, g.p, g.W, g.G);
+  sytrd_body<NC>(g.H, g.p, g.W, g.G);
 }
 
 void group_sytrd(const GroupStep* d, int count, int pmax, hipStream_t s) {
-  static bool lds_set = hipFuncSetAttribute((const void*)k_group_sytrd,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)((size_t)128 * 128 * sizeof(double))) ==
-                        hipSuccess;
+  if (pmax <= 64)
+    hipLaunchKernelGGL(k_group_sytrd<1>, dim3(count), dim3(256), 0, s, d);
+  else
+    hipLaunchKernelGGL(k_group_sytrd<2>, dim3(count), dim3(256), 0, s, d);
+}
+
+// The tridiagonals' eigenvector rows (in Rt) back to the Rayleigh-Ritz
+// matrices' rows, in place -- or, for environments diagonalised whole (dense),
+// to the rows of X (n columns: the padded index is dropped).
+template <int NC>
+__global__ __launch_bounds__(256) void k_group_back(const GroupStep* __restrict__ dsc, int dense) {
+  const GroupStep& g = dsc[blockIdx.y];
+  if (!g.ctl->iter || (int)blockIdx.x * kBackRows >= g.p) return;  // uniform
+  backtransform_body<NC>(g.H, g.p, g.Rt, 0, g.p, dense ? g.X : g.Rt, dense ? g.n : g.p,
+                         dense ? g.n : g.p, blockIdx.x);
+}
+
+void group_back(const GroupStep* d, int count, int pmax, bool dense, hipStream_t s) {
+  static const bool lds_set =
+      hipFuncSetAttribute((const void*)k_group_back<2>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)back_lds(128, 2)) == hipSuccess;
   (void)lds_set;
-  hipLaunchKernelGGL(k_group_sytrd, dim3(count), dim3(trd_threads(pmax)),
-                     (size_t)128 * pmax * sizeof(double), s, d);
+  const dim3 grid((pmax + kBackRows - 1) / kBackRows, count);
+  if (pmax <= 64)
+    hipLaunchKernelGGL(k_group_back<1>, grid, dim3(256), back_lds(pmax, 1), s, d, dense ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_group_back<2>, grid, dim3(256), back_lds(pmax, 2), s, d, dense ? 1 : 0);
 }
 
 __global__ void k_symmetrize_small(double* H, int p) {
@@ -997,10 +1177,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     return hipFuncSetAttribute((const void*)k_trsm_rows,
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)(((size_t)128 * 128 + 128 * 16) * sizeof(double))) ==
-               hipSuccess &&
-           hipFuncSetAttribute((const void*)k_sytrd_small,
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)((size_t)128 * 128 * sizeof(double))) == hipSuccess;
+           hipSuccess;
   }();
   const size_t trsm_lds = ((size_t)p * p + (size_t)p * 16) * sizeof(double);
   if (!lds_set || p > 128 || p % 16 != 0) return false;
@@ -1054,16 +1231,14 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     vm(V, Y, 0.0);
     gemm_f64_splitk(V, n, Y, n, B_KCONTIG, H, p, p, p, n, kc, part, s);
     hipLaunchKernelGGL(k_symmetrize_small, dim3(16), dim3(256), 0, s, H, p);
-    // tridiagonal form and its reduction matrix (H = Q^T, row-major) in one
-    // workgroup, then divide and conquer on the tridiagonal in another
-    // (Z^T into Rt, eigenvalues over its diagonal in W)
-    hipLaunchKernelGGL(k_sytrd_small, dim3(1), dim3(trd_threads(p)),
-                       (size_t)128 * p * sizeof(double), s, H, p, W, E);
+    // tridiagonal form and its reflectors (over H), then divide and conquer
+    // on the tridiagonal (Z^T into Rt, eigenvalues over its diagonal in W),
+    // then the rows of Rt back to H's basis: the Ritz coefficients
+    launch_sytrd(H, p, W, E, s);
     if (!tridiag_eig_small(W, E, p, W, Rt, dinfo, s)) return false;
-    // Ritz vectors of H as rows: G = Z^T Q^T
-    gemm_f64(Rt, p, H, p, B_NCONTIG, G, out_rowmajor(p), p, p, p, nullptr, s);
-    gemm_f64(G, p, V, n, B_NCONTIG, Xout, out_rowmajor(n), p, n, p, nullptr, s);
-    gemm_f64(G, p, Y, n, B_NCONTIG, Yx, out_rowmajor(n), p, n, p, nullptr, s);
+    if (!launch_backtransform(H, p, Rt, 0, p, Rt, s)) return false;
+    gemm_f64(Rt, p, V, n, B_NCONTIG, Xout, out_rowmajor(n), p, n, p, nullptr, s);
+    gemm_f64(Rt, p, Y, n, B_NCONTIG, Yx, out_rowmajor(n), p, n, p, nullptr, s);
     hipLaunchKernelGGL(k_ritz_residual, dim3(p), dim3(256), 0, s, Yx, Xout, W, n, res);
     int hinfo[3] = {0, 0, 0};
     (void)hipMemcpyAsync(th.data(), W, p * sizeof(double), hipMemcpyDeviceToHost, s);

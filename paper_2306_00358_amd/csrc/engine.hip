@@ -550,8 +550,9 @@ static bool eig_block(int n, int dn, int spec_len, int eig_mode, int* need_out, 
 }
 
 // Leading eigenpairs of the symmetric n x n matrix in Mb: eigenvalues
-// (ascending) into Wb, eigenvector rows into Xb (p rows, iterative) or over Mb
-// (n rows, dense); returns the rows and their count.  A non-converged dense
+// (ascending) into Wb, eigenvector rows into Xb (p rows, iterative; n rows of
+// which the last `need` count, small dense) or over Mb (n rows, dense); returns
+// the rows and their count.  A non-converged dense
 // solve is folded into *sticky; an iterative one that does not converge falls
 // back to the dense solver.
 static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n, int need, int p,
@@ -582,11 +583,17 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
       return (const double*)Xb.p;
     }
   }
-  ensure(c, c->E, (size_t)n * 8);
   c->last_eig_iters = 0;  // dense
-  // small environments: two single-workgroup launches (Householder reduction,
-  // divide and conquer with the back-transform); larger ones rocSOLVER dsyevd
-  if (!dense_eig_small((double*)Mb.p, n, (double*)Wb.p, (double*)c->E.p, inf, c->stream)) {
+  // small environments: Householder reduction, divide and conquer and the
+  // back-transform of the rows needed (the small solver keeps its eigenvectors
+  // apart from Mb, which holds the reflectors); larger ones rocSOLVER dsyevd
+  const bool small = n >= 3 && n <= 128;
+  ensure(c, c->E, (size_t)n * 8);
+  if (small) ensure(c, Xb, (size_t)n * n * 8);
+  double* vecs = (double*)(small ? Xb.p : Mb.p);
+  if (!small || !dense_eig_small((double*)Mb.p, n, std::min(need, n), (double*)Wb.p,
+                                 (double*)c->E.p, vecs, inf, c->stream)) {
+    if (small) fail(HOTRG_ERR_DEVICE, "small eigensolver launch failed");
     rocblas_status rs = rocsolver_dsyevd(c->blas, rocblas_evect_original, rocblas_fill_lower, n,
                                          (double*)Mb.p, n, (double*)Wb.p, (double*)c->E.p, inf);
     if (rs != rocblas_status_success)
@@ -595,7 +602,7 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
   // a non-converged solve marks the caller's flag: later solves overwrite `inf`
   launch_fold_info(inf, sticky, 0, c->stream);
   *cols_out = n;
-  return (const double*)Mb.p;
+  return vecs;
 }
 
 void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
@@ -970,8 +977,9 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     launch_f64_table(R.vm, B_NCONTIG, s);    // Y = V M
     launch_f64_table(R.rrH, B_KCONTIG, s);   // H = V Y^T
     group_symm_h(R.steps, G, s);
-    group_sytrd(R.steps, G, R.pmax, s);      // H -> Q^T, tridiagonal into W, G
-    group_stedc(R.steps, G, R.pmax, s);      // H <- Z^T, W ascending
+    group_sytrd(R.steps, G, R.pmax, s);      // H -> reflectors, tridiagonal into W, G
+    group_stedc(R.steps, G, R.pmax, s);      // tridiagonal's vectors into Rt, W ascending
+    group_back(R.steps, G, R.pmax, false, s);  // Rt <- Z^T
     launch_f64_table(R.rrX, B_NCONTIG, s);   // X = Z^T V
     launch_f64_table(R.rrYx, B_NCONTIG, s);  // Yx = Z^T Y
     group_resid(R.steps, G, round == kGroupRounds - 1, s);
@@ -1158,8 +1166,8 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   f64tab(R.apT2Y, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.T2, g->n, d.Y, g->n, g->p, g->n, g->p, g); });
   f64tab(R.apYV, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.V, g->n, g->p, g->n, g->p, g); });
   f64tab(R.rrH, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, d.Y, g->n, d.H, g->p, g->p, g->p, g->n, g); });
-  f64tab(R.rrX, [&](GProb* g) { auto d = stp(g); return item(d.H, g->p, d.V, g->n, d.X, g->n, g->p, g->n, g->p, g); });
-  f64tab(R.rrYx, [&](GProb* g) { auto d = stp(g); return item(d.H, g->p, d.Y, g->n, d.Yx, g->n, g->p, g->n, g->p, g); });
+  f64tab(R.rrX, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.V, g->n, d.X, g->n, g->p, g->n, g->p, g); });
+  f64tab(R.rrYx, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.Yx, g->n, g->p, g->n, g->p, g); });
   if (R.sp != HOTRG_FP64) {
     const bool split = R.mode == RP_BF16X3;
     auto op = [&](const Buf* b) { return RpOperand{b[0].p, split ? b[1].p : nullptr}; };

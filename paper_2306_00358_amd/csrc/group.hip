@@ -14,10 +14,10 @@
 // Block eigensolver of a batch: the subspace iteration of eigs.hip with a
 // fixed budget (rounds of sweeps, each round ending in a Rayleigh-Ritz check
 // on the device), so that no host read decides the number of sweeps; the
-// p x p Rayleigh-Ritz matrices go through the Householder reduction and the
-// tridiagonal divide and conquer of the per-problem path (one workgroup per
-// problem, eigs.hip and stedc.hip); small environments (n <= 128) go through
-// the same two kernels whole, copied into H with a zero row and column when
+// p x p Rayleigh-Ritz matrices go through the Householder reduction, the
+// tridiagonal divide and conquer and the back-transform of the per-problem path
+// (eigs.hip and stedc.hip); small environments (n <= 128) go through
+// the same kernels whole, copied into H with a zero row and column when
 // n is odd (one extra eigenvalue 0 below the spectrum).
 #include <hip/hip_runtime.h>
 
@@ -135,16 +135,6 @@ __global__ void k_group_dense_in(const GroupStep* __restrict__ d) {
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < p * p; e += gridDim.x * blockDim.x) {
     const int i = e / p, j = e % p;
     s.H[e] = (i < n && j < n) ? s.M[(long long)i * n + j] : 0.0;
-  }
-}
-
-__global__ void k_group_dense_out(const GroupStep* __restrict__ d) {
-  const GroupStep& s = d[blockIdx.y];
-  if (!s.ctl->iter) return;
-  const int p = s.p, n = s.n;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < p * n; e += gridDim.x * blockDim.x) {
-    const int i = e / n, j = e % n;
-    s.X[e] = s.H[(long long)i * p + j];
   }
 }
 
@@ -266,7 +256,7 @@ void group_dense(const GroupStep* d, int count, int pmax, hipStream_t s) {
   hipLaunchKernelGGL(k_group_dense_in, dim3(16, count), dim3(256), 0, s, d);
   group_sytrd(d, count, pmax, s);
   group_stedc(d, count, pmax, s);
-  hipLaunchKernelGGL(k_group_dense_out, dim3(16, count), dim3(256), 0, s, d);
+  group_back(d, count, pmax, true, s);
 }
 void group_spectrum(const GroupStep* d, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_group_spectrum, dim3(count), dim3(256), 0, s, d);

@@ -183,14 +183,12 @@ void launch_layout_u_rp(const double* Ucan, int dx, int dn, int mode, void* u1hi
 // finite.  False when the launch fails.
 bool tridiag_eig_small(const double* d, const double* e, int n, double* W, double* Zt, int* info,
                        hipStream_t s);
-// The same with the back-transform: Hb (n x n) holds Q^T of the Householder
-// reduction on entry and the eigenvector rows (row c for W[c]) on exit.
-bool tridiag_eig_small_back(const double* d, const double* e, int n, double* W, double* Hb,
-                            int* info, hipStream_t s);
-// All eigenpairs of a small symmetric matrix (3 <= n <= 128, row-major, over
-// M): W ascending, M <- eigenvector rows; E (n) scratch; false when not
+// Eigenpairs of a small symmetric matrix (3 <= n <= 128, row-major,
+// overwritten): W ascending, rows n - rows .. n - 1 of Zt (n x n) <- the
+// eigenvectors of the `rows` largest; E (n) scratch; false when not
 // applicable or the launch fails.
-bool dense_eig_small(double* M, int n, double* W, double* E, int* info, hipStream_t s);
+bool dense_eig_small(double* M, int n, int rows, double* W, double* E, double* Zt, int* info,
+                     hipStream_t s);
 
 // ---- small kernels (kernels.hip) ----
 void launch_maxabs(const void* x, long long n, bool is_f32, unsigned long long* maxbits, hipStream_t s);
@@ -276,14 +274,16 @@ void group_seed(const GroupStep* d, int count, long long max_pn, hipStream_t s);
 void group_symm_h(const GroupStep* d, int count, hipStream_t s);
 // Rayleigh-Ritz matrices H (p x p, p a multiple of 16, <= 128) of the
 // iterating problems: Householder reduction (diagonal into W, off-diagonal
-// into G, Q^T over H), then divide and conquer with the back-transform:
-// W ascending, H <- Z^T (row c = eigenvector c)
+// into G, reflectors over H), divide and conquer (W ascending, Rt <- the
+// tridiagonal's eigenvector rows), back-transform (Rt <- H's eigenvector
+// rows; with `dense` X <- them, n columns each)
 void group_sytrd(const GroupStep* d, int count, int pmax, hipStream_t s);
 void group_stedc(const GroupStep* d, int count, int pmax, hipStream_t s);
+void group_back(const GroupStep* d, int count, int pmax, bool dense, hipStream_t s);
 void group_resid(const GroupStep* d, int count, bool last, hipStream_t s);
 void group_restart(const GroupStep* d, int count, long long max_pn, hipStream_t s);
 void group_shift(const GroupStep* d, int count, long long max_pn, hipStream_t s);
-// whole small environments (n <= 128, p = n rounded up to even) by the same two kernels
+// whole small environments (n <= 128, p = n rounded up to even) by the same kernels
 void group_dense(const GroupStep* d, int count, int pmax, hipStream_t s);
 void group_spectrum(const GroupStep* d, int count, hipStream_t s);
 void group_norm(const GroupStep* d, int count, hipStream_t s);
