@@ -689,7 +689,7 @@ void launch_chol_inv_batched(const CholItem* d_items, int count, int pmax, int p
 // 4 partials through LDS; the update takes v_i, w_i the same way; the only
 // cross-lane sums are |x|^2 and v^T A v.  The wave that owns row k+1 publishes
 // it as soon as step k has updated it.  Two barriers per step, which wait
-// for LDS only (trd_barrier): the global stores of v_k stay in flight, where
+// for LDS only (lds_barrier): the global stores of v_k stay in flight, where
 // a fenced barrier waits for them.  Square root and divisions come from
 // v_rsq_f64 / v_rcp_f64 and Newton steps.  Against 8 lanes per row in up to 16
 // waves with d, e stored to global memory as they are found (and Q^T
@@ -719,14 +719,6 @@ __device__ __forceinline__ double trd_sum64(double v) {
   v = trd_sum8(v);
   v += trd_dpp<0x140>(v);
   return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-
-// workgroup barrier that orders LDS accesses only: global stores in flight
-// are not waited for
-__device__ __forceinline__ void trd_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // 1 / sqrt(x) and 1 / x from the hardware estimates and two Newton steps
@@ -770,7 +762,7 @@ __device__ __forceinline__ void sytrd_body(double* __restrict__ H, int p, double
     for (int q = 0; q < NC; ++q) xs[lane + 64 * q] = a[q][0];  // row 0
   }
   for (int k = 0; k + 2 < p; ++k) {
-    trd_barrier();
+    lds_barrier();
     double x[NC], v[NC];
     double s2 = 0.0;
 #pragma unroll
@@ -828,7 +820,7 @@ __device__ __forceinline__ void sytrd_body(double* __restrict__ H, int p, double
       for (int q = 0; q < NC; ++q)
         if (lane + 64 * q < p) H[k * p + lane + 64 * q] = v[q];
     }
-    trd_barrier();
+    lds_barrier();
     double ws[NC];
     double pv = 0.0;
 #pragma unroll

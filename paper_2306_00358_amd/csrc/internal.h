@@ -110,6 +110,14 @@ __device__ __forceinline__ void tile_order(int tm, int tn, int b, int gm, int& i
   in = r / rows;
 }
 
+// Workgroup barrier that orders LDS accesses only: global loads and stores in
+// flight are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---- reduced-precision contractions (gemm_rp.hip) ----
 enum RpMode { RP_F32 = 0, RP_BF16X3 = 1 };
 enum RpOut { RP_OUT_F32 = 0, RP_OUT_SPLIT = 1, RP_OUT_F64 = 2 };

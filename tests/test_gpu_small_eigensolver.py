@@ -1,7 +1,8 @@
 """Environments of at most 128 rows, diagonalised whole (Householder reduction
-with one or two columns per lane, divide and conquer, back-transform of the
-rows kept), against the oracle's projector at the sizes where the kernels'
-layouts change: the smallest, one below, at and above 64 rows, and at 128.
+with one or two columns per lane, divide and conquer from leaves of at most 8
+rows, back-transform of the rows kept), against the oracle's projector at the
+sizes where the kernels' layouts change: the smallest, one below, at and above
+8 and 64 rows, and at 128; spectra with equal groups rotate and deflate.
 
 Tolerances as for the larger environments (tests/test_gpu_projector.py): a
 backward-stable solver's errors are a few n u (n u = 1.4e-14 at n = 128), two
@@ -16,8 +17,8 @@ from tests.test_gpu_projector import _check, torch_cuda  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(3, 1), (4, 4), (5, 2), (16, 16), (17, 8), (63, 9), (64, 8), (64, 64), (65, 8),
-         (100, 40), (127, 10), (128, 11), (128, 128)]
+SIZES = [(3, 1), (4, 4), (5, 2), (7, 3), (8, 8), (9, 4), (16, 16), (17, 8), (33, 5), (63, 9),
+         (64, 8), (64, 64), (65, 8), (100, 40), (127, 10), (128, 11), (128, 128)]
 
 
 @pytest.mark.parametrize("n, d_new", SIZES)
@@ -42,3 +43,17 @@ def test_diagonal_and_multiplets(torch_cuda, n, d_new):  # noqa: F811
         vals = np.repeat(vals[: n // 4 + 1], 4)[:n]
         _check(torch_cuda, ctx, orthogonal_with_spectrum(vals, 300 + n), d_new, spec_len=n,
                label="multiplets", iterative=False)
+
+
+@pytest.mark.parametrize("n", [8, 40, 64, 128])
+def test_one_eigenvalue_and_two(torch_cuda, n):  # noqa: F811
+    from paper_2306_00358_amd import Context
+
+    with Context(0) as ctx:
+        # all poles of every merge equal
+        _check(torch_cuda, ctx, 0.5 * np.eye(n), n, spec_len=n, label="identity", iterative=False)
+        # two groups of n / 2 equal eigenvalues, in a random basis: long chains
+        # of rotations, one pole per group left
+        vals = np.repeat([1.0, 0.25], n // 2)
+        _check(torch_cuda, ctx, orthogonal_with_spectrum(vals, 500 + n), n // 2, spec_len=n,
+               label="two groups", iterative=False)
