@@ -563,7 +563,7 @@ __global__ __launch_bounds__(GW * GW) void k_chol_factor(const double* __restric
 // p a multiple of 16, at most 128; columns past n are computed but not
 // stored.
 constexpr int kTrsmCols = 64;
-__global__ __launch_bounds__(256) void k_trsm_rows(const double* __restrict__ Rf, int p,
+__global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__ Rf, int p,
                                                    const double* __restrict__ Y, int n,
                                                    double* __restrict__ Q) {
   extern __shared__ double lds[];

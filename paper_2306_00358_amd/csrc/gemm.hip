@@ -49,7 +49,9 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Block tile BM x BN, K slab BK; 4 waves in a 2 x 2 arrangement, each wave
+// Block tile BM x BN, K slab BK; 4 waves in a 2 x 2 arrangement (two waves per
+// SIMD promised to the compiler, which otherwise moves the accumulators to the
+// accumulation registers and back every slab: 64 x 64 tiles 8% slower), each wave
 // owns a (BM/2) x (BN/2) sub-tile made of 16x16 MFMA tiles.  Operand tiles
 // go global -> registers -> LDS; the next slab's global loads are issued
 // before the current slab's MFMAs so that they overlap.
@@ -173,7 +175,7 @@ __device__ __forceinline__ void f64_tile(const double* __restrict__ A, long long
 }
 
 template <int BM, int BN, int BK, int BL>
-__global__ __launch_bounds__(256) void k_gemm_f64(const double* __restrict__ A, long long lda,
+__global__ __launch_bounds__(256, 2) void k_gemm_f64(const double* __restrict__ A, long long lda,
                                                   const double* __restrict__ B, long long ldb,
                                                   double* __restrict__ C, OutMap om, int M, int N,
                                                   int K, unsigned long long* maxbits, int kchunk,
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256) void k_gemm_f64(const double* __restrict__ A, 
 // batch of problems): workgroup b takes tile b - begin[i] of the item i whose
 // range holds b; an item whose gate reads 0 skips its tiles.
 template <int BM, int BN, int BK, int BL>
-__global__ __launch_bounds__(256) void k_gemm_f64_grouped(const F64Item* __restrict__ items,
+__global__ __launch_bounds__(256, 2) void k_gemm_f64_grouped(const F64Item* __restrict__ items,
                                                           const int* __restrict__ begin,
                                                           int count) {
   int lo = 0, hi = count - 1;
@@ -231,7 +233,7 @@ void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, i
 // MFMAs of slab s).  TAG only gives each call site its own kernel symbol,
 // so per-contraction times can be read from a kernel trace.
 template <int BL, int TAG>
-__global__ __launch_bounds__(256) void k_gemm_f64_big(const double* __restrict__ A, long long lda,
+__global__ __launch_bounds__(256, 2) void k_gemm_f64_big(const double* __restrict__ A, long long lda,
                                                       const double* __restrict__ B, long long ldb,
                                                       double* __restrict__ C, OutMap om, int M,
                                                       int N, int K, unsigned long long* maxbits) {
@@ -425,7 +427,8 @@ static void launch_big(const double* A, long long lda, const double* B, long lon
 // forces one kernel.
 namespace {
 
-enum { C_LDS2 = 0, C_LDS3, C_LDS32, C_LDS_HALF, C_LDS_N64, C_BIG, C_G128, C_G64, C_COUNT };
+enum { C_LDS2 = 0, C_LDS3, C_LDS32, C_LDS_HALF, C_LDS_N64, C_LDS64, C_LDS128, C_BIG, C_G128,
+       C_G64, C_COUNT };
 
 struct TuneKey {
   long long v[16];
@@ -524,6 +527,10 @@ void gemm_f64(const double* A, long long lda, const double* B, long long ldb, in
         return N >= 128 && gemm_f64_lds(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s, tag, 4);
       case C_LDS_N64:
         return N <= 64 && gemm_f64_lds(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s, tag, 5);
+      case C_LDS64:
+        return gemm_f64_lds(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s, tag, 6);
+      case C_LDS128:
+        return N >= 128 && gemm_f64_lds(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s, tag, 7);
       case C_BIG:
         if (N < 128 || K < 64) return false;
         switch (tag) {
@@ -560,6 +567,10 @@ void gemm_f64(const double* A, long long lda, const double* B, long long ldb, in
   if ((long long)M * N >= (1LL << 20) && (N >= 128 || (variant == 5 && N <= 64)) &&
       variant != 2 && gemm_f64_lds(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s, tag, variant))
     return;
+  // below the tuner's range: 64 x 64 tiles through LDS where they apply and
+  // the slabs are enough to pipeline (1024 x 512 x 1024: 27 us, 33 staged
+  // through registers)
+  if (K >= 64 && (long long)M * N >= (1LL << 18) && cand(C_LDS64)) return;
   if ((long long)M * N >= (1LL << 22) && N >= 128 && K >= 64) {
     cand(C_BIG);
   } else if ((long long)M * N >= (1LL << 22) && N >= 128) {

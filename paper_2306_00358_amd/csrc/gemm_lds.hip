@@ -5,9 +5,17 @@
 //   C[map(m, n)] = sum_k A[m*lda + k] * B(k, n)
 //   B(k, n) = B[k*ldb + n] (B_NCONTIG) or B[n*ldb + k] (B_KCONTIG)
 //
-// Block: WGM x WGN waves, each owning a 64 x 64 output tile of 4 x 4
+// Block: WGM x WGN waves, each owning a WT x WT output tile (WT = 64 or 32) of
 // v_mfma_f64_16x16x4f64 tiles (accumulators stay in registers for the whole
-// K loop).  K advances in slabs of BK through NST LDS stages.  Two stages:
+// K loop).  The 64 x 64 block of four WT = 32 waves (48 KB of LDS, three blocks
+// per CU) is for products that the larger blocks leave too few of (1024^3: 48 us,
+// 65 us with 64 x 64 blocks staged through registers; 4096^3: 64-66 TFLOP/s,
+// the 256 x 128 block 68); the 128 x 128 block of eight 64 x 32 waves for those
+// in between (2025 x 2025 x 2032: 270 us, 300 with 64 x 64, 520 with 256 x 128).
+// At least two waves per SIMD are promised to the compiler, also where fewer
+// run: with all 512 registers on offer it keeps the accumulators in the
+// accumulation registers and moves them out and back every slab (64 x 64
+// blocks at 4096^3: 57 TFLOP/s so).  K advances in slabs of BK through NST LDS stages.  Two stages:
 // the slab s+1 copy is in flight while slab s is multiplied, with a barrier
 // after the copy lands and one before the stage is refilled.  Three stages:
 // slabs s+1 and s+2 are in flight; one barrier per slab both publishes slab
@@ -32,9 +40,10 @@
 // this lets each lane read its A values with 16-byte LDS loads.  The sum
 // over k is unchanged, only its rounding order differs.
 //
-// Requirements (checked by the launcher): K % BK == 0; lda, ldb even; N even
-// for B_NCONTIG; 16-byte aligned base pointers.  Rows m >= M and columns
-// n >= N are loaded from clamped (valid) addresses and never stored.
+// Requirements (checked by the launcher): K % BK == 0; lda, ldb even; for
+// B_NCONTIG with odd N one more column in every row (ldb > N); 16-byte
+// aligned base pointers.  Rows m >= M and columns n >= N are loaded from
+// clamped (valid) addresses and never stored.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -128,13 +137,14 @@ __device__ __forceinline__ void load_ncontig64(const double* __restrict__ G, lon
   }
 }
 
-template <int WGM, int WGN, int BK, int BL, int TAG, int NST>
-__global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
+template <int WGM, int WGN, int BK, int BL, int TAG, int NST, int WTM, int WTN>
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void k_gemm_f64_lds(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
     double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
     int sym, const double* __restrict__ A_2, double* __restrict__ C_2) {
   constexpr int NW = WGM * WGN;
-  constexpr int BM = 64 * WGM, BN = 64 * WGN;
+  constexpr int BM = WTM * WGM, BN = WTN * WGN;
+  constexpr int TM = WTM / 16, TN = WTN / 16;  // MFMA tiles per wave
   constexpr int CH = BK / 2;
   constexpr int A_BYTES = BM * BK * 8, B_BYTES = BK * BN * 8;
   constexpr int STAGE = A_BYTES + B_BYTES;
@@ -144,7 +154,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
                                           : BN / (1024 / (BK * 8)) / NW;
   constexpr int LOADS = A_INST + B_INST;  // global_load_lds per wave per slab
   static_assert(LOADS <= 63, "vmcnt range");
-  static_assert(NST == 2 || NST == 3, "two or three LDS stages");
+  constexpr int AHEAD = (NST - 2) * LOADS;  // copies that may be pending when a slab is read
+  static_assert(NST >= 2 && AHEAD <= 63, "LDS stages");
   __shared__ __attribute__((aligned(16))) char smem[NST * STAGE];
 
   const int tid = threadIdx.x;
@@ -179,13 +190,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
     bn = bm * BM / BN + rem;
   }
   const int m0 = bm * BM, n0 = bn * BN;
+  const int N2 = (N + 1) & ~1;  // columns of an N-contiguous B are loaded in pairs
   const int li = lane & 15, lg = lane >> 4;
 
-  d4 acc[4][4];
+  d4 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < TN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
   auto issue_a = [&](int k0, int stage) {
     load_kcontig<BM, BK, NW>(A, lda, m0, M, k0, smem + stage * STAGE, wave, lane);
@@ -193,9 +205,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
   auto issue_b = [&](int k0, int stage) {
     char* base = smem + stage * STAGE;
     if constexpr (BL == B_NCONTIG && BN == 64)
-      load_ncontig64<BK, NW>(B, ldb, k0, n0, N, base + A_BYTES, wave, lane);
+      load_ncontig64<BK, NW>(B, ldb, k0, n0, N2, base + A_BYTES, wave, lane);
     else if constexpr (BL == B_NCONTIG)
-      load_ncontig<BK, BN, NW>(B, ldb, k0, n0, N, base + A_BYTES, wave, lane);
+      load_ncontig<BK, BN, NW>(B, ldb, k0, n0, N2, base + A_BYTES, wave, lane);
     else
       load_kcontig<BN, BK, NW>(B, ldb, n0, N, k0, base + A_BYTES, wave, lane);
   };
@@ -206,17 +218,119 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
 
   const int nslab = K / BK;
   issue(0, 0);
-  if (NST == 3 && nslab > 1) issue(BK, 1);
-  if constexpr (NST == 3 && BL == B_NCONTIG) {
+#pragma unroll
+  for (int q = 1; q < NST - 1; ++q)
+    if (q < nslab) issue(q * BK, q);
+  if constexpr (NST >= 3 && TM * TN <= 8) {
+    // Small wave tiles: a whole slab's fragments of both operands in
+    // registers, two sets, the next slab's read into the other set (the loop
+    // is unrolled by two, so no set is copied) before the products of the
+    // last two k steps, whose time covers the LDS latency.  The order is
+    // pinned: with one wave per SIMD an earlier wait for those reads leaves
+    // the matrix unit idle.
+    struct Frag {
+      double a[TM][KQ], b[TN][KQ];
+    };
+    auto read = [&](int stage, Frag& f) {
+      const char* as = smem + stage * STAGE;
+      const char* bs = as + A_BYTES;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int r = wm * WTM + i * 16 + li;
+#pragma unroll
+        for (int u = 0; u < KQ / 2; ++u) {
+          const int c = lg * (KQ / 2) + u;
+          const d2 x = *(const d2*)(as + (r * CH + (c ^ swz<BK>(r))) * 16);
+          f.a[i][2 * u] = x.x;
+          f.a[i][2 * u + 1] = x.y;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (BL == B_NCONTIG) {
+#pragma unroll
+          for (int t = 0; t < KQ; ++t)
+            f.b[j][t] = *(const double*)(bs + ((lg * KQ + t) * BN + wn * WTN + j * 16 + li) * 8);
+        } else {
+          const int r = wn * WTN + j * 16 + li;
+#pragma unroll
+          for (int u = 0; u < KQ / 2; ++u) {
+            const int c = lg * (KQ / 2) + u;
+            const d2 x = *(const d2*)(bs + (r * CH + (c ^ swz<BK>(r))) * 16);
+            f.b[j][2 * u] = x.x;
+            f.b[j][2 * u + 1] = x.y;
+          }
+        }
+      }
+    };
+    if (nslab >= NST - 1)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    Frag f0, f1;
+    read(0, f0);
+    // slab s from `cur`; PRE: the copies of slab s + NST - 1 go out during it
+    // (to the stage slab s-1 held, free since the barrier that opened slab s),
+    // CROSS: slab s+1 follows, into `nxt`
+    auto slab = [&](int s, const Frag& cur, Frag& nxt, auto pre_c, auto cross_c) {
+      constexpr bool PRE = decltype(pre_c)::value;
+      constexpr bool CROSS = decltype(cross_c)::value;
+      if constexpr (PRE) issue((s + NST - 1) * BK, (s + NST - 1) % NST);
+      auto mul = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(cur.a[i][t], cur.b[j][t], acc[i][j], 0, 0, 0);
+      };
+#pragma unroll
+      for (int t = 0; t < KQ - 2; ++t) mul(t);
+      if constexpr (CROSS) {
+        __builtin_amdgcn_sched_barrier(0);
+        // slab s+1 has landed for this wave (later ones may be pending) and
+        // its reads of slab s have returned; after the barrier every wave's
+        if constexpr (PRE)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read((s + 1) % NST, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mul(KQ - 2);
+      mul(KQ - 1);
+    };
+    using yes = std::integral_constant<bool, true>;
+    using no = std::integral_constant<bool, false>;
+    int s = 0;
+    for (; s + NST < nslab; s += 2) {
+      slab(s, f0, f1, yes{}, yes{});
+      slab(s + 1, f1, f0, yes{}, yes{});
+    }
+    if (s + NST - 1 < nslab) {
+      slab(s++, f0, f1, yes{}, yes{});
+      f0 = f1;
+    }
+    for (; s + 1 < nslab; ++s) {
+      slab(s, f0, f1, no{}, yes{});
+      f0 = f1;
+    }
+    if (s < nslab) slab(s, f0, f1, no{}, no{});
+  } else if constexpr (NST >= 3 && BL == B_NCONTIG) {
     // Software-pipelined across slabs: the barrier into slab s+1 and the
     // reads of its first fragments come before the MFMAs of slab s's last k
     // step, so both waves of a SIMD still have MFMAs to issue while the
     // barrier and the LDS reads complete.
-    auto read_a = [&](int stage, double (&a)[4][KQ]) {
+    auto read_a = [&](int stage, double (&a)[TM][KQ]) {
       const char* as = smem + stage * STAGE;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = wm * 64 + i * 16 + li;
+      for (int i = 0; i < TM; ++i) {
+        const int r = wm * WTM + i * 16 + li;
 #pragma unroll
         for (int u = 0; u < KQ / 2; ++u) {
           const int c = lg * (KQ / 2) + u;
@@ -226,42 +340,42 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
         }
       }
     };
-    auto read_b = [&](int stage, int t, double (&b)[4]) {
+    auto read_b = [&](int stage, int t, double (&b)[TN]) {
       const char* bs = smem + stage * STAGE + A_BYTES;
       const int k = lg * KQ + t;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = *(const double*)(bs + (k * BN + wn * 64 + j * 16 + li) * 8);
+      for (int j = 0; j < TN; ++j) b[j] = *(const double*)(bs + (k * BN + wn * WTN + j * 16 + li) * 8);
     };
     // slab 0: this wave's copies (slab 1's may be pending), then everyone's
-    if (nslab > 1)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+    if (nslab >= NST - 1)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    double a[4][KQ], b[4];
+    double a[TM][KQ], b[TN];
     read_a(0, a);
     read_b(0, 0, b);
-    // one slab; PRE: copies of slab s+2 go out during it, CROSS: slab s+1
+    // one slab; PRE: copies of slab s + NST - 1 go out during it, CROSS: slab s+1
     // follows (compile-time flags, so the main loop body has no branches
     // and the compiler can interleave the LDS reads with the MFMAs)
     auto slab = [&](int s, auto pre_c, auto cross_c) {
       constexpr bool PRE = decltype(pre_c)::value;
       constexpr bool CROSS = decltype(cross_c)::value;
-      const int cur = s % 3;
-      double an[4][KQ];
+      const int cur = s % NST;
+      double an[TM][KQ];
 #pragma unroll
       for (int t = 0; t < KQ; ++t) {
-        double bn[4];
+        double bn[TN];
         if (t + 1 < KQ) {
           read_b(cur, t + 1, bn);
         } else if constexpr (CROSS) {
-          // this wave's copies of slab s+1 have landed (those of s+2 may be
+          // this wave's copies of slab s+1 have landed (later ones may be
           // pending) and its reads of slab s have returned; after the
           // barrier every wave's have, so slab s+1 may be read and, during
           // it, the stage of slab s refilled
           if constexpr (PRE)
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
           else
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           // lgkmcnt(0) as the builtin (vmcnt and expcnt left at their
@@ -269,28 +383,28 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
           __builtin_amdgcn_s_waitcnt(0xC07F);
           __builtin_amdgcn_s_barrier();
           asm volatile("" ::: "memory");
-          read_a((s + 1) % 3, an);
-          read_b((s + 1) % 3, 0, bn);
+          read_a((s + 1) % NST, an);
+          read_b((s + 1) % NST, 0, bn);
         }
-        // slab s+2 goes to the stage slab s-1 held, free since the barrier
+        // slab s + NST - 1 goes to the stage slab s-1 held, free since the barrier
         // that opened slab s
         if constexpr (PRE) {
-          if (t == 0) issue_a((s + 2) * BK, (s + 2) % 3);
-          if (t == 1) issue_b((s + 2) * BK, (s + 2) % 3);
+          if (t == 0) issue_a((s + NST - 1) * BK, (s + NST - 1) % NST);
+          if (t == 1) issue_b((s + NST - 1) * BK, (s + NST - 1) % NST);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j], acc[i][j], 0, 0, 0);
         if (t + 1 < KQ || CROSS) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) b[j] = bn[j];
+          for (int j = 0; j < TN; ++j) b[j] = bn[j];
         }
       }
       if constexpr (CROSS) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int u = 0; u < KQ; ++u) a[i][u] = an[i][u];
       }
@@ -298,8 +412,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
     int s = 0;
-    for (; s + 2 < nslab; ++s) slab(s, yes{}, yes{});
-    if (s + 1 < nslab) slab(s++, no{}, yes{});
+    for (; s + NST - 1 < nslab; ++s) slab(s, yes{}, yes{});
+    for (; s + 1 < nslab; ++s) slab(s, no{}, yes{});
     if (s < nslab) slab(s, no{}, no{});
   } else
   for (int s = 0; s < nslab; ++s) {
@@ -331,10 +445,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
     const char* as = smem + cur * STAGE;
     const char* bs = as + A_BYTES;
     // A values of this lane for the slab: rows wm*64 + i*16 + li, k in [lg*KQ, lg*KQ + KQ)
-    double a[4][KQ];
+    double a[TM][KQ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = wm * 64 + i * 16 + li;
+    for (int i = 0; i < TM; ++i) {
+      const int r = wm * WTM + i * 16 + li;
 #pragma unroll
       for (int u = 0; u < KQ / 2; ++u) {
         const int c = lg * (KQ / 2) + u;
@@ -347,22 +461,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
 #pragma unroll
       for (int t = 0; t < KQ; ++t) {
         const int k = lg * KQ + t;
-        double b[4];
+        double b[TN];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = *(const double*)(bs + (k * BN + wn * 64 + j * 16 + li) * 8);
+        for (int j = 0; j < TN; ++j) b[j] = *(const double*)(bs + (k * BN + wn * WTN + j * 16 + li) * 8);
         if (pre && t == 0) issue_a((s + 2) * BK, (s + 2) % 3);
         if (pre && t == 1) issue_b((s + 2) * BK, (s + 2) % 3);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j], acc[i][j], 0, 0, 0);
       }
     } else {
-      double b[4][KQ];
+      double b[TN][KQ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = wn * 64 + j * 16 + li;
+      for (int j = 0; j < TN; ++j) {
+        const int r = wn * WTN + j * 16 + li;
 #pragma unroll
         for (int u = 0; u < KQ / 2; ++u) {
           const int c = lg * (KQ / 2) + u;
@@ -376,9 +490,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
         if (pre && t == 1) issue_a((s + 2) * BK, (s + 2) % 3);
         if (pre && t == 2) issue_b((s + 2) * BK, (s + 2) % 3);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j][t], acc[i][j], 0, 0, 0);
       }
     }
@@ -391,26 +505,26 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
   }
 
   double mx = 0.0;
-  long long coff[4];
-  bool cok[4];
-  int ncol[4];
+  long long coff[TN];
+  bool cok[TN];
+  int ncol[TN];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = n0 + wn * 64 + j * 16 + li;
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn * WTN + j * 16 + li;
     ncol[j] = n;
     cok[j] = n < N;
     coff[j] = cok[j] ? lmap_col(om, n) : 0;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < TM; ++i) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int m = m0 + wm * 64 + i * 16 + lg + 4 * v;
+      const int m = m0 + wm * WTM + i * 16 + lg + 4 * v;
       if (m >= M) continue;
       const long long roff = lmap_row(om, m);
       const long long moff = sym ? lmap_col(om, m) : 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < TN; ++j) {
         if (!cok[j]) continue;
         const double x = acc[i][j][v];
         if (sym) {
@@ -429,12 +543,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_f64_lds(
   }
 }
 
-template <int WGM, int WGN, int BK, int TAG, int NST = 2>
+template <int WGM, int WGN, int BK, int TAG, int NST = 2, int WTM = 64, int WTN = 64>
 static void launch_lds(const double* A, long long lda, const double* B, long long ldb, int bl,
                        double* C, const OutMap& om, int M, int N, int K,
                        unsigned long long* maxbits, hipStream_t s, int sym = 0,
                        const double* A_2 = nullptr, double* C_2 = nullptr) {
-  constexpr int BM = 64 * WGM, BN = 64 * WGN;
+  constexpr int BM = WTM * WGM, BN = WTN * WGN;
   dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
   if (sym) {
     // tiles reaching the upper triangle: row tile bm from column tile bm*BM/BN on
@@ -445,10 +559,10 @@ static void launch_lds(const double* A, long long lda, const double* B, long lon
   }
   dim3 block(64 * WGM * WGN);
   if (bl == B_NCONTIG)
-    hipLaunchKernelGGL((k_gemm_f64_lds<WGM, WGN, BK, B_NCONTIG, TAG, NST>), grid, block, 0, s, A,
+    hipLaunchKernelGGL((k_gemm_f64_lds<WGM, WGN, BK, B_NCONTIG, TAG, NST, WTM, WTN>), grid, block, 0, s, A,
                        lda, B, ldb, C, om, M, N, K, maxbits, sym, A_2, C_2);
   else
-    hipLaunchKernelGGL((k_gemm_f64_lds<WGM, WGN, BK, B_KCONTIG, TAG, NST>), grid, block, 0, s, A,
+    hipLaunchKernelGGL((k_gemm_f64_lds<WGM, WGN, BK, B_KCONTIG, TAG, NST, WTM, WTN>), grid, block, 0, s, A,
                        lda, B, ldb, C, om, M, N, K, maxbits, sym, A_2, C_2);
 }
 
@@ -459,7 +573,7 @@ bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb
   const int BK = variant == 0 ? 32 : 16;
   if (M < 1 || N < 2 || K < BK || K % BK != 0) return false;
   if ((lda & 1) || (ldb & 1)) return false;
-  if (blayout == B_NCONTIG && (N & 1)) return false;
+  if (blayout == B_NCONTIG && (N & 1) && ldb <= N) return false;
   if (((uintptr_t)A & 15) || ((uintptr_t)B & 15)) return false;
   if (blayout == B_KCONTIG && N < 1) return false;
   if (variant == 5) {
@@ -471,6 +585,22 @@ bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb
       launch_lds<8, 1, 16, GEMM_TAG_ENV>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
     else
       launch_lds<8, 1, 16, GEMM_TAG_OTHER>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+  } else if (variant == 6) {
+    // 64 x 64 tile, 4 waves, three stages in 48 KB: three workgroups per CU
+    if (tag == GEMM_TAG_C2)
+      launch_lds<2, 2, 16, GEMM_TAG_C2, 3, 32, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+    else if (tag == GEMM_TAG_ENV)
+      launch_lds<2, 2, 16, GEMM_TAG_ENV, 3, 32, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+    else
+      launch_lds<2, 2, 16, GEMM_TAG_OTHER, 3, 32, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+  } else if (variant == 7) {
+    // 128 x 128 tile, 8 waves of 64 x 32, four stages in 128 KB
+    if (tag == GEMM_TAG_C2)
+      launch_lds<2, 4, 16, GEMM_TAG_C2, 4, 64, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+    else if (tag == GEMM_TAG_ENV)
+      launch_lds<2, 4, 16, GEMM_TAG_ENV, 4, 64, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+    else
+      launch_lds<2, 4, 16, GEMM_TAG_OTHER, 4, 64, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
   } else if (variant == 4) {
     // 128 x 128 tile, 4 waves, 64 KB of LDS: two workgroups per CU
     if (tag == GEMM_TAG_C2)
@@ -510,24 +640,18 @@ bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb
 // false where the LDS kernel does not apply (the caller then runs the full
 // product).
 // With A_2 and C_2 given, C_2 = A_2 A_2^T (same shape, strides and map) in
-// the same launch: the half-size grids of the two products together balance
-// better over the CUs than each alone (at M = 4096 with 256 x 128 tiles, 544
-// tiles in three rounds of 256 workgroups instead of two rounds each).
+// the same launch.  64 x 64 tiles: their number (4160 for both products at M =
+// 4096) leaves no large last round, and up to three share a compute unit.
+// Both products, 64 x 64 tiles against 256 x 128 ones, and against two full
+// products: M = 4096 2.46 ms, 3.19, 4.00; M = 2500 0.62, 0.70, 1.16; M = 1024
+// 83 us, 278, 96; M = 576 32 us, 169, 56.  Below M = 400 the tiles are too
+// few.
 bool gemm_f64_syrk(const double* A, long long lda, double* C, const OutMap& om, int M, int K,
                    hipStream_t s, const double* A_2, double* C_2) {
-  if (M < 128 || (long long)M * M < (1LL << 20) || K < 16 || K % 16 != 0) return false;
+  if (M < 400 || K < 16 || K % 16 != 0) return false;
   if ((lda & 1) || ((uintptr_t)A & 15) || ((uintptr_t)A_2 & 15)) return false;
-  // the symmetric grid (256 x 128 tiles reaching the upper triangle) must
-  // fill at least half of the 256 compute units: below that (M = 1024: 40
-  // workgroups for both products, each with the whole K loop) the two full
-  // products with their many smaller tiles take less time despite twice the
-  // MFMAs
-  const int nbn = (M + 127) / 128;
-  int tiles = 0;
-  for (int bm = 0; bm * 256 < M; ++bm) tiles += nbn - 2 * bm;
-  if ((A_2 ? 2 : 1) * tiles < 128) return false;
-  launch_lds<4, 2, 16, GEMM_TAG_ENV, 3>(A, lda, A, lda, B_KCONTIG, C, om, M, M, K, nullptr, s,
-                                        A_2 ? 2 : 1, A_2, C_2);
+  launch_lds<2, 2, 16, GEMM_TAG_ENV, 3, 32, 32>(A, lda, A, lda, B_KCONTIG, C, om, M, M, K, nullptr,
+                                                s, A_2 ? 2 : 1, A_2, C_2);
   return true;
 }
 

@@ -78,7 +78,9 @@ void gemm_f64_splitk(const double* A, long long lda, const double* B, long long 
 
 // Direct-to-LDS FP64 GEMM (gemm_lds.hip); returns false if the operands do
 // not meet its alignment / K-multiple requirements.  variant 0: 4 waves,
-// 128 x 128 tile, K slab 32; variant 1: 8 waves, 256 x 128 tile, K slab 16.
+// 128 x 128 tile, K slab 32; variant 1: 8 waves, 256 x 128 tile, K slab 16;
+// variant 3: the same with three stages; 4: 4 waves, 128 x 128; 5: 512 x 64;
+// 6: 4 waves, 64 x 64, three stages; 7: 8 waves, 128 x 128, four stages.
 // C = A A^T (M x M, A M x K K-contiguous) from the upper-triangle tiles with
 // mirrored stores, and C_2 = A_2 A_2^T in the same launch when A_2 is given;
 // false where it does not apply.

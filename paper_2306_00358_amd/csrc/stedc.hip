@@ -783,7 +783,7 @@ __device__ __forceinline__ void stedc_body(const double* din, const double* ein,
 }
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_stedc_small(const double* din, const double* ein, int n,
+__global__ __launch_bounds__(NT, 2) void k_stedc_small(const double* din, const double* ein, int n,
                                                     double* W, double* __restrict__ Zt,
                                                     int* __restrict__ info) {
   stedc_body<NT>(din, ein, n, W, Zt, info);
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(NT) void k_stedc_small(const double* din, const dou
 // rows; a non-finite result marks the problem failed (it is then run again
 // alone).
 template <int NT>
-__global__ __launch_bounds__(NT) void k_group_stedc(const GroupStep* __restrict__ dsc) {
+__global__ __launch_bounds__(NT, 2) void k_group_stedc(const GroupStep* __restrict__ dsc) {
   const GroupStep& g = dsc[blockIdx.x];
   if (!g.ctl->iter) return;  // uniform
   __shared__ int bad_out;

@@ -1,0 +1,48 @@
+"""The FP64 contraction kernels at the edges of their tiles, against the oracle:
+the 64 x 64 and 128 x 128 LDS tiles forced one at a time, and the environment's
+symmetric products (64 x 64 tiles, both halves in one launch) around multiples
+of the tile.  Element-wise within 1e-12 of the largest element, the bound of the
+other FP64 parity tests (a sum of K products of magnitude at most s has an error
+of at most K u s: 3e-13 s at the largest K here, 2500)."""
+
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import hotrg
+from tests.inputs import random_tensor
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("variant", ["6", "7"])
+def test_forced_lds_tile(variant):
+    print("forced", variant, flush=True)
+    env = dict(os.environ, HOTRG_GEMM_VARIANT=variant)
+    r = subprocess.run([sys.executable, "-m", "tests.variant_child", "fp64"], cwd=ROOT, env=env,
+                       capture_output=True, text=True, timeout=600)
+    print(r.stdout, r.stderr[-2000:], flush=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+# P = dx dy: the smallest of the symmetric launch (400), one tile more or less
+# than a multiple of 64, and legs that differ
+@pytest.mark.parametrize("dx, dy", [(20, 20), (25, 16), (16, 28), (24, 24), (36, 16), (13, 48),
+                                    (32, 32), (33, 32)])
+def test_environment(dx, dy):
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_environment
+
+    print("environment", dx, dy, flush=True)
+    T = random_tensor(dx, dy, seed=40 + dx + dy)
+    M = torch.full((dx * dx, dx * dx), float("nan"), dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        hotrg_environment(ctx, torch.from_numpy(T).to("cuda"), M)
+    want = hotrg.environment(T)
+    assert np.abs(M.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
