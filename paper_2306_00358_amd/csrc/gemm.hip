@@ -15,6 +15,7 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -227,6 +228,205 @@ void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, i
                        d_items, d_begin, count);
 }
 
+// Small products: one BT x BT output tile per workgroup, its K split over the
+// workgroup's NWV waves, operands loaded from global memory straight into the
+// MFMA's registers (no LDS until the partial tiles of the waves are summed, in
+// wave order).  Lane (i, g) = (lane % 16, lane / 16) takes k = 4 g .. 4 g + 3
+// of each 16-wide slab (two 16-byte loads per row when VEC: even strides and
+// 16-byte aligned bases; B_NCONTIG loads are 8 bytes, 16 lanes to a 128-byte
+// line); wave w takes slabs w, w + NWV, ...  K need not be a multiple of
+// anything: the last slab is loaded element by element with zeros past K.
+// With sub, C -= sigma * sub (sub laid out like C, row-major).
+// What bounds these products is latency and the few workgroups that larger
+// tiles would give; past a few hundred workgroups it is the K-contiguous
+// loads (64 cycles an instruction: 16 rows, each lane its own 16 bytes), which
+// the tiles in LDS make coalesced.  Against the 64 x 64 tiles staged through
+// registers: 64 x 64 x 64 7.0 -> 3.9 us, 256^3 17.7 -> 5.5, 576^3 35 -> 24,
+// 4096 x 16 x 256 18 -> 5.2; against 4- to 16-way split K with a launch for the
+// partial sums: 64 x 1024 x 1024 14.1 -> 8.4 us, 96 x 2304 x 2304 46 -> 35,
+// 128 x 4096 x 4096 101 -> 97.
+template <int BT, int NWV, int BL, bool VEC>
+__global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
+    const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
+    double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
+    const double* __restrict__ sub, double sigma) {
+  constexpr int TT = BT / 16, E = TT * TT * 256;
+  __shared__ double red[NWV > 1 ? NWV * E : 1];
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
+  const double *ar[TT], *br[TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i) {
+    ar[i] = A + (long long)min(m0 + 16 * i + li, M - 1) * lda;
+    const int n = min(n0 + 16 * i + li, N - 1);
+    br[i] = BL == B_NCONTIG ? B + n : B + (long long)n * ldb;
+  }
+  d4 acc[TT][TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  struct Frag {
+    double a[TT][4], b[TT][4];
+  };
+  auto load = [&](int s, Frag& f) {
+    const int k = 16 * s + 4 * lg;
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+#pragma unroll
+      for (int t = 0; t < 4; t += 2) {
+        if constexpr (VEC) {
+          const d2 v = *(const d2*)(ar[i] + k + t);
+          f.a[i][t] = v.x;
+          f.a[i][t + 1] = v.y;
+        } else {
+          f.a[i][t] = ar[i][k + t];
+          f.a[i][t + 1] = ar[i][k + t + 1];
+        }
+        if constexpr (BL == B_NCONTIG) {
+          f.b[i][t] = br[i][(long long)(k + t) * ldb];
+          f.b[i][t + 1] = br[i][(long long)(k + t + 1) * ldb];
+        } else if constexpr (VEC) {
+          const d2 v = *(const d2*)(br[i] + k + t);
+          f.b[i][t] = v.x;
+          f.b[i][t + 1] = v.y;
+        } else {
+          f.b[i][t] = br[i][k + t];
+          f.b[i][t + 1] = br[i][k + t + 1];
+        }
+      }
+    }
+  };
+  auto mul = [&](const Frag& f) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i][t], f.b[j][t], acc[i][j], 0, 0, 0);
+  };
+  const int full = K >> 4;
+  int s = w;
+  if (s < full) {
+    // two slabs in flight ahead of the products
+    Frag f0, f1;
+    load(s, f0);
+    load(s + NWV < full ? s + NWV : s, f1);
+    for (; s < full; s += NWV) {
+      Frag f2;
+      load(s + 2 * NWV < full ? s + 2 * NWV : s, f2);
+      mul(f0);
+      f0 = f1;
+      f1 = f2;
+    }
+  }
+  if ((K & 15) && s == full) {  // uniform: the wave whose turn the last slab is
+    Frag f;
+    const int k = 16 * full + 4 * lg;
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const bool in = k + t < K;
+        f.a[i][t] = in ? ar[i][k + t] : 0.0;
+        f.b[i][t] = in ? br[i][BL == B_NCONTIG ? (long long)(k + t) * ldb : k + t] : 0.0;
+      }
+    mul(f);
+  }
+  // element e = ((i TT + j) 4 + v) 64 + lane of the tile
+  double mx = 0.0;
+  auto put = [&](int i, int j, int v, int ln, double x) {
+    const int m = m0 + 16 * i + (ln >> 4) + 4 * v, n = n0 + 16 * j + (ln & 15);
+    if (m < M && n < N) {
+      const long long o = map_row(om, m) + map_col(om, n);
+      if (sub) x -= sigma * sub[o];
+      C[o] = x;
+      mx = fmax(mx, fabs(x));
+    }
+  };
+  if constexpr (NWV == 1) {
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) put(i, j, v, lane, acc[i][j][v]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[w * E + ((i * TT + j) * 4 + v) * 64 + lane] = acc[i][j][v];
+    lds_barrier();
+#pragma unroll
+    for (int e = tid; e < E; e += 64 * NWV) {
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < NWV; ++u) x += red[u * E + e];
+      put(e / (TT * 256), (e >> 8) % TT, (e >> 6) & 3, e & 63, x);
+    }
+  }
+  if (maxbits) {
+    mx = wave_max(mx);
+    if (lane == 0) atomic_max_bits(maxbits, mx);
+  }
+}
+
+template <int BT, int NWV>
+static void launch_small(const double* A, long long lda, const double* B, long long ldb, int bl,
+                         double* C, const OutMap& om, int M, int N, int K,
+                         unsigned long long* maxbits, hipStream_t s, const double* sub,
+                         double sigma) {
+  const dim3 grid((N + BT - 1) / BT, (M + BT - 1) / BT), block(64 * NWV);
+  const bool vec = !(lda & 1) && !((uintptr_t)A & 15) &&
+                   (bl == B_NCONTIG || (!(ldb & 1) && !((uintptr_t)B & 15)));
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub, sigma);
+  };
+  if (bl == B_NCONTIG) {
+    if (vec) go(k_gemm_f64_small<BT, NWV, B_NCONTIG, true>);
+    else go(k_gemm_f64_small<BT, NWV, B_NCONTIG, false>);
+  } else {
+    if (vec) go(k_gemm_f64_small<BT, NWV, B_KCONTIG, true>);
+    else go(k_gemm_f64_small<BT, NWV, B_KCONTIG, false>);
+  }
+}
+
+// C = A B (- sigma sub) by small tiles; false for the products that belong to
+// the larger ones.  The lines, both sides measured: up to 393216 outputs
+// K-contiguous (576^2: 24 us against 28 with 64 x 64 LDS tiles; 729^2: 51 against
+// 34) and 524288 N-contiguous (128 x 4096 x 4096, above); short K with many tiles
+// stays with the 64 x 64 ones (256 x 4096 x 16: 5.8 us, 8.7 here).  16 x 16 tiles
+// up to one per compute unit (256^3: 5.5 us, 8.7 with 32 x 32; 400^3: 13.7 and
+// 11.2); four waves once each has a slab.
+static bool gemm_f64_small(const double* A, long long lda, const double* B, long long ldb, int bl,
+                           double* C, const OutMap& om, int M, int N, int K,
+                           unsigned long long* maxbits, hipStream_t s, const double* sub = nullptr,
+                           double sigma = 0.0) {
+  const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16), mn = (long long)M * N;
+  if (K < 1 || mn > (bl == B_KCONTIG ? 393216 : 524288) || (K < 32 && t16 > 512)) return false;
+  const int slabs = (K + 15) / 16;
+  auto go = [&](auto nw) {
+    constexpr int NWV = decltype(nw)::value;
+    if (t16 <= 256)
+      launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma);
+    else
+      launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma);
+  };
+  if (slabs >= 4)
+    go(std::integral_constant<int, 4>{});
+  else if (slabs >= 2)
+    go(std::integral_constant<int, 2>{});
+  else
+    go(std::integral_constant<int, 1>{});
+  return true;
+}
+
 // Large-GEMM variant: 128 x 128 block tile, K slab BK = 32, LDS double
 // buffered so that one barrier per slab separates the MFMAs of slab s from
 // the LDS stores of slab s+1 (whose global loads were issued before the
@@ -389,6 +589,11 @@ void gemm_f64_splitk(const double* A, long long lda, const double* B, long long 
                      double* C, long long ldc, int M, int N, int K, int kchunk, double* partials,
                      hipStream_t s, const double* sub, double sigma) {
   if (M <= 0 || N <= 0) return;
+  // (long sums of few tiles keep the split: 64 x 64 x 1024 8.7 us, 9.8 by small
+  // tiles; 64 x 64 x 576 8.6 and 7.1)
+  if ((N > 256 || K <= 576) &&
+      gemm_f64_small(A, lda, B, ldb, blayout, C, out_rowmajor(N), M, N, K, nullptr, s, sub, sigma))
+    return;
   const int parts = (K + kchunk - 1) / kchunk;
   const long long cstride = (long long)M * N;
   launch_f64<64, 64, 16>(A, lda, B, ldb, blayout, partials, out_rowmajor(N), M, N, K, nullptr, s,
@@ -553,6 +758,9 @@ void gemm_f64(const double* A, long long lda, const double* B, long long ldb, in
         return true;
     }
   };
+  if (forced < 0 &&
+      gemm_f64_small(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s))
+    return;
   if (!no_tune && forced < 0 && autotune_on() && (long long)M * N >= (1LL << 20)) {
     bool tuned = false;
     const int c = tune(make_key(0, lda, ldb, blayout, om, M, N, K, maxbits != nullptr, tag),

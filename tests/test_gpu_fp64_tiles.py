@@ -46,3 +46,28 @@ def test_environment(dx, dy):
         hotrg_environment(ctx, torch.from_numpy(T).to("cuda"), M)
     want = hotrg.environment(T)
     assert np.abs(M.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
+
+
+# the small tiles (K split over the waves of a workgroup): one slab and less,
+# remainders past a slab, odd strides, more slabs than waves, both tile sizes
+@pytest.mark.parametrize("dx, dy, dn", [(2, 2, 2), (3, 2, 9), (4, 4, 7), (5, 5, 5), (8, 8, 8),
+                                        (7, 11, 13), (16, 16, 16), (9, 17, 20), (21, 21, 21),
+                                        (23, 23, 23)])
+def test_coarse_and_environment_small(dx, dy, dn):
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_coarse, hotrg_environment
+    from tests.inputs import random_projector
+
+    print("small", dx, dy, dn, flush=True)
+    T, U = random_tensor(dx, dy, seed=70 + dx), random_projector(dx, dn, seed=90 + dn)
+    Tg, Ug = torch.from_numpy(T).to("cuda"), torch.from_numpy(U).to("cuda")
+    M = torch.full((dx * dx, dx * dx), float("nan"), dtype=torch.float64, device="cuda")
+    Tt = torch.full((dn, dy, dn, dy), float("nan"), dtype=torch.float64, device="cuda")
+    mx = torch.zeros(1, dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        hotrg_environment(ctx, Tg, M)
+        hotrg_coarse(ctx, Tg, Ug, Tt, mx)
+    for got, want in ((M, hotrg.environment(T)), (Tt, hotrg.coarse_tensor(T, U))):
+        assert np.abs(got.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
+    assert mx.item() == Tt.abs().max().item()
