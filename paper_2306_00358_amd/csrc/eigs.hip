@@ -1073,25 +1073,6 @@ __global__ void k_ritz_residual(const double* __restrict__ Yx, const double* __r
   if (t == 0) res[i] = sqrt(red[0]);
 }
 
-// trace of M (n x n) -> *out, fixed-order tree
-__global__ void k_trace(const double* __restrict__ M, int n, double* out) {
-  __shared__ double red[256];
-  const int t = threadIdx.x;
-  double s = 0.0;
-  for (int i = t; i < n; i += 256) s += M[(long long)i * n + i];
-  red[t] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] += red[t + o];
-    __syncthreads();
-  }
-  if (t == 0) *out = red[0];
-}
-
-void launch_trace(const double* M, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, M, n, out);
-}
-
 static inline int splitk_chunk(int K) {
   // about 32 partial products, each K chunk a multiple of 16
   int c = (K + 31) / 32;

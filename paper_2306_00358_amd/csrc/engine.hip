@@ -77,7 +77,7 @@ struct hotrg_ctx {
   size_t in_use = 0;
   rocblas_handle blas = nullptr;
   // step workspace, grown on demand
-  Buf A1, A2, M, W, E, Ucan, U1, U3, X1, X2, Tt, scal, EW, Xr;
+  Buf A1, A2, M, W, E, U1, U3, X1, X2, Tt, scal, EW, Xr;
   // two-sided isometry: mirrored operands, right environment and its solve,
   // and its step record / kept count / trace / spectrum (Side)
   Buf Tm, Xm, M2, W2, Xr2, Side;
@@ -287,10 +287,13 @@ void environment_f64(hotrg_ctx* c, const double* Tn, const double* Xt, int dx, i
   // rows (i,e): i -> dx*dy^2, e -> dy; cols (k,f): k -> dy^2, f -> 1
   // A1[(j,e),(l,f)] = sum_{a,b} T[j,a,b,e] T[l,a,b,f] from Xt[(l,d),(u,r)], stored as A1'[(j,l),(e,f)]
   // Both halves are Gram matrices X X^T: where it applies, one launch
-  // computes the upper triangles of both and mirrors them (half the MFMAs).
+  // computes the upper triangles of both and mirrors them (half the MFMAs),
+  // and below that one launch of small tiles takes both.
   const OutMap o2 = omap2(dy, dx * K2, dy, dy, K2, 1);
   if (!gemm_f64_syrk(Tn, P, (double*)c->A2.p, o2, (int)P, (int)P, c->stream, Xt,
-                     (double*)c->A1.p)) {
+                     (double*)c->A1.p) &&
+      !gemm_f64_small_pair(Tn, Xt, P, (double*)c->A2.p, (double*)c->A1.p, o2, (int)P, (int)P,
+                           c->stream)) {
     gemm_f64(Tn, P, Tn, P, B_KCONTIG, (double*)c->A2.p, o2, (int)P, (int)P, (int)P, nullptr,
              c->stream, GEMM_TAG_ENV);
     gemm_f64(Xt, P, Xt, P, B_KCONTIG, (double*)c->A1.p, o2, (int)P, (int)P, (int)P, nullptr,
@@ -309,7 +312,7 @@ namespace hotrg {
 
 // C1, C2, C3 in FP64 on caller-provided buffers: X1 and X2 hold
 // dn*dx*dy*dx*dy doubles each, Tt receives T~[i,j,k,l] (dims dn,dy,dn,dy),
-// and *maxbits (cleared here by a kernel) max|T~|.  `tag_flags` is or-ed
+// and *maxbits (cleared by the caller's launch_layout_u) max|T~|.  `tag_flags` is or-ed
 // into every GEMM tag (GEMM_NO_TUNE: fixed tile rule, no measurement, and no
 // per-phase timing events: the allocation-free entry point's path).
 void coarse_f64_into(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1,
@@ -336,7 +339,6 @@ void coarse_f64_into(hotrg_ctx* c, const double* Tn, const double* Tp, const dou
   // C3: rows (i,j,l) = (ij)*dy + l, cols k; K = (d,e).
   //     T~[i,j,k,l] at ((ij)*dn + k)*dy + l
   if (marks) mark(c, HOTRG_PHASE_C3);
-  launch_store((double*)maxbits, 0.0, c->stream);  // a kernel, not a memset
   //     rows (ij,l): ij -> dn*dy, l -> 1; cols k -> dy
   const OutMap o3 = omap2(dy, (long long)dn * dy, 1, 1, dy, 0);
   gemm_f64(X2, n, U3, dn, B_NCONTIG, Tt, o3, dn * dy * dy, dn, (int)n, maxbits, c->stream,
@@ -361,7 +363,8 @@ void coarse_f64(hotrg_ctx* c, const double* Tn, const double* Tp, const double* 
 }
 
 void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, bool src_f32,
-                      bool rotate, int dx, int dy, const unsigned long long* mb);
+                      bool rotate, int dx, int dy, const unsigned long long* mb,
+                      const NormArgs* norm = nullptr);
 
 hotrg_state* new_state(hotrg_ctx* c, const std::vector<double>& T0, int dx, int dy, int prec) {
   for (double v : T0)
@@ -401,17 +404,50 @@ int step_precision(const hotrg_state* st, int k, int dx, int dy, int d_cut) {
 
 int rp_mode(int prec) { return prec == HOTRG_FP32 ? RP_F32 : RP_BF16X3; }
 
+// The operand layouts as strides over (l, u, r, d).  FP64: natural; Xt rows (l,d),
+// columns (u,r); Tp rows (l,u), columns (d,r) (T[a,c,e,l] read as rows (a,c),
+// columns (l,e)).
+PrepOut prep_natural(void* p, long long X, long long Y) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * X * Y, X * Y, Y, 1}};
+}
+PrepOut prep_xt(void* p, long long X, long long Y) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * Y * X, X, 1, Y * X}};
+}
+PrepOut prep_tp(void* p, long long X, long long Y) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * Y * X, Y * X, 1, X}};
+}
+
+// The reduced-precision operands of a state, rows zero-padded to multiples of 32:
+// OT rows (l,u), K (r,d) (and, in that order, the FP32 natural tensor); OX rows
+// (l,d), K (u,r); OC1 rows (u,r,d), K l; OC2 rows (d,r), K (l,u).
+void prep_reduced(PrepOut (&outs)[4], hotrg_state* st, int mode, long long X, long long Y) {
+  const long long ldP = pad32(X * Y), ldx = pad32(X);
+  const long long dsts[4][4] = {{Y * ldP, ldP, Y, 1},
+                                {Y * ldP, X, 1, ldP},
+                                {1, X * Y * ldx, Y * ldx, ldx},
+                                {Y, 1, ldP, X * ldP}};
+  for (int i = 0; i < 4; ++i) {
+    outs[i] = PrepOut{st->RO[i][0].p, mode == RP_F32 ? nullptr : st->RO[i][1].p,
+                      i == 0 ? (float*)st->Tn32.p : nullptr, mode, {}};
+    for (int q = 0; q < 4; ++q) outs[i].dst[q] = dsts[i][q];
+  }
+}
+
 // Operands of a step with dims (dx, dy) in precision `prec`, from the tensor
 // `src` (FP64 or FP32; legs transposed if `rotate`; divided by the max read
-// from `mb`).  Also records the state's natural tensor in matching format.
+// from `mb` when given), and the log-norm of `norm` when given.  Also records
+// the state's natural tensor in matching format.
 void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, bool src_f32,
-                      bool rotate, int dx, int dy, const unsigned long long* mb) {
+                      bool rotate, int dx, int dy, const unsigned long long* mb,
+                      const NormArgs* norm) {
   const size_t ne = (size_t)dx * dy * dx * dy;
   if (prec == HOTRG_FP64) {
     ensure_keep(c, st->Tn, ne * 8, 0);
     ensure_keep(c, st->Xt, ne * 8, 0);
     ensure_keep(c, st->Tp, ne * 8, 0);
-    launch_prep(src, src_f32, rotate, dx, dy, mb, st->Tn.p, st->Xt.p, st->Tp.p, false, c->stream);
+    const PrepOut outs[3] = {prep_natural(st->Tn.p, dx, dy), prep_xt(st->Xt.p, dx, dy),
+                             prep_tp(st->Tp.p, dx, dy)};
+    launch_prep(src, src_f32, rotate, dx, dy, mb, outs, 3, norm, c->stream);
     st->cur_f32 = false;
   } else {
     const int mode = rp_mode(prec);
@@ -420,18 +456,16 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
     const size_t rows[4] = {(size_t)P, (size_t)P, (size_t)dy * dx * dy, (size_t)P};
     const size_t ld[4] = {(size_t)ldP, (size_t)ldP, (size_t)ldx, (size_t)ldP};
     const bool padded[4] = {ldP != P, ldP != P, ldx != dx, ldP != P};
-    RpOps ops;
+    PrepOut outs[4];
     ensure_keep(c, st->Tn32, ne * 4, 0);
     for (int i = 0; i < 4; ++i) {
       for (int h = 0; h < (mode == RP_F32 ? 1 : 2); ++h) {
         ensure_keep(c, st->RO[i][h], rows[i] * ld[i] * es, 0);
         if (padded[i]) HIPCHK(hipMemsetAsync(st->RO[i][h].p, 0, rows[i] * ld[i] * es, c->stream));
       }
-      ops.hi[i] = st->RO[i][0].p;
-      ops.lo[i] = mode == RP_F32 ? nullptr : st->RO[i][1].p;
     }
-    launch_prep_rp(src, src_f32, rotate, dx, dy, mb, (float*)st->Tn32.p, mode, ops, ldP, ldx,
-                   c->stream);
+    prep_reduced(outs, st, mode, dx, dy);
+    launch_prep(src, src_f32, rotate, dx, dy, mb, outs, 4, norm, c->stream);
     st->cur_f32 = true;
   }
   st->ops_prec = prec;
@@ -511,7 +545,6 @@ void coarse_rp(hotrg_ctx* c, hotrg_state* st, int mode, int dx, int dy, int dn,
                      nullptr, c->stream, GEMM_TAG_C2);
   // C3: rows (ij,l): ij -> dn*dy, l -> 1; cols k -> dy
   mark(c, HOTRG_PHASE_C3);
-  launch_store((double*)maxbits, 0.0, c->stream);
   const OutMap o3 = omap2(dy, (long long)dn * dy, 1, 1, dy, 0);
   ok = ok && gemm_rp(mode, op(c->RX2), ldn, op(c->RU3), ldn, RP_OUT_F32, c->Tt.p, nullptr, o3,
                      (int)x2rows, dn, (int)ldn, maxbits, c->stream, GEMM_TAG_OTHER);
@@ -552,11 +585,11 @@ static bool eig_block(int n, int dn, int spec_len, int eig_mode, int* need_out, 
 // Leading eigenpairs of the symmetric n x n matrix in Mb: eigenvalues
 // (ascending) into Wb, eigenvector rows into Xb (p rows, iterative; n rows of
 // which the last `need` count, small dense) or over Mb (n rows, dense); returns
-// the rows and their count.  A non-converged dense
-// solve is folded into *sticky; an iterative one that does not converge falls
-// back to the dense solver.
+// the rows and their count.  A dense solve reports to **info (the caller's
+// launch_spectrum folds it into its sticky flag), an iterative one sets *info
+// to null; one that does not converge falls back to the dense solver.
 static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n, int need, int p,
-                                  bool sub_ok, EigHint& h, int* inf, int* sticky, int* cols_out,
+                                  bool sub_ok, EigHint& h, int** info, int* cols_out,
                                   double tol = 5e-14) {
   ensure(c, Wb, (size_t)n * 8);
   if (sub_ok) {
@@ -580,6 +613,7 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
     c->last_eig_resid = resid;
     if (ok) {
       *cols_out = p;
+      *info = nullptr;
       return (const double*)Xb.p;
     }
   }
@@ -588,6 +622,7 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
   // back-transform of the rows needed (the small solver keeps its eigenvectors
   // apart from Mb, which holds the reflectors); larger ones rocSOLVER dsyevd
   const bool small = n >= 3 && n <= 128;
+  int* inf = *info;
   ensure(c, c->E, (size_t)n * 8);
   if (small) ensure(c, Xb, (size_t)n * n * 8);
   double* vecs = (double*)(small ? Xb.p : Mb.p);
@@ -599,8 +634,6 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
     if (rs != rocblas_status_success)
       fail(HOTRG_ERR_DEVICE, "rocsolver_dsyevd failed with status " + std::to_string((int)rs));
   }
-  // a non-converged solve marks the caller's flag: later solves overwrite `inf`
-  launch_fold_info(inf, sticky, 0, c->stream);
   *cols_out = n;
   return vecs;
 }
@@ -618,21 +651,18 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   unsigned long long* mb = (unsigned long long*)c->scal.p;
   int* info = (int*)((char*)c->scal.p + 8);
   int* kept = (int*)((char*)c->scal.p + 16);
-  unsigned long long* one = (unsigned long long*)((char*)c->scal.p + 56);
   int* st_fail = (int*)((char*)st->acc.p + 8);
 
   const int sp = step_precision(st, k, dx, dy, o->d_cut);
   if (sp != st->ops_prec) {
     // operands were prepared for another precision (d_cut changed): rebuild
-    const unsigned long long one_bits = 0x3ff0000000000000ULL;
-    HIPCHK(hipMemcpyAsync(one, &one_bits, 8, hipMemcpyHostToDevice, c->stream));
     const size_t ne = (size_t)dx * dy * dx * dy;
     Buf tmp;
     ensure(c, tmp, ne * (st->cur_f32 ? 4 : 8));
     HIPCHK(hipMemcpyAsync(tmp.p, st->cur_f32 ? st->Tn32.p : st->Tn.p, ne * (st->cur_f32 ? 4 : 8),
                           hipMemcpyDeviceToDevice, c->stream));
     const bool f32 = st->cur_f32;
-    prepare_operands(c, st, sp, tmp.p, f32, false, dx, dy, one);
+    prepare_operands(c, st, sp, tmp.p, f32, false, dx, dy, nullptr);
     HIPCHK(hipStreamSynchronize(c->stream));
     ctx_free(c, tmp);
   }
@@ -647,26 +677,23 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
     environment_f64(c, (const double*)st->Tn.p, (const double*)st->Xt.p, dx, dy);
   else
     environment_rp(c, st, rp_mode(sp), dx, dy);
-  launch_symmetrize((double*)c->M.p, n, c->stream);
-  // FP64 eigendecomposition, spectrum and projector
-  ensure(c, c->E, (size_t)n * 8);
   double* trace = (double*)((char*)c->scal.p + 40);
-  launch_trace((const double*)c->M.p, n, trace, c->stream);
+  launch_symmetrize((double*)c->M.p, n, trace, c->stream);
+  // FP64 eigendecomposition, spectrum and projector
   mark(c, HOTRG_PHASE_EIGH);
   // leading eigenpairs: block subspace iteration when D' is small against n
   int need = 0, p = 0;
   const bool sub_ok = eig_block(n, dn, o->spec_len, o->eig, &need, &p);
-  auto solve = [&](Buf& Mb, Buf& Wb, Buf& Xb, int side, int* inf, int* cols_out) {
+  auto solve = [&](Buf& Mb, Buf& Wb, Buf& Xb, int side, int** inf, int* cols_out) {
     return leading_eigs(c, Mb, Wb, Xb, n, need, p, sub_ok, st->eig[(st->k & 1) + 2 * side], inf,
-                        st_fail, cols_out, eig_tolerance(sp));
+                        cols_out, eig_tolerance(sp));
   };
   int cols = n;
-  const double* evec = solve(c->M, c->W, c->Xr, 0, info, &cols);
-  if (k == c->test_fail_step) launch_fold_info(info, st_fail, 1, c->stream);
+  const double* evec = solve(c->M, c->W, c->Xr, 0, &info, &cols);
+  if (k == c->test_fail_step) launch_fail_flag(st_fail, c->stream);
   mark(c, HOTRG_PHASE_PROJ);
   launch_spectrum((const double*)c->W.p, cols, n, dn, o->trunc, o->degen_tol, st->spec_len,
-                  trace, spec, rec, kept, c->stream);
-  launch_store(rec + 5, 0.0, c->stream);
+                  trace, spec, rec, kept, info, st_fail, c->stream);
   if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
     // the right pair of legs: environment of the reflected tensor (FP64)
     if (sp != HOTRG_FP64) fail(HOTRG_ERR_INVALID, "two-sided isometry needs FP64 contractions");
@@ -683,14 +710,13 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
     launch_prep_mirror((const double*)st->Tn.p, dx, dy, (double*)c->Tm.p, (double*)c->Xm.p,
                        c->stream);
     environment_f64(c, (const double*)c->Tm.p, (const double*)c->Xm.p, dx, dy, &c->M2);
-    launch_symmetrize((double*)c->M2.p, n, c->stream);
-    launch_trace((const double*)c->M2.p, n, trace2, c->stream);
+    launch_symmetrize((double*)c->M2.p, n, trace2, c->stream);
     mark(c, HOTRG_PHASE_EIGH);
     int cols2 = n;
-    const double* evec2 = solve(c->M2, c->W2, c->Xr2, 1, info2, &cols2);
+    const double* evec2 = solve(c->M2, c->W2, c->Xr2, 1, &info2, &cols2);
     mark(c, HOTRG_PHASE_PROJ);
     launch_spectrum((const double*)c->W2.p, cols2, n, dn, o->trunc, o->degen_tol, st->spec_len,
-                    trace2, spec2, rec2, kept2, c->stream);
+                    trace2, spec2, rec2, kept2, info2, st_fail, c->stream);
     double errs[2] = {0.0, 0.0};
     int sticky = 0;
     HIPCHK(hipMemcpyAsync(&errs[0], rec + 1, 8, hipMemcpyDeviceToHost, c->stream));
@@ -710,12 +736,13 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
       cols = cols2;
     }
   }
-  ensure(c, c->Ucan, (size_t)n * dn * 8);
-  launch_isometry(evec, cols, n, dn, kept, (double*)c->Ucan.p, c->stream);
+  // the projector in the contractions' layouts, from the last eigenvector rows
+  const double* top = evec + (long long)(cols - 1) * n;
   if (sp == HOTRG_FP64) {
     ensure(c, c->U1, (size_t)n * dn * 8);
     ensure(c, c->U3, (size_t)n * dn * 8);
-    launch_layout_u((const double*)c->Ucan.p, dx, dn, c->U1.p, c->U3.p, false, c->stream);
+    launch_layout_u(top, 1, -n, kept, dx, dn, kFmtF64, c->U1.p, nullptr, c->U3.p, nullptr, dx, dn,
+                    mb, c->stream);
     // the three contractions, max|T~|
     coarse_f64(c, (const double*)st->Tn.p, (const double*)st->Tp.p, (const double*)c->U1.p,
                (const double*)c->U3.p, dx, dy, dn, mb);
@@ -729,18 +756,17 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
       if (ldx != dx) HIPCHK(hipMemsetAsync(c->RU1[h].p, 0, (size_t)dn * dx * ldx * es, c->stream));
       if (ldn != n) HIPCHK(hipMemsetAsync(c->RU3[h].p, 0, (size_t)dn * ldn * es, c->stream));
     }
-    launch_layout_u_rp((const double*)c->Ucan.p, dx, dn, mode, c->RU1[0].p,
-                       mode == RP_F32 ? nullptr : c->RU1[1].p, c->RU3[0].p,
-                       mode == RP_F32 ? nullptr : c->RU3[1].p, ldx, ldn, c->stream);
+    launch_layout_u(top, 1, -n, kept, dx, dn, mode, c->RU1[0].p, c->RU1[1].p, c->RU3[0].p,
+                    c->RU3[1].p, ldx, ldn, mb, c->stream);
     coarse_rp(c, st, mode, dx, dy, dn, mb);
   }
   // ln n_k, torus estimate; operands of the next step (legs transposed)
   mark(c, HOTRG_PHASE_NORM);
   const bool tt_f32 = sp != HOTRG_FP64;
-  launch_norm(mb, c->Tt.p, tt_f32, dn, dy, std::ldexp(1.0, -k), (double*)st->acc.p, rec, c->stream);
   const int ndx = dy, ndy = dn;
   const int nsp = step_precision(st, k + 1, ndx, ndy, o->d_cut);
-  prepare_operands(c, st, nsp, c->Tt.p, tt_f32, true, ndx, ndy, mb);
+  const NormArgs norm{c->Tt.p, tt_f32, dn, dy, std::ldexp(1.0, -k), (double*)st->acc.p, rec};
+  prepare_operands(c, st, nsp, c->Tt.p, tt_f32, true, ndx, ndy, mb, &norm);
   mark(c, -1);
   HIPCHK(hipGetLastError());
   if (sp != HOTRG_FP64) st->err_bound += kErrPerStep[sp] * std::ldexp(1.0, -k);
@@ -850,7 +876,7 @@ struct GProb {
   std::vector<int> dxs, dys, dns;
   int D = 0, n = 0, p = 0, need = 0, sp = HOTRG_FP64;  // steady dims, block size, precision
   bool dense = false;  // environment diagonalised whole (n <= 128) instead of a block
-  Buf M, eig, U, scal, Tt, U1, U3;
+  Buf M, eig, scal, Tt, U1, U3;
   Buf RA1[2], RA2[2], RX1[2], RX2[2], RU1[2], RU3[2];
   GroupCtl* ctl = nullptr;  // device
   int k_host = 0;           // steps done, as the host counts them
@@ -947,8 +973,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
       environment_f64(c, (const double*)g->st->Tn.p, (const double*)g->st->Xt.p, g->D, g->D, &g->M);
   }
   for (GProb* g : R.act) {
-    launch_symmetrize((double*)g->M.p, g->n, s);
-    launch_trace((const double*)g->M.p, g->n, (double*)((char*)g->scal.p + 8), s);
+    launch_symmetrize((double*)g->M.p, g->n, (double*)((char*)g->scal.p + 8), s);
   }
   // leading eigenpairs: block subspace iteration with a fixed budget (its
   // Rayleigh-Ritz matrices by tridiagonal divide and conquer), or the whole
@@ -989,20 +1014,17 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   group_spectrum(R.steps, G, s);
   for (GProb* g : R.act) {
     const int* kept = (const int*)((char*)g->scal.p + 16);
-    launch_isometry((const double*)((double*)g->eig.p + 4LL * g->p * g->n), g->p, g->n, g->D, kept,
-                    (double*)g->U.p, s);
-    if (red) {
-      const long long ldx = pad32(g->D), ldn = pad32(g->n);
-      launch_layout_u_rp((const double*)g->U.p, g->D, g->D, R.mode, g->RU1[0].p,
-                         split ? g->RU1[1].p : nullptr, g->RU3[0].p, split ? g->RU3[1].p : nullptr,
-                         ldx, ldn, s);
-    } else {
-      launch_layout_u((const double*)g->U.p, g->D, g->D, g->U1.p, g->U3.p, false, s);
-    }
+    const double* top = (const double*)g->eig.p + 4LL * g->p * g->n + (long long)(g->p - 1) * g->n;
+    unsigned long long* mb = (unsigned long long*)g->scal.p;
+    if (red)
+      launch_layout_u(top, 1, -g->n, kept, g->D, g->D, R.mode, g->RU1[0].p, g->RU1[1].p,
+                      g->RU3[0].p, g->RU3[1].p, pad32(g->D), pad32(g->n), mb, s);
+    else
+      launch_layout_u(top, 1, -g->n, kept, g->D, g->D, kFmtF64, g->U1.p, nullptr, g->U3.p, nullptr,
+                      g->D, g->D, mb, s);
   }
   // the three contractions, max|T~|
   if (red) {
-    group_zero_max(R.steps, G, s);
     GTable* tabs[3] = {&R.c1, &R.c2, &R.c3};
     const int outs[3] = {split ? RP_OUT_SPLIT : RP_OUT_F32, split ? RP_OUT_SPLIT : RP_OUT_F32,
                          RP_OUT_F32};
@@ -1047,16 +1069,13 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   for (GProb* g : R.act) {
     const unsigned long long* mb = (const unsigned long long*)g->scal.p;
     if (red) {
-      RpOps ops;
-      for (int i = 0; i < 4; ++i) {
-        ops.hi[i] = g->st->RO[i][0].p;
-        ops.lo[i] = split ? g->st->RO[i][1].p : nullptr;
-      }
-      launch_prep_rp(g->Tt.p, true, true, g->D, g->D, mb, (float*)g->st->Tn32.p, R.mode, ops,
-                     pad32((long long)g->D * g->D), pad32(g->D), s);
+      PrepOut outs[4];
+      prep_reduced(outs, g->st, R.mode, g->D, g->D);
+      launch_prep(g->Tt.p, true, true, g->D, g->D, mb, outs, 4, nullptr, s);
     } else {
-      launch_prep(g->Tt.p, false, true, g->D, g->D, mb, g->st->Tn.p, g->st->Xt.p, g->st->Tp.p,
-                  false, s);
+      const PrepOut outs[3] = {prep_natural(g->st->Tn.p, g->D, g->D), prep_xt(g->st->Xt.p, g->D, g->D),
+                               prep_tp(g->st->Tp.p, g->D, g->D)};
+      launch_prep(g->Tt.p, false, true, g->D, g->D, mb, outs, 3, nullptr, s);
     }
   }
   group_advance(R.steps, G, s);
@@ -1252,7 +1271,7 @@ int steady_step(const hotrg_opts& o, int prec, int dx, int dy, int first_reduced
 }
 
 void free_group_buffers(hotrg_ctx* c, GProb& g) {
-  Buf* bs[] = {&g.M, &g.eig, &g.U, &g.scal, &g.Tt, &g.U1, &g.U3};
+  Buf* bs[] = {&g.M, &g.eig, &g.scal, &g.Tt, &g.U1, &g.U3};
   for (Buf* b : bs) ctx_free(c, *b);
   for (Buf* arr : {g.RA1, g.RA2, g.RX1, g.RX2, g.RU1, g.RU3})
     for (int h = 0; h < 2; ++h) ctx_free(c, arr[h]);
@@ -1384,7 +1403,6 @@ void run_grouped_impl(hotrg_ctx* c, int N, const hotrg_model_params* params,
         const long long D = g.D, n = g.n, pn = (long long)g.p * n, pp = (long long)g.p * g.p;
         ensure(c, g.M, (size_t)(n * n) * 8);
         ensure(c, g.eig, (size_t)(5 * pn + 3 * pp + 2 * g.p + 16) * 8);
-        ensure(c, g.U, (size_t)(n * D) * 8);
         ensure(c, g.scal, 128);
         // sweep shifts of the two step parities (offset 64): none yet
         HIPCHK(hipMemsetAsync((char*)g.scal.p + 64, 0, 16, c->stream));
@@ -1579,7 +1597,7 @@ hotrg_status run_problem(hotrg_ctx* c, const hotrg_model_params* params, const h
 void ctx_trim(hotrg_ctx* c) {
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  Buf* bufs[] = {&c->A1, &c->A2, &c->M, &c->W, &c->E, &c->Ucan, &c->U1, &c->U3,
+  Buf* bufs[] = {&c->A1, &c->A2, &c->M, &c->W, &c->E, &c->U1, &c->U3,
                  &c->X1, &c->X2, &c->Tt, &c->EW, &c->Xr, &c->Tm, &c->Xm, &c->M2,
                  &c->W2, &c->Xr2, &c->Side};
   for (Buf* b : bufs) ctx_free(c, *b);
@@ -1642,7 +1660,7 @@ void hotrg_ctx_destroy(hotrg_ctx* c) {
   hotrg::sched_shutdown(c);
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  Buf* bufs[] = {&c->A1, &c->A2, &c->M, &c->W, &c->E, &c->Ucan, &c->U1, &c->U3,
+  Buf* bufs[] = {&c->A1, &c->A2, &c->M, &c->W, &c->E, &c->U1, &c->U3,
                  &c->X1, &c->X2, &c->Tt, &c->scal, &c->EW, &c->Xr, &c->Tm, &c->Xm,
                  &c->M2, &c->W2, &c->Xr2, &c->Side};
   for (Buf* b : bufs) ctx_free(c, *b);
@@ -1867,12 +1885,9 @@ hotrg_status hotrg_environment(hotrg_ctx* c, int prec, const double* T, int dx, 
     check_dims(dx, dy, 1);
     HIPCHK(hipSetDevice(c->device));
     ensure(c, c->scal, 64);
-    unsigned long long* one = (unsigned long long*)((char*)c->scal.p + 56);
-    const unsigned long long one_bits = 0x3ff0000000000000ULL;
-    HIPCHK(hipMemcpyAsync(one, &one_bits, 8, hipMemcpyHostToDevice, c->stream));
     hotrg_state tmp;  // operands only, freed below
     try {
-      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, one);
+      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, nullptr);
       c->m_step = 0;
       c->m_dx = dx;
       c->m_dy = dy;
@@ -1911,10 +1926,9 @@ hotrg_status hotrg_projector(hotrg_ctx* c, const double* M, int n, int dn, int t
     ensure(c, c->scal, 64);
     ensure(c, c->M, (size_t)n * n * 8);
     HIPCHK(hipMemcpyAsync(c->M.p, M, (size_t)n * n * 8, hipMemcpyDeviceToDevice, c->stream));
-    launch_symmetrize((double*)c->M.p, n, c->stream);
     double* trace = (double*)((char*)c->scal.p + 40);
     int* info = (int*)((char*)c->scal.p + 8);
-    launch_trace((const double*)c->M.p, n, trace, c->stream);
+    launch_symmetrize((double*)c->M.p, n, trace, c->stream);
     int need = 0, p = 0;
     const bool sub_ok = eig_block(n, dn, spec_len, HOTRG_EIG_AUTO, &need, &p);
     // record (6 doubles), sticky flag, kept count, spectrum
@@ -1929,9 +1943,9 @@ hotrg_status hotrg_projector(hotrg_ctx* c, const double* M, int n, int dn, int t
       EigHint h;  // a solve of its own
       int cols = n;
       const double* evec =
-          leading_eigs(c, c->M, c->W, c->Xr, n, need, p, sub_ok, h, info, sticky, &cols);
+          leading_eigs(c, c->M, c->W, c->Xr, n, need, p, sub_ok, h, &info, &cols);
       launch_spectrum((const double*)c->W.p, cols, n, dn, trunc, degen_tol, spec_len, trace,
-                      spec_d, rec, kept_d, c->stream);
+                      spec_d, rec, kept_d, info, sticky, c->stream);
       launch_isometry(evec, cols, n, dn, kept_d, U, c->stream);
       int hk[2] = {0, 0};
       HIPCHK(hipMemcpyAsync(hk, sticky, 2 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1960,13 +1974,10 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
     check_dims(dx, dy, dn);
     HIPCHK(hipSetDevice(c->device));
     ensure(c, c->scal, 64);
-    unsigned long long* one = (unsigned long long*)((char*)c->scal.p + 56);
-    const unsigned long long one_bits = 0x3ff0000000000000ULL;
-    HIPCHK(hipMemcpyAsync(one, &one_bits, 8, hipMemcpyHostToDevice, c->stream));
     unsigned long long* mb = (unsigned long long*)c->scal.p + 4;
     hotrg_state tmp;
     try {
-      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, one);
+      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, nullptr);
       c->m_step = 0;
       c->m_dx = dx;
       c->m_dy = dy;
@@ -1976,7 +1987,8 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
         const size_t nu = (size_t)dx * dx * dn;
         ensure(c, c->U1, nu * 8);
         ensure(c, c->U3, nu * 8);
-        launch_layout_u(U, dx, dn, c->U1.p, c->U3.p, false, c->stream);
+        launch_layout_u(U, dn, 1, nullptr, dx, dn, kFmtF64, c->U1.p, nullptr, c->U3.p, nullptr, dx,
+                        dn, mb, c->stream);
         coarse_f64(c, (const double*)tmp.Tn.p, (const double*)tmp.Tp.p, (const double*)c->U1.p,
                    (const double*)c->U3.p, dx, dy, dn, mb);
         mark(c, -1);
@@ -1991,9 +2003,8 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
           HIPCHK(hipMemsetAsync(c->RU1[h].p, 0, (size_t)dn * dx * ldx * es, c->stream));
           HIPCHK(hipMemsetAsync(c->RU3[h].p, 0, (size_t)dn * ldn * es, c->stream));
         }
-        launch_layout_u_rp(U, dx, dn, mode, c->RU1[0].p, mode == RP_F32 ? nullptr : c->RU1[1].p,
-                           c->RU3[0].p, mode == RP_F32 ? nullptr : c->RU3[1].p, ldx, ldn,
-                           c->stream);
+        launch_layout_u(U, dn, 1, nullptr, dx, dn, mode, c->RU1[0].p, c->RU1[1].p, c->RU3[0].p,
+                        c->RU3[1].p, ldx, ldn, mb, c->stream);
         coarse_rp(c, &tmp, mode, dx, dy, dn, mb);
         mark(c, -1);
         launch_f32_to_f64((const float*)c->Tt.p, Tt, (long long)no, c->stream);

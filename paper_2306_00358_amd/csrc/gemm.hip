@@ -249,7 +249,13 @@ template <int BT, int NWV, int BL, bool VEC>
 __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
     double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
-    const double* __restrict__ sub, double sigma) {
+    const double* __restrict__ sub, double sigma, const double* __restrict__ A_2,
+    double* __restrict__ C_2) {
+  if (blockIdx.z) {  // the second of two products A A^T
+    A = A_2;
+    B = A_2;
+    C = C_2;
+  }
   constexpr int TT = BT / 16, E = TT * TT * 256;
   __shared__ double red[NWV > 1 ? NWV * E : 1];
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -381,12 +387,13 @@ template <int BT, int NWV>
 static void launch_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                          double* C, const OutMap& om, int M, int N, int K,
                          unsigned long long* maxbits, hipStream_t s, const double* sub,
-                         double sigma) {
-  const dim3 grid((N + BT - 1) / BT, (M + BT - 1) / BT), block(64 * NWV);
-  const bool vec = !(lda & 1) && !((uintptr_t)A & 15) &&
+                         double sigma, const double* A_2, double* C_2) {
+  const dim3 grid((N + BT - 1) / BT, (M + BT - 1) / BT, A_2 ? 2 : 1), block(64 * NWV);
+  const bool vec = !(lda & 1) && !((uintptr_t)A & 15) && !((uintptr_t)A_2 & 15) &&
                    (bl == B_NCONTIG || (!(ldb & 1) && !((uintptr_t)B & 15)));
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub, sigma);
+    hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub,
+                       sigma, A_2, C_2);
   };
   if (bl == B_NCONTIG) {
     if (vec) go(k_gemm_f64_small<BT, NWV, B_NCONTIG, true>);
@@ -407,16 +414,19 @@ static void launch_small(const double* A, long long lda, const double* B, long l
 static bool gemm_f64_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                            double* C, const OutMap& om, int M, int N, int K,
                            unsigned long long* maxbits, hipStream_t s, const double* sub = nullptr,
-                           double sigma = 0.0) {
+                           double sigma = 0.0, const double* A_2 = nullptr,
+                           double* C_2 = nullptr) {
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16), mn = (long long)M * N;
   if (K < 1 || mn > (bl == B_KCONTIG ? 393216 : 524288) || (K < 32 && t16 > 512)) return false;
   const int slabs = (K + 15) / 16;
   auto go = [&](auto nw) {
     constexpr int NWV = decltype(nw)::value;
     if (t16 <= 256)
-      launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma);
+      launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma,
+                             A_2, C_2);
     else
-      launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma);
+      launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma,
+                            A_2, C_2);
   };
   if (slabs >= 4)
     go(std::integral_constant<int, 4>{});
@@ -425,6 +435,12 @@ static bool gemm_f64_small(const double* A, long long lda, const double* B, long
   else
     go(std::integral_constant<int, 1>{});
   return true;
+}
+
+bool gemm_f64_small_pair(const double* A1, const double* A2, long long lda, double* C1, double* C2,
+                         const OutMap& om, int M, int K, hipStream_t s) {
+  return gemm_f64_small(A1, lda, A1, lda, B_KCONTIG, C1, om, M, M, K, nullptr, s, nullptr, 0.0, A2,
+                        C2);
 }
 
 // Large-GEMM variant: 128 x 128 block tile, K slab BK = 32, LDS double

@@ -212,12 +212,6 @@ __global__ void k_group_norm(const GroupStep* __restrict__ d) {
   }
 }
 
-// max|T~| slots start at zero (a kernel: no memset node in a captured sweep)
-__global__ void k_group_zero_max(const GroupStep* __restrict__ d, int count) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < count && d[g].ctl->active) *d[g].maxbits = 0ULL;
-}
-
 // one step done: advance the counter, retire problems that have all their steps
 __global__ void k_group_advance(const GroupStep* __restrict__ d, int count) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
@@ -263,9 +257,6 @@ void group_spectrum(const GroupStep* d, int count, hipStream_t s) {
 }
 void group_norm(const GroupStep* d, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_group_norm, dim3(count), dim3(256), 0, s, d);
-}
-void group_zero_max(const GroupStep* d, int count, hipStream_t s) {
-  hipLaunchKernelGGL(k_group_zero_max, dim3((count + 63) / 64), dim3(64), 0, s, d, count);
 }
 void group_advance(const GroupStep* d, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_group_advance, dim3((count + 63) / 64), dim3(64), 0, s, d, count);

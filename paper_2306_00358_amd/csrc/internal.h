@@ -51,6 +51,11 @@ void gemm_f64(const double* A, long long lda, const double* B, long long ldb, in
               double* C, const OutMap& om, int M, int N, int K,
               unsigned long long* maxbits, hipStream_t s, int tag = GEMM_TAG_OTHER);
 
+// C1 = A1 A1^T and C2 = A2 A2^T (M x K operands, K-contiguous) in one launch of
+// small tiles; false where those do not apply.
+bool gemm_f64_small_pair(const double* A1, const double* A2, long long lda, double* C1, double* C2,
+                         const OutMap& om, int M, int K, hipStream_t s);
+
 // One product of a grouped FP64 launch (device table): C (row-major, leading
 // dimension ldc) = A B with B's layout given per launch; gate as for RpItem.
 struct F64Item {
@@ -167,26 +172,6 @@ int rp_group_tiles(const RpItem& it, int cfg);
 void gemm_rp_grouped(int mode, int out, int cfg, const RpItem* d_items, const int* d_begin,
                      int count, int tiles, hipStream_t s);
 
-// Reduced-precision operands of a step from the coarse tensor `src` (f64 or
-// f32, legs optionally transposed, divided by the max read from maxbits).
-// Each output is an RpOperand written in `mode`; rows are zero-padded to the
-// lengths given (multiples of 32):
-//   Tn   natural float tensor (dx,dy,dx,dy)               (also the state)
-//   OT   rows (l,u), K (r,d), row length ldP                (environment half)
-//   OX   rows (l,d), K (u,r), row length ldP                (environment half)
-//   OC1  rows (j,d,c), K b, row length ldx                  (first contraction)
-//   OC2  rows (l,e), K (a,c) of T[a,c,e,l], row length ldP  (O(D^7) contraction)
-struct RpOps {
-  void* hi[4];
-  void* lo[4];
-};
-void launch_prep_rp(const void* src, bool src_f32, bool rotate, int dx, int dy,
-                    const unsigned long long* maxbits, float* Tn, int mode, const RpOps& ops,
-                    long long ldP, long long ldx, hipStream_t s);
-// U1 rows (i,a), K b (row length ldx); U3 rows k, K (d,e) = U[e,d,k] (row length ldn)
-void launch_layout_u_rp(const double* Ucan, int dx, int dn, int mode, void* u1hi, void* u1lo,
-                        void* u3hi, void* u3lo, long long ldx, long long ldn, hipStream_t s);
-
 // All eigenpairs of the symmetric tridiagonal (d, e), n <= 128, in one
 // workgroup (divide and conquer): eigenvalues ascending into W (which may be
 // d), eigenvectors as the rows of Zt (n x n); *info = 1 if a result is not
@@ -203,26 +188,45 @@ bool dense_eig_small(double* M, int n, int rows, double* W, double* E, double* Z
 // ---- small kernels (kernels.hip) ----
 void launch_maxabs(const void* x, long long n, bool is_f32, unsigned long long* maxbits, hipStream_t s);
 void launch_init_acc(const unsigned long long* maxbits, double* acc, hipStream_t s);
-// Sticky eigensolver failure: *flag = 1 if *info != 0 or force.
-void launch_fold_info(const int* info, int* flag, int force, hipStream_t s);
-// Operands of the next step from the coarse tensor `src` (f64 or f32),
-// optionally with legs transposed (l,u,r,d) -> (u,l,d,r), scaled by
-// 1/max (read from maxbits): Tn natural (dx,dy,dx,dy); Xt [(l,d),(u,r)];
-// Tp [(l,u),(d,r)].  Outputs are f64 or f32 per out_f32.
+// The tests' injected eigensolver failure: *flag = 1.
+void launch_fail_flag(int* flag, hipStream_t s);
+// Operands of a step from the tensor `src` (f64 or f32; legs transposed
+// (l,u,r,d) -> (u,l,d,r) with `rotate`, divided by the maximum in *maxbits when
+// given), each at its own strides over (l, u, r, d) and in its own format
+// (RP_F32, RP_BF16X3: hi and lo; kFmtF64: hi), `tn` an FP32 copy in natural
+// order (may be null); one launch.  With `norm` the launch also takes the step's
+// log-norm and torus estimate from the coarse tensor.
+constexpr int kFmtF64 = 2;
+struct PrepOut {
+  void* hi;
+  void* lo;
+  float* tn;
+  int mode;
+  long long dst[4];
+};
+struct NormArgs {
+  const void* Tt;  // coarse tensor (dims (dn,dy,dn,dy))
+  bool f32;
+  int dn, dy;
+  double w;        // 2^-k
+  double* acc;
+  double* rec;
+};
+void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
+                 const unsigned long long* maxbits, const PrepOut* outs, int count,
+                 const NormArgs* norm, hipStream_t s);
 void launch_prep_mirror(const double* T, int dx, int dy, double* Tn, double* Xt, hipStream_t s);
 void launch_store(double* p, double v, hipStream_t s);
-void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
-                 const unsigned long long* maxbits, void* Tn, void* Xt, void* Tp, bool out_f32,
-                 hipStream_t s);
-void launch_symmetrize(double* M, int n, hipStream_t s);
+// M <- (M + M^T) / 2 and *trace = trace(M)
+void launch_symmetrize(double* M, int n, double* trace, hipStream_t s);
 // W: the `cnt` leading eigenvalues of M in ascending order (cnt <= n);
 // total: trace(M) (device scalar).
 void launch_spectrum(const double* W, int cnt, int n, int dn, int trunc, double tau, int spec_len,
-                     const double* total, double* spec_out, double* rec, int* kept, hipStream_t s);
+                     const double* total, double* spec_out, double* rec, int* kept,
+                     const int* info, int* sticky, hipStream_t s);
 // V: `cols` eigenvectors of length n, vector c at V[c*n], ascending order.
 void launch_isometry(const double* V, int cols, int n, int dn, const int* kept, double* Ucan,
                      hipStream_t s);
-void launch_trace(const double* M, int n, double* out, hipStream_t s);
 size_t topk_workspace_doubles(int n, int p);
 // Batched shifted Cholesky-QR step of the block eigensolver: per problem,
 // Rt = (R^-1)^T with G (+ shift) = R^T R (one workgroup each; p <= 128, a
@@ -242,13 +246,11 @@ void launch_chol_inv_batched(const CholItem* d_items, int count, int pmax, int p
 bool topk_eigs(const double* M, int n, int p, int need, double tol,
                int q_first, double* shift, int* nocheck, double* ws, double* W, double* Xout,
                int* dinfo, int* iters, int* enough, double* resid, hipStream_t s);
-void launch_layout_u(const double* Ucan, int dx, int dn, void* U1, void* U3, bool out_f32,
-                     hipStream_t s);
-void launch_norm(const unsigned long long* maxbits, const void* Tt, bool f32, int dn, int dy,
-                 double weight, double* acc, double* rec, hipStream_t s);
+void launch_layout_u(const double* src, long long sr, long long si, const int* kept, int dx, int dn,
+                     int mode, void* u1hi, void* u1lo, void* u3hi, void* u3lo, long long ld1,
+                     long long ld3, unsigned long long* clear, hipStream_t s);
 void launch_finish(const void* Tn, bool f32, int dx, int dy, double weight, const double* acc,
                    double* out, hipStream_t s);
-void launch_f64_to_f32(const double* x, float* y, long long n, hipStream_t s);
 void launch_f32_to_f64(const float* x, double* y, long long n, hipStream_t s);
 
 // ---- lockstep batch engine (group.hip) ----
@@ -297,12 +299,12 @@ void group_shift(const GroupStep* d, int count, long long max_pn, hipStream_t s)
 void group_dense(const GroupStep* d, int count, int pmax, hipStream_t s);
 void group_spectrum(const GroupStep* d, int count, hipStream_t s);
 void group_norm(const GroupStep* d, int count, hipStream_t s);
-void group_zero_max(const GroupStep* d, int count, hipStream_t s);
 void group_advance(const GroupStep* d, int count, hipStream_t s);
 
 // ---- engine hooks used by the scheduler (sched.cpp) ----
 // C1 -> C2 -> C3 in FP64 on caller buffers (X1, X2: dn*dx*dy*dx*dy doubles;
-// Tt: dn*dy*dn*dy); *maxbits is cleared by a kernel and receives max|Tt|.
+// Tt: dn*dy*dn*dy); *maxbits, cleared by the caller's layout kernel, receives
+// max|Tt|.
 void coarse_f64_into(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1,
                      const double* U3, int dx, int dy, int dn, double* X1, double* X2, double* Tt,
                      unsigned long long* maxbits, int tag_flags);

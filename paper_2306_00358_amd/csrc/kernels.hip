@@ -48,14 +48,14 @@ __global__ void k_init_acc(const unsigned long long* maxbits, double* acc) {
   }
 }
 
-// *flag = 1 when *info != 0 (or `force`): a failed eigensolve of any step stays
-// visible until the state is finished
-__global__ void k_fold_info(const int* info, int* flag, int force) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && (force || *info != 0)) *flag = 1;
+// *flag = 1: the failure the tests inject (a failed eigensolve stays visible
+// until the state is finished)
+__global__ void k_fail_flag(int* flag) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *flag = 1;
 }
 
-void launch_fold_info(const int* info, int* flag, int force, hipStream_t s) {
-  hipLaunchKernelGGL(k_fold_info, dim3(1), dim3(64), 0, s, info, flag, force);
+void launch_fail_flag(int* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_fail_flag, dim3(1), dim3(64), 0, s, flag);
 }
 
 void launch_init_acc(const unsigned long long* maxbits, double* acc, hipStream_t s) {
@@ -63,71 +63,114 @@ void launch_init_acc(const unsigned long long* maxbits, double* acc, hipStream_t
 }
 
 // ------------------------------------------------------------- operands --
-// Destination tensor T[l,u,r,d] of dims (dx,dy,dx,dy).  With `rotate`, the
-// source has dims (dy,dx,dy,dx) and T[l,u,r,d] = src[u,l,d,r].
-// One pass of an operand preparation: element (l, u, r, d) of the tensor
-// (dims n = (dx, dy, dx, dy)) is read at sum idx * sst, scaled by 1 / max|T~|
-// and written at sum idx * dst (and at sum idx * tst into an FP32 copy when
-// one is given).  The dims ta (unit source stride) and tb (unit destination
-// stride, or another one when that is ta) are tiled 32 x 32; blockIdx.y / z
-// run over the other two.  With different unit-stride dims the tile passes
-// through LDS, so reads run along ta and writes along tb, both coalesced;
-// otherwise both run along ta directly.
-struct PrepPass {
-  long long sst[4], dst[4], tst[4];
-  int n[4];
-  int ta, tb, o0, o1;
-};
-
-// the pass geometry: source strides sst, destination strides dst (index
-// order l, u, r, d), dims (dx, dy, dx, dy); returns the grid
-static dim3 prep_pass(PrepPass& P, const long long* sst, const long long* dst, int dx, int dy) {
-  const long long nat[4] = {(long long)dy * dx * dy, (long long)dx * dy, dy, 1};
-  for (int i = 0; i < 4; ++i) {
-    P.sst[i] = sst[i];
-    P.dst[i] = dst[i];
-    P.tst[i] = nat[i];
+__device__ __forceinline__ void st_rp(void* hi, void* lo, long long i, float v, int mode) {
+  if (mode == RP_F32) {
+    ((float*)hi)[i] = v;
+  } else {
+    const __bf16 h = (__bf16)v;
+    ((__bf16*)hi)[i] = h;
+    ((__bf16*)lo)[i] = (__bf16)(v - (float)h);
   }
-  P.n[0] = dx;
-  P.n[1] = dy;
-  P.n[2] = dx;
-  P.n[3] = dy;
-  int ta = 0, tb = -1;
-  for (int i = 0; i < 4; ++i)
-    if (sst[i] == 1) ta = i;
-  for (int i = 0; i < 4; ++i)
-    if (dst[i] == 1 && i != ta) tb = i;
-  if (tb < 0) tb = ta == 3 ? 2 : 3;  // the same unit-stride dim: any other one
-  int rest[2], nr = 0;
-  for (int i = 0; i < 4; ++i)
-    if (i != ta && i != tb) rest[nr++] = i;
-  P.ta = ta;
-  P.tb = tb;
-  P.o0 = rest[0];
-  P.o1 = rest[1];
-  return dim3((unsigned)(((P.n[ta] + 31) / 32) * ((P.n[tb] + 31) / 32)), (unsigned)P.n[rest[0]],
-              (unsigned)P.n[rest[1]]);
 }
 
-// FP64 (or FP32, out_f32) operands of the FP64 path
-__global__ __launch_bounds__(256) void k_prep_pass(const void* src, bool src_f32, PrepPass P,
-                                                   const unsigned long long* maxbits, void* out,
-                                                   bool out_f32) {
+// Log-norm and torus trace of the coarse tensor Tt (dims (dn,dy,dn,dy)), by one
+// workgroup of 256 threads: acc[0] += w ln n_k; rec[0] = ln n_k, rec[3] =
+// acc + w ln trace (NaN if trace <= 0), n_k from maxbits.
+__device__ __forceinline__ void norm_body(const NormArgs& a, const unsigned long long* maxbits) {
+  __shared__ double red[256];
+  const int t = threadIdx.x;
+  const double nk = __longlong_as_double((long long)*maxbits);
+  double s = 0.0;
+  const int cnt = a.dn * a.dy;
+  for (int e = t; e < cnt; e += 256) {
+    int i = e / a.dy, j = e % a.dy;
+    s += ld_any(a.Tt, (((long long)i * a.dy + j) * a.dn + i) * a.dy + j, a.f32);
+  }
+  red[t] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o) red[t] += red[t + o];
+    __syncthreads();
+  }
+  if (t == 0) {
+    double ln = log(nk);
+    double c = a.acc[0] + a.w * ln;
+    a.acc[0] = c;
+    double tr = red[0] / nk;
+    a.rec[0] = ln;
+    a.rec[3] = tr > 0.0 ? c + a.w * log(tr) : __longlong_as_double(0x7ff8000000000000LL);
+  }
+}
+
+// One operand of a step: element (l, u, r, d) of the tensor (dims n = (dx, dy,
+// dx, dy)) is read at sum idx * sst, scaled by 1 / max|T~| and written at sum
+// idx * dst in the operand's format (and at its natural position into an
+// FP32 copy when one is given).  The dims ta (unit source stride) and tb (unit
+// destination stride, or another one when that is ta) are tiled 32 x 32, one
+// workgroup per tile and index pair of the other two dims o0, o1.  With
+// different unit-stride dims the tile passes through LDS, so reads run along
+// ta and writes along tb, both coalesced; otherwise both run along ta.
+struct PrepPass {
+  long long sst[4], dst[4];
+  int n[4];
+  int ta, tb, o0, o1;
+  int tiles_a, tiles, blk0;  // tiles along ta, tiles of an index pair, first workgroup
+  int mode;                  // RP_F32, RP_BF16X3 or kFmtF64
+  void *hi, *lo;
+  float* tn;
+};
+
+// A step's operands in one launch (each operand a range of workgroups), with
+// the log-norm as its last workgroup: these are bandwidth-bound passes at
+// large D and launches of a few us each at small D.
+struct PrepSet {
+  PrepPass p[4];
+  int count, norm_blk;
+  NormArgs norm;
+  const void* src;
+  bool src_f32;
+  const unsigned long long* maxbits;  // null: scale 1
+};
+
+__global__ __launch_bounds__(256) void k_prep(PrepSet S) {
   __shared__ double tile[32][33];
-  const double inv = 1.0 / __longlong_as_double((long long)*maxbits);
+  const int blk = blockIdx.x;
+  if (blk == S.norm_blk) {  // uniform
+    norm_body(S.norm, S.maxbits);
+    return;
+  }
+  int q = 0;
+  while (q + 1 < S.count && blk >= S.p[q + 1].blk0) ++q;
+  const PrepPass& P = S.p[q];
+  const double inv = S.maxbits ? 1.0 / __longlong_as_double((long long)*S.maxbits) : 1.0;
   const int na = P.n[P.ta], nb = P.n[P.tb];
-  const int tiles_a = (na + 31) / 32;
-  const int a0 = (blockIdx.x % tiles_a) * 32, b0 = (blockIdx.x / tiles_a) * 32;
-  const long long sb = blockIdx.y * P.sst[P.o0] + blockIdx.z * P.sst[P.o1];
-  const long long db = blockIdx.y * P.dst[P.o0] + blockIdx.z * P.dst[P.o1];
+  const int local = blk - P.blk0, pair = local / P.tiles, tl = local - pair * P.tiles;
+  const int i1 = pair / P.n[P.o0], i0 = pair - i1 * P.n[P.o0];
+  const int a0 = (tl % P.tiles_a) * 32, b0 = (tl / P.tiles_a) * 32;
+  const long long sb = i0 * P.sst[P.o0] + i1 * P.sst[P.o1];
+  const long long db = i0 * P.dst[P.o0] + i1 * P.dst[P.o1];
+  const long long nat[4] = {(long long)P.n[1] * P.n[0] * P.n[1], (long long)P.n[0] * P.n[1], P.n[1],
+                            1};
+  const long long tb = i0 * nat[P.o0] + i1 * nat[P.o1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const bool direct = P.dst[P.ta] == 1;
+  const long long sa = P.sst[P.ta], sbb = P.sst[P.tb], da = P.dst[P.ta], dbb = P.dst[P.tb];
+  const long long ta = nat[P.ta], tbb = nat[P.tb];
+  auto put = [&](int a, int b, double v) {
+    const long long o = db + a * da + b * dbb;
+    if (P.mode == kFmtF64) {
+      ((double*)P.hi)[o] = v;
+    } else {
+      st_rp(P.hi, P.lo, o, (float)v, P.mode);
+      if (P.tn) P.tn[tb + a * ta + b * tbb] = (float)v;
+    }
+  };
   for (int k = ty; k < 32; k += 8) {
     const int a = a0 + tx, b = b0 + k;
     double v = 0.0;
     if (a < na && b < nb) {
-      v = ld_any(src, sb + a * P.sst[P.ta] + b * P.sst[P.tb], src_f32) * inv;
-      if (direct) st_any(out, db + a * P.dst[P.ta] + b * P.dst[P.tb], v, out_f32);
+      v = ld_any(S.src, sb + a * sa + b * sbb, S.src_f32) * inv;
+      if (direct) put(a, b, v);
     }
     tile[k][tx] = v;
   }
@@ -135,28 +178,60 @@ __global__ __launch_bounds__(256) void k_prep_pass(const void* src, bool src_f32
   __syncthreads();
   for (int k = ty; k < 32; k += 8) {
     const int b = b0 + tx, a = a0 + k;
-    if (a < na && b < nb) st_any(out, db + a * P.dst[P.ta] + b * P.dst[P.tb], tile[tx][k], out_f32);
+    if (a < na && b < nb) put(a, b, tile[tx][k]);
   }
 }
 
 void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
-                 const unsigned long long* maxbits, void* Tn, void* Xt, void* Tp, bool out_f32,
-                 hipStream_t s) {
+                 const unsigned long long* maxbits, const PrepOut* outs, int count,
+                 const NormArgs* norm, hipStream_t s) {
   // index order (l, u, r, d); the source is T~ itself or, rotated, T~[u, l, d, r]
   const long long X = dx, Y = dy;
   const long long src_rot[4] = {Y * X, X * Y * X, 1, X};
   const long long src_nat[4] = {Y * X * Y, X * Y, Y, 1};
-  // Tn natural; Xt[(l,d),(u,r)]; Tp[(l,u),(d,r)]: T[a,c,e,l] read as rows (a,c), columns (l,e)
-  const long long dsts[3][4] = {{Y * X * Y, X * Y, Y, 1},
-                                {Y * Y * X, X, 1, Y * X},
-                                {Y * Y * X, Y * X, 1, X}};
-  void* outs[3] = {Tn, Xt, Tp};
-  for (int o = 0; o < 3; ++o) {
-    PrepPass P{};
-    const dim3 grid = prep_pass(P, rotate ? src_rot : src_nat, dsts[o], dx, dy);
-    hipLaunchKernelGGL(k_prep_pass, grid, dim3(256), 0, s, src, src_f32, P, maxbits, outs[o],
-                       out_f32);
+  const long long* sst = rotate ? src_rot : src_nat;
+  PrepSet S{};
+  S.count = count;
+  S.src = src;
+  S.src_f32 = src_f32;
+  S.maxbits = maxbits;
+  int blocks = 0;
+  for (int o = 0; o < count; ++o) {
+    PrepPass& P = S.p[o];
+    const int n[4] = {dx, dy, dx, dy};
+    int ta = 0, tb = -1;
+    for (int i = 0; i < 4; ++i) {
+      P.sst[i] = sst[i];
+      P.dst[i] = outs[o].dst[i];
+      P.n[i] = n[i];
+    }
+    for (int i = 0; i < 4; ++i)
+      if (P.sst[i] == 1) ta = i;
+    for (int i = 0; i < 4; ++i)
+      if (P.dst[i] == 1 && i != ta) tb = i;
+    if (tb < 0) tb = ta == 3 ? 2 : 3;  // the same unit-stride dim: any other one
+    int rest[2], nr = 0;
+    for (int i = 0; i < 4; ++i)
+      if (i != ta && i != tb) rest[nr++] = i;
+    P.ta = ta;
+    P.tb = tb;
+    P.o0 = rest[0];
+    P.o1 = rest[1];
+    P.tiles_a = (n[ta] + 31) / 32;
+    P.tiles = P.tiles_a * ((n[tb] + 31) / 32);
+    P.blk0 = blocks;
+    P.mode = outs[o].mode;
+    P.hi = outs[o].hi;
+    P.lo = outs[o].lo;
+    P.tn = outs[o].tn;
+    blocks += P.tiles * n[rest[0]] * n[rest[1]];
   }
+  S.norm_blk = -1;
+  if (norm) {
+    S.norm = *norm;
+    S.norm_blk = blocks++;
+  }
+  if (blocks > 0) hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(256), 0, s, S);
 }
 
 // The reflected tensor T'[l,u,r,d] = T[r,u,l,d] (FP64, dims (dx,dy,dx,dy)) in
@@ -195,8 +270,25 @@ void launch_store(double* p, double v, hipStream_t s) {
 // M <- (M + M^T) / 2 by 32 x 32 tile pairs (I, J), I <= J: both tiles are
 // read coalesced into LDS and written back, each entry 0.5 (M_rc + M_cr)
 // with r < c the upper one; a diagonal tile is its own partner.
-__global__ __launch_bounds__(256) void k_symmetrize(double* M, int n) {
+__global__ __launch_bounds__(256) void k_symmetrize(double* M, int n, double* trace) {
   const int I = blockIdx.y, J = blockIdx.x;
+  if (I == (int)gridDim.x) {
+    // the last row of workgroups: trace(M), by the first of them (the
+    // diagonal is not written), fixed-order tree
+    if (J > 0) return;  // uniform
+    __shared__ double red[256];
+    const int t = threadIdx.x;
+    double s = 0.0;
+    for (int i = t; i < n; i += 256) s += M[(long long)i * n + i];
+    red[t] = s;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if (t < o) red[t] += red[t + o];
+      __syncthreads();
+    }
+    if (t == 0) *trace = red[0];
+    return;
+  }
   if (I > J) return;  // uniform
   __shared__ double A[32][33], B[32][33];  // tiles (I, J) and (J, I)
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -216,18 +308,20 @@ __global__ __launch_bounds__(256) void k_symmetrize(double* M, int n) {
   }
 }
 
-void launch_symmetrize(double* M, int n, hipStream_t s) {
+void launch_symmetrize(double* M, int n, double* trace, hipStream_t s) {
   const int T = (n + 31) / 32;
-  hipLaunchKernelGGL(k_symmetrize, dim3(T, T), dim3(256), 0, s, M, n);
+  hipLaunchKernelGGL(k_symmetrize, dim3(T, T + 1), dim3(256), 0, s, M, n, trace);
 }
 
 // --------------------------------------------------------------- spectrum --
 // W: the cnt leading eigenvalues of M, ascending; lambda_m = W[cnt-1-m]
 // (descending).  total = trace(M).  rec[1] = truncation error, rec[2] = cut
-// gap, rec[4] = kept (as double).  Sums use a fixed-order tree.
+// gap, rec[4] = kept (as double), rec[5] = 0 (left environment).  Sums use a
+// fixed-order tree.  A dense solve's *info (may be null) that is not zero
+// sets the sticky flag.
 __global__ void k_spectrum(const double* W, int cnt, int n, int dn, int trunc, double tau,
                            int spec_len, const double* total, double* spec_out, double* rec,
-                           int* kept_out) {
+                           int* kept_out, const int* info, int* sticky) {
   __shared__ double red[256];
   __shared__ int kept_s;
   const int t = threadIdx.x;
@@ -238,6 +332,7 @@ __global__ void k_spectrum(const double* W, int cnt, int n, int dn, int trunc, d
       while (kept > 0 && (W[cnt - kept] - W[cnt - 1 - kept]) <= tau * l1) --kept;
     kept_s = kept;
     *kept_out = kept;
+    if (info && *info != 0) *sticky = 1;
   }
   __syncthreads();
   const int kept = kept_s;
@@ -253,6 +348,7 @@ __global__ void k_spectrum(const double* W, int cnt, int n, int dn, int trunc, d
     rec[1] = 1.0 - red[0] / total[0];
     rec[2] = dn < n ? (W[cnt - dn] - W[cnt - 1 - dn]) / l1 : -1.0;
     rec[4] = (double)kept;
+    rec[5] = 0.0;
   }
   if (spec_out)
     for (int m = t; m < spec_len; m += 256) spec_out[m] = m < cnt ? W[cnt - 1 - m] / l1 : 0.0;
@@ -260,9 +356,9 @@ __global__ void k_spectrum(const double* W, int cnt, int n, int dn, int trunc, d
 
 void launch_spectrum(const double* W, int cnt, int n, int dn, int trunc, double tau, int spec_len,
                      const double* total, double* spec_out, double* rec, int* kept,
-                     hipStream_t s) {
+                     const int* info, int* sticky, hipStream_t s) {
   hipLaunchKernelGGL(k_spectrum, dim3(1), dim3(256), 0, s, W, cnt, n, dn, trunc, tau, spec_len,
-                     total, spec_out, rec, kept);
+                     total, spec_out, rec, kept, info, sticky);
 }
 
 // ------------------------------------------------------------- projector --
@@ -287,64 +383,45 @@ void launch_isometry(const double* V, int cols, int n, int dn, const int* kept, 
                      n, dn, kept, Ucan);
 }
 
-// U1[(i*dx + a)*dx + b] = U[a,b,i]     (A operand of the first contraction)
-// U3[(d*dx + e)*dn + k] = U[e,d,k]     (B operand of the last contraction)
-__global__ void k_layout_u(const double* Ucan, int dx, int dn, void* U1, void* U3, bool f32) {
-  long long total = (long long)dx * dx * dn;
+// The projector in the layouts the contractions read.  U[a,b,i] is read at
+// src + (a dx + b) sr + i si (eigenvector rows: sr = 1, si = -n from the last row;
+// a canonical U: sr = dn, si = 1), zero for i >= *kept (kept may be null).
+//   U1[(i,a)][b] = U[a,b,i], row length ld1      (A operand of the first contraction)
+//   FP64:    U3[(d,e)][k] = U[e,d,k], row length ld3 (B operand of the last one)
+//   reduced: U3[k][(d,e)] = U[e,d,k], row length ld3
+// *clear (may be null) = 0: the max|T~| slot of the contractions that follow.
+__global__ void k_layout_u(const double* src, long long sr, long long si, const int* kept, int dx,
+                           int dn, int mode, void* u1hi, void* u1lo, void* u3hi, void* u3lo,
+                           long long ld1, long long ld3, unsigned long long* clear) {
+  const int kp = kept ? *kept : dn;
+  const int n = dx * dx;
+  const long long total = (long long)n * dn;
+  if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ULL;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
        e += (long long)gridDim.x * blockDim.x) {
-    int i = (int)(e % dn);
-    int ab = (int)(e / dn);
-    int a = ab / dx, b = ab % dx;
-    double v = Ucan[e];
-    st_any(U1, ((long long)i * dx + a) * dx + b, v, f32);
-    // e index of U3 is (d,e) with U[e,d,k]: here (a,b) plays (e,d)
-    st_any(U3, ((long long)b * dx + a) * dn + i, v, f32);
+    const int ab = (int)(e % n), i = (int)(e / n);
+    const int a = ab / dx, b = ab % dx;
+    const double v = i < kp ? src[ab * sr + i * si] : 0.0;
+    const long long o1 = ((long long)i * dx + a) * ld1 + b;
+    const long long de = (long long)b * dx + a;  // (a,b) plays (e,d)
+    if (mode == kFmtF64) {
+      ((double*)u1hi)[o1] = v;
+      ((double*)u3hi)[de * ld3 + i] = v;
+    } else {
+      st_rp(u1hi, u1lo, o1, (float)v, mode);
+      st_rp(u3hi, u3lo, (long long)i * ld3 + de, (float)v, mode);
+    }
   }
 }
 
-void launch_layout_u(const double* Ucan, int dx, int dn, void* U1, void* U3, bool out_f32,
-                     hipStream_t s) {
-  hipLaunchKernelGGL(k_layout_u, dim3(nblocks((long long)dx * dx * dn, 256)), dim3(256), 0, s,
-                     Ucan, dx, dn, U1, U3, out_f32);
+void launch_layout_u(const double* src, long long sr, long long si, const int* kept, int dx, int dn,
+                     int mode, void* u1hi, void* u1lo, void* u3hi, void* u3lo, long long ld1,
+                     long long ld3, unsigned long long* clear, hipStream_t s) {
+  hipLaunchKernelGGL(k_layout_u, dim3(nblocks((long long)dx * dx * dn, 256)), dim3(256), 0, s, src,
+                     sr, si, kept, dx, dn, mode, u1hi, u1lo, u3hi, u3lo, ld1, ld3, clear);
 }
 
-// ------------------------------------------------------ log-norm and trace --
-// n_k from maxbits; acc += w ln n_k; trace of the normalised coarse tensor
-// Tt (dims (dn,dy,dn,dy)) gives the torus estimate.
-// rec[0] = ln n_k, rec[3] = acc + w ln trace (NaN if trace <= 0).
-__global__ void k_norm(const unsigned long long* maxbits, const void* Tt, bool f32, int dn, int dy,
-                       double w, double* acc, double* rec) {
-  __shared__ double red[256];
-  const int t = threadIdx.x;
-  const double nk = __longlong_as_double((long long)*maxbits);
-  double s = 0.0;
-  const int cnt = dn * dy;
-  for (int e = t; e < cnt; e += 256) {
-    int i = e / dy, j = e % dy;
-    s += ld_any(Tt, (((long long)i * dy + j) * dn + i) * dy + j, f32);
-  }
-  red[t] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] += red[t + o];
-    __syncthreads();
-  }
-  if (t == 0) {
-    double ln = log(nk);
-    double a = acc[0] + w * ln;
-    acc[0] = a;
-    double tr = red[0] / nk;
-    rec[0] = ln;
-    rec[3] = tr > 0.0 ? a + w * log(tr) : __longlong_as_double(0x7ff8000000000000LL);
-  }
-}
-
-void launch_norm(const unsigned long long* maxbits, const void* Tt, bool f32, int dn, int dy,
-                 double weight, double* acc, double* rec, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm, dim3(1), dim3(256), 0, s, maxbits, Tt, f32, dn, dy, weight, acc, rec);
-}
-
+// ---------------------------------------------------------------- finish --
 // ln Z / N = acc + w ln sum_{i,j} T[i,j,i,j]  (periodic trace, Sec. 2)
 __global__ void k_finish(const void* Tn, bool f32, int dx, int dy, double w, const double* acc,
                          double* out) {
@@ -371,108 +448,6 @@ void launch_finish(const void* Tn, bool f32, int dx, int dy, double weight, cons
   hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, Tn, f32, dx, dy, weight, acc, out);
 }
 
-// ----------------------------------------------- reduced-precision operands --
-__device__ __forceinline__ void st_rp(void* hi, void* lo, long long i, float v, int mode) {
-  if (mode == RP_F32) {
-    ((float*)hi)[i] = v;
-  } else {
-    const __bf16 h = (__bf16)v;
-    ((__bf16*)hi)[i] = h;
-    ((__bf16*)lo)[i] = (__bf16)(v - (float)h);
-  }
-}
-
-// The reduced-precision operands, one PrepPass each (rounded by st_rp).
-__global__ __launch_bounds__(256) void k_prep_rp_pass(const void* src, bool src_f32, PrepPass P,
-                                                      const unsigned long long* maxbits,
-                                                      void* hi, void* lo, int mode, float* Tn) {
-  __shared__ float tile[32][33];
-  const double inv = 1.0 / __longlong_as_double((long long)*maxbits);
-  const int na = P.n[P.ta], nb = P.n[P.tb];
-  const int tiles_a = (na + 31) / 32;
-  const int a0 = (blockIdx.x % tiles_a) * 32, b0 = (blockIdx.x / tiles_a) * 32;
-  const long long sb = blockIdx.y * P.sst[P.o0] + blockIdx.z * P.sst[P.o1];
-  const long long db = blockIdx.y * P.dst[P.o0] + blockIdx.z * P.dst[P.o1];
-  const long long tb = blockIdx.y * P.tst[P.o0] + blockIdx.z * P.tst[P.o1];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const bool direct = P.dst[P.ta] == 1;
-  for (int k = ty; k < 32; k += 8) {
-    const int a = a0 + tx, b = b0 + k;
-    float v = 0.0f;
-    if (a < na && b < nb) {
-      v = (float)(ld_any(src, sb + a * P.sst[P.ta] + b * P.sst[P.tb], src_f32) * inv);
-      if (direct) {
-        st_rp(hi, lo, db + a * P.dst[P.ta] + b * P.dst[P.tb], v, mode);
-        if (Tn) Tn[tb + a * P.tst[P.ta] + b * P.tst[P.tb]] = v;
-      }
-    }
-    tile[k][tx] = v;
-  }
-  if (direct) return;  // uniform
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int b = b0 + tx, a = a0 + k;
-    if (a < na && b < nb) {
-      const float v = tile[tx][k];
-      st_rp(hi, lo, db + a * P.dst[P.ta] + b * P.dst[P.tb], v, mode);
-      if (Tn) Tn[tb + a * P.tst[P.ta] + b * P.tst[P.tb]] = v;
-    }
-  }
-}
-
-void launch_prep_rp(const void* src, bool src_f32, bool rotate, int dx, int dy,
-                    const unsigned long long* maxbits, float* Tn, int mode, const RpOps& ops,
-                    long long ldP, long long ldx, hipStream_t s) {
-  // logical index order (l, u, r, d), dims (dx, dy, dx, dy); the source is
-  // T~ itself or, rotated, T~[u, l, d, r]
-  const long long X = dx, Y = dy;
-  const long long src_rot[4] = {Y * X, X * Y * X, 1, X};
-  const long long src_nat[4] = {Y * X * Y, X * Y, Y, 1};
-  const long long* sst = rotate ? src_rot : src_nat;
-  // OT rows (l,u), K (r,d); OX rows (l,d), K (u,r); OC1 rows (u,r,d), K l;
-  // OC2 rows (d,r), K (l,u)
-  const long long dsts[4][4] = {{Y * ldP, ldP, Y, 1},
-                                {Y * ldP, X, 1, ldP},
-                                {1, X * Y * ldx, Y * ldx, ldx},
-                                {Y, 1, ldP, X * ldP}};
-  for (int o = 0; o < 4; ++o) {
-    PrepPass P{};
-    const dim3 grid = prep_pass(P, sst, dsts[o], dx, dy);
-    // the FP32 copy goes with OT, whose order it shares
-    hipLaunchKernelGGL(k_prep_rp_pass, grid, dim3(256), 0, s, src, src_f32, P, maxbits,
-                       ops.hi[o], ops.lo[o], mode, o == 0 ? Tn : nullptr);
-  }
-}
-
-__global__ void k_layout_u_rp(const double* Ucan, int dx, int dn, int mode, void* u1hi,
-                              void* u1lo, void* u3hi, void* u3lo, long long ldx, long long ldn) {
-  const long long total = (long long)dx * dx * dn;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int i = (int)(e % dn);
-    const int ab = (int)(e / dn);
-    const int a = ab / dx, b = ab % dx;
-    const float v = (float)Ucan[e];
-    // U1 rows (i,a), k = b
-    st_rp(u1hi, u1lo, ((long long)i * dx + a) * ldx + b, v, mode);
-    // U3 rows k = i, K (d,e) with U[e,d,k]: (a,b) plays (e,d) -> column d*dx + e = b*dx + a
-    st_rp(u3hi, u3lo, (long long)i * ldn + (long long)b * dx + a, v, mode);
-  }
-}
-
-void launch_layout_u_rp(const double* Ucan, int dx, int dn, int mode, void* u1hi, void* u1lo,
-                        void* u3hi, void* u3lo, long long ldx, long long ldn, hipStream_t s) {
-  const long long total = (long long)dx * dx * dn;
-  hipLaunchKernelGGL(k_layout_u_rp, dim3(nblocks(total, 256)), dim3(256), 0, s, Ucan, dx, dn, mode,
-                     u1hi, u1lo, u3hi, u3lo, ldx, ldn);
-}
-
-__global__ void k_f64_to_f32(const double* x, float* y, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    y[i] = (float)x[i];
-}
-
 __global__ void k_f32_to_f64(const float* x, double* y, long long n) {
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -481,10 +456,6 @@ __global__ void k_f32_to_f64(const float* x, double* y, long long n) {
 
 void launch_f32_to_f64(const float* x, double* y, long long n, hipStream_t s) {
   hipLaunchKernelGGL(k_f32_to_f64, dim3(nblocks(n, 256)), dim3(256), 0, s, x, y, n);
-}
-
-void launch_f64_to_f32(const double* x, float* y, long long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_f64_to_f32, dim3(nblocks(n, 256)), dim3(256), 0, s, x, y, n);
 }
 
 }  // namespace hotrg

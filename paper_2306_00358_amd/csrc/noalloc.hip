@@ -32,11 +32,6 @@ double* g_ptr[kMaxDevices] = {};
 hipError_t g_err[kMaxDevices] = {};
 bool g_done[kMaxDevices] = {};
 
-// x[0] = 1.0: the unit scale the operand preparation divides by
-__global__ void k_unit(double* x) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) x[0] = 1.0;
-}
-
 thread_local std::string t_err;
 
 }  // namespace
@@ -70,10 +65,10 @@ hotrg_status hotrg_coarse_noalloc(hotrg_ctx* ctx, const double* T, const double*
     set_last_error("need dx, dy >= 1 and 1 <= dn <= dx*dx");
     return HOTRG_ERR_INVALID;
   }
-  // X1, X2 (dn dx^2 dy^2 each), three operand layouts of T (dx^2 dy^2 each),
-  // two layouts of U (dx^2 dn each), each starting on a 256-byte boundary
-  // (as hipMalloc'd buffers do), after 64 doubles for the unit scale and the
-  // max slot
+  // the documented limit: X1, X2 (dn dx^2 dy^2 each), three operand layouts of T
+  // (dx^2 dy^2 each; one is used: T itself serves as the others), two layouts of
+  // U (dx^2 dn each), each starting on a 256-byte boundary (as hipMalloc'd
+  // buffers do), after 64 doubles for the max slot
   auto slot = [](double count) { return std::ceil(count / 32.0) * 32.0; };
   const double t4 = (double)dx * dx * dy * dy, u2 = (double)dx * dx * dn;
   const double need = 64.0 + 2.0 * slot(dn * t4) + 3.0 * slot(t4) + 2.0 * slot(u2);
@@ -105,21 +100,19 @@ hotrg_status hotrg_coarse_noalloc(hotrg_ctx* ctx, const double* T, const double*
   auto up32 = [](long long c) { return (c + 31) / 32 * 32; };
   const long long n4 = up32((long long)dx * dx * dy * dy), nu = up32((long long)dx * dx * dn);
   const long long nx = up32((long long)dn * dx * dx * dy * dy);
-  // [0] unit scale, [8] max bits (each on its own 64-byte line)
-  double* unit = base;
+  // [8] max bits (on a 64-byte line of its own)
   unsigned long long* mb = max_abs ? (unsigned long long*)max_abs : (unsigned long long*)(base + 8);
-  double* Tn = base + 64;
-  double* Xt = Tn + n4;
-  double* Tp = Xt + n4;
+  double* Tp = base + 64;
   double* U1 = Tp + n4;
   double* U3 = U1 + nu;
   double* X1 = U3 + nu;
   double* X2 = X1 + nx;
   const hipStream_t s = ctx_stream(ctx);
-  hipLaunchKernelGGL(k_unit, dim3(1), dim3(64), 0, s, unit);
-  launch_prep(T, false, false, dx, dy, (const unsigned long long*)unit, Tn, Xt, Tp, false, s);
-  launch_layout_u(U, dx, dn, U1, U3, false, s);
-  coarse_f64_into(ctx, Tn, Tp, U1, U3, dx, dy, dn, X1, X2, Tt, mb, GEMM_NO_TUNE);
+  const long long X = dx, Y = dy;
+  const PrepOut tp{Tp, nullptr, nullptr, kFmtF64, {Y * Y * X, Y * X, 1, X}};
+  launch_prep(T, false, false, dx, dy, nullptr, &tp, 1, nullptr, s);
+  launch_layout_u(U, dn, 1, nullptr, dx, dn, kFmtF64, U1, nullptr, U3, nullptr, dx, dn, mb, s);
+  coarse_f64_into(ctx, T, Tp, U1, U3, dx, dy, dn, X1, X2, Tt, mb, GEMM_NO_TUNE);
   const hipError_t e = hipGetLastError();
   if (cdev != dev) (void)hipSetDevice(dev);
   if (e != hipSuccess) {
