@@ -127,6 +127,7 @@ struct hotrg_state {
   // precision the operands below were prepared for
   int ops_prec = HOTRG_FP64;
   Buf Tn, Xt, Tp;      // FP64 operands of the next step (normalised)
+  Buf Tq;              // natural with padded rows, where f64_ld pads them (else Tn serves)
   Buf RO[4][2];        // reduced-precision operands OT, OX, OC1, OC2 ([.][0] hi/float, [.][1] lo)
   Buf acc;             // device: double ln n_0 + sum_k 2^-k ln n_k, then an int
                        // sticky flag set when any step's eigensolve failed
@@ -273,75 +274,77 @@ void check_dims(int dx, int dy, int dn) {
     fail(HOTRG_ERR_INVALID, "GEMM dimension exceeds 2^31");
 }
 
-// FP64 operands of T (dims dx, dy) in the state: environment halves into M.
-void environment_f64(hotrg_ctx* c, const double* Tn, const double* Xt, int dx, int dy,
-                     Buf* out = nullptr) {
-  Buf& Mb = out ? *out : c->M;
+// Environment M (n x n, FP64) of a tensor with dims (dx, dy) from its operands
+// Tq (natural) and Xt, rows of f64_ld's p.
+void environment_f64(hotrg_ctx* c, const double* Tq, const double* Xt, int dx, int dy, double* M) {
   const long long P = (long long)dx * dy;  // rows / cols of the halves
-  const long long n = (long long)dx * dx;
-  const long long K2 = (long long)dy * dy;
-  ensure(c, c->A1, (size_t)(P * P) * 8);
-  ensure(c, c->A2, (size_t)(P * P) * 8);
-  ensure(c, Mb, (size_t)(n * n) * 8);
+  const long long n = (long long)dx * dx, K2 = (long long)dy * dy;
+  const F64Ld ld = f64_ld(dx, dy, 1);
+  ensure(c, c->A1, (size_t)(n * ld.k2) * 8);
+  ensure(c, c->A2, (size_t)(n * ld.k2) * 8);
+  PadSet pads;
+  pads.add(c->A1.p, n, ld.k2, K2, 8, c->stream);
+  pads.add(c->A2.p, n, ld.k2, K2, 8, c->stream);
+  pads.launch(c->stream);
   // A2[(i,e),(k,f)] = sum_{c,d} T[i,e,c,d] T[k,f,c,d], stored as A2'[(i,k),(e,f)]
-  // rows (i,e): i -> dx*dy^2, e -> dy; cols (k,f): k -> dy^2, f -> 1
+  // rows (i,e): i -> dx*ld, e -> dy; cols (k,f): k -> ld, f -> 1
   // A1[(j,e),(l,f)] = sum_{a,b} T[j,a,b,e] T[l,a,b,f] from Xt[(l,d),(u,r)], stored as A1'[(j,l),(e,f)]
   // Both halves are Gram matrices X X^T: where it applies, one launch
   // computes the upper triangles of both and mirrors them (half the MFMAs),
   // and below that one launch of small tiles takes both.
-  const OutMap o2 = omap2(dy, dx * K2, dy, dy, K2, 1);
-  if (!gemm_f64_syrk(Tn, P, (double*)c->A2.p, o2, (int)P, (int)P, c->stream, Xt,
+  const OutMap o2 = omap2(dy, dx * ld.k2, dy, dy, ld.k2, 1);
+  if (!gemm_f64_syrk(Tq, ld.p, (double*)c->A2.p, o2, (int)P, (int)ld.p, c->stream, Xt,
                      (double*)c->A1.p) &&
-      !gemm_f64_small_pair(Tn, Xt, P, (double*)c->A2.p, (double*)c->A1.p, o2, (int)P, (int)P,
-                           c->stream)) {
-    gemm_f64(Tn, P, Tn, P, B_KCONTIG, (double*)c->A2.p, o2, (int)P, (int)P, (int)P, nullptr,
-             c->stream, GEMM_TAG_ENV);
-    gemm_f64(Xt, P, Xt, P, B_KCONTIG, (double*)c->A1.p, o2, (int)P, (int)P, (int)P, nullptr,
-             c->stream, GEMM_TAG_ENV);
+      !gemm_f64_small_pair(Tq, Xt, ld.p, (double*)c->A2.p, (double*)c->A1.p, o2, (int)P,
+                           (int)ld.p, c->stream)) {
+    gemm_f64(Tq, ld.p, Tq, ld.p, B_KCONTIG, (double*)c->A2.p, o2, (int)P, (int)P, (int)ld.p,
+             nullptr, c->stream, GEMM_TAG_ENV);
+    gemm_f64(Xt, ld.p, Xt, ld.p, B_KCONTIG, (double*)c->A1.p, o2, (int)P, (int)P, (int)ld.p,
+             nullptr, c->stream, GEMM_TAG_ENV);
   }
   // M[(i,j),(k,l)] = sum_{e,f} A2'[(i,k),(e,f)] A1'[(j,l),(e,f)]: GEMM rows (i,k), cols (j,l)
   // rows (i,k): i -> dx*n, k -> dx; cols (j,l): j -> n, l -> 1
   const OutMap om = omap2(dx, dx * n, dx, dx, n, 1);
-  gemm_f64((const double*)c->A2.p, K2, (const double*)c->A1.p, K2, B_KCONTIG, (double*)Mb.p, om,
-           (int)n, (int)n, (int)K2, nullptr, c->stream, GEMM_TAG_ENV);
+  gemm_f64((const double*)c->A2.p, ld.k2, (const double*)c->A1.p, ld.k2, B_KCONTIG, M, om, (int)n,
+           (int)n, (int)ld.k2, nullptr, c->stream, GEMM_TAG_ENV);
 }
 
 }  // namespace
 
 namespace hotrg {
 
-// C1, C2, C3 in FP64 on caller-provided buffers: X1 and X2 hold
-// dn*dx*dy*dx*dy doubles each, Tt receives T~[i,j,k,l] (dims dn,dy,dn,dy),
+// C1, C2, C3 in FP64 on caller-provided buffers with rows as `ld` says, padding
+// zero (X1: dn*dy*dx rows, X2: dn*dy*dy rows; Tp rows and U3 rows to ld.p and
+// ld.n); Tt receives T~[i,j,k,l] (dims dn,dy,dn,dy),
 // and *maxbits (cleared by the caller's launch_layout_u) max|T~|.  `tag_flags` is or-ed
 // into every GEMM tag (GEMM_NO_TUNE: fixed tile rule, no measurement, and no
 // per-phase timing events: the allocation-free entry point's path).
 void coarse_f64_into(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1,
-                     const double* U3, int dx, int dy, int dn, double* X1, double* X2, double* Tt,
-                     unsigned long long* maxbits, int tag_flags) {
+                     const double* U3, int dx, int dy, int dn, const F64Ld& ld, double* X1,
+                     double* X2, double* Tt, unsigned long long* maxbits, int tag_flags) {
   const bool marks = tag_flags == 0;
   const long long Q = (long long)dx * dy;
   // C1: rows (i,a), cols (j,d,c) = j*(dx*dy) + (d*dy + c); K = b.
-  //     X1[(i,j,d),(a,c)] at ((i*dy + j)*dx + d)*Q + a*dy + c
-  //     rows (i,a): i -> dy*dx*Q, a -> dy; cols (j,d,c): j -> dx*Q, d -> Q, c -> 1
-  OutMap o1 = omap2(dx, (long long)dy * dx * Q, dy, 1, 0, 0);
-  o1.c1 = dx; o1.c2 = dy; o1.t0 = (long long)dx * Q; o1.t1 = Q; o1.t2 = 1;
+  //     X1[(i,j,d),(a,c)] at ((i*dy + j)*dx + d)*ld.p + a*dy + c
+  //     rows (i,a): i -> dy*dx*ld.p, a -> dy; cols (j,d,c): j -> dx*ld.p, d -> ld.p, c -> 1
+  OutMap o1 = omap2(dx, (long long)dy * dx * ld.p, dy, 1, 0, 0);
+  o1.c1 = dx; o1.c2 = dy; o1.t0 = (long long)dx * ld.p; o1.t1 = ld.p; o1.t2 = 1;
   if (marks) mark(c, HOTRG_PHASE_C1);
   gemm_f64(U1, dx, Tn, (long long)dy * dx * dy, B_NCONTIG, X1, o1, dn * dx, dy * dx * dy, dx,
            nullptr, c->stream, GEMM_TAG_OTHER | tag_flags);
   // C2: rows (i,j,d) = (ij)*dx + d, cols (l,e) = l*dx + e; K = (a,c).
-  //     X2[(i,j,l),(d,e)] at ((ij)*dy + l)*dx*dx + d*dx + e
-  const long long n = (long long)dx * dx;
-  //     rows (ij,d): ij -> dy*n, d -> dx; cols (l,e): l -> n, e -> 1
-  const OutMap o2 = omap2(dx, (long long)dy * n, dx, dx, n, 1);
+  //     X2[(i,j,l),(d,e)] at ((ij)*dy + l)*ld.n + d*dx + e
+  //     rows (ij,d): ij -> dy*ld.n, d -> dx; cols (l,e): l -> ld.n, e -> 1
+  const OutMap o2 = omap2(dx, (long long)dy * ld.n, dx, dx, ld.n, 1);
   if (marks) mark(c, HOTRG_PHASE_C2);
-  gemm_f64(X1, Q, Tp, Q, B_NCONTIG, X2, o2, dn * dy * dx, (int)Q, (int)Q, nullptr, c->stream,
-           GEMM_TAG_C2 | tag_flags);
+  gemm_f64(X1, ld.p, Tp, ld.tp, B_NCONTIG, X2, o2, dn * dy * dx, (int)Q, (int)ld.p, nullptr,
+           c->stream, GEMM_TAG_C2 | tag_flags);
   // C3: rows (i,j,l) = (ij)*dy + l, cols k; K = (d,e).
   //     T~[i,j,k,l] at ((ij)*dn + k)*dy + l
   if (marks) mark(c, HOTRG_PHASE_C3);
   //     rows (ij,l): ij -> dn*dy, l -> 1; cols k -> dy
   const OutMap o3 = omap2(dy, (long long)dn * dy, 1, 1, dy, 0);
-  gemm_f64(X2, n, U3, dn, B_NCONTIG, Tt, o3, dn * dy * dy, dn, (int)n, maxbits, c->stream,
+  gemm_f64(X2, ld.n, U3, ld.u3, B_NCONTIG, Tt, o3, dn * dy * dy, dn, (int)ld.n, maxbits, c->stream,
            GEMM_TAG_OTHER | tag_flags);
 }
 
@@ -351,15 +354,38 @@ hipStream_t ctx_stream(const hotrg_ctx* c) { return c->stream; }
 
 namespace {
 
-// C1, C2, C3 in FP64: T~[i,j,k,l] (dims dn,dy,dn,dy) into c->Tt, max into scal.
-void coarse_f64(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1,
-                const double* U3, int dx, int dy, int dn, unsigned long long* maxbits) {
-  const long long X = x_elems(dx, dy, dn);
-  ensure(c, c->X1, (size_t)X * 8);
-  ensure(c, c->X2, (size_t)X * 8);
-  ensure(c, c->Tt, (size_t)dn * dy * dn * dy * 8);
-  coarse_f64_into(c, Tn, Tp, U1, U3, dx, dy, dn, (double*)c->X1.p, (double*)c->X2.p,
-                  (double*)c->Tt.p, maxbits, 0);
+// Doubles of X1 and X2 of a step.
+long long x1_elems(int dx, int dy, int dn) { return (long long)dn * dy * dx * f64_ld(dx, dy, dn).p; }
+long long x2_elems(int dx, int dy, int dn) { return (long long)dn * dy * dy * f64_ld(dx, dy, dn).n; }
+
+// The projector of a step in FP64 layouts (`kept` null: src is canonical U[a,b,i];
+// else eigenvector rows, the leading one at src, the next at src - n, ...), and
+// the max slot cleared.
+void projector_f64(hotrg_ctx* c, Buf& U1, Buf& U3, const double* src, const int* kept, int dx,
+                   int dy, int dn, unsigned long long* maxbits) {
+  const long long n = (long long)dx * dx;
+  const F64Ld ld = f64_ld(dx, dy, dn);
+  ensure(c, U1, (size_t)(n * dn) * 8);
+  ensure(c, U3, (size_t)(ld.n * ld.u3) * 8);
+  launch_layout_u(src, kept ? 1 : dn, kept ? -n : 1, kept, dx, dn, kFmtF64, U1.p, nullptr, U3.p,
+                  nullptr, dx, ld.u3, maxbits, c->stream);
+}
+
+// C1, C2, C3 in FP64: T~[i,j,k,l] (dims dn,dy,dn,dy) into Tt; clears the padding
+// of X1, X2 and U3 first.
+void coarse_f64(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1, double* U3,
+                int dx, int dy, int dn, double* Tt, unsigned long long* maxbits) {
+  const long long P = (long long)dx * dy, n = (long long)dx * dx;
+  const F64Ld ld = f64_ld(dx, dy, dn);
+  ensure(c, c->X1, (size_t)x1_elems(dx, dy, dn) * 8);
+  ensure(c, c->X2, (size_t)x2_elems(dx, dy, dn) * 8);
+  PadSet pads;
+  pads.add(c->X1.p, (long long)dn * dy * dx, ld.p, P, 8, c->stream);
+  pads.add(c->X2.p, (long long)dn * dy * dy, ld.n, n, 8, c->stream);
+  pads.add(U3 + n * ld.u3, ld.n - n, ld.u3, 0, 8, c->stream);
+  pads.launch(c->stream);
+  coarse_f64_into(c, Tn, Tp, U1, U3, dx, dy, dn, ld, (double*)c->X1.p, (double*)c->X2.p, Tt,
+                  maxbits, 0);
 }
 
 void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, bool src_f32,
@@ -404,17 +430,41 @@ int step_precision(const hotrg_state* st, int k, int dx, int dy, int d_cut) {
 
 int rp_mode(int prec) { return prec == HOTRG_FP32 ? RP_F32 : RP_BF16X3; }
 
-// The operand layouts as strides over (l, u, r, d).  FP64: natural; Xt rows (l,d),
-// columns (u,r); Tp rows (l,u), columns (d,r) (T[a,c,e,l] read as rows (a,c),
-// columns (l,e)).
-PrepOut prep_natural(void* p, long long X, long long Y) {
-  return {p, nullptr, nullptr, kFmtF64, {Y * X * Y, X * Y, Y, 1}};
+// The FP64 operand layouts as strides over (l, u, r, d): natural rows (l,u) of ldp
+// elements; Xt rows (l,d), columns (u,r); Tp rows (l,u), columns (d,r) (T[a,c,e,l]
+// read as rows (a,c), columns (l,e)).
+PrepOut prep_natural(void* p, long long X, long long Y, long long ldp) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * ldp, ldp, Y, 1}};
 }
-PrepOut prep_xt(void* p, long long X, long long Y) {
-  return {p, nullptr, nullptr, kFmtF64, {Y * Y * X, X, 1, Y * X}};
+PrepOut prep_xt(void* p, long long X, long long Y, long long ldp) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * ldp, X, 1, ldp}};
 }
-PrepOut prep_tp(void* p, long long X, long long Y) {
-  return {p, nullptr, nullptr, kFmtF64, {Y * Y * X, Y * X, 1, X}};
+PrepOut prep_tp(void* p, long long X, long long Y, long long ldt) {
+  return {p, nullptr, nullptr, kFmtF64, {Y * ldt, ldt, 1, X}};
+}
+
+// The FP64 operands of a state (buffers large enough) and their padding.
+int prep_f64(PrepOut (&outs)[4], hotrg_state* st, int dx, int dy, hipStream_t s) {
+  const long long P = (long long)dx * dy;
+  const F64Ld ld = f64_ld(dx, dy, 1);
+  int k = 0;
+  outs[k++] = prep_natural(st->Tn.p, dx, dy, P);
+  outs[k++] = prep_xt(st->Xt.p, dx, dy, ld.p);
+  outs[k++] = prep_tp(st->Tp.p, dx, dy, ld.tp);
+  if (ld.p != P) {
+    outs[k++] = prep_natural(st->Tq.p, dx, dy, ld.p);
+    PadSet pads;
+    pads.add(st->Tq.p, P, ld.p, P, 8, s);
+    pads.add(st->Xt.p, P, ld.p, P, 8, s);
+    pads.add((double*)st->Tp.p + P * ld.tp, ld.p - P, ld.tp, 0, 8, s);
+    pads.launch(s);
+  }
+  return k;
+}
+
+// The environment's natural operand of a state.
+const double* env_natural(const hotrg_state* st, int dx, int dy) {
+  return (const double*)(f64_ld(dx, dy, 1).p != (long long)dx * dy ? st->Tq.p : st->Tn.p);
 }
 
 // The reduced-precision operands of a state, rows zero-padded to multiples of 32:
@@ -442,12 +492,15 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
                       const NormArgs* norm) {
   const size_t ne = (size_t)dx * dy * dx * dy;
   if (prec == HOTRG_FP64) {
+    const size_t P = (size_t)dx * dy;
+    const F64Ld ld = f64_ld(dx, dy, 1);
     ensure_keep(c, st->Tn, ne * 8, 0);
-    ensure_keep(c, st->Xt, ne * 8, 0);
-    ensure_keep(c, st->Tp, ne * 8, 0);
-    const PrepOut outs[3] = {prep_natural(st->Tn.p, dx, dy), prep_xt(st->Xt.p, dx, dy),
-                             prep_tp(st->Tp.p, dx, dy)};
-    launch_prep(src, src_f32, rotate, dx, dy, mb, outs, 3, norm, c->stream);
+    ensure_keep(c, st->Xt, P * ld.p * 8, 0);
+    ensure_keep(c, st->Tp, (size_t)ld.p * ld.tp * 8, 0);
+    if ((size_t)ld.p != P) ensure_keep(c, st->Tq, P * ld.p * 8, 0);
+    PrepOut outs[4];
+    const int k = prep_f64(outs, st, dx, dy, c->stream);
+    launch_prep(src, src_f32, rotate, dx, dy, mb, outs, k, norm, c->stream);
     st->cur_f32 = false;
   } else {
     const int mode = rp_mode(prec);
@@ -455,15 +508,17 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
     const long long P = (long long)dx * dy, ldP = pad32(P), ldx = pad32(dx);
     const size_t rows[4] = {(size_t)P, (size_t)P, (size_t)dy * dx * dy, (size_t)P};
     const size_t ld[4] = {(size_t)ldP, (size_t)ldP, (size_t)ldx, (size_t)ldP};
-    const bool padded[4] = {ldP != P, ldP != P, ldx != dx, ldP != P};
+    const long long used[4] = {P, P, dx, P};
     PrepOut outs[4];
+    PadSet pads;
     ensure_keep(c, st->Tn32, ne * 4, 0);
     for (int i = 0; i < 4; ++i) {
       for (int h = 0; h < (mode == RP_F32 ? 1 : 2); ++h) {
         ensure_keep(c, st->RO[i][h], rows[i] * ld[i] * es, 0);
-        if (padded[i]) HIPCHK(hipMemsetAsync(st->RO[i][h].p, 0, rows[i] * ld[i] * es, c->stream));
+        pads.add(st->RO[i][h].p, (long long)rows[i], (long long)ld[i], used[i], (int)es, c->stream);
       }
     }
+    pads.launch(c->stream);
     prep_reduced(outs, st, mode, dx, dy);
     launch_prep(src, src_f32, rotate, dx, dy, mb, outs, 4, norm, c->stream);
     st->cur_f32 = true;
@@ -472,28 +527,27 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
 }
 
 void release_operands(hotrg_ctx* c, hotrg_state* st) {
-  Buf* bufs[] = {&st->Tn, &st->Xt, &st->Tp, &st->Tn32};
+  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->Tn32};
   for (Buf* b : bufs) ctx_free(c, *b);
   for (auto& o : st->RO)
     for (auto& b : o) ctx_free(c, b);
 }
 
 // Environment M (FP64 output) from reduced-precision operands.
-void environment_rp(hotrg_ctx* c, hotrg_state* st, int mode, int dx, int dy) {
+void environment_rp(hotrg_ctx* c, hotrg_state* st, int mode, int dx, int dy, double* M) {
   const long long P = (long long)dx * dy, n = (long long)dx * dx, K2 = (long long)dy * dy;
   const long long ldP = pad32(P), ldK2 = pad32(K2);
   const size_t es = mode == RP_F32 ? 4 : 2;
   const int fmt = mode == RP_F32 ? RP_OUT_F32 : RP_OUT_SPLIT;
   const int halves = mode == RP_F32 ? 1 : 2;
+  PadSet pads;
   for (int h = 0; h < halves; ++h) {
     ensure(c, c->RA1[h], (size_t)n * ldK2 * es);
     ensure(c, c->RA2[h], (size_t)n * ldK2 * es);
-    if (ldK2 != K2) {
-      HIPCHK(hipMemsetAsync(c->RA1[h].p, 0, (size_t)n * ldK2 * es, c->stream));
-      HIPCHK(hipMemsetAsync(c->RA2[h].p, 0, (size_t)n * ldK2 * es, c->stream));
-    }
+    pads.add(c->RA1[h].p, n, ldK2, K2, (int)es, c->stream);
+    pads.add(c->RA2[h].p, n, ldK2, K2, (int)es, c->stream);
   }
-  ensure(c, c->M, (size_t)(n * n) * 8);
+  pads.launch(c->stream);
   auto op = [&](Buf* b) { return RpOperand{b[0].p, halves == 2 ? b[1].p : nullptr}; };
   const RpOperand OT = op(st->RO[0]), OX = op(st->RO[1]);
   // halves stored as [(i,k),(e,f)]: rows (i,e): i -> dx*ldK2, e -> dy; cols (k,f): k -> ldK2, f -> 1
@@ -504,9 +558,27 @@ void environment_rp(hotrg_ctx* c, hotrg_state* st, int mode, int dx, int dy) {
                      halves == 2 ? c->RA1[1].p : nullptr, o2, (int)P, (int)P, (int)ldP, nullptr,
                      c->stream, GEMM_TAG_ENV);
   const OutMap om = omap2(dx, dx * n, dx, dx, n, 1);
-  ok = ok && gemm_rp(mode, op(c->RA2), ldK2, op(c->RA1), ldK2, RP_OUT_F64, c->M.p, nullptr, om,
+  ok = ok && gemm_rp(mode, op(c->RA2), ldK2, op(c->RA1), ldK2, RP_OUT_F64, M, nullptr, om,
                      (int)n, (int)n, (int)ldK2, nullptr, c->stream, GEMM_TAG_ENV);
   if (!ok) fail(HOTRG_ERR_INVALID, "reduced-precision environment: unsupported operand shape");
+}
+
+// The projector of a step in the reduced formats (src and kept as for
+// projector_f64), padding and max slot cleared.
+void projector_rp(hotrg_ctx* c, int mode, const double* src, const int* kept, int dx, int dn,
+                  unsigned long long* maxbits) {
+  const size_t es = mode == RP_F32 ? 4 : 2;
+  const long long n = (long long)dx * dx, ldx = pad32(dx), ldn = pad32(n);
+  PadSet pads;
+  for (int h = 0; h < (mode == RP_F32 ? 1 : 2); ++h) {
+    ensure(c, c->RU1[h], (size_t)dn * dx * ldx * es);
+    ensure(c, c->RU3[h], (size_t)dn * ldn * es);
+    pads.add(c->RU1[h].p, (long long)dn * dx, ldx, dx, (int)es, c->stream);
+    pads.add(c->RU3[h].p, dn, ldn, n, (int)es, c->stream);
+  }
+  pads.launch(c->stream);
+  launch_layout_u(src, kept ? 1 : dn, kept ? -n : 1, kept, dx, dn, mode, c->RU1[0].p, c->RU1[1].p,
+                  c->RU3[0].p, c->RU3[1].p, ldx, ldn, maxbits, c->stream);
 }
 
 // C1, C2, C3 from reduced-precision operands; T~ (FP32) into c->Tt.
@@ -518,12 +590,14 @@ void coarse_rp(hotrg_ctx* c, hotrg_state* st, int mode, int dx, int dy, int dn,
   const int fmt = mode == RP_F32 ? RP_OUT_F32 : RP_OUT_SPLIT;
   const int halves = mode == RP_F32 ? 1 : 2;
   const long long x1rows = (long long)dn * dy * dx, x2rows = (long long)dn * dy * dy;
+  PadSet pads;
   for (int h = 0; h < halves; ++h) {
     ensure(c, c->RX1[h], (size_t)x1rows * ldP * es);
     ensure(c, c->RX2[h], (size_t)x2rows * ldn * es);
-    if (ldP != P) HIPCHK(hipMemsetAsync(c->RX1[h].p, 0, (size_t)x1rows * ldP * es, c->stream));
-    if (ldn != n) HIPCHK(hipMemsetAsync(c->RX2[h].p, 0, (size_t)x2rows * ldn * es, c->stream));
+    pads.add(c->RX1[h].p, x1rows, ldP, P, (int)es, c->stream);
+    pads.add(c->RX2[h].p, x2rows, ldn, n, (int)es, c->stream);
   }
+  pads.launch(c->stream);
   ensure(c, c->Tt, (size_t)dn * dy * dn * dy * 4);
   auto op = [&](Buf* b) { return RpOperand{b[0].p, halves == 2 ? b[1].p : nullptr}; };
   // C1: rows (i,a): i -> dy*dx*ldP, a -> dy; cols (j,d,c): j -> dx*ldP, d -> ldP, c -> 1
@@ -673,10 +747,11 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   c->m_dn = dn;
   mark(c, HOTRG_PHASE_ENV);
   // environment M (FP64 out)
+  ensure(c, c->M, (size_t)n * n * 8);
   if (sp == HOTRG_FP64)
-    environment_f64(c, (const double*)st->Tn.p, (const double*)st->Xt.p, dx, dy);
+    environment_f64(c, env_natural(st, dx, dy), (const double*)st->Xt.p, dx, dy, (double*)c->M.p);
   else
-    environment_rp(c, st, rp_mode(sp), dx, dy);
+    environment_rp(c, st, rp_mode(sp), dx, dy, (double*)c->M.p);
   double* trace = (double*)((char*)c->scal.p + 40);
   launch_symmetrize((double*)c->M.p, n, trace, c->stream);
   // FP64 eigendecomposition, spectrum and projector
@@ -697,9 +772,10 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
     // the right pair of legs: environment of the reflected tensor (FP64)
     if (sp != HOTRG_FP64) fail(HOTRG_ERR_INVALID, "two-sided isometry needs FP64 contractions");
-    const size_t ne = (size_t)dx * dy * dx * dy;
-    ensure(c, c->Tm, ne * 8);
-    ensure(c, c->Xm, ne * 8);
+    const long long P = (long long)dx * dy, ldp = f64_ld(dx, dy, dn).p;
+    ensure(c, c->Tm, (size_t)(P * ldp) * 8);
+    ensure(c, c->Xm, (size_t)(P * ldp) * 8);
+    ensure(c, c->M2, (size_t)n * n * 8);
     ensure(c, c->Side, (size_t)(kRec + 3 + st->spec_len) * 8);
     double* rec2 = (double*)c->Side.p;
     int* kept2 = (int*)(rec2 + kRec);
@@ -707,9 +783,13 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
     int* info2 = (int*)(rec2 + kRec + 2);
     double* spec2 = st->spec_len ? rec2 + kRec + 3 : nullptr;
     mark(c, HOTRG_PHASE_ENV);
-    launch_prep_mirror((const double*)st->Tn.p, dx, dy, (double*)c->Tm.p, (double*)c->Xm.p,
+    PadSet pads;
+    pads.add(c->Tm.p, P, ldp, P, 8, c->stream);
+    pads.add(c->Xm.p, P, ldp, P, 8, c->stream);
+    pads.launch(c->stream);
+    launch_prep_mirror((const double*)st->Tn.p, dx, dy, ldp, (double*)c->Tm.p, (double*)c->Xm.p,
                        c->stream);
-    environment_f64(c, (const double*)c->Tm.p, (const double*)c->Xm.p, dx, dy, &c->M2);
+    environment_f64(c, (const double*)c->Tm.p, (const double*)c->Xm.p, dx, dy, (double*)c->M2.p);
     launch_symmetrize((double*)c->M2.p, n, trace2, c->stream);
     mark(c, HOTRG_PHASE_EIGH);
     int cols2 = n;
@@ -739,26 +819,14 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   // the projector in the contractions' layouts, from the last eigenvector rows
   const double* top = evec + (long long)(cols - 1) * n;
   if (sp == HOTRG_FP64) {
-    ensure(c, c->U1, (size_t)n * dn * 8);
-    ensure(c, c->U3, (size_t)n * dn * 8);
-    launch_layout_u(top, 1, -n, kept, dx, dn, kFmtF64, c->U1.p, nullptr, c->U3.p, nullptr, dx, dn,
-                    mb, c->stream);
+    projector_f64(c, c->U1, c->U3, top, kept, dx, dy, dn, mb);
     // the three contractions, max|T~|
+    ensure(c, c->Tt, (size_t)dn * dy * dn * dy * 8);
     coarse_f64(c, (const double*)st->Tn.p, (const double*)st->Tp.p, (const double*)c->U1.p,
-               (const double*)c->U3.p, dx, dy, dn, mb);
+               (double*)c->U3.p, dx, dy, dn, (double*)c->Tt.p, mb);
   } else {
-    const int mode = rp_mode(sp);
-    const size_t es = mode == RP_F32 ? 4 : 2;
-    const long long ldx = pad32(dx), ldn = pad32(n);
-    for (int h = 0; h < (mode == RP_F32 ? 1 : 2); ++h) {
-      ensure(c, c->RU1[h], (size_t)dn * dx * ldx * es);
-      ensure(c, c->RU3[h], (size_t)dn * ldn * es);
-      if (ldx != dx) HIPCHK(hipMemsetAsync(c->RU1[h].p, 0, (size_t)dn * dx * ldx * es, c->stream));
-      if (ldn != n) HIPCHK(hipMemsetAsync(c->RU3[h].p, 0, (size_t)dn * ldn * es, c->stream));
-    }
-    launch_layout_u(top, 1, -n, kept, dx, dn, mode, c->RU1[0].p, c->RU1[1].p, c->RU3[0].p,
-                    c->RU3[1].p, ldx, ldn, mb, c->stream);
-    coarse_rp(c, st, mode, dx, dy, dn, mb);
+    projector_rp(c, rp_mode(sp), top, kept, dx, dn, mb);
+    coarse_rp(c, st, rp_mode(sp), dx, dy, dn, mb);
   }
   // ln n_k, torus estimate; operands of the next step (legs transposed)
   mark(c, HOTRG_PHASE_NORM);
@@ -970,7 +1038,8 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     }
   } else {
     for (GProb* g : R.act)
-      environment_f64(c, (const double*)g->st->Tn.p, (const double*)g->st->Xt.p, g->D, g->D, &g->M);
+      environment_f64(c, env_natural(g->st, g->D, g->D), (const double*)g->st->Xt.p, g->D, g->D,
+                      (double*)g->M.p);
   }
   for (GProb* g : R.act) {
     launch_symmetrize((double*)g->M.p, g->n, (double*)((char*)g->scal.p + 8), s);
@@ -1020,8 +1089,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
       launch_layout_u(top, 1, -g->n, kept, g->D, g->D, R.mode, g->RU1[0].p, g->RU1[1].p,
                       g->RU3[0].p, g->RU3[1].p, pad32(g->D), pad32(g->n), mb, s);
     else
-      launch_layout_u(top, 1, -g->n, kept, g->D, g->D, kFmtF64, g->U1.p, nullptr, g->U3.p, nullptr,
-                      g->D, g->D, mb, s);
+      projector_f64(c, g->U1, g->U3, top, kept, g->D, g->D, g->D, mb);
   }
   // the three contractions, max|T~|
   if (red) {
@@ -1059,10 +1127,9 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     }
   } else {
     for (GProb* g : R.act)
-      coarse_f64_into(c, (const double*)g->st->Tn.p, (const double*)g->st->Tp.p,
-                      (const double*)g->U1.p, (const double*)g->U3.p, g->D, g->D, g->D,
-                      (double*)c->X1.p, (double*)c->X2.p, (double*)g->Tt.p,
-                      (unsigned long long*)g->scal.p, 0);  // shapes tuned by the eager sweep
+      coarse_f64(c, (const double*)g->st->Tn.p, (const double*)g->st->Tp.p, (const double*)g->U1.p,
+                 (double*)g->U3.p, g->D, g->D, g->D, (double*)g->Tt.p,
+                 (unsigned long long*)g->scal.p);  // shapes tuned by the eager sweep
   }
   // ln n_k, torus estimate; operands of the next step (legs transposed)
   group_norm(R.steps, G, s);
@@ -1073,9 +1140,9 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
       prep_reduced(outs, g->st, R.mode, g->D, g->D);
       launch_prep(g->Tt.p, true, true, g->D, g->D, mb, outs, 4, nullptr, s);
     } else {
-      const PrepOut outs[3] = {prep_natural(g->st->Tn.p, g->D, g->D), prep_xt(g->st->Xt.p, g->D, g->D),
-                               prep_tp(g->st->Tp.p, g->D, g->D)};
-      launch_prep(g->Tt.p, false, true, g->D, g->D, mb, outs, 3, nullptr, s);
+      PrepOut outs[4];
+      const int k = prep_f64(outs, g->st, g->D, g->D, s);
+      launch_prep(g->Tt.p, false, true, g->D, g->D, mb, outs, k, nullptr, s);
     }
   }
   group_advance(R.steps, G, s);
@@ -1423,17 +1490,21 @@ void run_grouped_impl(hotrg_ctx* c, int N, const hotrg_model_params* params,
           }
         } else {
           ensure(c, g.Tt, (size_t)(D * D * D * D) * 8);
+          const F64Ld ld = f64_ld((int)D, (int)D, (int)D);
           ensure(c, g.U1, (size_t)(n * D) * 8);
-          ensure(c, g.U3, (size_t)(n * D) * 8);
+          ensure(c, g.U3, (size_t)(ld.n * ld.u3) * 8);
         }
       }
       if (!red) {
         // FP64 contractions run problem after problem through the context's
         // intermediates: sized for the largest
-        long long xmax = 1;
-        for (GProb* g : grp) xmax = std::max(xmax, (long long)g->D * g->D * g->D * g->D * g->D);
-        ensure(c, c->X1, (size_t)xmax * 8);
-        ensure(c, c->X2, (size_t)xmax * 8);
+        long long x1 = 1, x2 = 1;
+        for (GProb* g : grp) {
+          x1 = std::max(x1, x1_elems(g->D, g->D, g->D));
+          x2 = std::max(x2, x2_elems(g->D, g->D, g->D));
+        }
+        ensure(c, c->X1, (size_t)x1 * 8);
+        ensure(c, c->X2, (size_t)x2 * 8);
       }
       HIPCHK(hipMemcpyAsync(ctlbuf.p, ctl.data(), ctl.size() * sizeof(GroupCtl),
                             hipMemcpyHostToDevice, c->stream));
@@ -1775,7 +1846,7 @@ void hotrg_state_free(hotrg_ctx* c, hotrg_state* st) {
   if (!c || !st) return;
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  Buf* bufs[] = {&st->Tn, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
+  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
   for (Buf* b : bufs) ctx_free(c, *b);
   for (auto& o : st->RO)
     for (auto& b : o) ctx_free(c, b);
@@ -1894,12 +1965,10 @@ hotrg_status hotrg_environment(hotrg_ctx* c, int prec, const double* T, int dx, 
       c->m_dn = dx * dx;
       mark(c, HOTRG_PHASE_ENV);
       if (prec == HOTRG_FP64)
-        environment_f64(c, (const double*)tmp.Tn.p, (const double*)tmp.Xt.p, dx, dy);
+        environment_f64(c, env_natural(&tmp, dx, dy), (const double*)tmp.Xt.p, dx, dy, M);
       else
-        environment_rp(c, &tmp, rp_mode(prec), dx, dy);
+        environment_rp(c, &tmp, rp_mode(prec), dx, dy, M);
       mark(c, -1);
-      const size_t nn = (size_t)dx * dx * dx * dx;
-      HIPCHK(hipMemcpyAsync(M, c->M.p, nn * 8, hipMemcpyDeviceToDevice, c->stream));
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(c->stream));
     } catch (...) {
@@ -1984,28 +2053,13 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
       c->m_dn = dn;
       const size_t no = (size_t)dn * dy * dn * dy;
       if (prec == HOTRG_FP64) {
-        const size_t nu = (size_t)dx * dx * dn;
-        ensure(c, c->U1, nu * 8);
-        ensure(c, c->U3, nu * 8);
-        launch_layout_u(U, dn, 1, nullptr, dx, dn, kFmtF64, c->U1.p, nullptr, c->U3.p, nullptr, dx,
-                        dn, mb, c->stream);
+        projector_f64(c, c->U1, c->U3, U, nullptr, dx, dy, dn, mb);
         coarse_f64(c, (const double*)tmp.Tn.p, (const double*)tmp.Tp.p, (const double*)c->U1.p,
-                   (const double*)c->U3.p, dx, dy, dn, mb);
+                   (double*)c->U3.p, dx, dy, dn, Tt, mb);
         mark(c, -1);
-        HIPCHK(hipMemcpyAsync(Tt, c->Tt.p, no * 8, hipMemcpyDeviceToDevice, c->stream));
       } else {
-        const int mode = rp_mode(prec);
-        const size_t es = mode == RP_F32 ? 4 : 2;
-        const long long n = (long long)dx * dx, ldx = pad32(dx), ldn = pad32(n);
-        for (int h = 0; h < (mode == RP_F32 ? 1 : 2); ++h) {
-          ensure(c, c->RU1[h], (size_t)dn * dx * ldx * es);
-          ensure(c, c->RU3[h], (size_t)dn * ldn * es);
-          HIPCHK(hipMemsetAsync(c->RU1[h].p, 0, (size_t)dn * dx * ldx * es, c->stream));
-          HIPCHK(hipMemsetAsync(c->RU3[h].p, 0, (size_t)dn * ldn * es, c->stream));
-        }
-        launch_layout_u(U, dn, 1, nullptr, dx, dn, mode, c->RU1[0].p, c->RU1[1].p, c->RU3[0].p,
-                        c->RU3[1].p, ldx, ldn, mb, c->stream);
-        coarse_rp(c, &tmp, mode, dx, dy, dn, mb);
+        projector_rp(c, rp_mode(prec), U, nullptr, dx, dn, mb);
+        coarse_rp(c, &tmp, rp_mode(prec), dx, dy, dn, mb);
         mark(c, -1);
         launch_f32_to_f64((const float*)c->Tt.p, Tt, (long long)no, c->stream);
       }

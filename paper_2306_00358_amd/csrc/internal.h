@@ -148,6 +148,30 @@ bool gemm_rp(int mode, const RpOperand& A, long long lda, const RpOperand& B, lo
              unsigned long long* maxbits, hipStream_t s, int tag);
 inline long long pad32(long long k) { return (k + 31) / 32 * 32; }
 
+// Row lengths of the FP64 operands of a step with dims (dx, dy) and D' = dn.  A
+// contracted index of 128 or more is padded with zeros to a multiple of 16, the
+// K slab of the direct-to-LDS tiles, which refuse other K (and odd strides of an
+// N-contiguous operand); smaller ones go to the small tiles, which take any K.
+// D = 50 (K = 2500): C1, C2, C3 29.7 ms by register-staged tiles, 26.8 padded.
+inline long long pad16(long long k) { return k < 128 ? k : (k + 15) / 16 * 16; }
+struct F64Ld {
+  long long p;   // (r,d), (u,r), (a,c): environment operands, X1 and K of C2
+  long long tp;  // columns (l,e) of C2's B
+  long long n;   // (d,e): X2 and K of C3
+  long long u3;  // columns k of C3's B
+  long long k2;  // (e,f): the environment halves
+};
+inline F64Ld f64_ld(int dx, int dy, int dn) {
+  const long long P = (long long)dx * dy, n = (long long)dx * dx;
+  return F64Ld{pad16(P), P < 128 ? P : P + (P & 1), pad16(n), n < 128 ? dn : dn + (dn & 1LL),
+               pad16((long long)dy * dy)};
+}
+// the same, nothing padded
+inline F64Ld f64_ld_plain(int dx, int dy, int dn) {
+  const long long P = (long long)dx * dy;
+  return F64Ld{P, P, (long long)dx * dx, dn, (long long)dy * dy};
+}
+
 // One product of a grouped launch (device table): the operands and output
 // of gemm_rp, and a gate (device int, may be null) that skips the product's
 // tiles while it reads 0.
@@ -215,7 +239,21 @@ struct NormArgs {
 void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
                  const unsigned long long* maxbits, const PrepOut* outs, int count,
                  const NormArgs* norm, hipStream_t s);
-void launch_prep_mirror(const double* T, int dx, int dy, double* Tn, double* Xt, hipStream_t s);
+void launch_prep_mirror(const double* T, int dx, int dy, long long ld, double* Tn, double* Xt,
+                        hipStream_t s);
+// Padding to clear, several regions a launch (launched by itself when full).
+struct PadRegion {
+  void* p;
+  long long rows, ld, from;  // columns [from, ld) of each row
+  int es;                    // element size: 2, 4 or 8
+};
+struct PadSet {
+  static constexpr int kMax = 8;
+  PadRegion r[kMax];
+  int count = 0;
+  void add(void* p, long long rows, long long ld, long long from, int es, hipStream_t s);
+  void launch(hipStream_t s);
+};
 void launch_store(double* p, double v, hipStream_t s);
 // M <- (M + M^T) / 2 and *trace = trace(M)
 void launch_symmetrize(double* M, int n, double* trace, hipStream_t s);
@@ -302,12 +340,12 @@ void group_norm(const GroupStep* d, int count, hipStream_t s);
 void group_advance(const GroupStep* d, int count, hipStream_t s);
 
 // ---- engine hooks used by the scheduler (sched.cpp) ----
-// C1 -> C2 -> C3 in FP64 on caller buffers (X1, X2: dn*dx*dy*dx*dy doubles;
-// Tt: dn*dy*dn*dy); *maxbits, cleared by the caller's layout kernel, receives
+// C1 -> C2 -> C3 in FP64 on caller buffers with rows as `ld` says, padding zero
+// (X1: dn*dy*dx rows, X2: dn*dy*dy rows; Tt: dn*dy*dn*dy); *maxbits, cleared by the caller's layout kernel, receives
 // max|Tt|.
 void coarse_f64_into(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1,
-                     const double* U3, int dx, int dy, int dn, double* X1, double* X2, double* Tt,
-                     unsigned long long* maxbits, int tag_flags);
+                     const double* U3, int dx, int dy, int dn, const F64Ld& ld, double* X1,
+                     double* X2, double* Tt, unsigned long long* maxbits, int tag_flags);
 hipStream_t ctx_stream(const hotrg_ctx* c);
 // Allocation-free entry point's scratch (noalloc.hip): look up this device's
 // copy of the static array once (call with the device current).

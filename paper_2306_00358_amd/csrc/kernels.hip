@@ -234,11 +234,49 @@ void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
   if (blocks > 0) hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(256), 0, s, S);
 }
 
+// Columns [from, ld) of `rows` rows of ld elements of es bytes, for each region
+// (one grid row each) = 0: the padding of operands whose rows are longer than
+// their contracted index, so that the products need no remainder in K.  Only
+// the padding is written -- clearing the whole of a D^5 intermediate, as for
+// D^2 not a multiple of 32, cost as much as a contraction's own stores.
+__global__ __launch_bounds__(256) void k_zero_pads(PadSet S) {
+  const PadRegion& R = S.r[blockIdx.y];
+  const long long w = R.ld - R.from, total = R.rows * w;
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < total; e += gridDim.x * 256LL) {
+    const long long row = e / w, o = row * R.ld + R.from + (e - row * w);
+    if (R.es == 8)
+      ((double*)R.p)[o] = 0.0;
+    else if (R.es == 4)
+      ((float*)R.p)[o] = 0.0f;
+    else
+      ((unsigned short*)R.p)[o] = 0;
+  }
+}
+
+void PadSet::add(void* p, long long rows, long long ld, long long from, int es, hipStream_t s) {
+  if (!p || rows <= 0 || from >= ld) return;
+  if (count == kMax) launch(s);
+  r[count++] = PadRegion{p, rows, ld, from, es};
+}
+
+void PadSet::launch(hipStream_t s) {
+  if (count == 0) return;
+  long long most = 1;
+  for (int i = 0; i < count; ++i) {
+    const long long t = r[i].rows * (r[i].ld - r[i].from);
+    most = t > most ? t : most;
+  }
+  const long long blocks = (most + 255) / 256;
+  hipLaunchKernelGGL(k_zero_pads, dim3((unsigned)(blocks < 2048 ? blocks : 2048), count), dim3(256),
+                     0, s, *this);
+  count = 0;
+}
+
 // The reflected tensor T'[l,u,r,d] = T[r,u,l,d] (FP64, dims (dx,dy,dx,dy)) in
-// the natural layout and in the Xt layout [(l,d),(u,r)]: the operands whose
-// environment is that of the right pair of legs of T.
-__global__ void k_prep_mirror(const double* __restrict__ T, int dx, int dy, double* Tn,
-                              double* Xt) {
+// the natural layout and in the Xt layout [(l,d),(u,r)], rows of ld elements:
+// the operands whose environment is that of the right pair of legs of T.
+__global__ void k_prep_mirror(const double* __restrict__ T, int dx, int dy, long long ld,
+                              double* Tn, double* Xt) {
   const long long total = (long long)dx * dy * dx * dy;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
        e += (long long)gridDim.x * blockDim.x) {
@@ -248,14 +286,16 @@ __global__ void k_prep_mirror(const double* __restrict__ T, int dx, int dy, doub
     int u = (int)(q % dy); q /= dy;
     int l = (int)q;
     const double v = T[(((long long)r * dy + u) * dx + l) * dy + d];
-    Tn[e] = v;
-    Xt[(((long long)l * dy + d) * dy + u) * dx + r] = v;
+    Tn[((long long)l * dy + u) * ld + (long long)r * dy + d] = v;
+    Xt[((long long)l * dy + d) * ld + (long long)u * dx + r] = v;
   }
 }
 
-void launch_prep_mirror(const double* T, int dx, int dy, double* Tn, double* Xt, hipStream_t s) {
+void launch_prep_mirror(const double* T, int dx, int dy, long long ld, double* Tn, double* Xt,
+                        hipStream_t s) {
   long long total = (long long)dx * dy * dx * dy;
-  hipLaunchKernelGGL(k_prep_mirror, dim3(nblocks(total, 256)), dim3(256), 0, s, T, dx, dy, Tn, Xt);
+  hipLaunchKernelGGL(k_prep_mirror, dim3(nblocks(total, 256)), dim3(256), 0, s, T, dx, dy, ld, Tn,
+                     Xt);
 }
 
 __global__ void k_store(double* p, double v) {

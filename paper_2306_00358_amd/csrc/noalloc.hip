@@ -112,7 +112,8 @@ hotrg_status hotrg_coarse_noalloc(hotrg_ctx* ctx, const double* T, const double*
   const PrepOut tp{Tp, nullptr, nullptr, kFmtF64, {Y * Y * X, Y * X, 1, X}};
   launch_prep(T, false, false, dx, dy, nullptr, &tp, 1, nullptr, s);
   launch_layout_u(U, dn, 1, nullptr, dx, dn, kFmtF64, U1, nullptr, U3, nullptr, dx, dn, mb, s);
-  coarse_f64_into(ctx, T, Tp, U1, U3, dx, dy, dn, X1, X2, Tt, mb, GEMM_NO_TUNE);
+  coarse_f64_into(ctx, T, Tp, U1, U3, dx, dy, dn, f64_ld_plain(dx, dy, dn), X1, X2, Tt, mb,
+                  GEMM_NO_TUNE);
   const hipError_t e = hipGetLastError();
   if (cdev != dev) (void)hipSetDevice(dev);
   if (e != hipSuccess) {

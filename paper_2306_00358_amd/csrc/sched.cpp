@@ -128,26 +128,32 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
     if (b > peak[name]) peak[name] = b;
   };
   auto pad = [](long long k) { return (double)((k + 31) / 32 * 32); };
-  need("state", 3.0 * dx * dy * dx * dy * 8);
+  // FP64 operands of a step: natural, Tp, Xt and the padded natural copy
+  auto state = [](int dx, int dy) {
+    const double P = (double)dx * dy;
+    const F64Ld ld = f64_ld(dx, dy, 1);
+    return (P * P + (double)ld.p * ld.tp + 2 * P * ld.p) * 8;
+  };
+  need("state", state(dx, dy));
   for (int k = 0; k < o->n_steps; ++k) {
-    const double n = (double)dx * dx, P = (double)dx * dy;
+    const double n = (double)dx * dx;
     const int dn = (int)std::min<long long>(o->d_cut, (long long)dx * dx);
-    const double X = (double)dn * dx * dx * dy * dy;
+    const F64Ld ld = f64_ld(dx, dy, dn);
     const bool red = step_is_reduced(o->prec, k + 1, dx, dy, o->d_cut, k0);
     need("M", n * n * 8);
     need("WE", 2 * n * 8);
-    need("U", 3 * n * dn * 8);
+    need("U", (2 * n * dn + (double)ld.n * ld.u3) * 8);
     const int p = std::min(128, std::max(2 * dn, dn + 17));
     need("eig", (double)topk_workspace_doubles((int)n, (p + 15) / 16 * 16) * 8 + (double)p * n * 8);
     // dsyevd fallback workspace; the small dense solver's vectors of both sides
     need("dense", (n > 128 ? 1 : 2) * n * n * 8);
     if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
       // mirrored operands, right environment, its eigenpairs
-      need("side", 2.0 * dx * dy * dx * dy * 8 + n * n * 8 + n * 8 + (double)p * n * 8);
+      need("side", 2.0 * dx * dy * ld.p * 8 + n * n * 8 + n * 8 + (double)p * n * 8);
     }
     if (!red) {
-      need("A12", 2 * P * P * 8);
-      need("X12", 2 * X * 8);
+      need("A12", 2 * n * ld.k2 * 8);
+      need("X12", (double)dn * dy * ((double)dx * ld.p + (double)dy * ld.n) * 8);
       need("Tt", (double)dn * dy * dn * dy * 8);
     } else {
       const double es = 4;  // FP32, or two bf16 arrays
@@ -158,8 +164,8 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
       need("Tt", (double)dn * dy * dn * dy * 4);
       need("rstate", 4 * (double)dy * dn * dy * dn * 8);
     }
-    // next state (both generations exist while the operands are rebuilt)
-    need("state", 6.0 * dy * dn * dy * dn * 8);
+    // next state (an operand that grows has both generations while it moves)
+    need("state", state(dy, dn) + (double)dy * dn * f64_ld(dy, dn, 1).p * 8);
     const int ndx = dy;
     dy = dn;
     dx = ndx;

@@ -71,3 +71,32 @@ def test_coarse_and_environment_small(dx, dy, dn):
     for got, want in ((M, hotrg.environment(T)), (Tt, hotrg.coarse_tensor(T, U))):
         assert np.abs(got.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
     assert mx.item() == Tt.abs().max().item()
+
+
+# contracted indices of 128 and more not a multiple of 16: rows padded with
+# zeros, odd and even strides, in buffers that the shape before left full
+RAGGED = [(27, 31, 29), (12, 11, 13), (11, 12, 7), (15, 17, 16), (13, 13, 13), (41, 40, 9),
+          (12, 12, 12), (3, 43, 9), (20, 33, 20)]
+
+
+@pytest.mark.parametrize("prec, tol", [("fp64", 1e-12), ("fp32", 2e-5), ("bf16x3", 2e-4)])
+def test_ragged_sizes(prec, tol):
+    # (FP32: K <= 1681 products of 2^-24 each way, 1e-4 at worst and about 1e-6
+    # in practice; split BF16 drops products below 2^-16 of the largest.  Both
+    # far below an element lost or doubled by wrong padding.)
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_coarse, hotrg_environment
+    from tests.inputs import random_projector
+
+    with Context(0) as ctx:
+        for dx, dy, dn in RAGGED:
+            print("ragged", prec, dx, dy, dn, flush=True)
+            T, U = random_tensor(dx, dy, seed=dx + 3 * dy), random_projector(dx, dn, seed=dn)
+            Tg, Ug = torch.from_numpy(T).to("cuda"), torch.from_numpy(U).to("cuda")
+            M = torch.full((dx * dx, dx * dx), float("nan"), dtype=torch.float64, device="cuda")
+            Tt = torch.full((dn, dy, dn, dy), float("nan"), dtype=torch.float64, device="cuda")
+            hotrg_environment(ctx, Tg, M, prec=prec)
+            hotrg_coarse(ctx, Tg, Ug, Tt, prec=prec)
+            for got, want in ((M, hotrg.environment(T)), (Tt, hotrg.coarse_tensor(T, U))):
+                assert np.abs(got.cpu().numpy() - want).max() <= tol * np.abs(want).max()
