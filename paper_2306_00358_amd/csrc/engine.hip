@@ -87,6 +87,9 @@ struct hotrg_ctx {
   // 32 primitive max (u64), 40 trace(M) (double), 48 iterative solver info (int)
   int last_eig_iters = 0;      // sweeps of the last iterative solve (0: dense solver)
   double last_eig_resid = 0.0;
+  // the buffers of the last whole run or single operation, kept for the next
+  // (retire_state); null: none, or taken by the call under way
+  hotrg_state* spare = nullptr;
   // many-problem scheduler (sched.cpp), created on first use
   void* sched = nullptr;
   int n_workers = 16;
@@ -154,6 +157,53 @@ void ctx_free(hotrg_ctx* c, Buf& b) {
   }
 }
 
+void release_state(hotrg_ctx* c, hotrg_state* st) {
+  if (!st) return;
+  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
+  for (Buf* b : bufs) ctx_free(c, *b);
+  for (auto& o : st->RO)
+    for (auto& b : o) ctx_free(c, b);
+  delete st;
+}
+
+void release_spare(hotrg_ctx* c) {
+  release_state(c, c->spare);
+  c->spare = nullptr;
+}
+
+// A state without a tensor, with the spare's buffers if there are any.  Whole
+// runs and single operations begin here and end in retire_state: like the step
+// workspace, one state's operands stay with the context, because allocating
+// them each call cost more than the small products that use them (environment
+// at D = 45: 1311 us a call with, 679 without).  States that the
+// caller holds own their buffers and give them back when freed.
+hotrg_state* take_state(hotrg_ctx* c) {
+  hotrg_state* old = c->spare;
+  if (!old) return new hotrg_state();
+  auto* st = new hotrg_state();
+  c->spare = nullptr;
+  std::swap(st->Tn, old->Tn);
+  std::swap(st->Tq, old->Tq);
+  std::swap(st->Xt, old->Xt);
+  std::swap(st->Tp, old->Tp);
+  std::swap(st->acc, old->acc);
+  std::swap(st->recs, old->recs);
+  std::swap(st->spec, old->spec);
+  std::swap(st->Tn32, old->Tn32);
+  std::swap(st->RO, old->RO);
+  delete old;
+  return st;
+}
+
+// The end of take_state's user, its work on the stream waited for.  A context
+// with a memory budget keeps nothing: its budget is what later calls count on.
+void retire_state(hotrg_ctx* c, hotrg_state* st) {
+  if (c->budget || c->spare)
+    release_state(c, st);
+  else
+    c->spare = st;
+}
+
 // Make `b` hold at least `bytes`, keeping the HBM budget.  Growing frees the
 // old buffer first (its contents are not kept).
 void ensure(hotrg_ctx* c, Buf& b, size_t bytes) {
@@ -167,6 +217,11 @@ void ensure(hotrg_ctx* c, Buf& b, size_t bytes) {
                             std::to_string(c->budget) + " in use");
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory && c->spare) {
+    (void)hipGetLastError();
+    release_spare(c);
+    e = hipMalloc(&p, bytes);
+  }
   if (e != hipSuccess)
     fail(e == hipErrorOutOfMemory ? HOTRG_ERR_OOM : HOTRG_ERR_DEVICE,
          std::string("hipMalloc(") + std::to_string(bytes) + "): " + hipGetErrorString(e));
@@ -392,10 +447,12 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
                       bool rotate, int dx, int dy, const unsigned long long* mb,
                       const NormArgs* norm = nullptr);
 
-hotrg_state* new_state(hotrg_ctx* c, const std::vector<double>& T0, int dx, int dy, int prec) {
+// (`whole`: for a run that ends in retire_state)
+hotrg_state* new_state(hotrg_ctx* c, const std::vector<double>& T0, int dx, int dy, int prec,
+                       bool whole = false) {
   for (double v : T0)
     if (!std::isfinite(v)) fail(HOTRG_ERR_NUMERIC, "initial tensor has a non-finite element");
-  auto* st = new hotrg_state();
+  hotrg_state* st = whole ? take_state(c) : new hotrg_state();
   try {
     st->prec = prec;
     st->dx = dx;
@@ -526,11 +583,14 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
   st->ops_prec = prec;
 }
 
-void release_operands(hotrg_ctx* c, hotrg_state* st) {
-  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->Tn32};
-  for (Buf* b : bufs) ctx_free(c, *b);
-  for (auto& o : st->RO)
-    for (auto& b : o) ctx_free(c, b);
+// The natural FP64 tensor of a single operation: T itself where the products can
+// read it as it is (16-byte loads), else through a copy of the state's.
+const double* natural_f64(hotrg_ctx* c, hotrg_state* st, const double* T, int dx, int dy,
+                          PrepOut (&outs)[4], int& k) {
+  if (((uintptr_t)T & 15) == 0) return T;
+  ensure(c, st->Tn, (size_t)dx * dy * dx * dy * 8);
+  outs[k++] = prep_natural(st->Tn.p, dx, dy, (long long)dx * dy);
+  return (const double*)st->Tn.p;
 }
 
 // Environment M (FP64 output) from reduced-precision operands.
@@ -1633,7 +1693,7 @@ hotrg_status run_problem(hotrg_ctx* c, const hotrg_model_params* params, const h
     const hotrg_opts* o = &ro;
     check_opts(o);
     if (cancel && cancel->load()) fail(HOTRG_ERR_CANCELLED, "cancelled");
-    st = new_state(c, T0, dx, dy, o->prec);
+    st = new_state(c, T0, dx, dy, o->prec, true);
     st->first_reduced = first_reduced_step(o->prec, o->tol);
     std::vector<int> dxs, dys, dns;
     for (int k = 0; k < o->n_steps; ++k) {
@@ -1661,7 +1721,13 @@ hotrg_status run_problem(hotrg_ctx* c, const hotrg_model_params* params, const h
     res->err_bound = st->err_bound;
     res->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   });
-  if (st) hotrg_state_free(c, st);
+  if (st) {
+    (void)hipStreamSynchronize(c->stream);
+    if (s == HOTRG_OK)
+      retire_state(c, st);
+    else
+      release_state(c, st);
+  }
   return s;
 }
 
@@ -1674,6 +1740,7 @@ void ctx_trim(hotrg_ctx* c) {
   for (Buf* b : bufs) ctx_free(c, *b);
   for (Buf* arr : {c->RA1, c->RA2, c->RX1, c->RX2, c->RU1, c->RU3})
     for (int h = 0; h < 2; ++h) ctx_free(c, arr[h]);
+  release_spare(c);
 }
 
 double ctx_seconds(const hotrg_ctx* c) {
@@ -1737,6 +1804,7 @@ void hotrg_ctx_destroy(hotrg_ctx* c) {
   for (Buf* b : bufs) ctx_free(c, *b);
   for (Buf* arr : {c->RA1, c->RA2, c->RX1, c->RX2, c->RU1, c->RU3})
     for (int h = 0; h < 2; ++h) ctx_free(c, arr[h]);
+  release_spare(c);
   for (auto& m : c->marks) {
     c->pool.push_back(m.a);
     c->pool.push_back(m.b);
@@ -1846,11 +1914,7 @@ void hotrg_state_free(hotrg_ctx* c, hotrg_state* st) {
   if (!c || !st) return;
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
-  for (Buf* b : bufs) ctx_free(c, *b);
-  for (auto& o : st->RO)
-    for (auto& b : o) ctx_free(c, b);
-  delete st;
+  release_state(c, st);
 }
 
 hotrg_status hotrg_run(hotrg_ctx* c, const hotrg_model_params* params, const hotrg_opts* o,
@@ -1956,26 +2020,47 @@ hotrg_status hotrg_environment(hotrg_ctx* c, int prec, const double* T, int dx, 
     check_dims(dx, dy, 1);
     HIPCHK(hipSetDevice(c->device));
     ensure(c, c->scal, 64);
-    hotrg_state tmp;  // operands only, freed below
+    hotrg_state* ops = take_state(c);  // operands only
     try {
-      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, nullptr);
       c->m_step = 0;
       c->m_dx = dx;
       c->m_dy = dy;
       c->m_dn = dx * dx;
-      mark(c, HOTRG_PHASE_ENV);
-      if (prec == HOTRG_FP64)
-        environment_f64(c, env_natural(&tmp, dx, dy), (const double*)tmp.Xt.p, dx, dy, M);
-      else
-        environment_rp(c, &tmp, rp_mode(prec), dx, dy, M);
+      if (prec == HOTRG_FP64) {
+        const long long P = (long long)dx * dy, ldp = f64_ld(dx, dy, 1).p;
+        PrepOut outs[4];
+        int k = 0;
+        ensure(c, ops->Xt, (size_t)(P * ldp) * 8);
+        outs[k++] = prep_xt(ops->Xt.p, dx, dy, ldp);
+        const double* Tq;
+        if (ldp != P) {
+          ensure(c, ops->Tq, (size_t)(P * ldp) * 8);
+          outs[k++] = prep_natural(ops->Tq.p, dx, dy, ldp);
+          Tq = (const double*)ops->Tq.p;
+          PadSet pads;
+          pads.add(ops->Tq.p, P, ldp, P, 8, c->stream);
+          pads.add(ops->Xt.p, P, ldp, P, 8, c->stream);
+          pads.launch(c->stream);
+        } else {
+          Tq = natural_f64(c, ops, T, dx, dy, outs, k);
+        }
+        launch_prep(T, false, false, dx, dy, nullptr, outs, k, nullptr, c->stream);
+        mark(c, HOTRG_PHASE_ENV);
+        environment_f64(c, Tq, (const double*)ops->Xt.p, dx, dy, M);
+      } else {
+        prepare_operands(c, ops, prec, T, false, false, dx, dy, nullptr);
+        mark(c, HOTRG_PHASE_ENV);
+        environment_rp(c, ops, rp_mode(prec), dx, dy, M);
+      }
       mark(c, -1);
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(c->stream));
     } catch (...) {
-      release_operands(c, &tmp);
+      (void)hipStreamSynchronize(c->stream);
+      release_state(c, ops);
       throw;
     }
-    release_operands(c, &tmp);
+    retire_state(c, ops);
   });
 }
 
@@ -2044,22 +2129,33 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
     HIPCHK(hipSetDevice(c->device));
     ensure(c, c->scal, 64);
     unsigned long long* mb = (unsigned long long*)c->scal.p + 4;
-    hotrg_state tmp;
+    hotrg_state* ops = take_state(c);  // operands only
     try {
-      prepare_operands(c, &tmp, prec, T, false, false, dx, dy, nullptr);
       c->m_step = 0;
       c->m_dx = dx;
       c->m_dy = dy;
       c->m_dn = dn;
-      const size_t no = (size_t)dn * dy * dn * dy;
       if (prec == HOTRG_FP64) {
+        const long long P = (long long)dx * dy;
+        const F64Ld ld = f64_ld(dx, dy, dn);
+        PrepOut outs[4];
+        int k = 0;
+        ensure(c, ops->Tp, (size_t)(ld.p * ld.tp) * 8);
+        outs[k++] = prep_tp(ops->Tp.p, dx, dy, ld.tp);
+        const double* Tn = natural_f64(c, ops, T, dx, dy, outs, k);
+        PadSet pads;
+        pads.add((double*)ops->Tp.p + P * ld.tp, ld.p - P, ld.tp, 0, 8, c->stream);
+        pads.launch(c->stream);
+        launch_prep(T, false, false, dx, dy, nullptr, outs, k, nullptr, c->stream);
         projector_f64(c, c->U1, c->U3, U, nullptr, dx, dy, dn, mb);
-        coarse_f64(c, (const double*)tmp.Tn.p, (const double*)tmp.Tp.p, (const double*)c->U1.p,
-                   (double*)c->U3.p, dx, dy, dn, Tt, mb);
+        coarse_f64(c, Tn, (const double*)ops->Tp.p, (const double*)c->U1.p, (double*)c->U3.p, dx,
+                   dy, dn, Tt, mb);
         mark(c, -1);
       } else {
+        const size_t no = (size_t)dn * dy * dn * dy;
+        prepare_operands(c, ops, prec, T, false, false, dx, dy, nullptr);
         projector_rp(c, rp_mode(prec), U, nullptr, dx, dn, mb);
-        coarse_rp(c, &tmp, rp_mode(prec), dx, dy, dn, mb);
+        coarse_rp(c, ops, rp_mode(prec), dx, dy, dn, mb);
         mark(c, -1);
         launch_f32_to_f64((const float*)c->Tt.p, Tt, (long long)no, c->stream);
       }
@@ -2067,10 +2163,11 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(c->stream));
     } catch (...) {
-      release_operands(c, &tmp);
+      (void)hipStreamSynchronize(c->stream);
+      release_state(c, ops);
       throw;
     }
-    release_operands(c, &tmp);
+    retire_state(c, ops);
   });
 }
 
