@@ -68,299 +68,6 @@ __global__ void k_seed_block(double* V, long long count, unsigned long long seed
   }
 }
 
-// G (p x p, row-major) -> RinvT = (R^-1)^T where G + s I = R^T R, s =
-// shift_rel * trace(G).  One workgroup of 256 threads as a 16 x 16 grid;
-// thread (ty, tx) keeps the elements (ty + 16a, tx + 16b), a, b < 8, of the
-// working matrix in registers (p <= 128, p a multiple of 16; indices past p
-// are clamped, and those registers are never published or stored).
-//
-// Blocked right-looking Cholesky with blocks of 8 columns: the owners of the
-// block's 8 rows (final by then) publish them in LDS; thread c < p then
-// factors the 8 x 8 diagonal block itself (the same operations on the same
-// data in every such thread) and forms column c of the block rows of R by
-// forward substitution, straight into R in LDS; after a second barrier every
-// thread applies the rank-8 update to its elements.  The inverse X = R^-1 is
-// eliminated from X = I block by block from the bottom the same way: thread c
-// back-substitutes column c of the block's rows in place, and every row takes
-// the rank-8 update with column j0.. of R (zero below the diagonal, so rows
-// at and below the block are left alone; the block's rows then take their
-// final values).  Two barriers per block of 8 columns.
-//
-// R starts as zeros in LDS, so every load below is unconditional: rows and
-// columns that are already finished take updates nobody reads again, which
-// costs less than the waits a load under a branch would.  X^T leaves through
-// LDS for coalesced stores.  *fail is set if a pivot is not positive.
-constexpr int kCholThreads = 256;
-
-__device__ __forceinline__ void chol_inv_body(const double* __restrict__ G, int p,
-                                              double shift_rel, int scale, double identity_tol,
-                                              double* __restrict__ RinvT, int* fail) {
-  extern __shared__ double lds[];
-  double* R = lds;             // p * p: R (upper, zeros below), later X^T
-  double* P = R + p * p;       // 2 x 8 x 128 published rows
-  __shared__ int bad;
-  __shared__ double dev[kCholThreads];
-  __shared__ double dsc[128];  // diag(G)^-1/2 when scaling, else 1
-  const int t = threadIdx.x;
-  const int tx = t & 15, ty = t >> 4;
-  const int pm = p - 1;
-  double A[8][8];
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int i = min(ty + 16 * a, pm), k = min(tx + 16 * b, pm);
-      A[a][b] = G[min(i, k) * p + max(i, k)];  // upper part, mirrored
-    }
-  if (identity_tol > 0.0) {
-    // G already the identity to within identity_tol: R^-1 = I
-    double d = 0.0;
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const int i = ty + 16 * a, k = tx + 16 * b;
-        if (i < p && k < p) d = fmax(d, fabs(A[a][b] - (i == k ? 1.0 : 0.0)));
-      }
-    dev[t] = d;
-    __syncthreads();
-    double mx = 0.0;
-    for (int i = 0; i < kCholThreads; ++i) mx = fmax(mx, dev[i]);
-    if (mx <= identity_tol) {  // uniform: every thread reduced the same values
-      for (int e = t; e < p * p; e += kCholThreads) RinvT[e] = (e / p == e % p) ? 1.0 : 0.0;
-      return;
-    }
-  }
-  for (int e = t; e < p * p; e += kCholThreads) R[e] = 0.0;
-  // diagonal: the owners publish it
-  if (tx == ty) {
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-      if (ty + 16 * a < p) P[ty + 16 * a] = A[a][a];
-  }
-  if (t == 0) bad = 0;
-  __syncthreads();
-  // with `scale`, factor D^-1 G D^-1 (D = diag(G)^1/2) instead of G: the
-  // columns' lengths drop out of the conditioning, and the scaling is put
-  // back into the rows of R^-1 at the end
-  if (t < 128) dsc[t] = (scale && t < p) ? 1.0 / sqrt(P[t]) : 1.0;
-  __syncthreads();
-  if (scale) {
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const double dr = dsc[min(ty + 16 * a, pm)];
-#pragma unroll
-      for (int b = 0; b < 8; ++b) A[a][b] *= dr * dsc[min(tx + 16 * b, pm)];
-    }
-  }
-  // trace (of the matrix factored), every thread sums in the same order
-  double tr = 0.0;
-  if (scale)
-    tr = (double)p;
-  else
-    for (int i = 0; i < p; ++i) tr += P[i];
-  const double shift = shift_rel * tr;
-  if (tx == ty) {
-#pragma unroll
-    for (int a = 0; a < 8; ++a) A[a][a] += shift;
-  }
-  __syncthreads();  // everyone has read the trace before P is reused
-
-  const int nblk = p >> 3;
-  for (int J = 0; J < nblk; ++J) {
-    const int j0 = 8 * J, aj = j0 >> 4, tj = j0 & 15;
-    double* Pb = P + (J & 1) * 1024;
-    if (ty >= tj && ty < tj + 8) {
-#pragma unroll
-      for (int a = 0; a < 8; ++a)
-        if (a == aj) {
-#pragma unroll
-          for (int b = 0; b < 8; ++b) Pb[(ty - tj) * 128 + tx + 16 * b] = A[a][b];
-        }
-    }
-    __syncthreads();
-    if (t < p && t >= j0) {
-      // the 8 x 8 diagonal block: L[r][c] (c >= r) becomes R[j0+r][j0+c]
-      double L[8][8], inv[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = r; c < 8; ++c) L[r][c] = Pb[r * 128 + j0 + c];
-      bool ok = true;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const double d = L[r][r];
-        ok = ok && d > 0.0;
-        // 1 / sqrt(d) from v_rsq_f64 and two Newton steps; sqrt(d) = d / sqrt(d)
-        const double dd = d > 0.0 ? d : 1.0;
-        double y = __builtin_amdgcn_rsq(dd);
-        y = fma(y, fma(-0.5 * dd * y, y, 0.5), y);
-        y = fma(y, fma(-0.5 * dd * y, y, 0.5), y);
-        inv[r] = y;
-        L[r][r] = dd * y;
-#pragma unroll
-        for (int c = r + 1; c < 8; ++c) L[r][c] *= inv[r];
-#pragma unroll
-        for (int r2 = r + 1; r2 < 8; ++r2)
-#pragma unroll
-          for (int c = r2; c < 8; ++c) L[r2][c] -= L[r][r2] * L[r][c];
-      }
-      if (!ok) bad = 1;
-      if (t >= j0 + 8) {
-        double v[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          double w = Pb[r * 128 + t];
-#pragma unroll
-          for (int m = 0; m < r; ++m) w -= L[m][r] * v[m];
-          v[r] = w * inv[r];
-          R[(j0 + r) * p + t] = v[r];
-        }
-      } else {
-        const int cc = t - j0;  // column inside the block
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          double v = 0.0;
-#pragma unroll
-          for (int c = r; c < 8; ++c) v = cc == c ? L[r][c] : v;
-          R[(j0 + r) * p + t] = v;
-        }
-      }
-    }
-    __syncthreads();
-    if (bad) {
-      if (t == 0) *fail = 1;
-      return;  // uniform: every thread read the same flag after the barrier
-    }
-    // register rows / columns whose indices all lie before j0 + 8 are
-    // finished: skip them (a uniform test)
-    double Ri[8][8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      if (16 * a + 15 < j0 + 8) continue;
-      const int i = min(ty + 16 * a, pm);
-#pragma unroll
-      for (int r = 0; r < 8; ++r) Ri[a][r] = R[(j0 + r) * p + i];
-    }
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      if (16 * b + 15 < j0 + 8) continue;
-      const int k = min(tx + 16 * b, pm);
-      double Rk[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) Rk[r] = R[(j0 + r) * p + k];
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        if (16 * a + 15 < j0 + 8) continue;
-        double v = A[a][b];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v -= Ri[a][r] * Rk[r];
-        A[a][b] = v;
-      }
-    }
-  }
-  // X = I in registers
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) A[a][b] = (ty + 16 * a == tx + 16 * b) ? 1.0 : 0.0;
-  __syncthreads();  // the last reads of P and R rows are done
-  for (int J = nblk - 1; J >= 0; --J) {
-    const int j0 = 8 * J, aj = j0 >> 4, tj = j0 & 15;
-    double* Pb = P + (J & 1) * 1024;
-    if (ty >= tj && ty < tj + 8) {
-#pragma unroll
-      for (int a = 0; a < 8; ++a)
-        if (a == aj) {
-#pragma unroll
-          for (int b = 0; b < 8; ++b) Pb[(ty - tj) * 128 + tx + 16 * b] = A[a][b];
-        }
-    }
-    __syncthreads();
-    if (t < p) {  // column t of the block rows, back substitution in place
-      double L[8][8], inv[8], x[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-#pragma unroll
-        for (int c = r; c < 8; ++c) L[r][c] = R[(j0 + r) * p + j0 + c];
-        inv[r] = 1.0 / L[r][r];
-        x[r] = Pb[r * 128 + t];
-      }
-#pragma unroll
-      for (int r = 7; r >= 0; --r) {
-        double v = x[r];
-#pragma unroll
-        for (int m = r + 1; m < 8; ++m) v -= L[r][m] * x[m];
-        x[r] = v * inv[r];
-        Pb[r * 128 + t] = x[r];
-      }
-    }
-    __syncthreads();
-    // X is upper triangular: the block's rows vanish before column j0, and
-    // rows from j0 + 8 on are final; skip those register groups (uniform)
-    double Xb[8][8];  // the block's final rows at the thread's own columns
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      if (16 * b + 15 < j0) continue;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) Xb[b][r] = Pb[r * 128 + tx + 16 * b];
-    }
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      if (16 * a >= j0 + 8) continue;
-      const int i = ty + 16 * a;
-      const int ic = min(i, pm);
-      double Rr[8];  // R[i][j0 + r]: zero for rows at or below the block
-#pragma unroll
-      for (int r = 0; r < 8; ++r) Rr[r] = R[ic * p + j0 + r];
-      const bool in_blk = i >= j0 && i < j0 + 8;
-      const int rb = i - j0;
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        if (16 * b + 15 < j0) continue;
-        double v = A[a][b];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v -= Rr[r] * Xb[b][r];
-        double xr = Xb[b][0];
-#pragma unroll
-        for (int r = 1; r < 8; ++r) xr = rb == r ? Xb[b][r] : xr;
-        A[a][b] = in_blk ? xr : v;
-      }
-    }
-  }
-  __syncthreads();  // all reads of R are done: reuse it for X^T
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int i = ty + 16 * a, k = tx + 16 * b;
-      // with scaling R = R^ D, so row i of R^-1 = D^-1 R^^-1 carries G_ii^-1/2
-      if (i < p && k < p) R[k * p + i] = A[a][b] * dsc[i];
-    }
-  __syncthreads();
-  for (int e = t; e < p * p; e += kCholThreads) RinvT[e] = R[e];
-}
-
-
-// Factor-only Cholesky of a sweep's Gram matrix (Q = R^-T D^-1 Y then comes
-// from k_trsm_rows): R with R^T R = D^-1 G D^-1 + s I (`scale`; D = diag(G)^1/2) or
-// G + s I, s = shift_rel * trace of the matrix factored, into Rout (p x p
-// row-major, zeros below the diagonal) and D^-1 (ones without `scale`) into
-// Rout + p * p; with identity_tol > 0 and G the identity to within it, R = I.
-// One workgroup of GW x GW threads (GW = 32 for p <= 128, 16 for p <= 64:
-// the same register tiles, and barriers over 4 waves instead of 16); thread
-// (ty, tx) keeps the elements (ty + GW a, tx + GW b), a, b < 4, in registers
-// (p a multiple of 16; indices past p are clamped and never published).  Blocks of 8
-// columns: the owners of the block's 8 rows publish them in LDS; the first
-// wave factors the 8 x 8 diagonal block, one column per lane, the values of
-// other columns by readlane (1/sqrt of a pivot from v_rsq_f64 and two Newton
-// steps), into LDS; after a second barrier thread c < p forms column c of the
-// block's rows of R, into LDS (8 doubles per column) and Rout; after a third
-// every thread takes the rank-8 update on its register tiles that still
-// matter (not wholly finished, not wholly past p).  Only the current block
-// lives in LDS, so four waves per SIMD fit with their register tiles.  *fail
-// is set if a pivot is not positive.
-
 // value of v in lane l of the wave (l uniform)
 __device__ __forceinline__ double readlane_f64(double v, int l) {
   const long long b = __double_as_longlong(v);
@@ -369,206 +76,281 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-template <int GW>
-__global__ __launch_bounds__(GW * GW) void k_chol_factor(const double* __restrict__ G, int p,
-                                                               double shift_rel, int scale,
-                                                               double identity_tol,
-                                                               double* __restrict__ Rout,
-                                                               int* fail, int* missed) {
-  __shared__ double Pb[8 * 128];                 // the block's rows of the working matrix
-  __shared__ __align__(16) double Rb[128 * 8];   // the block's rows of R, by column
-  __shared__ __align__(16) double Ls[64];
-  __shared__ double dg[128], dsc[128], red[GW * GW / 64], Li[8];
-  __shared__ int bad;
-  const int t = threadIdx.x, tx = t % GW, ty = t / GW;
-  const int pm = p - 1;
-  double A[4][4];
+// Cholesky factor of a sweep's Gram matrix (Q = R^-T D^-1 Y then comes from
+// k_trsm_rows): R with R^T R = D^-1 G D^-1 + s I (`scale`; D = diag(G)^1/2) or
+// G + s I, s = shift_rel * trace of the matrix factored.  Rout receives R (p x p
+// row-major; right of the diagonal 16 x 16 blocks only, and in those the blocks'
+// inverses) and D^-1 (ones without `scale`) at p * p; with identity_tol > 0 and G
+// the identity to within it, R = I.  *fail is set if a pivot is not positive.
+//
+// One workgroup, p a multiple of 16 up to 16 NB.  The upper 16 x 16 tiles stay in
+// MFMA accumulators (negated, one of a row per wave), and each of the p / 16 steps
+// has two barriers: the owners publish the step's row of tiles, the first one or
+// two waves factor it while others store the rows of the step before, and the
+// tiles below take R^T R by MFMA.  What bounds the kernel is the chain of one
+// pivot after the other (v_rcp_f64, two Newton steps, the next pivot's row; the
+// square roots are off it), so a step keeps it inside a row of 16 lanes: lane c of
+// each has column c of the diagonal block, which every row of lanes factors again,
+// and each lane one column to the right of it or, the first 16, of the identity,
+// whose solution is the block's inverse.  Values of another column come by DPP
+// (through a scalar register, v_readlane, each costs its latency).  Against 8-wide
+// steps with the matrix in the registers of 256 or 1024 threads, three fenced
+// barriers each, and the inverses formed again by each workgroup of k_trsm_rows:
+// p = 64 18.0 -> 9.9 us, p = 128 47 -> 20, k_trsm_rows (64 x 1024)
+// 7.3 -> 5.2; in a batch, where the inverse of R was formed and multiplied by,
+// 17.9 + 9 -> 4.5 + 3.4 (p = 48, converged problems included).
+template <int NB>
+struct CholLds {
+  static constexpr int NW = NB > 4 ? 8 : 4;  // waves
+  static constexpr int W = 16 * NB, S = W + 16;
+  double P[16 * S];                  // the step's row of tiles
+  double R[W * W];                   // rows of R; odd ones with columns ^ 16
+  double dg[W], dsc[W], red[NW];
+  __device__ static int at(int r, int c) { return r * W + (c ^ ((r & 1) << 4)); }
+};
+
+// value of v in lane I of the row of 16 lanes (DPP row_newbcast)
+template <int I>
+__device__ __forceinline__ double bcast16(double v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + I, 0xf, 0xf, true);
+}
+
+// 1 / d (v_rcp_f64, two Newton steps); of a pivot not positive it is not used
+__device__ __forceinline__ double pivot_rcp(double d) {
+  double q = __builtin_amdgcn_rcp(d);
+  q = fma(q, fma(-d, q, 1.0), q);
+  return fma(q, fma(-d, q, 1.0), q);
+}
+
+// Rows R2 .. E of a step's columns less their multiple of row R, m = row R over its
+// pivot: row R of column R2 of the diagonal block times m.
+template <int R, int R2, int E>
+__device__ __forceinline__ void chol_elim(double (&xd)[16], double (&x)[16], double md, double m) {
+  if constexpr (R2 <= E) {
+    const double b = bcast16<R2>(xd[R]);
+    xd[R2] = fma(-b, md, xd[R2]);
+    x[R2] = fma(-b, m, x[R2]);
+    chol_elim<R, R2 + 1, E>(xd, x, md, m);
+  }
+}
+// From row R down, q = 1 / its pivot.  The next pivot's row goes first, and its
+// chain then runs between the other rows'; the fence keeps the rows of later steps
+// from being fetched before (256 registers and spills).
+template <int R>
+__device__ __forceinline__ bool chol_pivots(double (&xd)[16], double (&x)[16], double q, bool ok) {
+  if constexpr (R < 15) {
+    const double md = xd[R] * q, m = x[R] * q;
+    chol_elim<R, R + 1, R + 1>(xd, x, md, m);
+    const double d = bcast16<R + 1>(xd[R + 1]);
+    const double next = pivot_rcp(d);
+    chol_elim<R, R + 2, 15>(xd, x, md, m);
+    __builtin_amdgcn_sched_barrier(0);
+    return chol_pivots<R + 1>(xd, x, next, ok && d > 0.0);
+  } else {
+    return ok;
+  }
+}
+// x[R] over the root of pivot R, y in lane R of each row of lanes
+template <int R>
+__device__ __forceinline__ void chol_scale(double (&x)[16], double y) {
+  if constexpr (R < 16) {
+    x[R] *= bcast16<R>(y);
+    chol_scale<R + 1>(x, y);
+  }
+}
+
+template <int NB>
+__device__ __forceinline__ void chol_body(const double* __restrict__ G, int p, double shift_rel,
+                                          int scale, double identity_tol,
+                                          double* __restrict__ Rout, int* fail, int* missed,
+                                          CholLds<NB>& L) {
+  using LD = CholLds<NB>;
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  constexpr int S = LD::S, NW = LD::NW, NT = 64 * NW, Q = NB / 2 + 1;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int li = lane & 15, lg = lane >> 4, nb = p >> 4;
+  double* Dout = Rout + (size_t)p * p;
+  // this wave's tiles (ti, tk), ti <= tk: those with ti + tk = w modulo NB, from
+  // the middle outwards (an odd w has one fewer); ti = -1 past the end
+  static_assert(NB == NW, "one tile of a row per wave");
+  int ti[Q], tk[Q];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int q = 0; q < Q; ++q) {
+    const int a = ((w >> 1) - q) & (NB - 1), b = (w - a) & (NB - 1);
+    const bool in = max(a, b) < nb && !((w & 1) && q == Q - 1);
+    ti[q] = in ? min(a, b) : -1;
+    tk[q] = in ? max(a, b) : 0;
+  }
+  d4 acc[Q];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int i = min(ty + GW * a, pm), k = min(tx + GW * b, pm);
-      A[a][b] = G[min(i, k) * p + max(i, k)];  // upper part, mirrored
+  for (int q = 0; q < Q; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * max(ti[q], 0) + lg + 4 * v, k = 16 * tk[q] + li;
+      acc[q][v] = G[min(i, k) * p + max(i, k)];  // upper part, mirrored
     }
   if (identity_tol > 0.0) {
     double d = 0.0;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int q = 0; q < Q; ++q) {
+      if (ti[q] < 0) continue;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int i = ty + GW * a, k = tx + GW * b;
-        if (i < p && k < p) d = fmax(d, fabs(A[a][b] - (i == k ? 1.0 : 0.0)));
-      }
+      for (int v = 0; v < 4; ++v)
+        d = fmax(d, fabs(acc[q][v] - (ti[q] == tk[q] && lg + 4 * v == li ? 1.0 : 0.0)));
+    }
     for (int o = 32; o > 0; o >>= 1) d = fmax(d, __shfl_xor(d, o, 64));
-    if ((t & 63) == 0) red[t >> 6] = d;
-    __syncthreads();
+    if (lane == 0) L.red[w] = d;
+    lds_barrier();
     double mx = 0.0;
-    for (int w = 0; w < GW * GW / 64; ++w) mx = fmax(mx, red[w]);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) mx = fmax(mx, L.red[i]);
     if (mx <= identity_tol) {  // uniform: every thread reduced the same values
-      for (int e = t; e < p * p; e += GW * GW) Rout[e] = (e / p == e % p) ? 1.0 : 0.0;
-      if (t < p) Rout[p * p + t] = 1.0;
+      for (int e = t; e < p * p; e += NT) Rout[e] = (e / p == e % p) ? 1.0 : 0.0;
+      if (t < p) Dout[t] = 1.0;
       return;
     }
     if (missed && t == 0) *missed += 1;  // the check found a real factorisation to do
   }
-  if (tx == ty) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-      if (ty + GW * a < p) dg[ty + GW * a] = A[a][a];
-  }
-  if (t == 0) bad = 0;
-  __syncthreads();
-  if (t < 128) dsc[t] = (scale && t < p) ? 1.0 / sqrt(dg[t]) : 1.0;
-  // trace of the matrix factored, every thread summing in the same order
-  double tr = 0.0;
-  if (scale)
-    tr = (double)p;
-  else
-    for (int i = 0; i < p; ++i) tr += dg[i];
-  __syncthreads();
-  if (scale) {
+  for (int q = 0; q < Q; ++q)
+    if (ti[q] == tk[q]) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const double dr = dsc[min(ty + GW * a, pm)];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) A[a][b] *= dr * dsc[min(tx + GW * b, pm)];
+      for (int v = 0; v < 4; ++v)
+        if (lg + 4 * v == li) L.dg[16 * ti[q] + li] = acc[q][v];
     }
+  lds_barrier();
+  // trace of the matrix factored, every thread summing in the same order
+  double tr = (double)p;
+  if (!scale) {
+    tr = 0.0;
+    for (int i = 0; i < p; ++i) tr += L.dg[i];
   }
   const double shift = shift_rel * tr;
-  if (tx == ty) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) A[a][a] += shift;
+  if (t < p) {
+    double dv = 1.0;
+    if (scale) {
+      const double g = L.dg[t], h = -0.5 * g;
+      dv = __builtin_amdgcn_rsq(g);
+      dv = fma(dv, fma(h * dv, dv, 0.5), dv);
+      dv = fma(dv, fma(h * dv, dv, 0.5), dv);
+    }
+    L.dsc[t] = dv;
+    Dout[t] = dv;
   }
+  lds_barrier();
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double a = acc[q][v];
+      if (scale) a *= L.dsc[16 * max(ti[q], 0) + lg + 4 * v] * L.dsc[16 * tk[q] + li];
+      if (ti[q] == tk[q] && lg + 4 * v == li) a += shift;
+      acc[q][v] = -a;
+    }
+  // rows of step J of R to Rout (wave `first` and up); in LDS the diagonal block's
+  // place holds the inverse of the block of L, whose transpose goes out
+  auto dump = [&](int J, int first) {
+    const int c = 2 * lane, j0 = 16 * J;
+    for (int r = j0 + w - first; r < j0 + 16; r += NW - first)
+      if (c >= j0 && c < p) {
+        const bool in = c < j0 + 16;
+        const double a = L.R[in ? LD::at(c, r) : LD::at(r, c)];
+        const double b = L.R[in ? LD::at(c + 1, r) : LD::at(r, c + 1)];
+        *(d2*)(Rout + r * p + c) = d2{a, b};
+      }
+  };
+  bool ok = true;
+  for (int J = 0; J < nb; ++J) {
+    const int j0 = 16 * J;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (ti[q] == J) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) L.P[(lg + 4 * v) * S + 16 * tk[q] + li] = -acc[q][v];
+      }
+    lds_barrier();
+    if (64 * w < p - j0) {
+      // own column e: of the identity below 16, then j0 + e, past p repeats of the
+      // last one
+      const int e = 64 * w + lane;
+      const bool unit = e < 16;
+      const int col = min(j0 + e, p - 1);
+      double xd[16], x[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        xd[r] = L.P[r * S + j0 + li];
+        x[r] = L.P[r * S + col];
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        asm volatile("" : "+v"(x[r]));  // all the loads, then the selects: not 16 branches
+        if (unit) x[r] = r == e ? 1.0 : 0.0;
+      }
+      const double d0 = bcast16<0>(xd[0]);
+      ok = chol_pivots<0>(xd, x, pivot_rcp(d0), ok && d0 > 0.0);
+      double d = xd[15];  // pivot of row li
+#pragma unroll
+      for (int r = 0; r < 15; ++r) d = li == r ? xd[r] : d;
+      double y = __builtin_amdgcn_rsq(d);
+      const double h = -0.5 * d;
+      y = fma(y, fma(h * y, y, 0.5), y);
+      y = fma(y, fma(h * y, y, 0.5), y);
+      chol_scale<0>(x, y);
+      // (or the rows' arithmetic moves into the branch, with every b kept for it)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(x[r]));
+      if (e < p - j0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) L.R[LD::at(j0 + r, col)] = x[r];
+      }
+    } else if (w >= 2 && J > 0) {
+      dump(J - 1, 2);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (ti[q] > J) {
+        double fa[4], fb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          fa[u] = L.R[LD::at(j0 + 4 * u + lg, 16 * ti[q] + li)];
+          fb[u] = L.R[LD::at(j0 + 4 * u + lg, 16 * tk[q] + li)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[u], acc[q], 0, 0, 0);
+      }
+  }
+  dump(nb - 1, 0);
+  if (t == 0 && !ok) *fail = 1;
+}
 
-  const int nblk = p >> 3;
-  for (int J = 0; J < nblk; ++J) {
-    const int j0 = 8 * J, aj = j0 / GW, tj = j0 % GW;
-    if (ty >= tj && ty < tj + 8) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        if (a == aj) {
-#pragma unroll
-          for (int b = 0; b < 4; ++b) Pb[(ty - tj) * 128 + tx + GW * b] = A[a][b];
-        }
-    }
-    __syncthreads();
-    if (t < 64) {
-      // the 8 x 8 diagonal block, right-looking, one column per lane (lane
-      // c0 < 8 keeps L[r][c0] -> R[j0+r][j0+c0] in x[r], zeros below the
-      // diagonal; the other lanes repeat columns and are not used); the
-      // pivot and L[r][r2] of another column come from readlane, so no step
-      // waits on LDS
-      const int c0 = t & 7;
-      double x[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) x[r] = r <= c0 ? Pb[r * 128 + j0 + c0] : 0.0;
-      bool ok = true;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const double d = readlane_f64(x[r], r);
-        ok = ok && d > 0.0;
-        const double dd = d > 0.0 ? d : 1.0;
-        double y = __builtin_amdgcn_rsq(dd);
-        y = fma(y, fma(-0.5 * dd * y, y, 0.5), y);
-        y = fma(y, fma(-0.5 * dd * y, y, 0.5), y);
-        x[r] = c0 == r ? dd * y : (c0 > r ? x[r] * y : x[r]);
-        if (t == r) Li[r] = y;
-#pragma unroll
-        for (int r2 = r + 1; r2 < 8; ++r2) {
-          const double lr = readlane_f64(x[r], r2);  // L[r][r2]
-          if (c0 >= r2) x[r2] -= lr * x[r];
-        }
-      }
-      if (t < 8) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) Ls[t * 8 + r] = x[r];  // column t: Ls[c * 8 + r] = L[r][c]
-      }
-      if (t == 0 && !ok) bad = 1;
-    }
-    __syncthreads();
-    if (t < p) {
-      // column t of the block's rows of R: forward substitution past the
-      // block, the factor itself inside it, zeros before it
-      double v[8];
-      if (t >= j0 + 8) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          double w = Pb[r * 128 + t];
-#pragma unroll
-          for (int m = 0; m < r; ++m) w -= Ls[r * 8 + m] * v[m];
-          v[r] = w * Li[r];
-        }
-      } else {
-        const int cc = t - j0;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = cc >= 0 ? Ls[min(max(cc, 0), 7) * 8 + r] : 0.0;
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if (t >= j0) Rb[t * 8 + r] = v[r];
-        Rout[(j0 + r) * p + t] = v[r];
-      }
-    }
-    __syncthreads();
-    if (bad) {
-      if (t == 0) *fail = 1;
-      return;  // uniform: every thread read the same flag after the barrier
-    }
-    // rank-8 update; register rows / columns wholly before j0 + 8 are
-    // finished and those wholly past p hold only clamped copies: both are
-    // skipped (uniform tests); the others take it even where an element is
-    // finished -- nobody reads those again
-#pragma unroll
-    for (int h = 0; h < 8; h += 4) {  // two rank-4 halves keep the operands few
-      double Ri[4][4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (GW * a + GW - 1 < j0 + 8 || GW * a >= p) continue;
-        const int i = min(ty + GW * a, pm);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Ri[a][r] = Rb[i * 8 + h + r];
-      }
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (GW * b + GW - 1 < j0 + 8 || GW * b >= p) continue;
-        const int k = min(tx + GW * b, pm);
-        double Rk[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Rk[r] = Rb[k * 8 + h + r];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          if (GW * a + GW - 1 < j0 + 8 || GW * a >= p) continue;
-          double v = A[a][b];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v -= Ri[a][r] * Rk[r];
-          A[a][b] = v;
-        }
-      }
-    }
-  }
-  if (t < p) Rout[p * p + t] = dsc[t];
+template <int NB>
+__global__ __launch_bounds__(64 * CholLds<NB>::NW) void k_chol_factor(
+    const double* __restrict__ G, int p, double shift_rel, int scale, double identity_tol,
+    double* __restrict__ Rout, int* fail, int* missed) {
+  __shared__ CholLds<NB> L;
+  chol_body<NB>(G, p, shift_rel, scale, identity_tol, Rout, fail, missed, L);
 }
 
 // Q = R^-T D^-1 Y for the rows of Y (p x n, row-major): with L = R^T (lower
 // triangular), L Q = D^-1 Y is solved by blocks of 16 rows,
 //   Q_b = L_bb^-1 (D_b^-1 Y_b - sum_{a<b} L_ba Q_a),
-// where R and D^-1 are the output of k_chol_factor (R at Rf, D^-1 at
-// Rf + p * p).  One workgroup per 64 columns; each of its 4 waves owns 16
+// where R (with R_bb^-1 = L_bb^-T in the place of its diagonal blocks) and D^-1 are
+// the output of k_chol_factor (R at Rf, D^-1 at Rf + p * p).  One workgroup per 64 columns; each of its 4 waves owns 16
 // columns and keeps their Q blocks in registers: in the accumulator layout of
 // v_mfma_f64_16x16x4f64 (lane j + 16 l holds rows l + 4 v of column j) value
 // v of a lane is exactly the B operand the next products take at k step v,
 // so the blocks never leave the registers until the end.  R is staged in LDS
-// (the A operands of every wave) and the 16 x 16 inverses of the diagonal
-// blocks are formed there by forward substitution, one column per thread.
+// (the A operands of every wave).
 // p a multiple of 16, at most 128; columns past n are computed but not
 // stored.
 constexpr int kTrsmCols = 64;
-__global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__ Rf, int p,
-                                                   const double* __restrict__ Y, int n,
-                                                   double* __restrict__ Q) {
+__device__ __forceinline__ void trsm_body(const double* __restrict__ Rf, int p,
+                                          const double* __restrict__ Y, int n,
+                                          double* __restrict__ Q) {
   extern __shared__ double lds[];
   double* Rs = lds;              // p x p
-  double* Li = lds + p * p;      // p / 16 blocks of 16 x 16: Li[b][i][c]
   const double* dinv = Rf + p * p;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int nb = p >> 4;
@@ -595,21 +377,6 @@ __global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__
     for (int e = t; e < p * p / 2; e += 256) dst[e] = src[e];
   }
   __syncthreads();
-  if (t < 16 * nb) {
-    // column c of the inverse of L_bb, L_bb[i][j] = R[16b + j][16b + i]
-    const int b = t >> 4, c = t & 15, o = 16 * b;
-    double x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      double v = i == c ? 1.0 : 0.0;
-#pragma unroll
-      for (int j = 0; j < i; ++j) v -= Rs[(o + j) * p + o + i] * x[j];
-      x[i] = v / Rs[(o + i) * p + o + i];
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) Li[(b * 16 + i) * 16 + c] = x[i];
-  }
-  __syncthreads();
   d4 q[8];
 #pragma unroll
   for (int b = 0; b < 8; ++b) {
@@ -631,7 +398,7 @@ __global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__
     d4 qb = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const double av = Li[(b * 16 + j) * 16 + 4 * s + l];
+      const double av = Rs[(16 * b + 4 * s + l) * p + 16 * b + j];
       qb = __builtin_amdgcn_mfma_f64_16x16x4f64(av, x[s], qb, 0, 0, 0);
     }
     q[b] = qb;
@@ -646,27 +413,52 @@ __global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__
   }
 }
 
-// One workgroup per problem of a batch; a problem whose gate reads 0 (its
-// eigensolve has converged, or it has no steps left) is skipped.
-__global__ __launch_bounds__(kCholThreads) void k_chol_inv_b(const CholItem* __restrict__ items,
-                                                             int pass, int full) {
-  const CholItem& it = items[blockIdx.x];
-  if (it.gate && *it.gate == 0) return;
-  chol_inv_body(it.G, it.p, pass < 2 ? it.shift_rel : 0.0, pass < 2 ? 1 : 0,
-                (pass == 0 || full) ? 0.0 : 1e-2, it.Rt, it.fail);
+__global__ __launch_bounds__(256, 2) void k_trsm_rows(const double* __restrict__ Rf, int p,
+                                                      const double* __restrict__ Y, int n,
+                                                      double* __restrict__ Q) {
+  trsm_body(Rf, p, Y, n, Q);
 }
 
-void launch_chol_inv_batched(const CholItem* d_items, int count, int pmax, int pass, bool full,
-                             hipStream_t s) {
-  static bool lds_set = [] {
-    return hipFuncSetAttribute((const void*)k_chol_inv_b,
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(((size_t)128 * 128 + 2048) * sizeof(double))) == hipSuccess;
+// The same two for every problem of a batch; a problem whose eigensolve has
+// converged, or that has no steps left, is skipped.
+template <int NB>
+__global__ __launch_bounds__(64 * CholLds<NB>::NW) void k_group_chol(
+    const GroupStep* __restrict__ dsc, int pass, int full) {
+  __shared__ CholLds<NB> L;
+  const GroupStep& g = dsc[blockIdx.x];
+  if (g.ctl->iter == 0) return;
+  chol_body<NB>(g.G, g.p, pass < 2 ? g.shift_rel : 0.0, pass < 2 ? 1 : 0,
+                (pass == 0 || full) ? 0.0 : 1e-2, g.Rt, &g.ctl->fail, nullptr, L);
+}
+
+__global__ __launch_bounds__(256, 2) void k_group_trsm(const GroupStep* __restrict__ dsc, int src,
+                                                       int dst) {
+  const GroupStep& g = dsc[blockIdx.y];
+  if (g.ctl->iter == 0 || (int)blockIdx.x * kTrsmCols >= g.n) return;
+  double* const b[3] = {g.V, g.Y, g.T2};
+  trsm_body(g.Rt, g.p, b[src], g.n, b[dst]);
+}
+
+static bool trsm_lds_set() {
+  static const bool ok = [] {
+    const int bytes = (int)((size_t)128 * 128 * sizeof(double));
+    return hipFuncSetAttribute((const void*)k_trsm_rows,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
+           hipFuncSetAttribute((const void*)k_group_trsm,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
   }();
-  (void)lds_set;
-  const size_t lds = ((size_t)pmax * pmax + 2048) * sizeof(double);
-  hipLaunchKernelGGL(k_chol_inv_b, dim3(count), dim3(kCholThreads), lds, s, d_items, pass,
-                     full ? 1 : 0);
+  return ok;
+}
+
+void group_orth(const GroupStep* d, int count, int pmax, int max_n, int pass, bool full,
+                GroupRows src, GroupRows dst, hipStream_t s) {
+  (void)trsm_lds_set();
+  if (pmax <= 64)
+    hipLaunchKernelGGL(k_group_chol<4>, dim3(count), dim3(256), 0, s, d, pass, full ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_group_chol<8>, dim3(count), dim3(512), 0, s, d, pass, full ? 1 : 0);
+  hipLaunchKernelGGL(k_group_trsm, dim3((max_n + kTrsmCols - 1) / kTrsmCols, count), dim3(256),
+                     (size_t)pmax * pmax * sizeof(double), s, d, (int)src, (int)dst);
 }
 
 // Householder reduction of a small symmetric matrix to tridiagonal form in
@@ -1146,14 +938,8 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
   const double u = std::ldexp(1.0, -53);
   const double shift_rel = 11.0 * ((double)n * p + (double)p * (p + 1)) * u;
 
-  static bool lds_set = [] {
-    return hipFuncSetAttribute((const void*)k_trsm_rows,
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(((size_t)128 * 128 + 128 * 16) * sizeof(double))) ==
-           hipSuccess;
-  }();
-  const size_t trsm_lds = ((size_t)p * p + (size_t)p * 16) * sizeof(double);
-  if (!lds_set || p > 128 || p % 16 != 0) return false;
+  const size_t trsm_lds = (size_t)p * p * sizeof(double);
+  if (!trsm_lds_set() || p > 128 || p % 16 != 0) return false;
   (void)hipMemsetAsync(fail, 0, 2 * sizeof(int), s);
   hipLaunchKernelGGL(k_seed_block, dim3(256), dim3(256), 0, s, V, (long long)pn, 12345ULL);
 
@@ -1169,10 +955,10 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
       gemm_f64_splitk(src, n, src, n, B_KCONTIG, G, p, p, p, n, kc, part, s);
       const double sh = pass < 2 ? shift_rel : 0.0, itol = (pass == 0 || full) ? 0.0 : 1e-2;
       if (p <= 64)
-        hipLaunchKernelGGL(k_chol_factor<16>, dim3(1), dim3(256), 0, s, G, p, sh,
+        hipLaunchKernelGGL(k_chol_factor<4>, dim3(1), dim3(256), 0, s, G, p, sh,
                            pass < 2 ? 1 : 0, itol, Rf, fail, fail + 1);
       else
-        hipLaunchKernelGGL(k_chol_factor<32>, dim3(1), dim3(1024), 0, s, G, p, sh,
+        hipLaunchKernelGGL(k_chol_factor<8>, dim3(1), dim3(512), 0, s, G, p, sh,
                            pass < 2 ? 1 : 0, itol, Rf, fail, fail + 1);
       double* dst = (pass == last) ? Vout : (src == T2 ? Y : T2);
       if (dst == src) dst = (src == Y) ? T2 : Y;

@@ -1022,10 +1022,10 @@ struct GRun {
   bool dense = false;  // all problems' environments diagonalised whole
   int sp = HOTRG_FP64, mode = RP_F32, pmax = 16;
   long long max_pn = 1;
+  int max_n = 1;
   GroupStep* steps = nullptr;
-  CholItem* chol = nullptr;
   // eigensolver products
-  GTable vm, gramY, gramT2, apYT2, apT2V, apT2Y, apYV, rrH, rrX, rrYx;
+  GTable vm, gramY, gramT2, rrH, rrX, rrYx;
   // reduced-precision contractions and their tile configuration
   GTable halves, combine, c1, c2, c3;
   int cfg[5] = {-1, -1, -1, -1, -1};
@@ -1110,22 +1110,21 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   group_begin(R.steps, G, s);
   if (R.dense) group_dense(R.steps, G, R.pmax, s);
   if (!R.dense) group_seed(R.steps, G, R.max_pn, s);
-  auto pass = [&](const GTable& gram, int ps, bool full, const GTable& apply) {
+  auto pass = [&](const GTable& gram, int ps, bool full, GroupRows src, GroupRows dst) {
     launch_f64_table(gram, B_KCONTIG, s);
-    launch_chol_inv_batched(R.chol, G, R.pmax, ps, full, s);
-    launch_f64_table(apply, B_NCONTIG, s);
+    group_orth(R.steps, G, R.pmax, R.max_n, ps, full, src, dst, s);
   };
   for (int round = 0; round < (R.dense ? 0 : kGroupRounds); ++round) {
     for (int sw = 0; sw < kGroupSweepsPerRound; ++sw) {
       const bool full = sw == kGroupSweepsPerRound - 1;
       launch_f64_table(R.vm, B_NCONTIG, s);  // Y = V M
       group_shift(R.steps, G, R.max_pn, s);  // Y -= sigma V
-      pass(R.gramY, 0, full, R.apYT2);
+      pass(R.gramY, 0, full, ROWS_Y, ROWS_T2);
       if (full) {
-        pass(R.gramT2, 1, full, R.apT2Y);
-        pass(R.gramY, 2, full, R.apYV);
+        pass(R.gramT2, 1, full, ROWS_T2, ROWS_Y);
+        pass(R.gramY, 2, full, ROWS_Y, ROWS_V);
       } else {
-        pass(R.gramT2, 1, full, R.apT2V);
+        pass(R.gramT2, 1, full, ROWS_T2, ROWS_V);
       }
     }
     launch_f64_table(R.vm, B_NCONTIG, s);    // Y = V M
@@ -1252,7 +1251,6 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   };
   // descriptors
   std::vector<GroupStep> st;
-  std::vector<CholItem> ch;
   for (GProb* g : R.act) {
     const long long pn = (long long)g->p * g->n, pp = (long long)g->p * g->p;
     double* e = (double*)g->eig.p;
@@ -1288,13 +1286,11 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
     d.acc = (double*)g->st->acc.p;
     d.Tt = g->Tt.p;
     d.tt_f32 = R.sp != HOTRG_FP64;
+    d.shift_rel =
+        11.0 * ((double)g->n * g->p + (double)g->p * (g->p + 1)) * std::ldexp(1.0, -53);
     st.push_back(d);
-    CholItem ci{d.G, d.Rt, &g->ctl->fail, &g->ctl->iter, g->p,
-                11.0 * ((double)g->n * g->p + (double)g->p * (g->p + 1)) * std::ldexp(1.0, -53)};
-    ch.push_back(ci);
   }
   const size_t o_steps = put(st.data(), st.size() * sizeof(GroupStep));
-  const size_t o_chol = put(ch.data(), ch.size() * sizeof(CholItem));
   auto stp = [&](GProb* g) {
     for (size_t i = 0; i < R.act.size(); ++i)
       if (R.act[i] == g) return st[i];
@@ -1307,10 +1303,6 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   f64tab(R.vm, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, (const double*)g->M.p, g->n, d.Y, g->n, g->p, g->n, g->n, g); });
   f64tab(R.gramY, [&](GProb* g) { auto d = stp(g); return item(d.Y, g->n, d.Y, g->n, d.G, g->p, g->p, g->p, g->n, g); });
   f64tab(R.gramT2, [&](GProb* g) { auto d = stp(g); return item(d.T2, g->n, d.T2, g->n, d.G, g->p, g->p, g->p, g->n, g); });
-  f64tab(R.apYT2, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.T2, g->n, g->p, g->n, g->p, g); });
-  f64tab(R.apT2V, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.T2, g->n, d.V, g->n, g->p, g->n, g->p, g); });
-  f64tab(R.apT2Y, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.T2, g->n, d.Y, g->n, g->p, g->n, g->p, g); });
-  f64tab(R.apYV, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.V, g->n, g->p, g->n, g->p, g); });
   f64tab(R.rrH, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, d.Y, g->n, d.H, g->p, g->p, g->p, g->n, g); });
   f64tab(R.rrX, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.V, g->n, d.X, g->n, g->p, g->n, g->p, g); });
   f64tab(R.rrYx, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.Yx, g->n, g->p, g->n, g->p, g); });
@@ -1365,14 +1357,15 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   HIPCHK(hipStreamSynchronize(c->stream));
   char* base = (char*)store.p;
   R.steps = (GroupStep*)(base + o_steps);
-  R.chol = (CholItem*)(base + o_chol);
   for (const Pending& pe : pend) {
     pe.t->items = base + pe.items;
     for (int cf = 0; cf < 3; ++cf) pe.t->begin[cf] = (int*)(base + pe.begin[cf]);
   }
   R.pmax = 16;
   R.max_pn = 1;
+  R.max_n = 1;
   for (GProb* g : R.act) {
+    R.max_n = std::max(R.max_n, g->n);
     R.pmax = std::max(R.pmax, g->p);
     R.max_pn = std::max(R.max_pn, (long long)g->p * g->n);
   }

@@ -266,21 +266,6 @@ void launch_spectrum(const double* W, int cnt, int n, int dn, int trunc, double 
 void launch_isometry(const double* V, int cols, int n, int dn, const int* kept, double* Ucan,
                      hipStream_t s);
 size_t topk_workspace_doubles(int n, int p);
-// Batched shifted Cholesky-QR step of the block eigensolver: per problem,
-// Rt = (R^-1)^T with G (+ shift) = R^T R (one workgroup each; p <= 128, a
-// multiple of 16).  Pass 0 and 1 factor the diagonally scaled, shifted G,
-// pass 2 the plain one; pass 1 between checks (!full) is skipped when G is
-// the identity to 1e-2.  A non-positive pivot sets *fail.
-struct CholItem {
-  const double* G;
-  double* Rt;
-  int* fail;
-  const int* gate;
-  int p;
-  double shift_rel;
-};
-void launch_chol_inv_batched(const CholItem* d_items, int count, int pmax, int pass, bool full,
-                             hipStream_t s);
 bool topk_eigs(const double* M, int n, int p, int need, double tol,
                int q_first, double* shift, int* nocheck, double* ws, double* W, double* Xout,
                int* dinfo, int* iters, int* enough, double* resid, hipStream_t s);
@@ -318,7 +303,16 @@ struct GroupStep {
   int tt_f32;
   unsigned long long* maxbits;
   double* shift;  // sweep shift per step parity (theta_min / 2 of the last Rayleigh-Ritz)
+  double shift_rel;  // of the shifted Cholesky-QR passes
 };
+// Shifted Cholesky-QR of the iterating problems: dst = R^-T D^-1 src with R, D of
+// the Gram matrix G (p <= 128, a multiple of 16).  Pass 0 and 1 factor the
+// diagonally scaled, shifted G, pass 2 the plain one; pass 1 between checks
+// (!full) takes R = I when G is the identity to 1e-2.  A non-positive pivot sets
+// ctl->fail.
+enum GroupRows { ROWS_V, ROWS_Y, ROWS_T2 };
+void group_orth(const GroupStep* d, int count, int pmax, int max_n, int pass, bool full,
+                GroupRows src, GroupRows dst, hipStream_t s);
 void group_begin(const GroupStep* d, int count, hipStream_t s);
 void group_seed(const GroupStep* d, int count, long long max_pn, hipStream_t s);
 void group_symm_h(const GroupStep* d, int count, hipStream_t s);

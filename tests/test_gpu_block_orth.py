@@ -1,0 +1,56 @@
+"""The block eigensolver's orthonormalisation at each block size p (a multiple of
+16: 32 to 128, with and without a second wave of columns, 4 and 8 waves) through
+hotrg_projector, in buffers that a larger block left full, and a matrix whose
+Gram pivots fail (rank far below the block: the dense solver takes over).
+
+The projector's columns are orthonormal and the spectrum is right to 1e-12 of
+the leading value, the bounds of the other projector tests."""
+
+import numpy as np
+import pytest
+
+from oracle import hotrg
+from tests.inputs import graded_gram
+
+pytestmark = pytest.mark.gpu
+
+
+# d_new -> p = max(2 d_new, d_new + 17) rounded up to 16
+@pytest.mark.parametrize("order", [[64, 56, 48, 40, 33, 32, 20, 14, 4]])
+def test_block_sizes(order):
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_projector
+
+    with Context(0) as ctx:
+        for d in order:
+            for n in (320, 577):
+                print("block for", d, "of", n, flush=True)
+                M = graded_gram(n, n, 8.0, seed=d + n)
+                U = torch.empty((n, d), dtype=torch.float64, device="cuda")
+                kept, err, spec = hotrg_projector(ctx, torch.from_numpy(M).to("cuda"), U, d,
+                                                  spec_len=d + 1)
+                assert ctx.last_eig()[0] > 0  # the block solver converged
+                _, s, _, want = hotrg.projector(M, d, "plain", 1e-10)
+                u = U.cpu().numpy()
+                assert kept == want
+                assert np.abs(u.T @ u - np.eye(d)).max() <= 1e-12
+                assert np.abs(np.array(spec) - s[:d + 1] / s[0]).max() <= 1e-12
+
+
+def test_rank_below_the_block():
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_projector
+
+    n, d, r = 400, 32, 5
+    X = np.random.default_rng(3).standard_normal((n, r))
+    M = X @ X.T
+    U = torch.empty((n, d), dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        print("rank", r, flush=True)
+        kept, err, spec = hotrg_projector(ctx, torch.from_numpy(M).to("cuda"), U, d, spec_len=d)
+    u, s = U.cpu().numpy(), np.linalg.eigvalsh(M)[::-1]
+    assert np.abs(u[:, :r].T @ u[:, :r] - np.eye(r)).max() <= 1e-12
+    assert np.abs(np.array(spec) - s[:d] / s[0]).max() <= 1e-12
+    assert np.abs(u[:, :kept] @ (u[:, :kept].T @ M) - M).max() <= 1e-11 * np.abs(M).max()
