@@ -952,7 +952,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     const double* src = Yin;
     const int last = full ? 2 : (check ? 1 : 0);
     for (int pass = 0; pass <= last; ++pass) {
-      gemm_f64_splitk(src, n, src, n, B_KCONTIG, G, p, p, p, n, kc, part, s);
+      gemm_f64_gram(src, n, G, p, n, kc, part, s);
       const double sh = pass < 2 ? shift_rel : 0.0, itol = (pass == 0 || full) ? 0.0 : 1e-2;
       if (p <= 64)
         hipLaunchKernelGGL(k_chol_factor<4>, dim3(1), dim3(256), 0, s, G, p, sh,

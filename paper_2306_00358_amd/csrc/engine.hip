@@ -1031,8 +1031,12 @@ struct GRun {
   int cfg[5] = {-1, -1, -1, -1, -1};
 };
 
-void launch_f64_table(const GTable& t, int bl, hipStream_t s) {
-  gemm_f64_grouped(bl, (const F64Item*)t.items, t.begin[0], t.count, t.tiles[0], s);
+// (begin[0], tiles[0]: 64 x 64 tiles; [1]: small tiles, where every item may)
+void launch_f64_table(const GTable& t, int bl, hipStream_t s, bool sym = false) {
+  if (t.tiles[1] > 0)
+    gemm_f64_grouped_small(bl, sym, (const F64Item*)t.items, t.begin[1], t.count, t.tiles[1], s);
+  else
+    gemm_f64_grouped(bl, (const F64Item*)t.items, t.begin[0], t.count, t.tiles[0], s);
 }
 
 void launch_rp_table(const GTable& t, int mode, int out, int cfg, hipStream_t s) {
@@ -1111,7 +1115,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   if (R.dense) group_dense(R.steps, G, R.pmax, s);
   if (!R.dense) group_seed(R.steps, G, R.max_pn, s);
   auto pass = [&](const GTable& gram, int ps, bool full, GroupRows src, GroupRows dst) {
-    launch_f64_table(gram, B_KCONTIG, s);
+    launch_f64_table(gram, B_KCONTIG, s, true);
     group_orth(R.steps, G, R.pmax, R.max_n, ps, full, src, dst, s);
   };
   for (int round = 0; round < (R.dense ? 0 : kGroupRounds); ++round) {
@@ -1223,18 +1227,24 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
     size_t begin[3];
   };
   std::vector<Pending> pend;
-  auto f64tab = [&](GTable& t, auto make) {
+  auto f64tab = [&](GTable& t, int bl, auto make) {
     std::vector<F64Item> it;
-    std::vector<int> b(1, 0);
+    std::vector<int> b(1, 0), sb(1, 0);
+    bool small = true;
     for (GProb* g : R.act) {
       it.push_back(make(g));
       b.push_back(b.back() + f64_group_tiles(it.back()));
+      sb.push_back(sb.back() + f64_group_small_tiles(it.back(), bl));
+      small = small && f64_group_small(it.back(), bl);
     }
     t.count = G;
     t.tiles[0] = b.back();
+    t.tiles[1] = small ? sb.back() : 0;
     b.pop_back();
+    sb.pop_back();
     pend.push_back({&t, put(it.data(), it.size() * sizeof(F64Item)),
-                    {put(b.data(), b.size() * sizeof(int)), 0, 0}});
+                    {put(b.data(), b.size() * sizeof(int)),
+                     put(sb.data(), sb.size() * sizeof(int)), 0}});
   };
   auto rptab = [&](GTable& t, const std::vector<RpItem>& it, int op) {
     Pending pe{&t, put(it.data(), it.size() * sizeof(RpItem)), {0, 0, 0}};
@@ -1300,12 +1310,12 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
                   long long ldc, int M, int N, int K, GProb* g) {
     return F64Item{A, lda, B, ldb, C, ldc, M, N, K, &g->ctl->iter};
   };
-  f64tab(R.vm, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, (const double*)g->M.p, g->n, d.Y, g->n, g->p, g->n, g->n, g); });
-  f64tab(R.gramY, [&](GProb* g) { auto d = stp(g); return item(d.Y, g->n, d.Y, g->n, d.G, g->p, g->p, g->p, g->n, g); });
-  f64tab(R.gramT2, [&](GProb* g) { auto d = stp(g); return item(d.T2, g->n, d.T2, g->n, d.G, g->p, g->p, g->p, g->n, g); });
-  f64tab(R.rrH, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, d.Y, g->n, d.H, g->p, g->p, g->p, g->n, g); });
-  f64tab(R.rrX, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.V, g->n, d.X, g->n, g->p, g->n, g->p, g); });
-  f64tab(R.rrYx, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.Yx, g->n, g->p, g->n, g->p, g); });
+  f64tab(R.vm, B_NCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, (const double*)g->M.p, g->n, d.Y, g->n, g->p, g->n, g->n, g); });
+  f64tab(R.gramY, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.Y, g->n, d.Y, g->n, d.G, g->p, g->p, g->p, g->n, g); });
+  f64tab(R.gramT2, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.T2, g->n, d.T2, g->n, d.G, g->p, g->p, g->p, g->n, g); });
+  f64tab(R.rrH, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, d.Y, g->n, d.H, g->p, g->p, g->p, g->n, g); });
+  f64tab(R.rrX, B_NCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.V, g->n, d.X, g->n, g->p, g->n, g->p, g); });
+  f64tab(R.rrYx, B_NCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.Rt, g->p, d.Y, g->n, d.Yx, g->n, g->p, g->n, g->p, g); });
   if (R.sp != HOTRG_FP64) {
     const bool split = R.mode == RP_BF16X3;
     auto op = [&](const Buf* b) { return RpOperand{b[0].p, split ? b[1].p : nullptr}; };

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "lds_copy.h"
 
 namespace hotrg {
 
@@ -228,6 +229,56 @@ void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, i
                        d_items, d_begin, count);
 }
 
+// Sum of the waves' partial tiles in wave order (through red, NWV BT^2 doubles free
+// of other data once every wave is here) into C, less sigma * sub, and the maximum.
+template <int BT, int NWV>
+__device__ __forceinline__ void small_store(const d4 (&acc)[BT / 16][BT / 16], double* red,
+                                            double* __restrict__ C, const OutMap& om, int m0,
+                                            int n0, int M, int N, unsigned long long* maxbits,
+                                            const double* __restrict__ sub, double sigma) {
+  constexpr int TT = BT / 16, E = TT * TT * 256;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // element e = ((i TT + j) 4 + v) 64 + lane of the tile
+  double mx = 0.0;
+  auto put = [&](int i, int j, int v, int ln, double x) {
+    const int m = m0 + 16 * i + (ln >> 4) + 4 * v, n = n0 + 16 * j + (ln & 15);
+    if (m < M && n < N) {
+      const long long o = map_row(om, m) + map_col(om, n);
+      if (sub) x -= sigma * sub[o];
+      C[o] = x;
+      mx = fmax(mx, fabs(x));
+    }
+  };
+  if constexpr (NWV == 1) {
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) put(i, j, v, lane, acc[i][j][v]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[w * E + ((i * TT + j) * 4 + v) * 64 + lane] = acc[i][j][v];
+    lds_barrier();
+#pragma unroll
+    for (int e = tid; e < E; e += 64 * NWV) {
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < NWV; ++u) x += red[u * E + e];
+      put(e / (TT * 256), (e >> 8) % TT, (e >> 6) & 3, e & 63, x);
+    }
+  }
+  if (maxbits) {
+    mx = wave_max(mx);
+    if (lane == 0) atomic_max_bits(maxbits, mx);
+  }
+}
+
 // Small products: one BT x BT output tile per workgroup, its K split over the
 // workgroup's NWV waves, operands loaded from global memory straight into the
 // MFMA's registers (no LDS until the partial tiles of the waves are summed, in
@@ -246,23 +297,17 @@ void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, i
 // partial sums: 64 x 1024 x 1024 14.1 -> 8.4 us, 96 x 2304 x 2304 46 -> 35,
 // 128 x 4096 x 4096 101 -> 97.
 template <int BT, int NWV, int BL, bool VEC>
-__global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
-    const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
-    double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
-    const double* __restrict__ sub, double sigma, const double* __restrict__ A_2,
-    double* __restrict__ C_2) {
-  if (blockIdx.z) {  // the second of two products A A^T
-    A = A_2;
-    B = A_2;
-    C = C_2;
-  }
-  constexpr int TT = BT / 16, E = TT * TT * 256;
-  __shared__ double red[NWV > 1 ? NWV * E : 1];
+__device__ __forceinline__ void small_tile(const double* __restrict__ A, long long lda,
+                                           const double* __restrict__ B, long long ldb,
+                                           double* __restrict__ C, const OutMap& om, int m0, int n0,
+                                           int M, int N, int K, unsigned long long* maxbits,
+                                           const double* __restrict__ sub, double sigma,
+                                           double* red) {
+  constexpr int TT = BT / 16;
   typedef double d2 __attribute__((ext_vector_type(2)));
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
-  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
   const double *ar[TT], *br[TT];
 #pragma unroll
   for (int i = 0; i < TT; ++i) {
@@ -343,54 +388,200 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
       }
     mul(f);
   }
-  // element e = ((i TT + j) 4 + v) 64 + lane of the tile
-  double mx = 0.0;
-  auto put = [&](int i, int j, int v, int ln, double x) {
-    const int m = m0 + 16 * i + (ln >> 4) + 4 * v, n = n0 + 16 * j + (ln & 15);
-    if (m < M && n < N) {
-      const long long o = map_row(om, m) + map_col(om, n);
-      if (sub) x -= sigma * sub[o];
-      C[o] = x;
-      mx = fmax(mx, fabs(x));
-    }
-  };
-  if constexpr (NWV == 1) {
-#pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-      for (int j = 0; j < TT; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) put(i, j, v, lane, acc[i][j][v]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-      for (int j = 0; j < TT; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[w * E + ((i * TT + j) * 4 + v) * 64 + lane] = acc[i][j][v];
-    lds_barrier();
-#pragma unroll
-    for (int e = tid; e < E; e += 64 * NWV) {
-      double x = 0.0;
-#pragma unroll
-      for (int u = 0; u < NWV; ++u) x += red[u * E + e];
-      put(e / (TT * 256), (e >> 8) % TT, (e >> 6) & 3, e & 63, x);
-    }
-  }
-  if (maxbits) {
-    mx = wave_max(mx);
-    if (lane == 0) atomic_max_bits(maxbits, mx);
-  }
+  small_store<BT, NWV>(acc, red, C, om, m0, n0, M, N, maxbits, sub, sigma);
 }
+
+template <int BT, int NWV, int BL, bool VEC>
+__global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
+    const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
+    double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
+    const double* __restrict__ sub, double sigma, const double* __restrict__ A_2,
+    double* __restrict__ C_2) {
+  __shared__ double red[NWV > 1 ? NWV * BT * BT : 1];
+  if (blockIdx.z) {  // the second of two products A A^T
+    A = A_2;
+    B = A_2;
+    C = C_2;
+  }
+  small_tile<BT, NWV, BL, VEC>(A, lda, B, ldb, C, om, blockIdx.y * BT, blockIdx.x * BT, M, N, K,
+                               maxbits, sub, sigma, red);
+}
+
+// The same with both operands K-contiguous, 16-byte aligned with even strides:
+// each wave copies its slabs to its own part of LDS (coalesced 128-byte rows, two
+// stages, no barrier: it reads only what it copied) instead of loading them into
+// registers 16 bytes a lane, 64 cycles an instruction, which bounded them: two
+// products of 576^3 35 -> 22 us, of 400^3 19.8 -> 10.1, of 128^3 4.0 -> 3.1; 64 x 64
+// x 1024 8.9 -> 5.2 (there by 32 partial products and a launch that sums them),
+// 128 x 128 x 4096 16 -> 13.7.  More stages take LDS that a second workgroup uses
+// better (four: 576^3 27 us).
+// With `sym` (B = A) only tiles that reach the upper triangle are formed.
+constexpr int kSmallStages = 2;
+template <int BT, int NWV>
+struct SmallK {
+  static constexpr int NST = kSmallStages;
+  static constexpr int kStage = 2 * BT * 128;  // bytes of a wave's slab of A and B
+  static constexpr int kWave = NST * kStage > BT * BT * 8 ? NST * kStage : BT * BT * 8;
+  static constexpr int kBytes = NWV * kWave;
+};
+
+template <int BT, int NWV>
+__device__ __forceinline__ void small_k_tile(const double* __restrict__ A, long long lda,
+                                             const double* __restrict__ B, long long ldb,
+                                             double* __restrict__ C, const OutMap& om, int m0,
+                                             int n0, int M, int N, int K,
+                                             unsigned long long* maxbits,
+                                             const double* __restrict__ sub, double sigma,
+                                             char* smem) {
+  constexpr int TT = BT / 16, LOADS = 2 * BT / 8, STAGE = SmallK<BT, NWV>::kStage;
+  constexpr int NST = kSmallStages;
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  char* const base = smem + w * SmallK<BT, NWV>::kWave;
+  d4 acc[TT][TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  const int full = K >> 4;
+  const int mine = full > w ? (full - w + NWV - 1) / NWV : 0;  // slabs w, w + NWV, ...
+  auto issue = [&](int q) {
+    char* st = base + (q % NST) * STAGE;
+    load_kcontig<BT, 16, 1>(A, lda, m0, M, 16 * (w + q * NWV), st, 0, lane);
+    load_kcontig<BT, 16, 1>(B, ldb, n0, N, 16 * (w + q * NWV), st + BT * 128, 0, lane);
+  };
+  auto mul = [&](const double (&fa)[TT][4], const double (&fb)[TT][4]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][t], fb[j][t], acc[i][j], 0, 0, 0);
+  };
+  for (int q = 0; q < NST - 1; ++q)
+    if (q < mine) issue(q);
+  for (int q = 0; q < mine; ++q) {
+    // slab q has landed; the NST - 2 after it may be pending
+    if (q + NST - 1 <= mine)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * LOADS) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const char* st = base + (q % NST) * STAGE;
+    double fa[TT][4], fb[TT][4];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      const int r = 16 * i + li;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int c = (lg * 2 + u) ^ swz<16>(r);
+        const d2 x = *(const d2*)(st + (r * 8 + c) * 16);
+        const d2 y = *(const d2*)(st + BT * 128 + (r * 8 + c) * 16);
+        fa[i][2 * u] = x.x;
+        fa[i][2 * u + 1] = x.y;
+        fb[i][2 * u] = y.x;
+        fb[i][2 * u + 1] = y.y;
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage of slab q - 1 is free
+    asm volatile("" ::: "memory");
+    if (q + NST - 1 < mine) issue(q + NST - 1);
+    mul(fa, fb);
+  }
+  if ((K & 15) && full % NWV == w) {  // uniform: the wave whose turn the last slab is
+    double fa[TT][4], fb[TT][4];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      const double* ar = A + (long long)min(m0 + 16 * i + li, M - 1) * lda;
+      const double* br = B + (long long)min(n0 + 16 * i + li, N - 1) * ldb;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int k = 16 * full + 4 * lg + t;
+        fa[i][t] = k < K ? ar[k] : 0.0;
+        fb[i][t] = k < K ? br[k] : 0.0;
+      }
+    }
+    mul(fa, fb);
+  }
+  if (NWV > 1) lds_barrier();  // every wave is done with its stages
+  small_store<BT, NWV>(acc, (double*)smem, C, om, m0, n0, M, N, maxbits, sub, sigma);
+}
+
+template <int BT, int NWV>
+__global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_smallk(
+    const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
+    double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
+    const double* __restrict__ sub, double sigma, int sym, const double* __restrict__ A_2,
+    double* __restrict__ C_2) {
+  __shared__ __attribute__((aligned(16))) char smem[SmallK<BT, NWV>::kBytes];
+  if (sym && blockIdx.y > blockIdx.x) return;
+  if (blockIdx.z) {  // the second of two products A A^T
+    A = A_2;
+    B = A_2;
+    C = C_2;
+  }
+  small_k_tile<BT, NWV>(A, lda, B, ldb, C, om, blockIdx.y * BT, blockIdx.x * BT, M, N, K, maxbits,
+                        sub, sigma, smem);
+}
+
+// Grouped products by the small tiles (items as for k_gemm_f64_grouped, begin in
+// BT x BT tiles; K-contiguous items 16-byte aligned with even strides): a batch of
+// few problems leaves the chip idle by 64 x 64 tiles over the whole of K.
+template <int BT, int NWV, int BL>
+__global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small_grouped(
+    const F64Item* __restrict__ items, const int* __restrict__ begin, int count, int sym) {
+  __shared__ __attribute__((aligned(16))) char smem[SmallK<BT, NWV>::kBytes];
+  int lo = 0, hi = count - 1;
+  const int b = blockIdx.x;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (begin[mid] <= b) lo = mid; else hi = mid - 1;
+  }
+  const F64Item& it = items[lo];
+  if (it.gate && *it.gate == 0) return;
+  const int local = b - begin[lo], tn = (it.N + BT - 1) / BT;
+  const int tm = local / tn, tc = local % tn;
+  if (sym && tm > tc) return;
+  if constexpr (BL == B_KCONTIG)
+    small_k_tile<BT, NWV>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT, tc * BT,
+                          it.M, it.N, it.K, nullptr, nullptr, 0.0, smem);
+  else
+    small_tile<BT, NWV, BL, false>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
+                                   tc * BT, it.M, it.N, it.K, nullptr, nullptr, 0.0,
+                                   (double*)smem);
+}
+
+int f64_group_small_tiles(const F64Item& it, int bl) {
+  const int bt = bl == B_KCONTIG ? 16 : 32;
+  return ((it.M + bt - 1) / bt) * ((it.N + bt - 1) / bt);
+}
+
+bool f64_group_small(const F64Item& it, int bl) {
+  return bl == B_NCONTIG || !((it.lda | it.ldb) & 1 || ((uintptr_t)it.A | (uintptr_t)it.B) & 15);
+}
+
+void gemm_f64_grouped_small(int bl, bool sym, const F64Item* d_items, const int* d_begin,
+                            int count, int tiles, hipStream_t s) {
+  if (tiles <= 0) return;
+  if (bl == B_KCONTIG)
+    hipLaunchKernelGGL((k_gemm_f64_small_grouped<16, 8, B_KCONTIG>), dim3(tiles), dim3(512), 0, s,
+                       d_items, d_begin, count, sym ? 1 : 0);
+  else
+    hipLaunchKernelGGL((k_gemm_f64_small_grouped<32, 4, B_NCONTIG>), dim3(tiles), dim3(256), 0, s,
+                       d_items, d_begin, count, 0);
+}
+
+static bool vec_ok(const double* p, long long ld) { return !(ld & 1) && !((uintptr_t)p & 15); }
 
 template <int BT, int NWV>
 static void launch_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                          double* C, const OutMap& om, int M, int N, int K,
                          unsigned long long* maxbits, hipStream_t s, const double* sub,
-                         double sigma, const double* A_2, double* C_2) {
+                         double sigma, int sym, const double* A_2, double* C_2) {
   const dim3 grid((N + BT - 1) / BT, (M + BT - 1) / BT, A_2 ? 2 : 1), block(64 * NWV);
-  const bool vec = !(lda & 1) && !((uintptr_t)A & 15) && !((uintptr_t)A_2 & 15) &&
-                   (bl == B_NCONTIG || (!(ldb & 1) && !((uintptr_t)B & 15)));
+  const bool vec = vec_ok(A, lda) && vec_ok(A_2, lda) && (bl == B_NCONTIG || vec_ok(B, ldb));
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub,
                        sigma, A_2, C_2);
@@ -399,36 +590,44 @@ static void launch_small(const double* A, long long lda, const double* B, long l
     if (vec) go(k_gemm_f64_small<BT, NWV, B_NCONTIG, true>);
     else go(k_gemm_f64_small<BT, NWV, B_NCONTIG, false>);
   } else {
-    if (vec) go(k_gemm_f64_small<BT, NWV, B_KCONTIG, true>);
-    else go(k_gemm_f64_small<BT, NWV, B_KCONTIG, false>);
+    if (vec)
+      hipLaunchKernelGGL((k_gemm_f64_smallk<BT, NWV>), grid, block, 0, s, A, lda, B, ldb, C, om, M,
+                         N, K, maxbits, sub, sigma, sym, A_2, C_2);
+    else
+      go(k_gemm_f64_small<BT, NWV, B_KCONTIG, false>);
   }
 }
 
 // C = A B (- sigma sub) by small tiles; false for the products that belong to
-// the larger ones.  The lines, both sides measured: up to 393216 outputs
-// K-contiguous (576^2: 24 us against 28 with 64 x 64 LDS tiles; 729^2: 51 against
-// 34) and 524288 N-contiguous (128 x 4096 x 4096, above); short K with many tiles
-// stays with the 64 x 64 ones (256 x 4096 x 16: 5.8 us, 8.7 here).  16 x 16 tiles
-// up to one per compute unit (256^3: 5.5 us, 8.7 with 32 x 32; 400^3: 13.7 and
-// 11.2); four waves once each has a slab.
+// the larger ones.  The lines, both sides measured: up to 524288 outputs (729^2 K-
+// contiguous: 28.6 us, 34 with 64 x 64 LDS tiles; 128 x 4096 x 4096 N-contiguous,
+// above); short K with many tiles stays with the 64 x 64 ones (256 x 4096 x 16: 5.8
+// us, 8.7 here).  16 x 16 tiles up to one per compute unit (256^3 N-contiguous: 5.5
+// us, 8.7 with 32 x 32), K-contiguous to six (two of 400^3: 10.1 us, 12.3 with
+// 32 x 32; two of 484^3: 17.3 and 14.5); four waves once each has a slab, eight with
+// K of 256 and at most a tile per unit (64 x 64 x 1024: 5.2 us, 6.2 with four).
+// `sym` (K-contiguous, B = A): the lower triangle's tiles are left as they are.
 static bool gemm_f64_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                            double* C, const OutMap& om, int M, int N, int K,
                            unsigned long long* maxbits, hipStream_t s, const double* sub = nullptr,
-                           double sigma = 0.0, const double* A_2 = nullptr,
+                           double sigma = 0.0, int sym = 0, const double* A_2 = nullptr,
                            double* C_2 = nullptr) {
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16), mn = (long long)M * N;
-  if (K < 1 || mn > (bl == B_KCONTIG ? 393216 : 524288) || (K < 32 && t16 > 512)) return false;
+  if (K < 1 || mn > 524288 || (K < 32 && t16 > 512)) return false;
   const int slabs = (K + 15) / 16;
+  const bool t32 = bl == B_KCONTIG ? (A_2 ? 2 : 1) * t16 > 1536 : t16 > 256;
   auto go = [&](auto nw) {
     constexpr int NWV = decltype(nw)::value;
-    if (t16 <= 256)
-      launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma,
-                             A_2, C_2);
-    else
-      launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma,
-                            A_2, C_2);
+    if (!t32)
+      launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma, sym, A_2,
+                            C_2);
+    else if constexpr (NWV <= 4)
+      launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma, sym, A_2,
+                            C_2);
   };
-  if (slabs >= 4)
+  if (bl == B_KCONTIG && slabs >= 16 && t16 <= 256)
+    go(std::integral_constant<int, 8>{});
+  else if (slabs >= 4)
     go(std::integral_constant<int, 4>{});
   else if (slabs >= 2)
     go(std::integral_constant<int, 2>{});
@@ -439,8 +638,8 @@ static bool gemm_f64_small(const double* A, long long lda, const double* B, long
 
 bool gemm_f64_small_pair(const double* A1, const double* A2, long long lda, double* C1, double* C2,
                          const OutMap& om, int M, int K, hipStream_t s) {
-  return gemm_f64_small(A1, lda, A1, lda, B_KCONTIG, C1, om, M, M, K, nullptr, s, nullptr, 0.0, A2,
-                        C2);
+  return gemm_f64_small(A1, lda, A1, lda, B_KCONTIG, C1, om, M, M, K, nullptr, s, nullptr, 0.0, 0,
+                        A2, C2);
 }
 
 // Large-GEMM variant: 128 x 128 block tile, K slab BK = 32, LDS double
@@ -601,13 +800,21 @@ __global__ void k_sum_partials(const double* __restrict__ P, int parts, long lon
   }
 }
 
+void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
+                   double* partials, hipStream_t s) {
+  if (vec_ok(A, lda) && gemm_f64_small(A, lda, A, lda, B_KCONTIG, C, out_rowmajor(M), M, M, K,
+                                       nullptr, s, nullptr, 0.0, 1))
+    return;
+  gemm_f64_splitk(A, lda, A, lda, B_KCONTIG, C, M, M, M, K, kchunk, partials, s);
+}
+
 void gemm_f64_splitk(const double* A, long long lda, const double* B, long long ldb, int blayout,
                      double* C, long long ldc, int M, int N, int K, int kchunk, double* partials,
                      hipStream_t s, const double* sub, double sigma) {
   if (M <= 0 || N <= 0) return;
-  // (long sums of few tiles keep the split: 64 x 64 x 1024 8.7 us, 9.8 by small
-  // tiles; 64 x 64 x 576 8.6 and 7.1)
-  if ((N > 256 || K <= 576) &&
+  // (where the small tiles load operands into registers, long sums of few tiles keep
+  // the split: 64 x 64 x 1024 8.7 us, 9.8 by small tiles; 64 x 64 x 576 8.6 and 7.1)
+  if ((N > 256 || K <= 576 || (blayout == B_KCONTIG && vec_ok(A, lda) && vec_ok(B, ldb))) &&
       gemm_f64_small(A, lda, B, ldb, blayout, C, out_rowmajor(N), M, N, K, nullptr, s, sub, sigma))
     return;
   const int parts = (K + kchunk - 1) / kchunk;

@@ -71,6 +71,17 @@ struct F64Item {
 int f64_group_tiles(const F64Item& it);  // 64 x 64 output tiles
 void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, int count,
                       int tiles, hipStream_t s);
+// The same by small tiles (16 x 16 K-contiguous, 32 x 32 N-contiguous) for the
+// items that f64_group_small takes; with `sym` (B = A) the lower triangle's tiles
+// are left as they are.
+bool f64_group_small(const F64Item& it, int bl);
+int f64_group_small_tiles(const F64Item& it, int bl);
+void gemm_f64_grouped_small(int bl, bool sym, const F64Item* d_items, const int* d_begin,
+                            int count, int tiles, hipStream_t s);
+// C (M x M, row-major) = A A^T, A K-contiguous, M at most 128; elements below the
+// diagonal may be left as they are.  kchunk, partials as for gemm_f64_splitk.
+void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
+                   double* partials, hipStream_t s);
 
 // Split-K FP64 GEMM for products with small M x N and long K: partial
 // products of K chunks go to `partials` (ceil(K/kchunk) * M * N doubles) and

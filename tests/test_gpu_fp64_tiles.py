@@ -52,7 +52,8 @@ def test_environment(dx, dy):
 # remainders past a slab, odd strides, more slabs than waves, both tile sizes
 @pytest.mark.parametrize("dx, dy, dn", [(2, 2, 2), (3, 2, 9), (4, 4, 7), (5, 5, 5), (8, 8, 8),
                                         (7, 11, 13), (16, 16, 16), (9, 17, 20), (21, 21, 21),
-                                        (23, 23, 23)])
+                                        (23, 23, 23), (1, 2, 1), (2, 22, 3), (3, 26, 5),
+                                        (18, 9, 11), (18, 18, 18), (22, 22, 5)])
 def test_coarse_and_environment_small(dx, dy, dn):
     import torch
 
