@@ -106,6 +106,23 @@ __device__ __forceinline__ void load_ncontig64(const double* __restrict__ G, lon
   }
 }
 
+// The same for 32 columns: four rows of 256 bytes an instruction.
+template <int BK, int NW>
+__device__ __forceinline__ void load_ncontig32(const double* __restrict__ G, long long ld, int k0,
+                                               int col0, int cols_valid, char* lds, int wave,
+                                               int lane) {
+  static_assert((BK / 4) % NW == 0, "row quads must split over waves");
+#pragma unroll
+  for (int q = 0; q < BK / 4 / NW; ++q) {
+    const int qr = wave + q * NW;
+    const int r = 4 * qr + (lane >> 4);
+    int gc = col0 + 2 * (lane & 15);
+    gc = gc < cols_valid ? gc : cols_valid - 2;
+    const double* src = G + (long long)(k0 + r) * ld + gc;
+    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(lds + qr * 1024), 16, 0, 0);
+  }
+}
+
 template <int WGM, int WGN, int BK, int BL, int TAG, int NST, int WTM, int WTN>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void k_gemm_f64_lds(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
@@ -119,7 +136,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void k_gemm_f64_lds(
   constexpr int STAGE = A_BYTES + B_BYTES;
   constexpr int KQ = BK / 4;  // k values per lane group per slab
   constexpr int A_INST = BM / (1024 / (BK * 8)) / NW;
-  constexpr int B_INST = BL == B_NCONTIG ? (BN == 64 ? BK / 2 / NW : BK / NW)
+  constexpr int B_INST = BL == B_NCONTIG ? BK * BN / 128 / NW
                                           : BN / (1024 / (BK * 8)) / NW;
   constexpr int LOADS = A_INST + B_INST;  // global_load_lds per wave per slab
   static_assert(LOADS <= 63, "vmcnt range");
@@ -173,7 +190,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void k_gemm_f64_lds(
   };
   auto issue_b = [&](int k0, int stage) {
     char* base = smem + stage * STAGE;
-    if constexpr (BL == B_NCONTIG && BN == 64)
+    if constexpr (BL == B_NCONTIG && BN == 32)
+      load_ncontig32<BK, NW>(B, ldb, k0, n0, N2, base + A_BYTES, wave, lane);
+    else if constexpr (BL == B_NCONTIG && BN == 64)
       load_ncontig64<BK, NW>(B, ldb, k0, n0, N2, base + A_BYTES, wave, lane);
     else if constexpr (BL == B_NCONTIG)
       load_ncontig<BK, BN, NW>(B, ldb, k0, n0, N2, base + A_BYTES, wave, lane);
@@ -562,6 +581,11 @@ bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb
       launch_lds<2, 2, 16, GEMM_TAG_ENV, 3, 32, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
     else
       launch_lds<2, 2, 16, GEMM_TAG_OTHER, 3, 32, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
+  } else if (variant == 8) {
+    // 64 x 32 tile, 4 waves of 16 x 32, four stages in 48 KB (the last coarse
+    // contraction, N = D'): 32768 x 32 x 1024 82 -> 52 us (64 x 64 tiles, half of
+    // them padding), 19900 x 50 x 2512 185 -> 146
+    launch_lds<4, 1, 16, GEMM_TAG_OTHER, 4, 16, 32>(A, lda, B, ldb, blayout, C, om, M, N, K, maxbits, s);
   } else if (variant == 7) {
     // 128 x 128 tile, 8 waves of 64 x 32, four stages in 128 KB
     if (tag == GEMM_TAG_C2)

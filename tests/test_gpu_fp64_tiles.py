@@ -1,5 +1,5 @@
 """The FP64 contraction kernels at the edges of their tiles, against the oracle:
-the 64 x 64 and 128 x 128 LDS tiles forced one at a time, and the environment's
+the 64 x 64, 128 x 128 and 64 x 32 LDS tiles forced one at a time, and the environment's
 symmetric products (64 x 64 tiles, both halves in one launch) around multiples
 of the tile.  Element-wise within 1e-12 of the largest element, the bound of the
 other FP64 parity tests (a sum of K products of magnitude at most s has an error
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("variant", ["6", "7"])
+@pytest.mark.parametrize("variant", ["6", "7", "8"])
 def test_forced_lds_tile(variant):
     print("forced", variant, flush=True)
     env = dict(os.environ, HOTRG_GEMM_VARIANT=variant)
