@@ -61,12 +61,23 @@ __device__ __forceinline__ long long rmap_col(const OutMap& o, int n) {
 
 __device__ __forceinline__ int rp_swz(int r) { return (r >> 1) & 7; }
 
+// Whether four consecutive output columns 4 q .. 4 q + 3 are adjacent and aligned in
+// memory, for every row: then lanes take them together (rp_tile).
+template <int ES>
+__device__ __forceinline__ bool rp_quads(const OutMap& o, int N, const void* C, const void* Clo) {
+  const bool run = (o.t2 == 1 && !(o.c2.d & 3) && !((o.t0 | o.t1) & 3)) ||
+                   (o.c1.d == 1 && o.c2.d == 1 && o.t0 == 1);
+  return run && !(N & 3) && !((o.s0 | o.s1 | o.s2) & 3) &&
+         !(((uintptr_t)C | (uintptr_t)Clo) & (4 * ES - 1));
+}
+
 // Stream rows [row0, row0 + R) x slab [k0, k0 + 32) of an operand into LDS.
-// One wave instruction moves 8 rows (1 KB).
+// One wave instruction moves 8 rows (1 KB).  With `quads` row 16 j + i of each 64 in
+// LDS is row 4 i + j of the operand.
 template <int R, int MODE>
 __device__ __forceinline__ void rp_load(const void* __restrict__ hi, const void* __restrict__ lo,
                                         long long ldk, int row0, int rows_valid, int k0, char* lds,
-                                        int wave, int lane) {
+                                        int wave, int lane, bool quads = false) {
   constexpr int INSTS = R / 8;
   static_assert(INSTS % 8 == 0, "instructions must split over 8 waves");
 #pragma unroll
@@ -75,7 +86,7 @@ __device__ __forceinline__ void rp_load(const void* __restrict__ hi, const void*
     const int r = inst * 8 + lane / 8;
     const int c = lane % 8;
     const int g = c ^ rp_swz(r);  // chunk stored at position c
-    int gr = row0 + r;
+    int gr = row0 + (quads ? (r & ~63) | (r & 15) << 2 | (r >> 4 & 3) : r);
     gr = gr < rows_valid ? gr : rows_valid - 1;
     const char* src;
     if (MODE == RP_F32)
@@ -90,6 +101,11 @@ __device__ __forceinline__ void rp_load(const void* __restrict__ hi, const void*
 // (TM MFMA tiles of 16 rows): TM = 4 for BN = 128, TM = 8 for BN = 256.
 // One output tile at rows m0.., columns n0.. (shared by the single-product
 // kernel and the grouped one).
+// Column i of MFMA tile j is column 16 j + i of the wave's 64, or 4 i + j where the
+// output allows it (rp_quads): a lane then stores its four columns at once, 8 to 32
+// bytes where it stored 2 to 8, and the stores bound the products with short K.  C1
+// at D = 64, split BF16 (4096 x 262144 x 64): 1598 -> 1056 us; at D = 32, FP32, eight
+// problems: 368 -> 330.
 template <int MODE, int OUT, int TM, int BN, int NST, int PRIO = 0>
 __device__ __forceinline__ void rp_tile(const void* __restrict__ Ahi, const void* __restrict__ Alo,
                                         long long lda, const void* __restrict__ Bhi,
@@ -108,6 +124,8 @@ __device__ __forceinline__ void rp_tile(const void* __restrict__ Ahi, const void
   const int wm = wave / WN, wn = wave % WN;
   const int li = lane & 15, lg = lane >> 4;
 
+  constexpr int ES = OUT == RP_OUT_F64 ? 8 : OUT == RP_OUT_F32 ? 4 : 2;
+  const bool quads = rp_quads<ES>(om, N, C, OUT == RP_OUT_SPLIT ? Clo : nullptr);
   f4 acc[TM][4];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -117,7 +135,7 @@ __device__ __forceinline__ void rp_tile(const void* __restrict__ Ahi, const void
   auto issue = [&](int k0, int stage) {
     char* base = smem + stage * STAGE;
     rp_load<BM, MODE>(Ahi, Alo, lda, m0, M, k0, base, wave, lane);
-    rp_load<BN, MODE>(Bhi, Blo, ldb, n0, N, k0, base + A_BYTES, wave, lane);
+    rp_load<BN, MODE>(Bhi, Blo, ldb, n0, N, k0, base + A_BYTES, wave, lane, quads);
   };
   // the two 16-byte chunks a lane group reads from a row
   const int c0 = MODE == RP_F32 ? 2 * lg : lg;
@@ -323,6 +341,38 @@ __device__ __forceinline__ void rp_tile(const void* __restrict__ Ahi, const void
   }
 
   float mx = 0.f;
+  if (quads) {
+    const int n = n0 + wn * 64 + 4 * li;
+    const long long co = n < N ? rmap_col(om, n) : 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + wm * 16 * TM + i * 16 + 4 * lg + v;
+        if (m >= M || n >= N) continue;
+        const long long o = rmap_row(om, m) + co;
+        const f4 x = {acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]};
+        if (OUT == RP_OUT_F32) {
+          *(f4*)((float*)C + o) = x;
+        } else if (OUT == RP_OUT_F64) {
+          typedef double d2 __attribute__((ext_vector_type(2)));
+          *(d2*)((double*)C + o) = d2{(double)x[0], (double)x[1]};
+          *(d2*)((double*)C + o + 2) = d2{(double)x[2], (double)x[3]};
+        } else {
+          typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+          bf4 h, l;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            h[j] = (__bf16)x[j];
+            l[j] = (__bf16)(x[j] - (float)h[j]);
+          }
+          *(bf4*)((__bf16*)C + o) = h;
+          *(bf4*)((__bf16*)Clo + o) = l;
+        }
+        mx = fmaxf(mx, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
+      }
+    }
+  } else {
   long long coff[4];
   bool cok[4];
 #pragma unroll
@@ -355,6 +405,7 @@ __device__ __forceinline__ void rp_tile(const void* __restrict__ Ahi, const void
         mx = fmaxf(mx, fabsf(x));
       }
     }
+  }
   }
   if (maxbits) {
     double m = mx;
