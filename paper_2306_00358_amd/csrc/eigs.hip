@@ -47,6 +47,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "internal.h"
@@ -56,7 +57,8 @@ namespace hotrg {
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 // deterministic start block: splitmix64 of the element index -> [-1, 1)
-__global__ void k_seed_block(double* V, long long count, unsigned long long seed) {
+__global__ void k_seed_block(double* V, long long count, unsigned long long seed, int* fail) {
+  if (blockIdx.x == 0 && threadIdx.x < 2) fail[threadIdx.x] = 0;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < count;
        e += (long long)gridDim.x * blockDim.x) {
     unsigned long long z = (unsigned long long)e + seed * 0x9E3779B97F4A7C15ULL;
@@ -845,9 +847,12 @@ __global__ void k_symmetrize_small(double* H, int p) {
   }
 }
 
-// res[i] = |Yx[i,:] - theta[i] X[i,:]| (one block per row, fixed-order tree)
+// res[i] = |Yx[i,:] - theta[i] X[i,:]| (one block per row, fixed-order tree); and what
+// the host reads of a Rayleigh-Ritz step beside them: theta at res + p, then the
+// ints dinfo, fail[0] and fail[1], which starts again at 0.
 __global__ void k_ritz_residual(const double* __restrict__ Yx, const double* __restrict__ X,
-                                const double* __restrict__ theta, int n, double* res) {
+                                const double* __restrict__ theta, int n, double* res, int p,
+                                const int* __restrict__ dinfo, int* fail) {
   __shared__ double red[256];
   const int i = blockIdx.x, t = threadIdx.x;
   const double th = theta[i];
@@ -862,7 +867,17 @@ __global__ void k_ritz_residual(const double* __restrict__ Yx, const double* __r
     if (t < o) red[t] += red[t + o];
     __syncthreads();
   }
-  if (t == 0) res[i] = sqrt(red[0]);
+  if (t == 0) {
+    res[i] = sqrt(red[0]);
+    res[p + i] = th;
+    if (i == 0) {
+      int* flags = (int*)(res + 2 * p);
+      flags[0] = *dinfo;
+      flags[1] = fail[0];
+      flags[2] = fail[1];
+      fail[1] = 0;
+    }
+  }
 }
 
 static inline int splitk_chunk(int K) {
@@ -930,8 +945,8 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
   double* Rt = G + pp;
   double* H = Rt + pp;
   double* E = H + pp;          // off-diagonal of the tridiagonal form (p - 1)
-  double* res = E + pp;        // p
-  int* fail = (int*)(res + p); // fail flag, then the count of checks that missed
+  double* res = E + pp;        // p, the host's copy of the eigenvalues (p) and flags (2)
+  int* fail = (int*)(res + 2 * p + 2);  // fail flag, then the count of checks that missed
   // a pass's Cholesky factor (p x p) at Rt and its row scaling (p) in the
   // first p entries of H, which only the Rayleigh-Ritz step uses
   double* Rf = Rt;
@@ -940,8 +955,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
 
   const size_t trsm_lds = (size_t)p * p * sizeof(double);
   if (!trsm_lds_set() || p > 128 || p % 16 != 0) return false;
-  (void)hipMemsetAsync(fail, 0, 2 * sizeof(int), s);
-  hipLaunchKernelGGL(k_seed_block, dim3(256), dim3(256), 0, s, V, (long long)pn, 12345ULL);
+  hipLaunchKernelGGL(k_seed_block, dim3(256), dim3(256), 0, s, V, (long long)pn, 12345ULL, fail);
 
   // one orthonormalisation of rows of Y into V: shifted Cholesky-QR of the
   // column-scaled Gram matrix twice, then a plain pass -- all three before a
@@ -978,7 +992,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
   int it = 0, q = q_first > 0 ? q_first : 3;
   const int max_it = 80;
   double prev = 1e300;
-  std::vector<double> th(p), rs(p);
+  std::vector<double> host(2 * p + 2);
   while (true) {
     const bool skip = nocheck && *nocheck;
     for (int r = 0; r < q; ++r) {
@@ -988,26 +1002,27 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     }
     // Rayleigh-Ritz
     vm(V, Y, 0.0);
-    gemm_f64_splitk(V, n, Y, n, B_KCONTIG, H, p, p, p, n, kc, part, s);
-    hipLaunchKernelGGL(k_symmetrize_small, dim3(16), dim3(256), 0, s, H, p);
+    if (!gemm_f64_symmetric(V, Y, n, H, p, n, s)) {
+      gemm_f64_splitk(V, n, Y, n, B_KCONTIG, H, p, p, p, n, kc, part, s);
+      hipLaunchKernelGGL(k_symmetrize_small, dim3(16), dim3(256), 0, s, H, p);
+    }
     // tridiagonal form and its reflectors (over H), then divide and conquer
     // on the tridiagonal (Z^T into Rt, eigenvalues over its diagonal in W),
     // then the rows of Rt back to H's basis: the Ritz coefficients
     launch_sytrd(H, p, W, E, s);
     if (!tridiag_eig_small(W, E, p, W, Rt, dinfo, s)) return false;
     if (!launch_backtransform(H, p, Rt, 0, p, Rt, s)) return false;
-    gemm_f64(Rt, p, V, n, B_NCONTIG, Xout, out_rowmajor(n), p, n, p, nullptr, s);
-    gemm_f64(Rt, p, Y, n, B_NCONTIG, Yx, out_rowmajor(n), p, n, p, nullptr, s);
-    hipLaunchKernelGGL(k_ritz_residual, dim3(p), dim3(256), 0, s, Yx, Xout, W, n, res);
-    int hinfo[3] = {0, 0, 0};
-    (void)hipMemcpyAsync(th.data(), W, p * sizeof(double), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(rs.data(), res, p * sizeof(double), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(&hinfo[0], dinfo, sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(&hinfo[1], fail, 2 * sizeof(int), hipMemcpyDeviceToHost, s);
+    gemm_f64_two(Rt, p, V, Y, n, Xout, Yx, p, n, p, s);
+    hipLaunchKernelGGL(k_ritz_residual, dim3(p), dim3(256), 0, s, Yx, Xout, W, n, res, p, dinfo,
+                       fail);
+    // everything the host decides by in one copy: four cost 30 us more a step
+    (void)hipMemcpyAsync(host.data(), res, (2 * p + 2) * sizeof(double), hipMemcpyDeviceToHost, s);
     if (hipStreamSynchronize(s) != hipSuccess) return false;
+    const double *rs = host.data(), *th = rs + p;
+    int hinfo[3];
+    std::memcpy(hinfo, th + p, sizeof hinfo);
     if (hinfo[0] != 0 || hinfo[1] != 0) return false;
     if (nocheck) *nocheck = hinfo[2] == 0 ? 1 : 0;
-    (void)hipMemsetAsync(fail + 1, 0, sizeof(int), s);
     const double t1 = th[p - 1];
     if (!(t1 > 0.0)) return false;
     double top = 0.0;

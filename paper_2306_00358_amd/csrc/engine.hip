@@ -1032,7 +1032,7 @@ struct GRun {
 };
 
 // (begin[0], tiles[0]: 64 x 64 tiles; [1]: small tiles, where every item may)
-void launch_f64_table(const GTable& t, int bl, hipStream_t s, bool sym = false) {
+void launch_f64_table(const GTable& t, int bl, hipStream_t s, int sym = SYM_NONE) {
   if (t.tiles[1] > 0)
     gemm_f64_grouped_small(bl, sym, (const F64Item*)t.items, t.begin[1], t.count, t.tiles[1], s);
   else
@@ -1115,7 +1115,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   if (R.dense) group_dense(R.steps, G, R.pmax, s);
   if (!R.dense) group_seed(R.steps, G, R.max_pn, s);
   auto pass = [&](const GTable& gram, int ps, bool full, GroupRows src, GroupRows dst) {
-    launch_f64_table(gram, B_KCONTIG, s, true);
+    launch_f64_table(gram, B_KCONTIG, s, SYM_UPPER);
     group_orth(R.steps, G, R.pmax, R.max_n, ps, full, src, dst, s);
   };
   for (int round = 0; round < (R.dense ? 0 : kGroupRounds); ++round) {
@@ -1132,8 +1132,8 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
       }
     }
     launch_f64_table(R.vm, B_NCONTIG, s);    // Y = V M
-    launch_f64_table(R.rrH, B_KCONTIG, s);   // H = V Y^T
-    group_symm_h(R.steps, G, s);
+    launch_f64_table(R.rrH, B_KCONTIG, s, SYM_BOTH);  // H = V Y^T
+    if (R.rrH.tiles[1] == 0) group_symm_h(R.steps, G, s);
     group_sytrd(R.steps, G, R.pmax, s);      // H -> reflectors, tridiagonal into W, G
     group_stedc(R.steps, G, R.pmax, s);      // tridiagonal's vectors into Rt, W ascending
     group_back(R.steps, G, R.pmax, false, s);  // Rt <- Z^T

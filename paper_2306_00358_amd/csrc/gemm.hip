@@ -231,11 +231,13 @@ void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, i
 
 // Sum of the waves' partial tiles in wave order (through red, NWV BT^2 doubles free
 // of other data once every wave is here) into C, less sigma * sub, and the maximum.
+// mirror: a symmetric C (row-major) from its upper triangle.
 template <int BT, int NWV>
 __device__ __forceinline__ void small_store(const d4 (&acc)[BT / 16][BT / 16], double* red,
                                             double* __restrict__ C, const OutMap& om, int m0,
                                             int n0, int M, int N, unsigned long long* maxbits,
-                                            const double* __restrict__ sub, double sigma) {
+                                            const double* __restrict__ sub, double sigma,
+                                            bool mirror = false) {
   constexpr int TT = BT / 16, E = TT * TT * 256;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -243,8 +245,9 @@ __device__ __forceinline__ void small_store(const d4 (&acc)[BT / 16][BT / 16], d
   double mx = 0.0;
   auto put = [&](int i, int j, int v, int ln, double x) {
     const int m = m0 + 16 * i + (ln >> 4) + 4 * v, n = n0 + 16 * j + (ln & 15);
-    if (m < M && n < N) {
+    if (m < M && n < N && !(mirror && m > n)) {
       const long long o = map_row(om, m) + map_col(om, n);
+      if (mirror) C[map_row(om, n) + map_col(om, m)] = x;
       if (sub) x -= sigma * sub[o];
       C[o] = x;
       mx = fmax(mx, fabs(x));
@@ -396,11 +399,11 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
     double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
     const double* __restrict__ sub, double sigma, const double* __restrict__ A_2,
-    double* __restrict__ C_2) {
+    double* __restrict__ C_2, const double* __restrict__ B_2) {
   __shared__ double red[NWV > 1 ? NWV * BT * BT : 1];
-  if (blockIdx.z) {  // the second of two products A A^T
+  if (blockIdx.z) {  // the second of two products
     A = A_2;
-    B = A_2;
+    B = B_2;
     C = C_2;
   }
   small_tile<BT, NWV, BL, VEC>(A, lda, B, ldb, C, om, blockIdx.y * BT, blockIdx.x * BT, M, N, K,
@@ -415,7 +418,8 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
 // x 1024 8.9 -> 5.2 (there by 32 partial products and a launch that sums them),
 // 128 x 128 x 4096 16 -> 13.7.  More stages take LDS that a second workgroup uses
 // better (four: 576^3 27 us).
-// With `sym` (B = A) only tiles that reach the upper triangle are formed.
+// With `sym` (a symmetric C) only tiles that reach the upper triangle are formed, and
+// mirrored or not.
 constexpr int kSmallStages = 2;
 template <int BT, int NWV>
 struct SmallK {
@@ -432,7 +436,7 @@ __device__ __forceinline__ void small_k_tile(const double* __restrict__ A, long 
                                              int n0, int M, int N, int K,
                                              unsigned long long* maxbits,
                                              const double* __restrict__ sub, double sigma,
-                                             char* smem) {
+                                             bool mirror, char* smem) {
   constexpr int TT = BT / 16, LOADS = 2 * BT / 8, STAGE = SmallK<BT, NWV>::kStage;
   constexpr int NST = kSmallStages;
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -506,7 +510,7 @@ __device__ __forceinline__ void small_k_tile(const double* __restrict__ A, long 
     mul(fa, fb);
   }
   if (NWV > 1) lds_barrier();  // every wave is done with its stages
-  small_store<BT, NWV>(acc, (double*)smem, C, om, m0, n0, M, N, maxbits, sub, sigma);
+  small_store<BT, NWV>(acc, (double*)smem, C, om, m0, n0, M, N, maxbits, sub, sigma, mirror);
 }
 
 template <int BT, int NWV>
@@ -514,16 +518,16 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_smallk(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
     double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
     const double* __restrict__ sub, double sigma, int sym, const double* __restrict__ A_2,
-    double* __restrict__ C_2) {
+    double* __restrict__ C_2, const double* __restrict__ B_2) {
   __shared__ __attribute__((aligned(16))) char smem[SmallK<BT, NWV>::kBytes];
   if (sym && blockIdx.y > blockIdx.x) return;
-  if (blockIdx.z) {  // the second of two products A A^T
+  if (blockIdx.z) {  // the second of two products
     A = A_2;
-    B = A_2;
+    B = B_2;
     C = C_2;
   }
   small_k_tile<BT, NWV>(A, lda, B, ldb, C, om, blockIdx.y * BT, blockIdx.x * BT, M, N, K, maxbits,
-                        sub, sigma, smem);
+                        sub, sigma, sym == SYM_BOTH, smem);
 }
 
 // Grouped products by the small tiles (items as for k_gemm_f64_grouped, begin in
@@ -546,7 +550,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small_grouped(
   if (sym && tm > tc) return;
   if constexpr (BL == B_KCONTIG)
     small_k_tile<BT, NWV>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT, tc * BT,
-                          it.M, it.N, it.K, nullptr, nullptr, 0.0, smem);
+                          it.M, it.N, it.K, nullptr, nullptr, 0.0, sym == SYM_BOTH, smem);
   else
     small_tile<BT, NWV, BL, false>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
                                    tc * BT, it.M, it.N, it.K, nullptr, nullptr, 0.0,
@@ -562,12 +566,12 @@ bool f64_group_small(const F64Item& it, int bl) {
   return bl == B_NCONTIG || !((it.lda | it.ldb) & 1 || ((uintptr_t)it.A | (uintptr_t)it.B) & 15);
 }
 
-void gemm_f64_grouped_small(int bl, bool sym, const F64Item* d_items, const int* d_begin,
+void gemm_f64_grouped_small(int bl, int sym, const F64Item* d_items, const int* d_begin,
                             int count, int tiles, hipStream_t s) {
   if (tiles <= 0) return;
   if (bl == B_KCONTIG)
     hipLaunchKernelGGL((k_gemm_f64_small_grouped<16, 8, B_KCONTIG>), dim3(tiles), dim3(512), 0, s,
-                       d_items, d_begin, count, sym ? 1 : 0);
+                       d_items, d_begin, count, sym);
   else
     hipLaunchKernelGGL((k_gemm_f64_small_grouped<32, 4, B_NCONTIG>), dim3(tiles), dim3(256), 0, s,
                        d_items, d_begin, count, 0);
@@ -579,12 +583,13 @@ template <int BT, int NWV>
 static void launch_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                          double* C, const OutMap& om, int M, int N, int K,
                          unsigned long long* maxbits, hipStream_t s, const double* sub,
-                         double sigma, int sym, const double* A_2, double* C_2) {
+                         double sigma, int sym, const double* A_2, double* C_2,
+                         const double* B_2) {
   const dim3 grid((N + BT - 1) / BT, (M + BT - 1) / BT, A_2 ? 2 : 1), block(64 * NWV);
-  const bool vec = vec_ok(A, lda) && vec_ok(A_2, lda) && (bl == B_NCONTIG || vec_ok(B, ldb));
+  const bool vec = vec_ok(A, lda) && vec_ok(A_2, lda) && (bl == B_NCONTIG || (vec_ok(B, ldb) && vec_ok(B_2, ldb)));
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub,
-                       sigma, A_2, C_2);
+                       sigma, A_2, C_2, B_2);
   };
   if (bl == B_NCONTIG) {
     if (vec) go(k_gemm_f64_small<BT, NWV, B_NCONTIG, true>);
@@ -592,7 +597,7 @@ static void launch_small(const double* A, long long lda, const double* B, long l
   } else {
     if (vec)
       hipLaunchKernelGGL((k_gemm_f64_smallk<BT, NWV>), grid, block, 0, s, A, lda, B, ldb, C, om, M,
-                         N, K, maxbits, sub, sigma, sym, A_2, C_2);
+                         N, K, maxbits, sub, sigma, sym, A_2, C_2, B_2);
     else
       go(k_gemm_f64_small<BT, NWV, B_KCONTIG, false>);
   }
@@ -606,12 +611,13 @@ static void launch_small(const double* A, long long lda, const double* B, long l
 // us, 8.7 with 32 x 32), K-contiguous to six (two of 400^3: 10.1 us, 12.3 with
 // 32 x 32; two of 484^3: 17.3 and 14.5); four waves once each has a slab, eight with
 // K of 256 and at most a tile per unit (64 x 64 x 1024: 5.2 us, 6.2 with four).
-// `sym` (K-contiguous, B = A): the lower triangle's tiles are left as they are.
+// `sym` (K-contiguous, a symmetric C): SymTiles.  A_2: a second product into C_2, of
+// A_2 with B_2, or with itself.
 static bool gemm_f64_small(const double* A, long long lda, const double* B, long long ldb, int bl,
                            double* C, const OutMap& om, int M, int N, int K,
                            unsigned long long* maxbits, hipStream_t s, const double* sub = nullptr,
                            double sigma = 0.0, int sym = 0, const double* A_2 = nullptr,
-                           double* C_2 = nullptr) {
+                           double* C_2 = nullptr, const double* B_2 = nullptr) {
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16), mn = (long long)M * N;
   if (K < 1 || mn > 524288 || (K < 32 && t16 > 512)) return false;
   const int slabs = (K + 15) / 16;
@@ -620,10 +626,10 @@ static bool gemm_f64_small(const double* A, long long lda, const double* B, long
     constexpr int NWV = decltype(nw)::value;
     if (!t32)
       launch_small<16, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma, sym, A_2,
-                            C_2);
+                            C_2, B_2 ? B_2 : A_2);
     else if constexpr (NWV <= 4)
       launch_small<32, NWV>(A, lda, B, ldb, bl, C, om, M, N, K, maxbits, s, sub, sigma, sym, A_2,
-                            C_2);
+                            C_2, B_2 ? B_2 : A_2);
   };
   if (bl == B_KCONTIG && slabs >= 16 && t16 <= 256)
     go(std::integral_constant<int, 8>{});
@@ -800,10 +806,26 @@ __global__ void k_sum_partials(const double* __restrict__ P, int parts, long lon
   }
 }
 
+bool gemm_f64_symmetric(const double* A, const double* B, long long ld, double* C, int M, int K,
+                        hipStream_t s) {
+  return vec_ok(A, ld) && vec_ok(B, ld) &&
+         gemm_f64_small(A, ld, B, ld, B_KCONTIG, C, out_rowmajor(M), M, M, K, nullptr, s, nullptr,
+                        0.0, SYM_BOTH);
+}
+
+void gemm_f64_two(const double* A, long long lda, const double* B1, const double* B2,
+                  long long ldb, double* C1, double* C2, int M, int N, int K, hipStream_t s) {
+  if (gemm_f64_small(A, lda, B1, ldb, B_NCONTIG, C1, out_rowmajor(N), M, N, K, nullptr, s, nullptr,
+                     0.0, 0, A, C2, B2))
+    return;
+  gemm_f64(A, lda, B1, ldb, B_NCONTIG, C1, out_rowmajor(N), M, N, K, nullptr, s);
+  gemm_f64(A, lda, B2, ldb, B_NCONTIG, C2, out_rowmajor(N), M, N, K, nullptr, s);
+}
+
 void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
                    double* partials, hipStream_t s) {
   if (vec_ok(A, lda) && gemm_f64_small(A, lda, A, lda, B_KCONTIG, C, out_rowmajor(M), M, M, K,
-                                       nullptr, s, nullptr, 0.0, 1))
+                                       nullptr, s, nullptr, 0.0, SYM_UPPER))
     return;
   gemm_f64_splitk(A, lda, A, lda, B_KCONTIG, C, M, M, M, K, kchunk, partials, s);
 }

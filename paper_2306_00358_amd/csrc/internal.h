@@ -92,16 +92,28 @@ int f64_group_tiles(const F64Item& it);  // 64 x 64 output tiles
 void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, int count,
                       int tiles, hipStream_t s);
 // The same by small tiles (16 x 16 K-contiguous, 32 x 32 N-contiguous) for the
-// items that f64_group_small takes; with `sym` (B = A) the lower triangle's tiles
-// are left as they are.
+// items that f64_group_small takes; `sym` as below.
+enum SymTiles {
+  SYM_NONE = 0,
+  SYM_UPPER,  // a symmetric C: the lower triangle's tiles are left as they are
+  SYM_BOTH    // its lower triangle mirrors the upper one
+};
 bool f64_group_small(const F64Item& it, int bl);
 int f64_group_small_tiles(const F64Item& it, int bl);
-void gemm_f64_grouped_small(int bl, bool sym, const F64Item* d_items, const int* d_begin,
+void gemm_f64_grouped_small(int bl, int sym, const F64Item* d_items, const int* d_begin,
                             int count, int tiles, hipStream_t s);
 // C (M x M, row-major) = A A^T, A K-contiguous, M at most 128; elements below the
 // diagonal may be left as they are.  kchunk, partials as for gemm_f64_splitk.
 void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
                    double* partials, hipStream_t s);
+// C (M x M) = A B^T, K-contiguous operands whose product is symmetric but for
+// rounding: its upper triangle, mirrored.  false where the small tiles don't apply.
+bool gemm_f64_symmetric(const double* A, const double* B, long long ld, double* C, int M, int K,
+                        hipStream_t s);
+// C1 = A B1 and C2 = A B2 (N-contiguous, C row-major), in one launch where the small
+// tiles apply.
+void gemm_f64_two(const double* A, long long lda, const double* B1, const double* B2,
+                  long long ldb, double* C1, double* C2, int M, int N, int K, hipStream_t s);
 
 // Split-K FP64 GEMM for products with small M x N and long K: partial
 // products of K chunks go to `partials` (ceil(K/kchunk) * M * N doubles) and
