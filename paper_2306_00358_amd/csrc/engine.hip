@@ -114,11 +114,11 @@ struct hotrg_ctx {
 };
 
 // What an iterative eigensolve learnt, for the next solve of the same kind:
-// its n, the sweeps it is estimated to have needed, the shift of its sweeps
-// and whether its orthogonality checks stopped missing.
+// its n, the sweeps it is estimated to have needed, the shift of its sweeps,
+// whether its orthogonality checks stopped missing and its theta_1 / theta_p.
 struct EigHint {
   int n = 0, sweeps = 0, nocheck = 0;
-  double shift = 0.0;
+  double shift = 0.0, cond = 0.0;
 };
 
 struct hotrg_state {
@@ -735,12 +735,12 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
     // is estimated to have needed, at its shift
     const int q_first = h.n == n ? h.sweeps + 1 : 3;
     if (h.n != n) {
-      h.shift = 0.0;
+      h.shift = h.cond = 0.0;
       h.nocheck = 0;
     }
     const bool ok = topk_eigs((const double*)Mb.p, n, p, need, tol, q_first, &h.shift,
-                              &h.nocheck, (double*)c->EW.p, (double*)Wb.p, (double*)Xb.p,
-                              (int*)((char*)c->scal.p + 48), &iters, &enough, &resid, c->stream);
+                              &h.nocheck, &h.cond, (double*)c->EW.p, (double*)Wb.p,
+                              (double*)Xb.p, (int*)((char*)c->scal.p + 48), &iters, &enough, &resid, c->stream);
     h.n = ok ? n : 0;
     h.sweeps = enough;
     c->last_eig_iters = ok ? iters : 0;

@@ -310,7 +310,7 @@ void launch_isometry(const double* V, int cols, int n, int dn, const int* kept, 
                      hipStream_t s);
 size_t topk_workspace_doubles(int n, int p);
 bool topk_eigs(const double* M, int n, int p, int need, double tol,
-               int q_first, double* shift, int* nocheck, double* ws, double* W, double* Xout,
+               int q_first, double* shift, int* nocheck, double* cond, double* ws, double* W, double* Xout,
                int* dinfo, int* iters, int* enough, double* resid, hipStream_t s);
 void launch_layout_u(const double* src, long long sr, long long si, const int* kept, int dx, int dn,
                      int mode, void* u1hi, void* u1lo, void* u3hi, void* u3lo, long long ld1,
