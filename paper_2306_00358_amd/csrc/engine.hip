@@ -1032,9 +1032,11 @@ struct GRun {
 };
 
 // (begin[0], tiles[0]: 64 x 64 tiles; [1]: small tiles, where every item may)
-void launch_f64_table(const GTable& t, int bl, hipStream_t s, int sym = SYM_NONE) {
+void launch_f64_table(const GTable& t, int bl, hipStream_t s, int sym = SYM_NONE,
+                      bool shifted = false) {
   if (t.tiles[1] > 0)
-    gemm_f64_grouped_small(bl, sym, (const F64Item*)t.items, t.begin[1], t.count, t.tiles[1], s);
+    gemm_f64_grouped_small(bl, sym, shifted, (const F64Item*)t.items, t.begin[1], t.count,
+                           t.tiles[1], s);
   else
     gemm_f64_grouped(bl, (const F64Item*)t.items, t.begin[0], t.count, t.tiles[0], s);
 }
@@ -1121,8 +1123,9 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
   for (int round = 0; round < (R.dense ? 0 : kGroupRounds); ++round) {
     for (int sw = 0; sw < kGroupSweepsPerRound; ++sw) {
       const bool full = sw == kGroupSweepsPerRound - 1;
-      launch_f64_table(R.vm, B_NCONTIG, s);  // Y = V M
-      group_shift(R.steps, G, R.max_pn, s);  // Y -= sigma V
+      // Y = V (M - sigma I): M is positive semidefinite, its unwanted eigenvalues lie in
+      // [0, lambda_{p+1}], sigma = theta_min / 2 <= lambda_p / 2
+      launch_f64_table(R.vm, B_NCONTIG, s, SYM_NONE, true);
       pass(R.gramY, 0, full, ROWS_Y, ROWS_T2);
       if (full) {
         pass(R.gramT2, 1, full, ROWS_T2, ROWS_Y);
@@ -1308,9 +1311,16 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   };
   auto item = [&](const double* A, long long lda, const double* B, long long ldb, double* C,
                   long long ldc, int M, int N, int K, GProb* g) {
-    return F64Item{A, lda, B, ldb, C, ldc, M, N, K, &g->ctl->iter};
+    return F64Item{A, lda, B, ldb, C, ldc, M, N, K, &g->ctl->iter, nullptr, nullptr, nullptr};
   };
-  f64tab(R.vm, B_NCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, (const double*)g->M.p, g->n, d.Y, g->n, g->p, g->n, g->n, g); });
+  f64tab(R.vm, B_NCONTIG, [&](GProb* g) {
+    auto d = stp(g);
+    F64Item it = item(d.V, g->n, d.M, g->n, d.Y, g->n, g->p, g->n, g->n, g);
+    it.sub = d.V;
+    it.shift = d.shift;
+    it.step = &g->ctl->k;
+    return it;
+  });
   f64tab(R.gramY, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.Y, g->n, d.Y, g->n, d.G, g->p, g->p, g->p, g->n, g); });
   f64tab(R.gramT2, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.T2, g->n, d.T2, g->n, d.G, g->p, g->p, g->p, g->n, g); });
   f64tab(R.rrH, B_KCONTIG, [&](GProb* g) { auto d = stp(g); return item(d.V, g->n, d.Y, g->n, d.H, g->p, g->p, g->p, g->n, g); });

@@ -533,9 +533,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_smallk(
 // Grouped products by the small tiles (items as for k_gemm_f64_grouped, begin in
 // BT x BT tiles; K-contiguous items 16-byte aligned with even strides): a batch of
 // few problems leaves the chip idle by 64 x 64 tiles over the whole of K.
+// An item with a shift subtracts it times sub where `shifted` (the sweeps of the block
+// eigensolver, Y = V (M - sigma I)).
 template <int BT, int NWV, int BL>
 __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small_grouped(
-    const F64Item* __restrict__ items, const int* __restrict__ begin, int count, int sym) {
+    const F64Item* __restrict__ items, const int* __restrict__ begin, int count, int sym,
+    int shifted) {
   __shared__ __attribute__((aligned(16))) char smem[SmallK<BT, NWV>::kBytes];
   int lo = 0, hi = count - 1;
   const int b = blockIdx.x;
@@ -551,10 +554,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small_grouped(
   if constexpr (BL == B_KCONTIG)
     small_k_tile<BT, NWV>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT, tc * BT,
                           it.M, it.N, it.K, nullptr, nullptr, 0.0, sym == SYM_BOTH, smem);
-  else
+  else {
+    const double sg = shifted && it.sub ? it.shift[*it.step & 1] : 0.0;
     small_tile<BT, NWV, BL, false>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
-                                   tc * BT, it.M, it.N, it.K, nullptr, nullptr, 0.0,
-                                   (double*)smem);
+                                   tc * BT, it.M, it.N, it.K, nullptr, sg > 0.0 ? it.sub : nullptr,
+                                   sg, (double*)smem);
+  }
 }
 
 int f64_group_small_tiles(const F64Item& it, int bl) {
@@ -566,15 +571,15 @@ bool f64_group_small(const F64Item& it, int bl) {
   return bl == B_NCONTIG || !((it.lda | it.ldb) & 1 || ((uintptr_t)it.A | (uintptr_t)it.B) & 15);
 }
 
-void gemm_f64_grouped_small(int bl, int sym, const F64Item* d_items, const int* d_begin,
-                            int count, int tiles, hipStream_t s) {
+void gemm_f64_grouped_small(int bl, int sym, bool shifted, const F64Item* d_items,
+                            const int* d_begin, int count, int tiles, hipStream_t s) {
   if (tiles <= 0) return;
   if (bl == B_KCONTIG)
     hipLaunchKernelGGL((k_gemm_f64_small_grouped<16, 8, B_KCONTIG>), dim3(tiles), dim3(512), 0, s,
-                       d_items, d_begin, count, sym);
+                       d_items, d_begin, count, sym, 0);
   else
     hipLaunchKernelGGL((k_gemm_f64_small_grouped<32, 4, B_NCONTIG>), dim3(tiles), dim3(256), 0, s,
-                       d_items, d_begin, count, 0);
+                       d_items, d_begin, count, 0, shifted ? 1 : 0);
 }
 
 static bool vec_ok(const double* p, long long ld) { return !(ld & 1) && !((uintptr_t)p & 15); }

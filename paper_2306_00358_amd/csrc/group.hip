@@ -65,30 +65,31 @@ __global__ void k_group_symm_h(const GroupStep* __restrict__ d) {
 // Residuals of the `need` leading Ritz pairs, |Yx_i - theta_i X_i|, against
 // tol * theta_1: converged problems stop iterating; in the last round a
 // problem that has not converged stops too and is marked failed.
-__global__ void k_group_resid(const GroupStep* __restrict__ d, int last) {
+__global__ __launch_bounds__(1024) void k_group_resid(const GroupStep* __restrict__ d, int last) {
   const GroupStep& s = d[blockIdx.x];
   if (!s.ctl->iter) return;
-  __shared__ double red[256];
-  const int t = threadIdx.x, p = s.p, n = s.n;
+  __shared__ double red[16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, p = s.p, n = s.n;
   const double th1 = s.W[p - 1];
-  double worst = 0.0;
-  for (int q = 0; q < s.need; ++q) {
+  double worst = 0.0;  // of the rows of this wave
+  for (int q = w; q < s.need; q += 16) {
     const int i = p - 1 - q;
     const double th = s.W[i];
     double acc = 0.0;
-    for (int j = t; j < n; j += 256) {
+#pragma unroll 4
+    for (int j = lane; j < n; j += 64) {
       const double r = s.Yx[(long long)i * n + j] - th * s.X[(long long)i * n + j];
       acc += r * r;
     }
-    red[t] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (t < o) red[t] += red[t + o];
-      __syncthreads();
-    }
-    worst = fmax(worst, sqrt(red[0]));
-    __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    // (fmax would drop a NaN)
+    const double r = sqrt(acc);
+    worst = r > worst || !(r == r) ? r : worst;
   }
+  if (lane == 0) red[w] = worst;
+  __syncthreads();
+  if (t == 0)
+    for (int i = 1; i < 16; ++i) worst = red[i] > worst || !(red[i] == red[i]) ? red[i] : worst;
   if (t == 0) {
     s.res[0] = th1 > 0.0 ? worst / th1 : 1.0;
     const bool ok = th1 > 0.0 && worst <= s.tol * th1;
@@ -97,21 +98,6 @@ __global__ void k_group_resid(const GroupStep* __restrict__ d, int last) {
     // the shift of the sweeps to come, and of the next solve of this parity
     s.shift[s.ctl->k & 1] = 0.5 * fmax(s.W[0], 0.0);
   }
-}
-
-// Y <- Y - sigma V after a sweep's product Y = V M: the sweeps iterate with
-// M - sigma I (M positive semidefinite, unwanted eigenvalues in
-// [0, lambda_{p+1}]; sigma = theta_min / 2 <= lambda_p / 2), the
-// Rayleigh-Ritz products with M
-__global__ void k_group_shift(const GroupStep* __restrict__ d) {
-  const GroupStep& s = d[blockIdx.y];
-  if (!s.ctl->iter) return;
-  const double sg = s.shift[s.ctl->k & 1];
-  if (!(sg > 0.0)) return;
-  const long long count = (long long)s.p * s.n;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < count;
-       e += (long long)gridDim.x * blockDim.x)
-    s.Y[e] -= sg * s.V[e];
 }
 
 // continue from the Ritz vectors: V <- X while still iterating
@@ -238,10 +224,7 @@ void group_symm_h(const GroupStep* d, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_group_symm_h, dim3(16, count), dim3(256), 0, s, d);
 }
 void group_resid(const GroupStep* d, int count, bool last, hipStream_t s) {
-  hipLaunchKernelGGL(k_group_resid, dim3(count), dim3(256), 0, s, d, last ? 1 : 0);
-}
-void group_shift(const GroupStep* d, int count, long long max_pn, hipStream_t s) {
-  hipLaunchKernelGGL(k_group_shift, dim3(gblocks(max_pn), count), dim3(256), 0, s, d);
+  hipLaunchKernelGGL(k_group_resid, dim3(count), dim3(1024), 0, s, d, last ? 1 : 0);
 }
 void group_restart(const GroupStep* d, int count, long long max_pn, hipStream_t s) {
   hipLaunchKernelGGL(k_group_restart, dim3(gblocks(max_pn), count), dim3(256), 0, s, d);

@@ -87,6 +87,11 @@ struct F64Item {
   long long ldc;
   int M, N, K;
   const int* gate;
+  // C -= shift[*step & 1] sub (laid out like C) where the launch asks for it and the
+  // shift is positive (small N-contiguous tiles only)
+  const double* sub;
+  const double* shift;
+  const int* step;
 };
 int f64_group_tiles(const F64Item& it);  // 64 x 64 output tiles
 void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, int count,
@@ -100,8 +105,8 @@ enum SymTiles {
 };
 bool f64_group_small(const F64Item& it, int bl);
 int f64_group_small_tiles(const F64Item& it, int bl);
-void gemm_f64_grouped_small(int bl, int sym, const F64Item* d_items, const int* d_begin,
-                            int count, int tiles, hipStream_t s);
+void gemm_f64_grouped_small(int bl, int sym, bool shifted, const F64Item* d_items,
+                            const int* d_begin, int count, int tiles, hipStream_t s);
 // C (M x M, row-major) = A A^T, A K-contiguous, M at most 128; elements below the
 // diagonal may be left as they are.  kchunk, partials as for gemm_f64_splitk.
 void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
@@ -369,7 +374,6 @@ void group_stedc(const GroupStep* d, int count, int pmax, hipStream_t s);
 void group_back(const GroupStep* d, int count, int pmax, bool dense, hipStream_t s);
 void group_resid(const GroupStep* d, int count, bool last, hipStream_t s);
 void group_restart(const GroupStep* d, int count, long long max_pn, hipStream_t s);
-void group_shift(const GroupStep* d, int count, long long max_pn, hipStream_t s);
 // whole small environments (n <= 128, p = n rounded up to even) by the same kernels
 void group_dense(const GroupStep* d, int count, int pmax, hipStream_t s);
 void group_spectrum(const GroupStep* d, int count, hipStream_t s);
