@@ -127,6 +127,8 @@ struct hotrg_state {
   // current normalised tensor: Tn (FP64) when !cur_f32, Tn32 (FP32) otherwise
   bool cur_f32 = false;
   Buf Tn32;
+  // a context with a memory budget: no padded rows (step_ld)
+  bool plain = false;
   // precision the operands below were prepared for
   int ops_prec = HOTRG_FP64;
   Buf Tn, Xt, Tp;      // FP64 operands of the next step (normalised)
@@ -179,8 +181,9 @@ void release_spare(hotrg_ctx* c) {
 // caller holds own their buffers and give them back when freed.
 hotrg_state* take_state(hotrg_ctx* c) {
   hotrg_state* old = c->spare;
-  if (!old) return new hotrg_state();
   auto* st = new hotrg_state();
+  st->plain = c->budget != 0;
+  if (!old) return st;
   c->spare = nullptr;
   std::swap(st->Tn, old->Tn);
   std::swap(st->Tq, old->Tq);
@@ -329,12 +332,19 @@ void check_dims(int dx, int dy, int dn) {
     fail(HOTRG_ERR_INVALID, "GEMM dimension exceeds 2^31");
 }
 
+// Row lengths of a step.  Under a memory budget (`plain`) nothing is padded: what
+// fitted a budget without padding still does.
+F64Ld step_ld(bool plain, int dx, int dy, int dn) {
+  return plain ? f64_ld_plain(dx, dy, dn) : f64_ld(dx, dy, dn);
+}
+
 // Environment M (n x n, FP64) of a tensor with dims (dx, dy) from its operands
-// Tq (natural) and Xt, rows of f64_ld's p.
-void environment_f64(hotrg_ctx* c, const double* Tq, const double* Xt, int dx, int dy, double* M) {
+// Tq (natural) and Xt, rows of step_ld's p.
+void environment_f64(hotrg_ctx* c, bool plain, const double* Tq, const double* Xt, int dx, int dy,
+                     double* M) {
   const long long P = (long long)dx * dy;  // rows / cols of the halves
   const long long n = (long long)dx * dx, K2 = (long long)dy * dy;
-  const F64Ld ld = f64_ld(dx, dy, 1);
+  const F64Ld ld = step_ld(plain, dx, dy, 1);
   ensure(c, c->A1, (size_t)(n * ld.k2) * 8);
   ensure(c, c->A2, (size_t)(n * ld.k2) * 8);
   PadSet pads;
@@ -410,16 +420,20 @@ hipStream_t ctx_stream(const hotrg_ctx* c) { return c->stream; }
 namespace {
 
 // Doubles of X1 and X2 of a step.
-long long x1_elems(int dx, int dy, int dn) { return (long long)dn * dy * dx * f64_ld(dx, dy, dn).p; }
-long long x2_elems(int dx, int dy, int dn) { return (long long)dn * dy * dy * f64_ld(dx, dy, dn).n; }
+long long x1_elems(bool plain, int dx, int dy, int dn) {
+  return (long long)dn * dy * dx * step_ld(plain, dx, dy, dn).p;
+}
+long long x2_elems(bool plain, int dx, int dy, int dn) {
+  return (long long)dn * dy * dy * step_ld(plain, dx, dy, dn).n;
+}
 
 // The projector of a step in FP64 layouts (`kept` null: src is canonical U[a,b,i];
 // else eigenvector rows, the leading one at src, the next at src - n, ...), and
 // the max slot cleared.
-void projector_f64(hotrg_ctx* c, Buf& U1, Buf& U3, const double* src, const int* kept, int dx,
-                   int dy, int dn, unsigned long long* maxbits) {
+void projector_f64(hotrg_ctx* c, bool plain, Buf& U1, Buf& U3, const double* src, const int* kept,
+                   int dx, int dy, int dn, unsigned long long* maxbits) {
   const long long n = (long long)dx * dx;
-  const F64Ld ld = f64_ld(dx, dy, dn);
+  const F64Ld ld = step_ld(plain, dx, dy, dn);
   ensure(c, U1, (size_t)(n * dn) * 8);
   ensure(c, U3, (size_t)(ld.n * ld.u3) * 8);
   launch_layout_u(src, kept ? 1 : dn, kept ? -n : 1, kept, dx, dn, kFmtF64, U1.p, nullptr, U3.p,
@@ -428,12 +442,12 @@ void projector_f64(hotrg_ctx* c, Buf& U1, Buf& U3, const double* src, const int*
 
 // C1, C2, C3 in FP64: T~[i,j,k,l] (dims dn,dy,dn,dy) into Tt; clears the padding
 // of X1, X2 and U3 first.
-void coarse_f64(hotrg_ctx* c, const double* Tn, const double* Tp, const double* U1, double* U3,
+void coarse_f64(hotrg_ctx* c, bool plain, const double* Tn, const double* Tp, const double* U1, double* U3,
                 int dx, int dy, int dn, double* Tt, unsigned long long* maxbits) {
   const long long P = (long long)dx * dy, n = (long long)dx * dx;
-  const F64Ld ld = f64_ld(dx, dy, dn);
-  ensure(c, c->X1, (size_t)x1_elems(dx, dy, dn) * 8);
-  ensure(c, c->X2, (size_t)x2_elems(dx, dy, dn) * 8);
+  const F64Ld ld = step_ld(plain, dx, dy, dn);
+  ensure(c, c->X1, (size_t)x1_elems(plain, dx, dy, dn) * 8);
+  ensure(c, c->X2, (size_t)x2_elems(plain, dx, dy, dn) * 8);
   PadSet pads;
   pads.add(c->X1.p, (long long)dn * dy * dx, ld.p, P, 8, c->stream);
   pads.add(c->X2.p, (long long)dn * dy * dy, ld.n, n, 8, c->stream);
@@ -453,6 +467,7 @@ hotrg_state* new_state(hotrg_ctx* c, const std::vector<double>& T0, int dx, int 
   for (double v : T0)
     if (!std::isfinite(v)) fail(HOTRG_ERR_NUMERIC, "initial tensor has a non-finite element");
   hotrg_state* st = whole ? take_state(c) : new hotrg_state();
+  st->plain = c->budget != 0;
   try {
     st->prec = prec;
     st->dx = dx;
@@ -503,7 +518,7 @@ PrepOut prep_tp(void* p, long long X, long long Y, long long ldt) {
 // The FP64 operands of a state (buffers large enough) and their padding.
 int prep_f64(PrepOut (&outs)[4], hotrg_state* st, int dx, int dy, hipStream_t s) {
   const long long P = (long long)dx * dy;
-  const F64Ld ld = f64_ld(dx, dy, 1);
+  const F64Ld ld = step_ld(st->plain, dx, dy, 1);
   int k = 0;
   outs[k++] = prep_natural(st->Tn.p, dx, dy, P);
   outs[k++] = prep_xt(st->Xt.p, dx, dy, ld.p);
@@ -521,7 +536,8 @@ int prep_f64(PrepOut (&outs)[4], hotrg_state* st, int dx, int dy, hipStream_t s)
 
 // The environment's natural operand of a state.
 const double* env_natural(const hotrg_state* st, int dx, int dy) {
-  return (const double*)(f64_ld(dx, dy, 1).p != (long long)dx * dy ? st->Tq.p : st->Tn.p);
+  return (const double*)(step_ld(st->plain, dx, dy, 1).p != (long long)dx * dy ? st->Tq.p
+                                                                          : st->Tn.p);
 }
 
 // The reduced-precision operands of a state, rows zero-padded to multiples of 32:
@@ -550,7 +566,7 @@ void prepare_operands(hotrg_ctx* c, hotrg_state* st, int prec, const void* src, 
   const size_t ne = (size_t)dx * dy * dx * dy;
   if (prec == HOTRG_FP64) {
     const size_t P = (size_t)dx * dy;
-    const F64Ld ld = f64_ld(dx, dy, 1);
+    const F64Ld ld = step_ld(st->plain, dx, dy, 1);
     ensure_keep(c, st->Tn, ne * 8, 0);
     ensure_keep(c, st->Xt, P * ld.p * 8, 0);
     ensure_keep(c, st->Tp, (size_t)ld.p * ld.tp * 8, 0);
@@ -809,7 +825,7 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   // environment M (FP64 out)
   ensure(c, c->M, (size_t)n * n * 8);
   if (sp == HOTRG_FP64)
-    environment_f64(c, env_natural(st, dx, dy), (const double*)st->Xt.p, dx, dy, (double*)c->M.p);
+    environment_f64(c, st->plain, env_natural(st, dx, dy), (const double*)st->Xt.p, dx, dy, (double*)c->M.p);
   else
     environment_rp(c, st, rp_mode(sp), dx, dy, (double*)c->M.p);
   double* trace = (double*)((char*)c->scal.p + 40);
@@ -832,7 +848,7 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
     // the right pair of legs: environment of the reflected tensor (FP64)
     if (sp != HOTRG_FP64) fail(HOTRG_ERR_INVALID, "two-sided isometry needs FP64 contractions");
-    const long long P = (long long)dx * dy, ldp = f64_ld(dx, dy, dn).p;
+    const long long P = (long long)dx * dy, ldp = step_ld(st->plain, dx, dy, dn).p;
     ensure(c, c->Tm, (size_t)(P * ldp) * 8);
     ensure(c, c->Xm, (size_t)(P * ldp) * 8);
     ensure(c, c->M2, (size_t)n * n * 8);
@@ -849,7 +865,7 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
     pads.launch(c->stream);
     launch_prep_mirror((const double*)st->Tn.p, dx, dy, ldp, (double*)c->Tm.p, (double*)c->Xm.p,
                        c->stream);
-    environment_f64(c, (const double*)c->Tm.p, (const double*)c->Xm.p, dx, dy, (double*)c->M2.p);
+    environment_f64(c, st->plain, (const double*)c->Tm.p, (const double*)c->Xm.p, dx, dy, (double*)c->M2.p);
     launch_symmetrize((double*)c->M2.p, n, trace2, c->stream);
     mark(c, HOTRG_PHASE_EIGH);
     int cols2 = n;
@@ -879,10 +895,10 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   // the projector in the contractions' layouts, from the last eigenvector rows
   const double* top = evec + (long long)(cols - 1) * n;
   if (sp == HOTRG_FP64) {
-    projector_f64(c, c->U1, c->U3, top, kept, dx, dy, dn, mb);
+    projector_f64(c, st->plain, c->U1, c->U3, top, kept, dx, dy, dn, mb);
     // the three contractions, max|T~|
     ensure(c, c->Tt, (size_t)dn * dy * dn * dy * 8);
-    coarse_f64(c, (const double*)st->Tn.p, (const double*)st->Tp.p, (const double*)c->U1.p,
+    coarse_f64(c, st->plain, (const double*)st->Tn.p, (const double*)st->Tp.p, (const double*)c->U1.p,
                (double*)c->U3.p, dx, dy, dn, (double*)c->Tt.p, mb);
   } else {
     projector_rp(c, rp_mode(sp), top, kept, dx, dn, mb);
@@ -1104,7 +1120,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     }
   } else {
     for (GProb* g : R.act)
-      environment_f64(c, env_natural(g->st, g->D, g->D), (const double*)g->st->Xt.p, g->D, g->D,
+      environment_f64(c, g->st->plain, env_natural(g->st, g->D, g->D), (const double*)g->st->Xt.p, g->D, g->D,
                       (double*)g->M.p);
   }
   for (GProb* g : R.act) {
@@ -1155,7 +1171,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
       launch_layout_u(top, 1, -g->n, kept, g->D, g->D, R.mode, g->RU1[0].p, g->RU1[1].p,
                       g->RU3[0].p, g->RU3[1].p, pad32(g->D), pad32(g->n), mb, s);
     else
-      projector_f64(c, g->U1, g->U3, top, kept, g->D, g->D, g->D, mb);
+      projector_f64(c, g->st->plain, g->U1, g->U3, top, kept, g->D, g->D, g->D, mb);
   }
   // the three contractions, max|T~|
   if (red) {
@@ -1193,7 +1209,7 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     }
   } else {
     for (GProb* g : R.act)
-      coarse_f64(c, (const double*)g->st->Tn.p, (const double*)g->st->Tp.p, (const double*)g->U1.p,
+      coarse_f64(c, g->st->plain, (const double*)g->st->Tn.p, (const double*)g->st->Tp.p, (const double*)g->U1.p,
                  (double*)g->U3.p, g->D, g->D, g->D, (double*)g->Tt.p,
                  (unsigned long long*)g->scal.p);  // shapes tuned by the eager sweep
   }
@@ -1563,7 +1579,7 @@ void run_grouped_impl(hotrg_ctx* c, int N, const hotrg_model_params* params,
           }
         } else {
           ensure(c, g.Tt, (size_t)(D * D * D * D) * 8);
-          const F64Ld ld = f64_ld((int)D, (int)D, (int)D);
+          const F64Ld ld = step_ld(g.st->plain, (int)D, (int)D, (int)D);
           ensure(c, g.U1, (size_t)(n * D) * 8);
           ensure(c, g.U3, (size_t)(ld.n * ld.u3) * 8);
         }
@@ -1573,8 +1589,8 @@ void run_grouped_impl(hotrg_ctx* c, int N, const hotrg_model_params* params,
         // intermediates: sized for the largest
         long long x1 = 1, x2 = 1;
         for (GProb* g : grp) {
-          x1 = std::max(x1, x1_elems(g->D, g->D, g->D));
-          x2 = std::max(x2, x2_elems(g->D, g->D, g->D));
+          x1 = std::max(x1, x1_elems(g->st->plain, g->D, g->D, g->D));
+          x2 = std::max(x2, x2_elems(g->st->plain, g->D, g->D, g->D));
         }
         ensure(c, c->X1, (size_t)x1 * 8);
         ensure(c, c->X2, (size_t)x2 * 8);
@@ -2040,7 +2056,7 @@ hotrg_status hotrg_environment(hotrg_ctx* c, int prec, const double* T, int dx, 
       c->m_dy = dy;
       c->m_dn = dx * dx;
       if (prec == HOTRG_FP64) {
-        const long long P = (long long)dx * dy, ldp = f64_ld(dx, dy, 1).p;
+        const long long P = (long long)dx * dy, ldp = step_ld(ops->plain, dx, dy, 1).p;
         PrepOut outs[4];
         int k = 0;
         ensure(c, ops->Xt, (size_t)(P * ldp) * 8);
@@ -2059,7 +2075,7 @@ hotrg_status hotrg_environment(hotrg_ctx* c, int prec, const double* T, int dx, 
         }
         launch_prep(T, false, false, dx, dy, nullptr, outs, k, nullptr, c->stream);
         mark(c, HOTRG_PHASE_ENV);
-        environment_f64(c, Tq, (const double*)ops->Xt.p, dx, dy, M);
+        environment_f64(c, ops->plain, Tq, (const double*)ops->Xt.p, dx, dy, M);
       } else {
         prepare_operands(c, ops, prec, T, false, false, dx, dy, nullptr);
         mark(c, HOTRG_PHASE_ENV);
@@ -2150,7 +2166,7 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
       c->m_dn = dn;
       if (prec == HOTRG_FP64) {
         const long long P = (long long)dx * dy;
-        const F64Ld ld = f64_ld(dx, dy, dn);
+        const F64Ld ld = step_ld(ops->plain, dx, dy, dn);
         PrepOut outs[4];
         int k = 0;
         ensure(c, ops->Tp, (size_t)(ld.p * ld.tp) * 8);
@@ -2160,8 +2176,8 @@ hotrg_status hotrg_coarse(hotrg_ctx* c, int prec, const double* T, const double*
         pads.add((double*)ops->Tp.p + P * ld.tp, ld.p - P, ld.tp, 0, 8, c->stream);
         pads.launch(c->stream);
         launch_prep(T, false, false, dx, dy, nullptr, outs, k, nullptr, c->stream);
-        projector_f64(c, c->U1, c->U3, U, nullptr, dx, dy, dn, mb);
-        coarse_f64(c, Tn, (const double*)ops->Tp.p, (const double*)c->U1.p, (double*)c->U3.p, dx,
+        projector_f64(c, ops->plain, c->U1, c->U3, U, nullptr, dx, dy, dn, mb);
+        coarse_f64(c, ops->plain, Tn, (const double*)ops->Tp.p, (const double*)c->U1.p, (double*)c->U3.p, dx,
                    dy, dn, Tt, mb);
         mark(c, -1);
       } else {

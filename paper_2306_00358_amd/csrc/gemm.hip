@@ -286,19 +286,18 @@ __device__ __forceinline__ void small_store(const d4 (&acc)[BT / 16][BT / 16], d
 // workgroup's NWV waves, operands loaded from global memory straight into the
 // MFMA's registers (no LDS until the partial tiles of the waves are summed, in
 // wave order).  Lane (i, g) = (lane % 16, lane / 16) takes k = 4 g .. 4 g + 3
-// of each 16-wide slab (two 16-byte loads per row when VEC: even strides and
+// of each 16-wide slab (two 16-byte loads per row of A when VEC: even strides and
 // 16-byte aligned bases; B_NCONTIG loads are 8 bytes, 16 lanes to a 128-byte
 // line); wave w takes slabs w, w + NWV, ...  K need not be a multiple of
 // anything: the last slab is loaded element by element with zeros past K.
 // With sub, C -= sigma * sub (sub laid out like C, row-major).
 // What bounds these products is latency and the few workgroups that larger
-// tiles would give; past a few hundred workgroups it is the K-contiguous
-// loads (64 cycles an instruction: 16 rows, each lane its own 16 bytes), which
-// the tiles in LDS make coalesced.  Against the 64 x 64 tiles staged through
-// registers: 64 x 64 x 64 7.0 -> 3.9 us, 256^3 17.7 -> 5.5, 576^3 35 -> 24,
-// 4096 x 16 x 256 18 -> 5.2; against 4- to 16-way split K with a launch for the
-// partial sums: 64 x 1024 x 1024 14.1 -> 8.4 us, 96 x 2304 x 2304 46 -> 35,
-// 128 x 4096 x 4096 101 -> 97.
+// tiles would give; past a few hundred workgroups the loads of A (64 cycles an
+// instruction: 16 rows, each lane its own 16 bytes).  N-contiguous, against 4- to
+// 16-way split K by 64 x 64 tiles with a launch for the partial sums:
+// 64 x 1024 x 1024 14.1 -> 8.2 us, 96 x 2304 x 2304 46 -> 35, 128 x 4096 x 4096
+// 101 -> 97; 4096 x 16 x 256 18 -> 5.2.  K-contiguous only where the operands are not
+// 16-byte aligned with even strides; else k_gemm_f64_smallk.
 template <int BT, int NWV, int BL, bool VEC>
 __device__ __forceinline__ void small_tile(const double* __restrict__ A, long long lda,
                                            const double* __restrict__ B, long long ldb,

@@ -39,7 +39,9 @@ namespace {
 
 using namespace hotrg;
 
-constexpr size_t kSolverMargin = 256ull << 20;  // rocBLAS / rocSOLVER internal workspace
+// rocBLAS / rocSOLVER internal workspace (the padded operands of ragged sizes, below,
+// take at most the other 2 of 256 MB more than unpadded ones did)
+constexpr size_t kSolverMargin = 254ull << 20;
 
 enum ReqState { Q_QUEUED = 0, Q_RUNNING = 1, Q_DONE = 2 };
 
