@@ -54,3 +54,22 @@ def test_rank_below_the_block():
     assert np.abs(u[:, :r].T @ u[:, :r] - np.eye(r)).max() <= 1e-12
     assert np.abs(np.array(spec) - s[:d] / s[0]).max() <= 1e-12
     assert np.abs(u[:, :kept] @ (u[:, :kept].T @ M) - M).max() <= 1e-11 * np.abs(M).max()
+
+
+@pytest.mark.parametrize("cuts", [[13], [13, 15, 21], [13, 16, 24], [16, 20]])
+def test_lockstep_odd_environments(cuts):
+    # odd D: rows of odd length, which the copies into LDS refuse, alone and beside
+    # even ones (the whole table then takes the general tiles)
+    import torch  # noqa: F401  (one HIP runtime for the process)
+
+    from paper_2306_00358_amd import Context, hotrg_run, hotrg_run_grouped, make_opts, model_params
+
+    P = [model_params("ising", beta=0.42 + 0.01 * i) for i in range(len(cuts))]
+    O = [make_opts(d, 12) for d in cuts]
+    print("lockstep", cuts, flush=True)
+    with Context(0) as ctx:
+        got, statuses = hotrg_run_grouped(ctx, P, O)
+        assert statuses == [0] * len(cuts)
+        for p, o, g in zip(P, O, got):
+            want = hotrg_run(ctx, p, o)["lnz_per_site"]
+            assert abs(g["lnz_per_site"] - want) <= 1e-12 * abs(want)
