@@ -836,17 +836,6 @@ void group_back(const GroupStep* d, int count, int pmax, bool dense, hipStream_t
     hipLaunchKernelGGL(k_group_back<2>, grid, dim3(256), back_lds(pmax, 2), s, d, dense ? 1 : 0);
 }
 
-__global__ void k_symmetrize_small(double* H, int p) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < p * p; e += gridDim.x * blockDim.x) {
-    const int i = e / p, j = e % p;
-    if (i < j) {
-      const double v = 0.5 * (H[i * p + j] + H[j * p + i]);
-      H[i * p + j] = v;
-      H[j * p + i] = v;
-    }
-  }
-}
-
 // res[i] = |Yx[i,:] - theta[i] X[i,:]| (one block per row, fixed-order tree); and what
 // the host reads of a Rayleigh-Ritz step beside them: theta at res + p, then the
 // ints dinfo, fail[0] and fail[1], which starts again at 0.
@@ -880,13 +869,6 @@ __global__ void k_ritz_residual(const double* __restrict__ Yx, const double* __r
   }
 }
 
-static inline int splitk_chunk(int K) {
-  // about 32 partial products, each K chunk a multiple of 16
-  int c = (K + 31) / 32;
-  c = (c + 15) / 16 * 16;
-  return c < 16 ? 16 : c;
-}
-
 // K chunk of the block products V M (p x n times n x n) by 64 x 64 tiles:
 // enough partial products for about 1024 workgroups (at least 4, at most
 // 16), so that p = 128, n = 4096 takes 8 x 2 x 64 (four workgroups per CU
@@ -900,10 +882,7 @@ static inline int vm_chunk(int n, int p) {
 }
 
 static inline size_t partial_doubles(int n, int p) {
-  const size_t pn = (size_t)p * n, pp = (size_t)p * p;
-  const size_t gram = (size_t)((n + splitk_chunk(n) - 1) / splitk_chunk(n)) * pp;
-  const size_t vm = (size_t)((n + vm_chunk(n, p) - 1) / vm_chunk(n, p)) * pn;
-  return gram > vm ? gram : vm;
+  return (size_t)((n + vm_chunk(n, p) - 1) / vm_chunk(n, p)) * p * n;
 }
 
 size_t topk_workspace_doubles(int n, int p) {
@@ -944,7 +923,6 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
                int q_first, double* shift, int* nocheck, double* cond, double* ws, double* W,
                double* Xout, int* dinfo, int* iters, int* enough, double* resid, hipStream_t s) {
   const size_t pn = (size_t)p * n, pp = (size_t)p * p;
-  const int kc = splitk_chunk(n);
   const int kv = vm_chunk(n, p);
   double* V = ws;
   double* Y = V + pn;
@@ -976,7 +954,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     const double* src = Yin;
     const int last = full ? 2 : (check ? 1 : 0);
     for (int pass = 0; pass <= last; ++pass) {
-      gemm_f64_gram(src, n, G, p, n, kc, part, s);
+      gemm_f64_symmetric(src, src, n, G, p, n, SYM_UPPER, s);
       const double sh = pass < 2 ? shift_rel : 0.0, itol = (pass == 0 || full) ? 0.0 : 1e-2;
       if (p <= 64)
         hipLaunchKernelGGL(k_chol_factor<4>, dim3(1), dim3(256), 0, s, G, p, sh,
@@ -1017,10 +995,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     }
     // Rayleigh-Ritz
     vm(V, Y, 0.0);
-    if (!gemm_f64_symmetric(V, Y, n, H, p, n, s)) {
-      gemm_f64_splitk(V, n, Y, n, B_KCONTIG, H, p, p, p, n, kc, part, s);
-      hipLaunchKernelGGL(k_symmetrize_small, dim3(16), dim3(256), 0, s, H, p);
-    }
+    gemm_f64_symmetric(V, Y, n, H, p, n, SYM_BOTH, s);
     // tridiagonal form and its reflectors (over H), then divide and conquer
     // on the tridiagonal (Z^T into Rt, eigenvalues over its diagonal in W),
     // then the rows of Rt back to H's basis: the Ritz coefficients

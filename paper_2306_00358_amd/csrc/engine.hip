@@ -1047,14 +1047,9 @@ struct GRun {
   int cfg[5] = {-1, -1, -1, -1, -1};
 };
 
-// (begin[0], tiles[0]: 64 x 64 tiles; [1]: small tiles, where every item may)
 void launch_f64_table(const GTable& t, int bl, hipStream_t s, int sym = SYM_NONE,
                       bool shifted = false) {
-  if (t.tiles[1] > 0)
-    gemm_f64_grouped_small(bl, sym, shifted, (const F64Item*)t.items, t.begin[1], t.count,
-                           t.tiles[1], s);
-  else
-    gemm_f64_grouped(bl, (const F64Item*)t.items, t.begin[0], t.count, t.tiles[0], s);
+  gemm_f64_grouped(bl, sym, shifted, (const F64Item*)t.items, t.begin[0], t.count, t.tiles[0], s);
 }
 
 void launch_rp_table(const GTable& t, int mode, int out, int cfg, hipStream_t s) {
@@ -1152,7 +1147,6 @@ void group_sweep(hotrg_ctx* c, GRun& R, bool tune, std::vector<std::vector<long 
     }
     launch_f64_table(R.vm, B_NCONTIG, s);    // Y = V M
     launch_f64_table(R.rrH, B_KCONTIG, s, SYM_BOTH);  // H = V Y^T
-    if (R.rrH.tiles[1] == 0) group_symm_h(R.steps, G, s);
     group_sytrd(R.steps, G, R.pmax, s);      // H -> reflectors, tridiagonal into W, G
     group_stedc(R.steps, G, R.pmax, s);      // tridiagonal's vectors into Rt, W ascending
     group_back(R.steps, G, R.pmax, false, s);  // Rt <- Z^T
@@ -1248,22 +1242,16 @@ void group_tables(hotrg_ctx* c, GRun& R, Buf& store, std::vector<std::vector<lon
   std::vector<Pending> pend;
   auto f64tab = [&](GTable& t, int bl, auto make) {
     std::vector<F64Item> it;
-    std::vector<int> b(1, 0), sb(1, 0);
-    bool small = true;
+    std::vector<int> b(1, 0);
     for (GProb* g : R.act) {
       it.push_back(make(g));
-      b.push_back(b.back() + f64_group_tiles(it.back()));
-      sb.push_back(sb.back() + f64_group_small_tiles(it.back(), bl));
-      small = small && f64_group_small(it.back(), bl);
+      b.push_back(b.back() + f64_group_tiles(it.back(), bl));
     }
     t.count = G;
     t.tiles[0] = b.back();
-    t.tiles[1] = small ? sb.back() : 0;
     b.pop_back();
-    sb.pop_back();
     pend.push_back({&t, put(it.data(), it.size() * sizeof(F64Item)),
-                    {put(b.data(), b.size() * sizeof(int)),
-                     put(sb.data(), sb.size() * sizeof(int)), 0}});
+                    {put(b.data(), b.size() * sizeof(int)), 0, 0}});
   };
   auto rptab = [&](GTable& t, const std::vector<RpItem>& it, int op) {
     Pending pe{&t, put(it.data(), it.size() * sizeof(RpItem)), {0, 0, 0}};

@@ -48,20 +48,6 @@ __global__ void k_group_seed(const GroupStep* __restrict__ d) {
   }
 }
 
-__global__ void k_group_symm_h(const GroupStep* __restrict__ d) {
-  const GroupStep& s = d[blockIdx.y];
-  if (!s.ctl->iter) return;
-  const int p = s.p;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < p * p; e += gridDim.x * blockDim.x) {
-    const int i = e / p, j = e % p;
-    if (i < j) {
-      const double v = 0.5 * (s.H[i * p + j] + s.H[j * p + i]);
-      s.H[i * p + j] = v;
-      s.H[j * p + i] = v;
-    }
-  }
-}
-
 // Residuals of the `need` leading Ritz pairs, |Yx_i - theta_i X_i|, against
 // tol * theta_1: converged problems stop iterating; in the last round a
 // problem that has not converged stops too and is marked failed.
@@ -219,9 +205,6 @@ void group_begin(const GroupStep* d, int count, hipStream_t s) {
 }
 void group_seed(const GroupStep* d, int count, long long max_pn, hipStream_t s) {
   hipLaunchKernelGGL(k_group_seed, dim3(gblocks(max_pn), count), dim3(256), 0, s, d);
-}
-void group_symm_h(const GroupStep* d, int count, hipStream_t s) {
-  hipLaunchKernelGGL(k_group_symm_h, dim3(16, count), dim3(256), 0, s, d);
 }
 void group_resid(const GroupStep* d, int count, bool last, hipStream_t s) {
   hipLaunchKernelGGL(k_group_resid, dim3(count), dim3(1024), 0, s, d, last ? 1 : 0);

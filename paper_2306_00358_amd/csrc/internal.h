@@ -88,33 +88,24 @@ struct F64Item {
   int M, N, K;
   const int* gate;
   // C -= shift[*step & 1] sub (laid out like C) where the launch asks for it and the
-  // shift is positive (small N-contiguous tiles only)
+  // shift is positive (N-contiguous only)
   const double* sub;
   const double* shift;
   const int* step;
 };
-int f64_group_tiles(const F64Item& it);  // 64 x 64 output tiles
-void gemm_f64_grouped(int blayout, const F64Item* d_items, const int* d_begin, int count,
-                      int tiles, hipStream_t s);
-// The same by small tiles (16 x 16 K-contiguous, 32 x 32 N-contiguous) for the
-// items that f64_group_small takes; `sym` as below.
+// Of a symmetric C (or all but rounding) only the tiles that reach the upper triangle:
 enum SymTiles {
-  SYM_NONE = 0,
-  SYM_UPPER,  // a symmetric C: the lower triangle's tiles are left as they are
-  SYM_BOTH    // its lower triangle mirrors the upper one
+  SYM_NONE = 0,  // no: every tile
+  SYM_UPPER,     // the lower triangle's tiles are left as they are
+  SYM_BOTH       // the lower triangle mirrors the upper one
 };
-bool f64_group_small(const F64Item& it, int bl);
-int f64_group_small_tiles(const F64Item& it, int bl);
-void gemm_f64_grouped_small(int bl, int sym, bool shifted, const F64Item* d_items,
-                            const int* d_begin, int count, int tiles, hipStream_t s);
-// C (M x M, row-major) = A A^T, A K-contiguous, M at most 128; elements below the
-// diagonal may be left as they are.  kchunk, partials as for gemm_f64_splitk.
-void gemm_f64_gram(const double* A, long long lda, double* C, int M, int K, int kchunk,
-                   double* partials, hipStream_t s);
-// C (M x M) = A B^T, K-contiguous operands whose product is symmetric but for
-// rounding: its upper triangle, mirrored.  false where the small tiles don't apply.
-bool gemm_f64_symmetric(const double* A, const double* B, long long ld, double* C, int M, int K,
-                        hipStream_t s);
+int f64_group_tiles(const F64Item& it, int bl);  // 16 x 16 (K-contiguous) or 32 x 32
+void gemm_f64_grouped(int bl, int sym, bool shifted, const F64Item* d_items, const int* d_begin,
+                      int count, int tiles, hipStream_t s);
+// C (M x M, row-major) = A B^T, K-contiguous operands whose product is symmetric but for
+// rounding, M at most 128; `sym` says what becomes of the lower triangle.
+void gemm_f64_symmetric(const double* A, const double* B, long long ld, double* C, int M, int K,
+                        int sym, hipStream_t s);
 // C1 = A B1 and C2 = A B2 (N-contiguous, C row-major), in one launch where the small
 // tiles apply.
 void gemm_f64_two(const double* A, long long lda, const double* B1, const double* B2,
@@ -363,7 +354,6 @@ void group_orth(const GroupStep* d, int count, int pmax, int max_n, int pass, bo
                 GroupRows src, GroupRows dst, hipStream_t s);
 void group_begin(const GroupStep* d, int count, hipStream_t s);
 void group_seed(const GroupStep* d, int count, long long max_pn, hipStream_t s);
-void group_symm_h(const GroupStep* d, int count, hipStream_t s);
 // Rayleigh-Ritz matrices H (p x p, p a multiple of 16, <= 128) of the
 // iterating problems: Householder reduction (diagonal into W, off-diagonal
 // into G, reflectors over H), divide and conquer (W ascending, Rt <- the

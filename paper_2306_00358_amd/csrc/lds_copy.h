@@ -39,4 +39,20 @@ __device__ __forceinline__ void load_kcontig(const double* __restrict__ G, long 
   }
 }
 
+// The same for rows aligned to 8 bytes only: 4 bytes a lane, two rows of BK = 16 an
+// instruction, into the same places.
+template <int R>
+__device__ __forceinline__ void load_kcontig_any(const double* __restrict__ G, long long ld,
+                                                 int row0, int rows_valid, int k0, char* lds,
+                                                 int lane) {
+#pragma unroll
+  for (int q = 0; q < R / 2; ++q) {
+    const int r = 2 * q + (lane >> 5), p = lane & 31;
+    int gr = row0 + r;
+    gr = gr < rows_valid ? gr : rows_valid - 1;
+    const int* src = (const int*)(G + (long long)gr * ld + k0) + 4 * ((p >> 2) ^ swz<16>(r)) + (p & 3);
+    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(lds + q * 256), 4, 0, 0);
+  }
+}
+
 }  // namespace hotrg
