@@ -236,7 +236,10 @@ hotrg_status hotrg_release(hotrg_ctx* ctx, uint64_t ticket);
  * may be NULL. */
 hotrg_status hotrg_plan(const hotrg_model_params* params, const hotrg_opts* opts, int* prec,
                         int* first_reduced, double* err_bound);
-/* Estimated peak device bytes of one problem (the admission footprint). */
+/* Estimated peak device bytes of one problem (the admission footprint): a
+ * problem is refused only where this exceeds the budget.  It counts unpadded
+ * FP64 operands; ragged sizes take padded ones (a few percent more, counted
+ * while they run) where the budget has room for those. */
 hotrg_status hotrg_footprint(const hotrg_model_params* params, const hotrg_opts* opts,
                              size_t* bytes);
 /* Run n problems on the worker pool and wait for all; `statuses` (may be

@@ -74,6 +74,9 @@ struct hotrg_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   size_t budget = 0;
+  // states take unpadded rows (step_ld): a context with a memory budget, or a pool
+  // worker whose problem fits its pool only so
+  bool plain = false;
   size_t in_use = 0;
   rocblas_handle blas = nullptr;
   // step workspace, grown on demand
@@ -127,8 +130,7 @@ struct hotrg_state {
   // current normalised tensor: Tn (FP64) when !cur_f32, Tn32 (FP32) otherwise
   bool cur_f32 = false;
   Buf Tn32;
-  // a context with a memory budget: no padded rows (step_ld)
-  bool plain = false;
+  bool plain = false;  // the context's when the state was made
   // precision the operands below were prepared for
   int ops_prec = HOTRG_FP64;
   Buf Tn, Xt, Tp;      // FP64 operands of the next step (normalised)
@@ -182,7 +184,7 @@ void release_spare(hotrg_ctx* c) {
 hotrg_state* take_state(hotrg_ctx* c) {
   hotrg_state* old = c->spare;
   auto* st = new hotrg_state();
-  st->plain = c->budget != 0;
+  st->plain = c->plain;
   if (!old) return st;
   c->spare = nullptr;
   std::swap(st->Tn, old->Tn);
@@ -467,7 +469,7 @@ hotrg_state* new_state(hotrg_ctx* c, const std::vector<double>& T0, int dx, int 
   for (double v : T0)
     if (!std::isfinite(v)) fail(HOTRG_ERR_NUMERIC, "initial tensor has a non-finite element");
   hotrg_state* st = whole ? take_state(c) : new hotrg_state();
-  st->plain = c->budget != 0;
+  st->plain = c->plain;
   try {
     st->prec = prec;
     st->dx = dx;
@@ -1765,6 +1767,7 @@ double ctx_seconds(const hotrg_ctx* c) {
 }
 int ctx_device(const hotrg_ctx* c) { return c->device; }
 size_t ctx_budget(const hotrg_ctx* c) { return c->budget; }
+bool& ctx_plain(hotrg_ctx* c) { return c->plain; }
 int& ctx_workers(hotrg_ctx* c) { return c->n_workers; }
 int& ctx_test_fail_step(hotrg_ctx* c) { return c->test_fail_step; }
 void*& ctx_sched(hotrg_ctx* c) { return c->sched; }
@@ -1790,6 +1793,7 @@ hotrg_status hotrg_ctx_create(int device, void* hip_stream, size_t hbm_budget, h
     c->device = device;
     if (const char* e = getenv("HOTRG_TEST_EIG_FAIL_STEP")) c->test_fail_step = atoi(e);
     c->budget = hbm_budget;
+    c->plain = hbm_budget != 0;
     if (hip_stream) {
       c->stream = (hipStream_t)hip_stream;
     } else {

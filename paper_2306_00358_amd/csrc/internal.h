@@ -388,6 +388,7 @@ void ctx_trim(hotrg_ctx* c);  // release the step workspace
 double ctx_seconds(const hotrg_ctx* c);
 int ctx_device(const hotrg_ctx* c);
 size_t ctx_budget(const hotrg_ctx* c);
+bool& ctx_plain(hotrg_ctx* c);  // states made from now on: unpadded FP64 rows
 int& ctx_workers(hotrg_ctx* c);
 int& ctx_test_fail_step(hotrg_ctx* c);  // failure-injection hook, 0: off
 void*& ctx_sched(hotrg_ctx* c);

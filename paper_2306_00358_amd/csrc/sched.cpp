@@ -39,9 +39,7 @@ namespace {
 
 using namespace hotrg;
 
-// rocBLAS / rocSOLVER internal workspace (the padded operands of ragged sizes, below,
-// take at most the other 2 of 256 MB more than unpadded ones did)
-constexpr size_t kSolverMargin = 254ull << 20;
+constexpr size_t kSolverMargin = 256ull << 20;  // rocBLAS / rocSOLVER internal workspace
 
 enum ReqState { Q_QUEUED = 0, Q_RUNNING = 1, Q_DONE = 2 };
 
@@ -56,6 +54,7 @@ struct Request {
   hotrg_status status = HOTRG_ERR_NOT_READY;
   std::string err;
   size_t footprint = 0;
+  bool plain = false;  // FP64 operands with unpadded rows (admit_footprint)
   int skips = 0;
   bool retried = false;
 };
@@ -118,7 +117,7 @@ hotrg_opts resolved(const hotrg_model_params* p, const hotrg_opts* o) {
   return r;
 }
 
-size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
+size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in, bool plain) {
   int dx = 0, dy = 0;
   if (!initial_dims(p, &dx, &dy)) return 0;
   const hotrg_opts ro = resolved(p, o_in);
@@ -130,25 +129,30 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
     if (b > peak[name]) peak[name] = b;
   };
   auto pad = [](long long k) { return (double)((k + 31) / 32 * 32); };
-  // FP64 operands of a step: natural, Tp, Xt and the padded natural copy
-  auto state = [](int dx, int dy) {
+  auto lens = [&](int dx, int dy, int dn) {
+    return plain ? f64_ld_plain(dx, dy, dn) : f64_ld(dx, dy, dn);
+  };
+  // FP64 operands of a step: natural, Tp, Xt and, where rows are padded, a padded
+  // natural copy
+  auto state = [&](int dx, int dy) {
     const double P = (double)dx * dy;
-    const F64Ld ld = f64_ld(dx, dy, 1);
-    return (P * P + (double)ld.p * ld.tp + 2 * P * ld.p) * 8;
+    const F64Ld ld = lens(dx, dy, 1);
+    return (P * P + (double)ld.p * ld.tp + (ld.p != (long long)dx * dy ? 2 : 1) * P * ld.p) * 8;
   };
   need("state", state(dx, dy));
   for (int k = 0; k < o->n_steps; ++k) {
     const double n = (double)dx * dx;
     const int dn = (int)std::min<long long>(o->d_cut, (long long)dx * dx);
-    const F64Ld ld = f64_ld(dx, dy, dn);
+    const F64Ld ld = lens(dx, dy, dn);
     const bool red = step_is_reduced(o->prec, k + 1, dx, dy, o->d_cut, k0);
     need("M", n * n * 8);
     need("WE", 2 * n * 8);
-    need("U", (2 * n * dn + (double)ld.n * ld.u3) * 8);
+    need("U", (n * dn + (double)ld.n * ld.u3) * 8);
     const int p = std::min(128, std::max(2 * dn, dn + 17));
+    // (up to n = 128, where no block solver runs, this and "side" hold the small dense
+    // solver's vectors: p >= 32)
     need("eig", (double)topk_workspace_doubles((int)n, (p + 15) / 16 * 16) * 8 + (double)p * n * 8);
-    // dsyevd fallback workspace; the small dense solver's vectors of both sides
-    need("dense", (n > 128 ? 1 : 2) * n * n * 8);
+    need("dense", n > 128 ? n * n * 8 : 0);  // dsyevd fallback workspace
     if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
       // mirrored operands, right environment, its eigenpairs
       need("side", 2.0 * dx * dy * ld.p * 8 + n * n * 8 + n * 8 + (double)p * n * 8);
@@ -166,8 +170,8 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
       need("Tt", (double)dn * dy * dn * dy * 4);
       need("rstate", 4 * (double)dy * dn * dy * dn * 8);
     }
-    // next state (an operand that grows has both generations while it moves)
-    need("state", state(dy, dn) + (double)dy * dn * f64_ld(dy, dn, 1).p * 8);
+    // next state (both generations exist while the operands are rebuilt)
+    need("state", state(dy, dn) + 3 * (double)dy * dn * dy * dn * 8);
     const int ndx = dy;
     dy = dn;
     dx = ndx;
@@ -175,6 +179,14 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in) {
   size_t total = kSolverMargin;
   for (auto& kv : peak) total += kv.second;
   return total;
+}
+
+// The request's footprint in a pool of `budget` bytes, and its layout: padded rows
+// where those fit the budget, unpadded ones (never larger) where only those may.
+void admit_footprint(Request& r, size_t budget) {
+  r.footprint = footprint_of(&r.params, &r.opts, false);
+  r.plain = r.footprint > budget;
+  if (r.plain) r.footprint = footprint_of(&r.params, &r.opts, true);
 }
 
 // ------------------------------------------------------------------ server --
@@ -231,15 +243,18 @@ void worker_loop(Server* S, int w) {
       S->cv.notify_all();
     }
     if (!r) continue;
+    ctx_plain(c) = r->plain;
     hotrg_status st = run_problem(c, &r->params, &r->opts, r->out, &r->cancel);
     r->out->prec_used = r->opts.prec;
     std::string err = st == HOTRG_OK ? "" : last_error_text();
     const size_t held = hotrg_ctx_bytes_in_use(c);
     const bool retry = st == HOTRG_ERR_NUMERIC && r->opts.prec != HOTRG_FP64 && !r->retried &&
                        !r->cancel.load();
-    hotrg_opts o64 = r->opts;
-    o64.prec = HOTRG_FP64;
-    const size_t f64 = retry ? footprint_of(&r->params, &o64) : 0;
+    Request r64;
+    r64.params = r->params;
+    r64.opts = r->opts;
+    r64.opts.prec = HOTRG_FP64;
+    if (retry) admit_footprint(r64, S->budget);
     {
       std::lock_guard<std::mutex> lk(S->mu);
       S->reserved -= r->footprint + hold;
@@ -247,10 +262,11 @@ void worker_loop(Server* S, int w) {
       S->reserved += hold;
       // a cancel that arrived while the request ran found it Q_RUNNING and did
       // not take it off the queue: it must not be queued again
-      if (retry && f64 <= S->budget && !r->cancel.load()) {
+      if (retry && r64.footprint <= S->budget && !r->cancel.load()) {
         // reduced-precision noise drove the run off: queue it once more in FP64
-        r->opts = o64;
-        r->footprint = f64;
+        r->opts = r64.opts;
+        r->footprint = r64.footprint;
+        r->plain = r64.plain;
         r->retried = true;
         r->state = Q_QUEUED;
         r->skips = 0;
@@ -342,7 +358,7 @@ hotrg_status hotrg_footprint(const hotrg_model_params* params, const hotrg_opts*
     set_last_error("NULL argument");
     return HOTRG_ERR_INVALID;
   }
-  size_t b = footprint_of(params, opts);
+  size_t b = footprint_of(params, opts, true);
   if (b == 0) {
     set_last_error("unknown model or bad dimensions");
     return HOTRG_ERR_INVALID;
@@ -379,8 +395,7 @@ hotrg_status hotrg_submit(hotrg_ctx* ctx, const hotrg_model_params* params, cons
   // the precision is chosen at admission: the cheapest that meets tol
   r->opts = resolved(params, opts);
   r->out = result;
-  r->footprint = footprint_of(params, &r->opts);
-  if (r->footprint == 0) {
+  if (footprint_of(params, &r->opts, true) == 0) {
     set_last_error("unknown model or bad dimensions");
     return HOTRG_ERR_INVALID;
   }
@@ -389,6 +404,7 @@ hotrg_status hotrg_submit(hotrg_ctx* ctx, const hotrg_model_params* params, cons
     set_last_error("could not start workers");
     return HOTRG_ERR_DEVICE;
   }
+  admit_footprint(*r, S->budget);
   {
     std::lock_guard<std::mutex> lk(S->mu);
     if (r->footprint > S->budget) {
@@ -512,7 +528,7 @@ hotrg_status hotrg_run_batch(hotrg_ctx* ctx, int n, const hotrg_model_params* pa
   std::vector<size_t> cost(n);
   for (int i = 0; i < n; ++i) {
     order[i] = i;
-    cost[i] = footprint_of(&params[i], &opts[i]);
+    cost[i] = footprint_of(&params[i], &opts[i], true);
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
   std::vector<uint64_t> tickets(n, 0);
