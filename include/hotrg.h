@@ -155,8 +155,11 @@ typedef struct hotrg_state hotrg_state;
 /* Context on one GPU.  `hip_stream` is a hipStream_t to run on (borrowed, may
  * be NULL for a stream of the context's own).  `hbm_budget` bounds the
  * device memory the context may hold, in bytes (0: no bound).  The context
- * owns all device buffers and states it creates.  Not thread-safe except for
- * the submit/poll/wait/cancel family. */
+ * owns all device buffers and states it creates.  Its workspace grows with the
+ * calls and stays until hotrg_ctx_destroy; without a budget so do the operand
+ * buffers of the last whole run or single operation, where they take at most
+ * 1 GiB (given back too when an allocation of the context fails).
+ * Not thread-safe except for the submit/poll/wait/cancel family. */
 hotrg_status hotrg_ctx_create(int device, void* hip_stream, size_t hbm_budget, hotrg_ctx** out);
 void hotrg_ctx_destroy(hotrg_ctx* ctx);
 const char* hotrg_last_error(void);

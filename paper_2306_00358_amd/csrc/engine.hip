@@ -161,12 +161,17 @@ void ctx_free(hotrg_ctx* c, Buf& b) {
   }
 }
 
+template <class F>
+void each_buffer(hotrg_state* st, F f) {
+  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
+  for (Buf* b : bufs) f(*b);
+  for (auto& o : st->RO)
+    for (auto& b : o) f(b);
+}
+
 void release_state(hotrg_ctx* c, hotrg_state* st) {
   if (!st) return;
-  Buf* bufs[] = {&st->Tn, &st->Tq, &st->Xt, &st->Tp, &st->acc, &st->recs, &st->spec, &st->Tn32};
-  for (Buf* b : bufs) ctx_free(c, *b);
-  for (auto& o : st->RO)
-    for (auto& b : o) ctx_free(c, b);
+  each_buffer(st, [&](Buf& b) { ctx_free(c, b); });
   delete st;
 }
 
@@ -202,8 +207,14 @@ hotrg_state* take_state(hotrg_ctx* c) {
 
 // The end of take_state's user, its work on the stream waited for.  A context
 // with a memory budget keeps nothing: its budget is what later calls count on.
+// Others keep up to kKeepBytes: a run's operands at D = 64 (0.4 GB in FP64, 0.7 GB
+// after split-BF16 steps), past which a call takes tenths of a second and its
+// allocations one or two milliseconds.
+constexpr size_t kKeepBytes = 1ull << 30;
 void retire_state(hotrg_ctx* c, hotrg_state* st) {
-  if (c->budget || c->spare)
+  size_t bytes = 0;
+  each_buffer(st, [&](Buf& b) { bytes += b.bytes; });
+  if (c->budget || c->spare || bytes > kKeepBytes)
     release_state(c, st);
   else
     c->spare = st;

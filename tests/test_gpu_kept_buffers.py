@@ -69,3 +69,22 @@ def test_unaligned_and_overwritten_inputs(D):
             Tg.copy_(torch.from_numpy(T))
             hotrg_environment(ctx, Tg, Tg.view(D * D, D * D))
             _close(Tg.view(D * D, D * D), hotrg.environment(T))
+
+
+def test_large_operands_are_given_back():
+    # FP32 operands of D = 88: five arrays of 240 MB, over the 1 GiB that a context
+    # keeps; the two environment halves (workspace) stay
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_environment
+
+    D = 88
+    T = torch.ones((D, D, D, D), dtype=torch.float64, device="cuda")
+    M = torch.empty((D * D, D * D), dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        for _ in range(2):
+            print("given back", D, flush=True)
+            hotrg_environment(ctx, T, M, prec="fp32")
+            assert ctx.bytes_in_use() <= 2 * 4 * D**4 + (1 << 20)
+        # D^2 equal terms in FP32: D^2 2^-24
+        assert float((M / float(D) ** 6 - 1.0).abs().max()) <= D * D * 2.0 ** -24
