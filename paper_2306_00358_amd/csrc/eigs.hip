@@ -917,7 +917,9 @@ size_t topk_workspace_doubles(int n, int p) {
 // find work to do).
 // Every Rayleigh-Ritz step still sees a basis from three passes, and its
 // residuals decide convergence.
-constexpr double kPairCond = 1e8;
+// Two products leave Gram entries of theta^4: theta_1 within kPairRange keeps them
+// (theta_p^4 too) inside the range of doubles; past it every product is orthonormalised.
+constexpr double kPairCond = 1e8, kPairRange = 0x1p200;
 
 bool topk_eigs(const double* M, int n, int p, int need, double tol,
                int q_first, double* shift, int* nocheck, double* cond, double* ws, double* W,
@@ -1025,7 +1027,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
     rate = std::fmin(std::fmax(rate, 1e-6), 0.95);
     sigma = 0.5 * lo;
     if (shift) *shift = sigma;
-    if (cond) *cond = lo > 0.0 ? t1 / lo : 0.0;
+    if (cond) *cond = lo > 0.0 && t1 <= kPairRange && t1 >= 1.0 / kPairRange ? t1 / lo : 0.0;
     if (iters) *iters = it;
     if (resid) *resid = top;
     if (top <= tol) {

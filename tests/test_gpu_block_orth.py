@@ -73,3 +73,33 @@ def test_lockstep_odd_environments(cuts):
         for p, o, g in zip(P, O, got):
             want = hotrg_run(ctx, p, o)["lnz_per_site"]
             assert abs(g["lnz_per_site"] - want) <= 1e-12 * abs(want)
+
+
+@pytest.mark.parametrize("ratio, scale", [(5e7, 1.0), (2e8, 1.0), (5e7, 2.0**-260), (5e7, 2.0**260),
+                                          (2e8, 2.0**260)])
+def test_two_products_per_orthonormalisation(ratio, scale):
+    # one eigenvalue `ratio` times the 64th, the others a slow decay (2 over the 31
+    # vectors of the block past the needed ones): several sweeps after the first
+    # check, paired below a ratio of 1e8 where the fourth powers of the eigenvalues
+    # are in range, and not else; the block solver converges in each case
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_projector
+    from tests.inputs import orthogonal_with_spectrum
+
+    n, d = 640, 32
+    i = np.arange(n)
+    vals = np.where(i < 64, 2.0 ** ((63 - i) / 31.0), 10.0 ** (-(i - 63) / 200.0)) / ratio
+    vals[0] = 1.0
+    M = scale * orthogonal_with_spectrum(vals, 7)
+    U = torch.empty((n, d), dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        print("ratio", ratio, "scale", scale, flush=True)
+        kept, err, spec = hotrg_projector(ctx, torch.from_numpy(M).to("cuda"), U, d, spec_len=d + 1)
+        sweeps = ctx.last_eig()[0]
+        print("sweeps", sweeps, flush=True)
+    assert sweeps >= 3 + 4
+    u = U.cpu().numpy()
+    assert np.abs(np.array(spec) - vals[:d + 1]).max() <= 1e-12
+    assert np.abs(u.T @ u - np.eye(d)).max() <= 1e-12
+    assert np.linalg.norm(M @ u - u * (scale * vals[:d]), axis=0).max() <= 1e-12 * scale
