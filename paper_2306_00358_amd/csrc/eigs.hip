@@ -869,12 +869,10 @@ __global__ void k_ritz_residual(const double* __restrict__ Yx, const double* __r
   }
 }
 
-// K chunk of the block products V M (p x n times n x n) by 64 x 64 tiles:
+// K chunk of the block products V M (p x n times n x n) that go by 64 x 64 tiles:
 // enough partial products for about 1024 workgroups (at least 4, at most
 // 16), so that p = 128, n = 4096 takes 8 x 2 x 64 (four workgroups per CU
 // hide each other's slab loads: 2% less eigensolver time than 4 x 2 x 64)
-// and p = 64, n = 1024 takes 16 x 1 x 16 instead of the 64 workgroups of a
-// 4-way split that left most of the chip idle
 static inline int vm_chunk(int n, int p) {
   const int tiles = ((p + 63) / 64) * ((n + 63) / 64);
   const int parts = std::min(16, std::max(4, (1024 + tiles - 1) / tiles));
@@ -882,6 +880,7 @@ static inline int vm_chunk(int n, int p) {
 }
 
 static inline size_t partial_doubles(int n, int p) {
+  if (block_product_small(p, n)) return 0;
   return (size_t)((n + vm_chunk(n, p) - 1) / vm_chunk(n, p)) * p * n;
 }
 
@@ -975,8 +974,7 @@ bool topk_eigs(const double* M, int n, int p, int need, double tol,
   // Y = V (M - sigma I)
   double sigma = shift && *shift > 0.0 ? *shift : 0.0;
   auto vm = [&](const double* Vin, double* Yout, double sg) {
-    gemm_f64_splitk(Vin, n, M, n, B_NCONTIG, Yout, n, p, n, n, kv, part, s,
-                    sg > 0.0 ? Vin : nullptr, sg);
+    gemm_f64_block(Vin, M, Yout, p, n, sg, kv, part, s);
   };
 
   int it = 0, q = q_first > 0 ? q_first : 3;

@@ -261,8 +261,8 @@ __device__ __forceinline__ void small_store(const d4 (&acc)[BT / 16][BT / 16], d
 // tiles would give; past a few hundred workgroups the loads of A (64 cycles an
 // instruction: 16 rows, each lane its own 16 bytes).  N-contiguous, against 4- to
 // 16-way split K by 64 x 64 tiles with a launch for the partial sums:
-// 64 x 1024 x 1024 14.1 -> 8.2 us, 96 x 2304 x 2304 46 -> 35, 128 x 4096 x 4096
-// 101 -> 97; 4096 x 16 x 256 18 -> 5.2.
+// 64 x 1024 x 1024 14.1 -> 8.2 us, 96 x 2304 x 2304 46 -> 35 (where the split is the
+// faster one: block_product_small); 4096 x 16 x 256 18 -> 5.2.
 template <int BT, int NWV, bool VEC>
 __device__ __forceinline__ void small_tile(const double* __restrict__ A, long long lda,
                                            const double* __restrict__ B, long long ldb,
@@ -390,9 +390,8 @@ __device__ __forceinline__ void small_k_tile(const double* __restrict__ A, long 
                                              const double* __restrict__ B, long long ldb,
                                              double* __restrict__ C, const OutMap& om, int m0,
                                              int n0, int M, int N, int K,
-                                             unsigned long long* maxbits,
-                                             const double* __restrict__ sub, double sigma,
-                                             bool mirror, char* smem) {
+                                             unsigned long long* maxbits, bool mirror,
+                                             char* smem) {
   constexpr int TT = BT / 16, LOADS = VEC ? 2 * BT / 8 : BT, STAGE = SmallK<BT, NWV>::kStage;
   constexpr int NST = kSmallStages;
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -472,15 +471,15 @@ __device__ __forceinline__ void small_k_tile(const double* __restrict__ A, long 
     mul(fa, fb);
   }
   if (NWV > 1) lds_barrier();  // every wave is done with its stages
-  small_store<BT, NWV>(acc, (double*)smem, C, om, m0, n0, M, N, maxbits, sub, sigma, mirror);
+  small_store<BT, NWV>(acc, (double*)smem, C, om, m0, n0, M, N, maxbits, nullptr, 0.0, mirror);
 }
 
 template <int BT, int NWV, bool VEC>
 __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_smallk(
     const double* __restrict__ A, long long lda, const double* __restrict__ B, long long ldb,
     double* __restrict__ C, OutMap om, int M, int N, int K, unsigned long long* maxbits,
-    const double* __restrict__ sub, double sigma, int sym, const double* __restrict__ A_2,
-    double* __restrict__ C_2, const double* __restrict__ B_2) {
+    int sym, const double* __restrict__ A_2, double* __restrict__ C_2,
+    const double* __restrict__ B_2) {
   __shared__ __attribute__((aligned(16))) char smem[SmallK<BT, NWV>::kBytes];
   if (sym && blockIdx.y > blockIdx.x) return;
   if (blockIdx.z) {  // the second of two products
@@ -489,7 +488,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_smallk(
     C = C_2;
   }
   small_k_tile<BT, NWV, VEC>(A, lda, B, ldb, C, om, blockIdx.y * BT, blockIdx.x * BT, M, N, K, maxbits,
-                        sub, sigma, sym == SYM_BOTH, smem);
+                             sym == SYM_BOTH, smem);
 }
 
 // Grouped form over a device table of products (the block eigensolver of a batch of
@@ -518,12 +517,10 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small_grouped(
   if constexpr (BL == B_KCONTIG) {
     if ((it.lda | it.ldb) & 1 || ((uintptr_t)it.A | (uintptr_t)it.B) & 15)
       small_k_tile<BT, NWV, false>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
-                                   tc * BT, it.M, it.N, it.K, nullptr, nullptr, 0.0,
-                                   sym == SYM_BOTH, smem);
+                                   tc * BT, it.M, it.N, it.K, nullptr, sym == SYM_BOTH, smem);
     else
       small_k_tile<BT, NWV, true>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
-                                  tc * BT, it.M, it.N, it.K, nullptr, nullptr, 0.0,
-                                  sym == SYM_BOTH, smem);
+                                  tc * BT, it.M, it.N, it.K, nullptr, sym == SYM_BOTH, smem);
   } else {
     const double sg = shifted && it.sub ? it.shift[*it.step & 1] : 0.0;
     small_tile<BT, NWV, false>(it.A, it.lda, it.B, it.ldb, it.C, out_rowmajor(it.ldc), tm * BT,
@@ -567,18 +564,17 @@ static void launch_small(const double* A, long long lda, const double* B, long l
     else go(k_gemm_f64_small<BT, NWV, false>);
   } else {
     auto gok = [&](auto kern) {
-      hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sub,
-                         sigma, sym, A_2, C_2, B_2);
+      hipLaunchKernelGGL(kern, grid, block, 0, s, A, lda, B, ldb, C, om, M, N, K, maxbits, sym,
+                         A_2, C_2, B_2);
     };
     if (vec) gok(k_gemm_f64_smallk<BT, NWV, true>);
     else gok(k_gemm_f64_smallk<BT, NWV, false>);
   }
 }
 
-// C = A B (- sigma sub) by small tiles; false for the products that belong to
+// C = A B (- sigma sub, N-contiguous) by small tiles; false for the products that belong to
 // the larger ones.  The lines, both sides measured: up to 524288 outputs (729^2 K-
-// contiguous: 28.6 us, 34 with 64 x 64 LDS tiles; 128 x 4096 x 4096 N-contiguous,
-// above); short K with many tiles stays with the 64 x 64 ones (256 x 4096 x 16: 5.8
+// contiguous: 28.6 us, 34 with 64 x 64 LDS tiles); short K with many tiles stays with the 64 x 64 ones (256 x 4096 x 16: 5.8
 // us, 8.7 here).  16 x 16 tiles up to one per compute unit (256^3 N-contiguous: 5.5
 // us, 8.7 with 32 x 32), K-contiguous to six (two of 400^3: 10.1 us, 12.3 with
 // 32 x 32; two of 484^3: 17.3 and 14.5); four waves once each has a slab, eight with
@@ -794,24 +790,26 @@ void gemm_f64_two(const double* A, long long lda, const double* B1, const double
   gemm_f64(A, lda, B2, ldb, B_NCONTIG, C2, out_rowmajor(N), M, N, K, nullptr, s);
 }
 
-void gemm_f64_splitk(const double* A, long long lda, const double* B, long long ldb, int blayout,
-                     double* C, long long ldc, int M, int N, int K, int kchunk, double* partials,
-                     hipStream_t s, const double* sub, double sigma) {
-  if (M <= 0 || N <= 0) return;
-  // (N-contiguous, long sums of few tiles keep the split: 64 x 64 x 1024 8.7 us, 9.8 by
-  // small tiles; 64 x 64 x 576 8.6 and 7.1)
-  if ((blayout == B_KCONTIG || N > 256 || K <= 576) &&
-      gemm_f64_small(A, lda, B, ldb, blayout, C, out_rowmajor(N), M, N, K, nullptr, s, sub, sigma))
+bool block_product_small(int p, int n) {
+  const long long t16 = (long long)((p + 15) / 16) * ((n + 15) / 16);
+  const long long t32 = (long long)((p + 31) / 32) * ((n + 31) / 32);
+  if (t16 <= 256) return !(n & 1) || n <= 640;
+  return !(n & 1) && p > 64 && t32 <= 256;
+}
+
+void gemm_f64_block(const double* V, const double* M, double* Y, int p, int n, double sigma,
+                    int kchunk, double* partials, hipStream_t s) {
+  const double* sub = sigma > 0.0 ? V : nullptr;
+  if (block_product_small(p, n) &&
+      gemm_f64_small(V, n, M, n, B_NCONTIG, Y, out_rowmajor(n), p, n, n, nullptr, s, sub, sigma))
     return;
-  const int parts = (K + kchunk - 1) / kchunk;
-  const long long cstride = (long long)M * N;
-  launch_f64<64, 64, 16>(A, lda, B, ldb, blayout, partials, out_rowmajor(N), M, N, K, nullptr, s,
-                         kchunk, cstride);
-  long long count = (long long)M * N;
-  int blocks = (int)((count + 255) / 256);
-  hipLaunchKernelGGL(k_sum_partials, dim3(blocks < 4096 ? blocks : 4096), dim3(256), 0, s,
-                     partials, parts, count, cstride, C, sub, sigma);
-  (void)ldc;
+  const long long count = (long long)p * n;
+  const int parts = (n + kchunk - 1) / kchunk;
+  launch_f64<64, 64, 16>(V, n, M, n, B_NCONTIG, partials, out_rowmajor(n), p, n, n, nullptr, s,
+                         kchunk, count);
+  const long long blocks = (count + 255) / 256;
+  hipLaunchKernelGGL(k_sum_partials, dim3(blocks < 4096 ? (int)blocks : 4096), dim3(256), 0, s,
+                     partials, parts, count, count, Y, sub, sigma);
 }
 
 template <int TAG>

@@ -111,14 +111,20 @@ void gemm_f64_symmetric(const double* A, const double* B, long long ld, double* 
 void gemm_f64_two(const double* A, long long lda, const double* B1, const double* B2,
                   long long ldb, double* C1, double* C2, int M, int N, int K, hipStream_t s);
 
-// Split-K FP64 GEMM for products with small M x N and long K: partial
-// products of K chunks go to `partials` (ceil(K/kchunk) * M * N doubles) and
-// are summed in a fixed order into the row-major M x N matrix C.
-// C = A B over K chunks of kchunk summed in order; with sub, C -= sigma * sub
-// (sub laid out like C)
-void gemm_f64_splitk(const double* A, long long lda, const double* B, long long ldb, int blayout,
-                     double* C, long long ldc, int M, int N, int K, int kchunk, double* partials,
-                     hipStream_t s, const double* sub = nullptr, double sigma = 0.0);
+// Y = V (M - sigma I), the product of the block eigensolver (V p x n, p a multiple of
+// 16, M n x n, all row-major and 16-byte aligned).
+void gemm_f64_block(const double* V, const double* M, double* Y, int p, int n, double sigma,
+                    int kchunk, double* partials, hipStream_t s);
+// By one launch of small tiles, or else by 64 x 64 tiles with K in chunks of kchunk
+// (products to `partials`, ceil(n / kchunk) p n doubles) and a launch that sums them.
+// Small tiles take it while there are at most 256 of them, one a compute unit: 16 x 16
+// (64 x 1024: 8.5 us, 13.3 in chunks; 32 x 1936: 19.7 and 19.0), or 32 x 32 where the 64
+// x 64 ones would be of two rows (96 x 2304: 34.9 and 40.4; 128 x 1936: 31.8 and 33.6;
+// not 64 x 1600: 26.0 and 20.8).  Past that a second tile a unit costs more than the
+// chunks' sum (128 x 2304: 53.7 and 42.6; 96 x 2916: 66 and 56; level at 128 x 4096: 92
+// and 90).  Odd rows of V are loaded 8 bytes a lane: chunks from n = 641 on (64 x 625:
+// 8.7 and 11.9; x 729: 12.9 and 11.1; 96 x 2025: 45 and 33; 64 x 4225: 131 and 64).
+bool block_product_small(int p, int n);
 
 // Direct-to-LDS FP64 GEMM (gemm_lds.hip); returns false if the operands do
 // not meet its alignment / K-multiple requirements.  variant 0: 4 waves,

@@ -103,3 +103,29 @@ def test_two_products_per_orthonormalisation(ratio, scale):
     assert np.abs(np.array(spec) - vals[:d + 1]).max() <= 1e-12
     assert np.abs(u.T @ u - np.eye(d)).max() <= 1e-12
     assert np.linalg.norm(M @ u - u * (scale * vals[:d]), axis=0).max() <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("n, d", [(256, 4), (625, 14), (641, 14), (1025, 32), (2048, 14), (2064, 14),
+                                  (2048, 64), (2064, 64), (4097, 64), (4225, 64), (4240, 20)])
+def test_block_product_by_tiles_and_by_chunks(n, d):
+    # either side of the lines between the two ways of V M: even and odd rows, a
+    # tile a compute unit, and past the small tiles' 2^19 outputs; M of rank 256
+    # with known eigenpairs (formed to 256 u, two orders below the bounds)
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_projector
+
+    r = min(n, 256)
+    Q = np.linalg.qr(np.random.default_rng(n + d).standard_normal((n, r)))[0]
+    vals = 10.0 ** (-8.0 * np.arange(r) / r)
+    M = (Q * vals) @ Q.T
+    U = torch.empty((n, d), dtype=torch.float64, device="cuda")
+    with Context(0) as ctx:
+        print("block product", n, d, flush=True)
+        kept, err, spec = hotrg_projector(ctx, torch.from_numpy(M).to("cuda"), U, d, spec_len=d + 1)
+        assert ctx.last_eig()[0] > 0
+    u = U.cpu().numpy()
+    assert kept == d
+    assert np.abs(np.array(spec) - vals[:d + 1]).max() <= 1e-12
+    assert np.abs(u.T @ u - np.eye(d)).max() <= 1e-12
+    assert np.linalg.norm(M @ u - u * vals[:d], axis=0).max() <= 1e-12
