@@ -126,15 +126,19 @@ struct PrepPass {
 struct PrepSet {
   PrepPass p[4];
   int count, norm_blk;
+  int blocks;  // workgroups with work: the grid's rows may end in others
   NormArgs norm;
   const void* src;
   bool src_f32;
   const unsigned long long* maxbits;  // null: scale 1
 };
 
+constexpr int kPrepRow = 1 << 20;
+
 __global__ __launch_bounds__(256) void k_prep(PrepSet S) {
   __shared__ double tile[32][33];
-  const int blk = blockIdx.x;
+  const int blk = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (blk >= S.blocks) return;  // uniform
   if (blk == S.norm_blk) {  // uniform
     norm_body(S.norm, S.maxbits);
     return;
@@ -231,7 +235,12 @@ void launch_prep(const void* src, bool src_f32, bool rotate, int dx, int dy,
     S.norm = *norm;
     S.norm_blk = blocks++;
   }
-  if (blocks > 0) hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(256), 0, s, S);
+  S.blocks = blocks;
+  // one row of workgroups, or several: a grid dimension holds fewer than 2^32 threads
+  // (a leg of 23184 beside one of 1 takes more)
+  const int row = blocks < kPrepRow ? blocks : kPrepRow;
+  if (blocks > 0)
+    hipLaunchKernelGGL(k_prep, dim3(row, (blocks + row - 1) / row), dim3(256), 0, s, S);
 }
 
 // Columns [from, ld) of `rows` rows of ld elements of es bytes, for each region

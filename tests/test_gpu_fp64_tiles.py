@@ -101,3 +101,23 @@ def test_ragged_sizes(prec, tol):
             hotrg_coarse(ctx, Tg, Ug, Tt, prec=prec)
             for got, want in ((M, hotrg.environment(T)), (Tt, hotrg.coarse_tensor(T, U))):
                 assert np.abs(got.cpu().numpy() - want).max() <= tol * np.abs(want).max()
+
+
+def test_more_tiles_than_a_grid_row():
+    # one leg of 1 beside one of 23184: the operand layouts are over 2^24 tiles of 256
+    # threads, more than one grid dimension holds.  T = a b^T, so that M = |a|^2 |b|^2
+    # (a . b)^2; 2^29 terms summed in 32 chains: 2^24 2^-53 at most
+    import torch
+
+    from paper_2306_00358_amd import Context, hotrg_environment
+
+    dy = 23184
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a, b = (torch.rand(dy, dtype=torch.float64, device="cuda", generator=g) + 0.5 for _ in range(2))
+    T = (a[:, None] * b).reshape(1, dy, 1, dy)
+    M = torch.zeros((1, 1), dtype=torch.float64, device="cuda")
+    print("long leg", dy, flush=True)
+    with Context(0) as ctx:
+        hotrg_environment(ctx, T, M)
+    want = float((a @ a) * (b @ b) * (a @ b) ** 2)
+    assert abs(float(M[0, 0]) - want) <= 2.0 ** -29 * want
