@@ -220,6 +220,11 @@ void retire_state(hotrg_ctx* c, hotrg_state* st) {
     c->spare = st;
 }
 
+// Whether the budget lets `b` hold `bytes`.
+bool has_room(const hotrg_ctx* c, const Buf& b, size_t bytes) {
+  return b.bytes >= bytes || !c->budget || c->in_use - b.bytes + bytes <= c->budget;
+}
+
 // Make `b` hold at least `bytes`, keeping the HBM budget.  Growing frees the
 // old buffer first (its contents are not kept).
 void ensure(hotrg_ctx* c, Buf& b, size_t bytes) {
@@ -746,13 +751,13 @@ static bool eig_block(int n, int dn, int spec_len, int eig_mode, int* need_out, 
 }
 
 // Leading eigenpairs of the symmetric n x n matrix in Mb: eigenvalues
-// (ascending) into Wb, eigenvector rows into Xb (p rows, iterative; n rows of
+// (ascending) into Wb, eigenvector rows into Xb (p rows, iterative), Db (n rows of
 // which the last `need` count, small dense) or over Mb (n rows, dense); returns
 // the rows and their count.  A dense solve reports to **info (the caller's
 // launch_spectrum folds it into its sticky flag), an iterative one sets *info
 // to null; one that does not converge falls back to the dense solver.
-static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n, int need, int p,
-                                  bool sub_ok, EigHint& h, int** info, int* cols_out,
+static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, Buf& Db, int n,
+                                  int need, int p, bool sub_ok, EigHint& h, int** info, int* cols_out,
                                   double tol = 5e-14) {
   ensure(c, Wb, (size_t)n * 8);
   if (sub_ok) {
@@ -783,12 +788,14 @@ static const double* leading_eigs(hotrg_ctx* c, Buf& Mb, Buf& Wb, Buf& Xb, int n
   c->last_eig_iters = 0;  // dense
   // small environments: Householder reduction, divide and conquer and the
   // back-transform of the rows needed (the small solver keeps its eigenvectors
-  // apart from Mb, which holds the reflectors); larger ones rocSOLVER dsyevd
-  const bool small = n >= 3 && n <= 128;
+  // apart from Mb, which holds the reflectors); larger ones, and those without
+  // room for that under a budget, rocSOLVER dsyevd, in place
   int* inf = *info;
   ensure(c, c->E, (size_t)n * 8);
-  if (small) ensure(c, Xb, (size_t)n * n * 8);
-  double* vecs = (double*)(small ? Xb.p : Mb.p);
+  const size_t db = (size_t)n * n * 8;
+  const bool small = n >= 3 && n <= 128 && has_room(c, Db, db);
+  if (small) ensure(c, Db, db);
+  double* vecs = (double*)(small ? Db.p : Mb.p);
   if (!small || !dense_eig_small((double*)Mb.p, n, std::min(need, n), (double*)Wb.p,
                                  (double*)c->E.p, vecs, inf, c->stream)) {
     if (small) fail(HOTRG_ERR_DEVICE, "small eigensolver launch failed");
@@ -848,12 +855,15 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
   // leading eigenpairs: block subspace iteration when D' is small against n
   int need = 0, p = 0;
   const bool sub_ok = eig_block(n, dn, o->spec_len, o->eig, &need, &p);
-  auto solve = [&](Buf& Mb, Buf& Wb, Buf& Xb, int side, int** inf, int* cols_out) {
-    return leading_eigs(c, Mb, Wb, Xb, n, need, p, sub_ok, st->eig[(st->k & 1) + 2 * side], inf,
+  // (the small dense solver's vectors are in X1, of the step's precision, and X2, which
+  // the contractions take once the projector's layouts are made)
+  auto solve = [&](Buf& Mb, Buf& Wb, Buf& Xb, Buf& Db, int side, int** inf, int* cols_out) {
+    return leading_eigs(c, Mb, Wb, Xb, Db, n, need, p, sub_ok, st->eig[(st->k & 1) + 2 * side], inf,
                         cols_out, eig_tolerance(sp));
   };
   int cols = n;
-  const double* evec = solve(c->M, c->W, c->Xr, 0, &info, &cols);
+  const double* evec = solve(c->M, c->W, c->Xr, sp == HOTRG_FP64 ? c->X1 : c->RX1[0], 0, &info,
+                             &cols);
   if (k == c->test_fail_step) launch_fail_flag(st_fail, c->stream);
   mark(c, HOTRG_PHASE_PROJ);
   launch_spectrum((const double*)c->W.p, cols, n, dn, o->trunc, o->degen_tol, st->spec_len,
@@ -882,7 +892,7 @@ void do_step(hotrg_ctx* c, hotrg_state* st, const hotrg_opts* o) {
     launch_symmetrize((double*)c->M2.p, n, trace2, c->stream);
     mark(c, HOTRG_PHASE_EIGH);
     int cols2 = n;
-    const double* evec2 = solve(c->M2, c->W2, c->Xr2, 1, &info2, &cols2);
+    const double* evec2 = solve(c->M2, c->W2, c->Xr2, c->X2, 1, &info2, &cols2);
     mark(c, HOTRG_PHASE_PROJ);
     launch_spectrum((const double*)c->W2.p, cols2, n, dn, o->trunc, o->degen_tol, st->spec_len,
                     trace2, spec2, rec2, kept2, info2, st_fail, c->stream);
@@ -2129,7 +2139,7 @@ hotrg_status hotrg_projector(hotrg_ctx* c, const double* M, int n, int dn, int t
       EigHint h;  // a solve of its own
       int cols = n;
       const double* evec =
-          leading_eigs(c, c->M, c->W, c->Xr, n, need, p, sub_ok, h, &info, &cols);
+          leading_eigs(c, c->M, c->W, c->Xr, c->X1, n, need, p, sub_ok, h, &info, &cols);
       launch_spectrum((const double*)c->W.p, cols, n, dn, trunc, degen_tol, spec_len, trace,
                       spec_d, rec, kept_d, info, sticky, c->stream);
       launch_isometry(evec, cols, n, dn, kept_d, U, c->stream);

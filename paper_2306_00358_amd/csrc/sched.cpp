@@ -149,8 +149,8 @@ size_t footprint_of(const hotrg_model_params* p, const hotrg_opts* o_in, bool pl
     need("WE", 2 * n * 8);
     need("U", (n * dn + (double)ld.n * ld.u3) * 8);
     const int p = std::min(128, std::max(2 * dn, dn + 17));
-    // (up to n = 128, where no block solver runs, this and "side" hold the small dense
-    // solver's vectors: p >= 32)
+    // (up to n = 128, where no block solver runs, room for the small dense solver's
+    // vectors of both sides where X1 and X2 are smaller: p >= 32)
     need("eig", (double)topk_workspace_doubles((int)n, (p + 15) / 16 * 16) * 8 + (double)p * n * 8);
     need("dense", n > 128 ? n * n * 8 : 0);  // dsyevd fallback workspace
     if (o->isometry == HOTRG_ISO_TWO_SIDED && dn < n) {
