@@ -205,7 +205,7 @@ __device__ __forceinline__ void dc_range(const unsigned long long* m, int lo, in
   w1 = m[1] & below(hi - 64) & ~below(lo - 64);
 }
 
-// din may be W: it is read before the first barrier and W written after the
+// din may be W: it is read before the second barrier and W written after the
 // last.  NT threads: 256 for n <= 64, 512 up to 128.
 template <int NT>
 __device__ __forceinline__ void stedc_body(const double* din, const double* ein, int n, double* W,
@@ -237,7 +237,13 @@ __device__ __forceinline__ void stedc_body(const double* din, const double* ein,
 
   for (int r = w; r < n; r += NW)
     for (int c = lane; c < n; c += 64) Z[r * kDcLd + c] = 0.0;
-  if (t < n) e[t] = t < n - 1 ? ein[t] : 0.0;
+  if (t < n) {
+    e[t] = t < n - 1 ? ein[t] : 0.0;
+    // a pole that is not a number has no rank, and the place that it leaves in an order
+    // is not written: it holds an index of the range all the same, never what LDS held
+    scol[t] = 0;
+    ord[t] = t;
+  }
   if (t == 0) bad = 0;
   if (t < 2) alive[t] = trig[t] = 0;
   // leaf t / 8 (the lanes past the last leaf carry zeros)
@@ -264,6 +270,8 @@ __device__ __forceinline__ void stedc_body(const double* din, const double* ein,
     }
   }
   lds_barrier();
+  if (const int i = NT - 1 - t; i < n && !(fabs(din[i]) < INFINITY && fabs(e[i]) < INFINITY))
+    bad = 1;  // (found by the last waves, beside the leaves)
   if (w * 8 < (1 << DL)) {  // uniform
     for (int it = 0; it < 12; ++it) {
       double off = 0.0, nrm = fabs(jb[0]);

@@ -57,3 +57,21 @@ def test_one_eigenvalue_and_two(torch_cuda, n):  # noqa: F811
         vals = np.repeat([1.0, 0.25], n // 2)
         _check(torch_cuda, ctx, orthogonal_with_spectrum(vals, 500 + n), n // 2, spec_len=n,
                label="two groups", iterative=False)
+
+
+@pytest.mark.parametrize("n", [4, 8, 16, 64, 65, 128])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_not_finite_is_an_error(torch_cuda, n, value):  # noqa: F811
+    from paper_2306_00358_amd import Context, HotrgError, hotrg_projector
+
+    M = graded_gram(n, n, 8.0, 100 + n)
+    M[n // 2, n - 1] = M[n - 1, n // 2] = value
+    U = torch_cuda.empty((n, 2), dtype=torch_cuda.float64, device="cuda")
+    with Context(0) as ctx:
+        print("not finite", n, value, flush=True)
+        with pytest.raises(HotrgError) as e:
+            hotrg_projector(ctx, torch_cuda.from_numpy(M).to("cuda"), U, 2, spec_len=2)
+        assert e.value.status == 4  # HOTRG_ERR_NUMERIC
+        # the context is as good as before
+        M = graded_gram(n, n, 8.0, 100 + n)
+        hotrg_projector(ctx, torch_cuda.from_numpy(M).to("cuda"), U, 2, spec_len=2)
