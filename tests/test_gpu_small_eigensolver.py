@@ -59,6 +59,36 @@ def test_one_eigenvalue_and_two(torch_cuda, n):  # noqa: F811
                label="two groups", iterative=False)
 
 
+def _tridiagonals(n):
+    rng = np.random.default_rng(n)
+    yield "random", rng.standard_normal(n), rng.standard_normal(n - 1)
+    yield "graded", 10.0 ** (-8.0 * np.arange(n) / n), 10.0 ** (-8.0 * (np.arange(n - 1) + 0.5) / n)
+    yield "wilkinson", np.abs(np.arange(n) - (n - 1) / 2.0), np.ones(n - 1)
+    yield "split", rng.standard_normal(n), rng.standard_normal(n - 1) * (np.arange(n - 1) % 3 > 0)
+    yield "clustered", np.round(rng.standard_normal(n)), 1e-3 * rng.standard_normal(n - 1)
+    yield "zero diagonal", np.zeros(n), np.ones(n - 1)
+
+
+@pytest.mark.parametrize("n", [3, 8, 9, 17, 33, 64, 65, 128])
+def test_tridiagonals(torch_cuda, n):  # noqa: F811
+    # matrices that are tridiagonal from the start, made positive by a shift: the
+    # spectra the divide and conquer finds hard (1e-12: the other tests' bound)
+    from paper_2306_00358_amd import Context, hotrg_projector
+
+    with Context(0) as ctx:
+        for label, d, e in _tridiagonals(n):
+            print(label, n, flush=True)
+            T = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+            T += np.eye(n) * (np.abs(d).max() + 2.0 * np.abs(e).max() + 1.0)
+            U = torch_cuda.empty((n, n), dtype=torch_cuda.float64, device="cuda")
+            kept, err, spec = hotrg_projector(ctx, torch_cuda.from_numpy(T).to("cuda"), U, n,
+                                              spec_len=n)
+            s, u = np.linalg.eigvalsh(T)[::-1], U.cpu().numpy()
+            assert np.abs(np.array(spec) - s / s[0]).max() <= 1e-12
+            assert np.abs(u.T @ u - np.eye(n)).max() <= 1e-12
+            assert np.abs(T @ u - u * s).max() <= 1e-12 * s[0]
+
+
 @pytest.mark.parametrize("n", [4, 8, 16, 64, 65, 128])
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_not_finite_is_an_error(torch_cuda, n, value):  # noqa: F811
