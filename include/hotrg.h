@@ -333,7 +333,10 @@ hotrg_status hotrg_ctx_last_eig(hotrg_ctx* ctx, int* sweeps, double* resid);
 /* ---- primitive contractions on caller device buffers (same kernels) -----
  * All pointers are device pointers of FP64 arrays, row-major; `prec`
  * selects the arithmetic of the contractions (inputs are rounded to it,
- * results are returned as FP64).  They wait for the context's stream. */
+ * results are returned as FP64).  They read their inputs on the context's
+ * stream, so work on other streams that writes those has to be complete (or
+ * ordered before that stream) when they are called, and they wait for that
+ * stream before they return. */
 
 /* Environment: M[(i,j),(k,l)] = sum T[j,a,b,e] T[i,e,c,d] T[l,a,b,f] T[k,f,c,d]
  * (Sec. 2), T of shape (dx,dy,dx,dy), M of shape (dx*dx, dx*dx). */

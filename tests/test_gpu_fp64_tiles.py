@@ -116,6 +116,7 @@ def test_more_tiles_than_a_grid_row():
     a, b = (torch.rand(dy, dtype=torch.float64, device="cuda", generator=g) + 0.5 for _ in range(2))
     T = (a[:, None] * b).reshape(1, dy, 1, dy)
     M = torch.zeros((1, 1), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
     print("long leg", dy, flush=True)
     with Context(0) as ctx:
         hotrg_environment(ctx, T, M)

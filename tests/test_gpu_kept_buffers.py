@@ -81,6 +81,7 @@ def test_large_operands_are_given_back():
     D = 88
     T = torch.ones((D, D, D, D), dtype=torch.float64, device="cuda")
     M = torch.empty((D * D, D * D), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
     with Context(0) as ctx:
         for _ in range(2):
             print("given back", D, flush=True)
