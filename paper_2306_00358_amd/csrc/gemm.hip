@@ -794,7 +794,7 @@ bool block_product_small(int p, int n) {
   const long long t16 = (long long)((p + 15) / 16) * ((n + 15) / 16);
   const long long t32 = (long long)((p + 31) / 32) * ((n + 31) / 32);
   if (t16 <= 256) return !(n & 1) || n <= 640;
-  return !(n & 1) && p > 64 && t32 <= 256;
+  return !(n & 1) && p > 64 && t32 <= (n < 3500 ? 256 : 512);
 }
 
 void gemm_f64_block(const double* V, const double* M, double* Y, int p, int n, double sigma,

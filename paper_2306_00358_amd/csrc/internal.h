@@ -120,9 +120,10 @@ void gemm_f64_block(const double* V, const double* M, double* Y, int p, int n, d
 // Small tiles take it while there are at most 256 of them, one a compute unit: 16 x 16
 // (64 x 1024: 8.5 us, 13.3 in chunks; 32 x 1936: 19.7 and 19.0), or 32 x 32 where the 64
 // x 64 ones would be of two rows (96 x 2304: 34.9 and 40.4; 128 x 1936: 31.8 and 33.6;
-// not 64 x 1600: 26.0 and 20.8).  Past that a second tile a unit costs more than the
-// chunks' sum (128 x 2304: 53.7 and 42.6; 96 x 2916: 66 and 56; level at 128 x 4096: 92
-// and 90).  Odd rows of V are loaded 8 bytes a lane: chunks from n = 641 on (64 x 625:
+// not 64 x 1600: 26.0 and 20.8).  A second tile a unit costs more than the chunks' sum
+// (128 x 2304: 53.7 and 42.6; 96 x 2916: 66 and 56) up to n = 3500; there two tiles
+// hide each other's loads, and the chunks' n^2 has caught up (128 x 3600: 83 and 91,
+// 96 x 5184: 116 and 150, level at 128 x 4096: 92 and 90).  Odd rows of V are loaded 8 bytes a lane: chunks from n = 641 on (64 x 625:
 // 8.7 and 11.9; x 729: 12.9 and 11.1; 96 x 2025: 45 and 33; 64 x 4225: 131 and 64).
 bool block_product_small(int p, int n);
 

@@ -106,7 +106,8 @@ def test_two_products_per_orthonormalisation(ratio, scale):
 
 
 @pytest.mark.parametrize("n, d", [(256, 4), (625, 14), (641, 14), (1025, 32), (2048, 14), (2064, 14),
-                                  (2048, 64), (2064, 64), (4097, 64), (4225, 64), (4240, 20)])
+                                  (2048, 64), (2064, 64), (3498, 64), (3500, 64), (4097, 64),
+                                  (4225, 64), (4240, 20), (5184, 48), (5472, 48)])
 def test_block_product_by_tiles_and_by_chunks(n, d):
     # either side of the lines between the two ways of V M: even and odd rows, a
     # tile a compute unit, and past the small tiles' 2^19 outputs; M of rank 256
