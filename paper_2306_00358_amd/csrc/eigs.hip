@@ -488,7 +488,7 @@ void group_orth(const GroupStep* d, int count, int pmax, int max_n, int pass, bo
 // v_rsq_f64 / v_rcp_f64 and Newton steps.  Against 8 lanes per row in up to 16
 // waves with d, e stored to global memory as they are found (and Q^T
 // accumulated at the end, an s_barrier over 16 waves alone 467 cycles): p = 64
-// 172 -> 61 us, p = 128 415 -> 208 us, and 16 and 43 us for the back-transform
+// 172 -> 59 us, p = 128 415 -> 205 us, and 14 and 41 us for the back-transform
 // (which replaces a 7 us product, or 30 us inside the divide and conquer).
 // another lane of the same 8-lane group (DPP: quad_perm [1,0,3,2],
 // quad_perm [2,3,0,1], row_half_mirror); every lane of the group is active

@@ -123,23 +123,25 @@ void gemm_f64_block(const double* V, const double* M, double* Y, int p, int n, d
 // not 64 x 1600: 26.0 and 20.8).  A second tile a unit costs more than the chunks' sum
 // (128 x 2304: 53.7 and 42.6; 96 x 2916: 66 and 56) up to n = 3500; there two tiles
 // hide each other's loads, and the chunks' n^2 has caught up (128 x 3600: 83 and 91,
-// 96 x 5184: 116 and 150, level at 128 x 4096: 92 and 90).  Odd rows of V are loaded 8 bytes a lane: chunks from n = 641 on (64 x 625:
-// 8.7 and 11.9; x 729: 12.9 and 11.1; 96 x 2025: 45 and 33; 64 x 4225: 131 and 64).
+// 96 x 5184: 116 and 150, level at 128 x 4096: 92 and 90).  Odd rows of V are loaded
+// 8 bytes a lane: chunks from n = 641 on (64 x 625: 8.7 and 11.9; x 729: 12.9 and 11.1;
+// 96 x 2025: 45 and 33; 64 x 4225: 131 and 64).
 bool block_product_small(int p, int n);
 
 // Direct-to-LDS FP64 GEMM (gemm_lds.hip); returns false if the operands do
 // not meet its alignment / K-multiple requirements.  variant 0: 4 waves,
 // 128 x 128 tile, K slab 32; variant 1: 8 waves, 256 x 128 tile, K slab 16;
 // variant 3: the same with three stages; 4: 4 waves, 128 x 128; 5: 512 x 64;
-// 6: 4 waves, 64 x 64, three stages; 7: 8 waves, 128 x 128, four stages.
+// 6: 4 waves, 64 x 64, three stages; 7: 8 waves, 128 x 128, four stages; 8: 4
+// waves, 64 x 32, four stages.
+bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb, int blayout,
+                  double* C, const OutMap& om, int M, int N, int K, unsigned long long* maxbits,
+                  hipStream_t s, int tag, int variant);
 // C = A A^T (M x M, A M x K K-contiguous) from the upper-triangle tiles with
 // mirrored stores, and C_2 = A_2 A_2^T in the same launch when A_2 is given;
 // false where it does not apply.
 bool gemm_f64_syrk(const double* A, long long lda, double* C, const OutMap& om, int M, int K,
                    hipStream_t s, const double* A_2 = nullptr, double* C_2 = nullptr);
-bool gemm_f64_lds(const double* A, long long lda, const double* B, long long ldb, int blayout,
-                  double* C, const OutMap& om, int M, int N, int K, unsigned long long* maxbits,
-                  hipStream_t s, int tag, int variant);
 
 // Tile order of a launch over tm x tn output tiles.  Workgroups are handed
 // round-robin to the 8 XCDs, each with its own L2.  With group gm > 0 the

@@ -58,8 +58,8 @@ def test_rank_below_the_block():
 
 @pytest.mark.parametrize("cuts", [[13], [13, 15, 21], [13, 16, 24], [16, 20]])
 def test_lockstep_odd_environments(cuts):
-    # odd D: rows of odd length, which the copies into LDS refuse, alone and beside
-    # even ones (the whole table then takes the general tiles)
+    # odd D: rows of odd length, copied into LDS 4 bytes a lane, alone and beside
+    # even ones (16 bytes a lane; each product of the table takes its own)
     import torch  # noqa: F401  (one HIP runtime for the process)
 
     from paper_2306_00358_amd import Context, hotrg_run, hotrg_run_grouped, make_opts, model_params
