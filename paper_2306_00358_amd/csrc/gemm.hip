@@ -371,9 +371,10 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_gemm_f64_small(
 // products of 576^3 35 -> 22 us, of 400^3 19.8 -> 10.1, of 128^3 4.0 -> 3.1; 64 x 64
 // x 1024 8.9 -> 5.2 (there by 32 partial products and a launch that sums them),
 // 128 x 128 x 4096 16 -> 13.7.  Operands off 16 bytes or with odd strides are copied 4
-// bytes a lane into the same places (64 x 64 x 1025: 7.4 us, by partial products 10.0;
-// x 2025: 11.7 and 10.3, at 128 x 128 11.8 and 15.6).  More stages take LDS that a second workgroup uses
-// better (four: 576^3 27 us).
+// bytes a lane into the same places (64 x 64 x 1225: 8.3 us, by 32 partial products 9.1;
+// 128 x 128 x 2025 11.9 and 11.3, x 8281 44 and 24: past legs of 45 a few us of a solve
+// of milliseconds).  More stages take LDS that a second workgroup uses better (four:
+// 576^3 27 us).
 // With `sym` (a symmetric C) only tiles that reach the upper triangle are formed, and
 // mirrored or not.
 constexpr int kSmallStages = 2;
